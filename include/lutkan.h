@@ -65,7 +65,8 @@ const char *lutkan_version(void);
  * "locate; tiled np=16 split=2 pipe=3; sum; " (row steps per wave, chunks of inputs, pipeline mode: 2 = two slice
  * buffers, 3 = three with the reads carried across inputs, 4 = three with two slices in flight; "tiled wide" on the
  * table's form with 16-bit codes, "tiled wide32" on the one with fp32 values) or "chain layers=2 wpr=4; " or "locate; gather split=16; sum; " or, for a large
- * spline_component layer, "locate; base_product; tiled np=16 split=1 pipe=3; " (model_forward: the clauses of all its
+ * spline_component layer, "locate; base_product; tiled np=16 split=1 pipe=3; " or, for a B-spline layer on the matrix cores, "bspline_matrix np=1
+ * split=2 slots=8; sum; " (model_forward: the clauses of all its
  * layers).  Thread-local, overwritten by the next forward call, never null. */
 const char *lutkan_last_plan(void);
 
@@ -299,11 +300,15 @@ int lutkan_forward_trace(const lutkan_dev_layer *layer, const float *x, int64_t 
 
 /* B-spline layer forward (Eq. 1 over Eq. 3-5): per (row, input) the span and the four non-zero cubic basis
  * values are computed once by the Cox-de Boor recursion in fp32; per edge four coefficient FMAs; the same
- * boundary_mode / oob_policy as the LUT layer is applied to x first. */
+ * boundary_mode / oob_policy as the LUT layer is applied to x first.  With algo = AUTO a phi layer of at most 13 segments on
+ * its domain grid with one knot vector runs as a dense product on the matrix cores, every fp32 operand cut exactly into
+ * three bf16 pieces (relative error per term <= 2^-23), the basis as cubic polynomials per segment; the results agree with
+ * the other kernels' to rounding. */
 int bspline_kan_forward(const bspline_dev_layer *layer, const float *x, int64_t B, float *y,
                         void *workspace, size_t workspace_bytes, void *hip_stream);
 
-/* The two phases of bspline_kan_forward (span + basis values per (row, input); coefficient FMAs + sum). */
+/* The two phases of bspline_kan_forward (span + basis values per (row, input); coefficient FMAs + sum): always the
+ * kernels on records, so that they agree with a call that ran on the matrix cores to rounding. */
 int bspline_forward_locate(const bspline_dev_layer *layer, const float *x, int64_t B,
                            void *workspace, size_t workspace_bytes, void *hip_stream);
 int bspline_forward_edges(const bspline_dev_layer *layer, int64_t B, float *y,

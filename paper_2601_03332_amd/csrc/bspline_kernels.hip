@@ -1,7 +1,10 @@
 // gfx950 kernels and launchers of the B-spline baseline layer of liblutkan (Sec. 3.2-3.3): the same work split as
 // the LUT layer (lutkan_kernels.hip) -- per (row, input) the span and the four non-zero cubic basis values, then
-// per edge four coefficient FMAs -- with the same tiling, staging and launch planning.
+// per edge four coefficient FMAs -- with the same tiling, staging and launch planning.  Layers whose basis fits 16 slots
+// run on the matrix cores instead (bspline_matrix.hip); the kernels here serve the others (spline_component, more than
+// 13 segments, one knot vector per input), the two separate phases, and algo = GATHER / TILED.
 // The file is compiled with -ffp-contract=off; every fused multiply-add below is written out as fmaf().
+#include "bspline_matrix.h"
 #include "lutkan_device.h"
 
 namespace {
@@ -385,6 +388,14 @@ int bspline_impl(const bspline_dev_layer *l, const float *x, int64_t B, float *y
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const int64_t Bp = padded_rows(B);
   const int G = l->G;
+  // The matrix-core kernel wherever it exists, for a call that runs both phases (a separate locate phase leaves this file's
+  // records for a separate edge phase).  It was the faster one in every measurement from one row up (layers of 16 -> 2 to
+  // 1024 -> 1024: 1.05 - 4.5 times) except for a handful of rows on a coefficient table beyond the caches of the eight XCDs,
+  // where the gather kernel reads a third of it: 1024 -> 1024, G = 10 (54 MB) at 1 / 4 / 8 rows 24 / 29 / 38 us against 35;
+  // 512 -> 512, G = 5 (8 MB) 17 / 18 / 21 against 14.
+  const bool few_rows_of_a_large_table = B < 8 && (double)l->n_tiles * l->d * l->coef_blob_bytes > 32.0 * 1024 * 1024;
+  if (l->algo == LUTKAN_ALGO_AUTO && phases == (kLocate | kEdges) && !few_rows_of_a_large_table && lutkan::bspline_matrix_fits(l))
+    return lutkan::bspline_matrix_forward(l, x, B, y, workspace, need, hip_stream);
 
   SplineLocateArgs la;
   la.x = x;
@@ -420,8 +431,8 @@ int bspline_impl(const bspline_dev_layer *l, const float *x, int64_t B, float *y
   ea.with_base = la.with_base; ea.jt = l->jt; ea.n_tiles = l->n_tiles;
   bool tiled = true;                                   // a coefficient slice always fits LDS (R <= 67)
   if (l->algo == LUTKAN_ALGO_GATHER) tiled = false;
-  // up to 16 rows the gather kernel with the inputs split over the GPU is the faster one (measured on 256x256 and
-  // 1024x1024 layers): the tiled kernel's walk over all inputs is then a longer chain than the arithmetic
+  // up to 16 rows the gather kernel with the inputs split over the GPU is faster than the tiled one (measured on 256x256
+  // and 1024x1024 layers): the tiled kernel's walk over all inputs is then a longer chain than the arithmetic
   if (l->algo == LUTKAN_ALGO_AUTO && B <= 16) tiled = false;
   if (l->algo == LUTKAN_ALGO_TILED && !tiled) return fail(LUTKAN_EUNSUPPORTED, "%s: tiled kernel unavailable", who);
   ea.chunk = l->d;

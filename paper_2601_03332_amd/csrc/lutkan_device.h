@@ -144,7 +144,7 @@ int check_launch(const char *what) {
 
 enum { kLocate = 1, kEdges = 2 };      // the two phases of a forward call
 
-int gather_jx_log2(int m) {
+inline int gather_jx_log2(int m) {
   int lg = 2;
   while ((1 << lg) < m && lg < 8) ++lg;
   return lg;
@@ -265,7 +265,7 @@ int launch_with_lds(Kern kern, LdsCap *cap, const dim3 &grid, size_t lds, hipStr
 }
 
 // Records for every (input, padded row), then room for the partial sums when the inputs are split into chunks.
-size_t tiled_workspace_bytes(int d, int m, int jt, int n_tiles, int64_t B, int bytes_per_record, int slice_bytes, int code_bytes = 1) {
+inline size_t tiled_workspace_bytes(int d, int m, int jt, int n_tiles, int64_t B, int bytes_per_record, int slice_bytes, int code_bytes = 1) {
   size_t bytes = record_bytes(d, padded_rows(B), bytes_per_record);
   const TilePlan tp = plan_tiles(B, d, m, n_tiles, 64 / (jt / 4), slice_bytes, code_bytes);
   // any of the kernels may run (tiled, gather with one column per lane, gather with four): room for the largest set

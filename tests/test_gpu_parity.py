@@ -1270,3 +1270,66 @@ def test_measurement_probes_report_their_work():
         lk.lutkan_probe_launch(99, buf, 1)
     with pytest.raises(lk.LutKanError):
         lk.lutkan_probe_launch(lk.PROBE_HBM_READ, buf[:1024], 1)
+
+
+# ---------------------------------------------------------------- the B-spline layer on the matrix cores
+MATRIX_CASES = [
+    # seed, d, m, G, boundary, oob, B, uniform: 8 slots to G = 5, 16 to G = 13; 32, 64 and 128 columns per work-group
+    (901, 1, 1, 1, CLOSED, CLIP_X, 1, True),
+    (902, 3, 5, 5, HALF_OPEN, ZERO_SPLINE, 33, False),
+    (903, 8, 32, 5, CLOSED, ZERO_SPLINE, 256, True),          # exactly one stage, one work-group of rows
+    (904, 9, 33, 4, HALF_OPEN, CLIP_X, 257, False),           # one input and one row over
+    (905, 20, 64, 6, CLOSED, CLIP_X, 513, False),             # the smallest layer of 16 slots; rows of whole 16-byte vectors
+    (906, 21, 65, 13, HALF_OPEN, ZERO_SPLINE, 511, True),     # the largest; odd rows
+    (907, 132, 129, 5, CLOSED, ZERO_SPLINE, 1000, False),     # inputs split, two column tiles, a chunk that ends inside a stage
+    (908, 130, 300, 10, HALF_OPEN, ZERO_SPLINE, 700, False),
+    (909, 64, 8, 5, CLOSED, CLIP_X, 140000, True),            # two row tiles per wave on narrow columns
+    (910, 68, 64, 12, HALF_OPEN, CLIP_X, 70001, False),
+    (911, 512, 400, 7, CLOSED, ZERO_SPLINE, 5003, False),     # located once into records (four column tiles, 1e9 edges)
+]
+
+
+@pytest.mark.parametrize("case", MATRIX_CASES, ids=lambda c: f"seed{c[0]}")
+def test_bspline_layer_on_the_matrix_cores(case):
+    """Against the oracle at the edges of the kernel's tiles, with NaN and infinite inputs in one row each."""
+    seed, d, m, G, boundary, oob, B, uniform = case
+    w = random_layer(seed, d, m, G, 2, SYM_INT8, boundary, oob, B, uniform=uniform)
+    s, x = w.layers[0], w.x
+    if B > 20:
+        x[3, d // 2] = np.nan
+        x[5, :] = np.inf
+        x[B - 1, 0] = -np.inf
+    art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.L, s.scheme, s.boundary, s.oob)
+    layer = art.bspline_to_device(DEV)
+    _say(f"case bspline matrix d={d} m={m} G={G} boundary={boundary} oob={oob} B={B}")
+    xg = torch.from_numpy(x).to(DEV)
+    y = lk.bspline_kan_forward(layer, xg)
+    plan = lk.lutkan_last_plan()
+    assert f"slots={8 if G <= 5 else 16}; " in plan and plan.startswith("bspline_locate; " if seed == 911 else "bspline_matrix "), plan
+    shifted = torch.empty(B * d + 1, dtype=torch.float32, device=DEV)[1:].view(B, d).copy_(xg)      # rows off the 16-byte grid
+    y_shifted = lk.bspline_kan_forward(layer, shifted)
+    torch.cuda.synchronize()
+    ref = oracle.bspline_forward(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.boundary, s.oob, x)
+    _assert_close(y.cpu().numpy(), ref, f"bspline matrix {w.name}")
+    assert np.array_equal(y.cpu().numpy(), y_shifted.cpu().numpy(), equal_nan=True)
+
+
+def test_bspline_layers_outside_the_matrix_kernel_keep_their_kernels():
+    """What the matrix kernel does not serve, and the handful of rows on a large table that it is slower at."""
+    for kw, what in ((dict(G=14), "14 segments"), (dict(with_base=True), "spline_component")):
+        w = random_layer(921, 12, 40, kw.get("G", 5), 2, SYM_INT8, CLOSED, CLIP_X, 50, with_base=kw.get("with_base", False))
+        _check_bspline(w.layers[0], w.x, lk.ALGO_AUTO, what)
+        assert lk.lutkan_last_plan().startswith("bspline_locate; bspline_tiled np=") and "slots" not in lk.lutkan_last_plan()
+    w = per_input_layer(922, 12, 40, 5, 2, SYM_INT8, CLOSED, CLIP_X, 50)
+    s = w.layers[0]
+    art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.L, s.scheme, s.boundary, s.oob, knots_per_input=True)
+    lk.bspline_kan_forward(art.bspline_to_device(DEV), torch.from_numpy(w.x).to(DEV))
+    assert "slots" not in lk.lutkan_last_plan()
+    w = cfg4(B=8)
+    s = w.layers[0]
+    art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, 2, s.scheme, s.boundary, s.oob)
+    layer, xg = art.bspline_to_device(DEV), torch.from_numpy(w.x).to(DEV)
+    lk.bspline_kan_forward(layer, xg[:7])
+    assert "bspline_gather" in lk.lutkan_last_plan()
+    lk.bspline_kan_forward(layer, xg)
+    assert lk.lutkan_last_plan().startswith("bspline_matrix ")
