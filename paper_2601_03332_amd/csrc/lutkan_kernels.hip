@@ -11,10 +11,13 @@
 //                      "tiled" variant: a work-group owns (row tile) x (column tile), walks the inputs, and
 //                      stages each input's table slice in LDS;  "gather" variant: codes straight from global
 //                      memory (used for table slices too large for LDS and for the code trace).
+//   (narrow layers at large batches: 1. and 2. in one kernel, lutkan_narrow.hip)
 //   3. chain kernel    both steps for every layer of a narrow network in one launch, activations in LDS (small
 //                      batches, where the launches of 1. and 2. per layer cost more than the arithmetic).
 // The file is compiled with -ffp-contract=off; every fused multiply-add below is written out as fmaf().
 #include "lutkan_device.h"
+#include "lutkan_locate.h"
+#include "lutkan_narrow.h"
 #include "lutkan_pieces.h"
 
 namespace {
@@ -37,43 +40,6 @@ struct LocateArgs {
   uint16_t *silu_pieces;       // nullable, [3][Bp][d]: SiLU(x) cut into three bf16 pieces (rows B .. Bp-1 zero), the first
                                // operand of the base branch when it runs as a matrix product of its own
 };
-
-struct Located {
-  int k, l0;
-  float w;
-  bool inside, is_nan;
-};
-
-
-// s_knots: the K+1 knots of this element's input in LDS.  With one vector per layer (PERIN false) the comparisons
-// run against the copy in the kernel arguments (scalar registers) and LDS serves the two lookups by the lane's own
-// segment index; with one vector per input every lane reads its own input's row.
-template <bool PERIN, typename Args>
-__device__ __forceinline__ Located locate_one(const Args &a, const float *s_knots, float x) {
-  Located o;
-  const float t0 = PERIN ? s_knots[0] : a.knots[0];
-  const float tK = PERIN ? s_knots[a.K] : a.knots[a.K];
-  const float tKs = PERIN ? (a.closed ? tK : next_float_below(tK)) : a.tKs;
-  o.is_nan = (x != x);
-  o.inside = a.closed ? (x >= t0 && x <= tK) : (x >= t0 && x < tK);
-  float xc = o.is_nan ? t0 : x;
-  xc = (xc < t0) ? t0 : xc;
-  xc = (xc > tKs) ? tKs : xc;
-  // k = #{kappa in 1..K-1 : T[kappa] <= x'}; T[0] <= x' always holds and T[K] is clipped away (Eq. 14).
-  int k = 0;
-  for (int kappa = 1; kappa < a.K; ++kappa) k += ((PERIN ? s_knots[kappa] : a.knots[kappa]) <= xc) ? 1 : 0;
-  const float tk = s_knots[k], tk1 = s_knots[k + 1];
-  const float num = __fsub_rn(xc, tk);
-  const float den = __fsub_rn(tk1, tk);
-  const float u = __fdiv_rn(num, den);                       // Eq. 15, correctly rounded
-  const float z = __fmul_rn(u, (float)(a.L - 1));            // Eq. 16
-  int l0 = (int)floorf(z);
-  l0 = min(max(l0, 0), a.L - 1);
-  o.k = k;
-  o.l0 = l0;
-  o.w = __fsub_rn(z, (float)l0);
-  return o;
-}
 
 constexpr int kLocTile = 2048;  // (row, input) pairs per block of the LUT locate kernel: 256 threads x 8
 
@@ -228,12 +194,6 @@ template <int SCHEME>
 __device__ __forceinline__ float code_to_float(unsigned byte) {
   if (SCHEME == LUTKAN_SYM_INT8) return (float)((int)(byte & 0xffu) - 128);
   return (float)(byte & 0xffu);
-}
-
-__device__ __forceinline__ f16x2 bits_to_f16x2(unsigned v) {
-  union { unsigned u; f16x2 h; } c;
-  c.u = v;
-  return c.h;
 }
 
 // Gather variant: one thread per (row, output column); consecutive threads take consecutive columns so the
@@ -1114,6 +1074,17 @@ bool small_layer_runs_as_chain(const lutkan_dev_layer *l, int64_t B) {
   return (double)B * (0.30 + 0.00053 * l->d * l->jt) <= 10000.0;
 }
 
+// The OOB counters of a layer's inputs, added to `stats`.
+int count_oob(const lutkan_dev_layer *l, const float *x, int64_t B, lutkan_oob_stats *stats, hipStream_t s) {
+  const int64_t rows_per_group = 4 * kOobRowsPerWave;
+  hipLaunchKernelGGL(oob_count_kernel, dim3((unsigned)((B + rows_per_group - 1) / rows_per_group)), dim3(256), 0, s, x, B, l->d,
+                     l->knots[0], l->knots[l->K], l->boundary == LUTKAN_CLOSED ? 1 : 0, l->knots_per_input ? l->input_knots : nullptr, l->K,
+                     reinterpret_cast<unsigned long long *>(stats));
+  if (int rc = check_launch("oob_count_kernel")) return rc;
+  lutkan::plan_note("oob; ");
+  return LUTKAN_OK;
+}
+
 int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y, lutkan_oob_stats *stats,
                  int32_t *k_out, int32_t *l0_out, uint8_t *in_out, float *w_out, int16_t *q01_out, bool trace,
                  void *workspace, size_t workspace_bytes, void *hip_stream, const char *who, int phases = kLocate | kEdges) {
@@ -1172,6 +1143,16 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   uint16_t *w_pieces = reinterpret_cast<uint16_t *>(ws_bytes + records_end);
   float *const partials = reinterpret_cast<float *>(ws_bytes + records_end + (with_base ? lutkan::base_product_workspace_bytes(l->d, l->m) : 0));
 
+  // A narrow layer in one launch, where its plan is priced below the tiled kernel's plus the locate pass (about 5 us and its
+  // 12 bytes per (row, input) at the rate of a large copy).  Both phases in one call only: it leaves no records.
+  if (l->algo == LUTKAN_ALGO_AUTO && tiled && phases == (kLocate | kEdges) && !trace) {
+    const lutkan::NarrowPlan np = lutkan::narrow_plan(l, B, need);
+    if (np.waves && np.cost < tp.cost + 5.0 + (double)B * l->d * 12.0 / 4.7e6) {
+      if (int rc = lutkan::narrow_forward(l, np, x, B, y, workspace, hip_stream)) return rc;
+      return stats ? count_oob(l, x, B, stats, s) : LUTKAN_OK;
+    }
+  }
+
   LocateArgs la;
   la.x = x;
   la.rec = workspace;
@@ -1200,11 +1181,7 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
     if (int rc = check_launch("lutkan_locate_kernel")) return rc;
     lutkan::plan_note("locate; ");
     if (stats) {
-      const int64_t rows_per_group = 4 * kOobRowsPerWave;
-      hipLaunchKernelGGL(oob_count_kernel, dim3((unsigned)((B + rows_per_group - 1) / rows_per_group)), dim3(256), 0, s, x, B, l->d,
-                         l->knots[0], l->knots[l->K], la.closed, la.input_knots, l->K, reinterpret_cast<unsigned long long *>(stats));
-      if (int rc = check_launch("oob_count_kernel")) return rc;
-      lutkan::plan_note("oob; ");
+      if (int rc = count_oob(l, x, B, stats, s)) return rc;
     }
   }
   if (!(phases & kEdges)) return LUTKAN_OK;

@@ -1,0 +1,71 @@
+// What the kernels that locate inputs share: steps 1-4 of Sec. 4.5 with the domain test of Sec. 5.2 for one (row, input), and
+// the interpolation of byte codes.  Included by files compiled with -ffp-contract=off.
+#pragma once
+
+#include "lutkan_device.h"
+
+namespace {
+
+__device__ __forceinline__ f16x2 bits_to_f16x2(unsigned v) {
+  union { unsigned u; f16x2 h; } c;
+  c.u = v;
+  return c.h;
+}
+
+struct Located {
+  int k, l0;
+  float w;
+  bool inside, is_nan;
+};
+
+
+// s_knots: the K+1 knots of this element's input in LDS.  With one vector per layer (PERIN false) the comparisons
+// run against the copy in the kernel arguments (scalar registers) and LDS serves the two lookups by the lane's own
+// segment index; with one vector per input every lane reads its own input's row.
+template <bool PERIN, typename Args>
+__device__ __forceinline__ Located locate_one(const Args &a, const float *s_knots, float x) {
+  Located o;
+  const float t0 = PERIN ? s_knots[0] : a.knots[0];
+  const float tK = PERIN ? s_knots[a.K] : a.knots[a.K];
+  const float tKs = PERIN ? (a.closed ? tK : next_float_below(tK)) : a.tKs;
+  o.is_nan = (x != x);
+  o.inside = a.closed ? (x >= t0 && x <= tK) : (x >= t0 && x < tK);
+  float xc = o.is_nan ? t0 : x;
+  xc = (xc < t0) ? t0 : xc;
+  xc = (xc > tKs) ? tKs : xc;
+  // k = #{kappa in 1..K-1 : T[kappa] <= x'}; T[0] <= x' always holds and T[K] is clipped away (Eq. 14).
+  int k = 0;
+  for (int kappa = 1; kappa < a.K; ++kappa) k += ((PERIN ? s_knots[kappa] : a.knots[kappa]) <= xc) ? 1 : 0;
+  const float tk = s_knots[k], tk1 = s_knots[k + 1];
+  const float num = __fsub_rn(xc, tk);
+  const float den = __fsub_rn(tk1, tk);
+  const float u = __fdiv_rn(num, den);                       // Eq. 15, correctly rounded
+  const float z = __fmul_rn(u, (float)(a.L - 1));            // Eq. 16
+  int l0 = (int)floorf(z);
+  l0 = min(max(l0, 0), a.L - 1);
+  o.k = k;
+  o.l0 = l0;
+  o.w = __fsub_rn(z, (float)l0);
+  return o;
+}
+
+// Eq. 17 on the four codes of a lane (one dword of table row l0, one of row l0+1) as t = (q0 + w * (q1 - q0)) * 2^-24: a byte
+// zero-extended to 16 bits is the binary16 denormal byte * 2^-24, so the difference and the removal of the excess-128 bias of
+// symmetric codes are exact packed arithmetic and the interpolation has one fp32 rounding.
+template <int SCHEME>
+__device__ __forceinline__ void interpolate_codes(unsigned c0, unsigned c1, float w, float t[4]) {
+  f16x2 q0lo = bits_to_f16x2(__builtin_amdgcn_perm(c0, c0, 0x0c010c00u)), q0hi = bits_to_f16x2(__builtin_amdgcn_perm(c0, c0, 0x0c030c02u));
+  const f16x2 q1lo = bits_to_f16x2(__builtin_amdgcn_perm(c1, c1, 0x0c010c00u)), q1hi = bits_to_f16x2(__builtin_amdgcn_perm(c1, c1, 0x0c030c02u));
+  const f16x2 dlo = q1lo - q0lo, dhi = q1hi - q0hi;
+  if (SCHEME == LUTKAN_SYM_INT8) {
+    const f16x2 bias = bits_to_f16x2(0x00800080u);
+    q0lo = q0lo - bias;
+    q0hi = q0hi - bias;
+  }
+  t[0] = fmaf(w, (float)dlo.x, (float)q0lo.x);
+  t[1] = fmaf(w, (float)dlo.y, (float)q0lo.y);
+  t[2] = fmaf(w, (float)dhi.x, (float)q0hi.x);
+  t[3] = fmaf(w, (float)dhi.y, (float)q0hi.y);
+}
+
+}  // namespace

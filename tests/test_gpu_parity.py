@@ -1333,3 +1333,73 @@ def test_bspline_layers_outside_the_matrix_kernel_keep_their_kernels():
     assert "bspline_gather" in lk.lutkan_last_plan()
     lk.bspline_kan_forward(layer, xg)
     assert lk.lutkan_last_plan().startswith("bspline_matrix ")
+
+
+# ---------------------------------------------------------------- narrow layers in one launch
+NARROW_CASES = [
+    # seed, d, m, G, L, scheme, boundary, oob, B, with_base, fp16: tiles of 4, 8, 16, 32 columns; stages of 8 and of 4 slices
+    (931, 1000, 4, 10, 16, SYM_INT8, CLOSED, CLIP_X, 5000, False, False),          # inputs split
+    (932, 17, 3, 5, 64, ASYM_UINT8, HALF_OPEN, ZERO_SPLINE, 60000, False, False),  # 8 + 8 + 1 inputs, ragged columns
+    (933, 64, 8, 5, 32, ASYM_UINT8, CLOSED, CLIP_X, 40001, False, False),
+    (934, 63, 5, 13, 32, SYM_INT8, HALF_OPEN, ZERO_SPLINE, 30000, True, False),    # 13 segments; base branch: stages of 4
+    (935, 78, 16, 5, 64, ASYM_UINT8, CLOSED, ZERO_SPLINE, 20011, False, False),
+    (936, 90, 13, 10, 64, SYM_INT8, HALF_OPEN, CLIP_X, 20000, False, True),        # long slices: stages of 4; binary16 parameters
+    (937, 130, 30, 5, 16, ASYM_UINT8, HALF_OPEN, ZERO_SPLINE, 30000, False, True),
+    (938, 133, 32, 8, 64, SYM_INT8, CLOSED, CLIP_X, 20000, False, False),
+    (939, 131, 15, 30, 8, ASYM_UINT8, CLOSED, CLIP_X, 25000, True, False),         # segments searched in steps of eight
+    (940, 300, 10, 64, 4, SYM_INT8, HALF_OPEN, ZERO_SPLINE, 3000, False, False),   # the most segments
+]
+
+
+@pytest.mark.parametrize("case", NARROW_CASES, ids=lambda c: f"seed{c[0]}")
+def test_narrow_layer_in_one_launch(case):
+    """Against the oracle and its OOB counters, with NaN, infinite, zero (of both signs) and end-of-domain inputs; rows off
+    the 16-byte grid give the same bits."""
+    seed, d, m, G, L, scheme, boundary, oob, B, with_base, fp16 = case
+    w = random_layer(seed, d, m, G, L, scheme, boundary, oob, B, uniform=(seed % 2 == 0), with_base=with_base)
+    s, x = w.layers[0], w.x
+    x[7, :] = -0.0
+    x[8, :] = 0.0
+    x[9, 0] = np.nan
+    x[10, d - 1] = np.inf
+    x[11, d // 2] = -np.inf
+    if with_base:                                          # (an infinite base branch: only its class is defined)
+        x[10, d - 1] = x[11, d // 2] = 3.0e38 ** 0.25
+    art, ora = _compile_both(s, fp16)
+    layer = _device_layer(art, s)
+    _say(f"case narrow d={d} m={m} K={G} L={L} scheme={scheme} boundary={boundary} oob={oob} B={B} base={with_base} fp16={fp16}")
+    xg = torch.from_numpy(x).to(DEV)
+    stats = torch.zeros(2, dtype=torch.int64, device=DEV)
+    y = lk.lutkan_forward(layer, xg, stats=stats)
+    assert "one_launch" in lk.lutkan_last_plan(), lk.lutkan_last_plan()
+    shifted = torch.empty(B * d + 1, dtype=torch.float32, device=DEV)[1:].view(B, d).copy_(xg)
+    y_shifted = lk.lutkan_forward(layer, shifted)
+    torch.cuda.synchronize()
+    ref = oracle.lut_forward(ora, s.boundary, s.oob, x, trace=True, edge_scalars=s.edge_scales)
+    _assert_close(y.cpu().numpy(), ref, f"narrow {w.name}")
+    assert np.array_equal(y.cpu().numpy(), y_shifted.cpu().numpy(), equal_nan=True)
+    assert stats.cpu().tolist() == [ref.oob_count, ref.oob_any_rows]
+
+
+def test_narrow_layer_locates_bit_exactly():
+    """Codes q[k][l] = l, alpha_k = 2^k on one input make the output 2^k (l0 + w), exact in fp32: the one-launch kernel's index
+    work is the oracle's bit for bit, at the knots, beside them and between."""
+    K, L = 12, 16
+    for width, (lo, hi) in ((4, (-1.0, 1.0)), (16, (0.0, 3.0))):
+        knots = np.linspace(lo, hi, K + 1).astype(np.float32)
+        q = np.tile(np.arange(L, dtype=np.uint8), (width, K, 1))
+        scale = np.tile((2.0 ** np.arange(K)).astype(np.float32), (width, 1))
+        art = lk.lutkan_artifact_from_arrays(1, width, knots, q, scale, np.zeros((width, K), np.float32), CLOSED, CLIP_X)
+        rng = np.random.Generator(np.random.PCG64(77))
+        x = rng.uniform(lo - 0.1, hi + 0.1, size=(70000, 1)).astype(np.float32)
+        near = np.concatenate([knots, np.nextafter(knots, np.float32(-9)), np.nextafter(knots, np.float32(9)), np.float32([0.0, -0.0, 1e-40, -1e-40])])
+        x[:near.size, 0] = near
+        layer = art.to_device(DEV)
+        xg = torch.from_numpy(x).to(DEV)
+        y = lk.lutkan_forward(layer, xg)
+        assert "one_launch" in lk.lutkan_last_plan(), lk.lutkan_last_plan()
+        _, k, l0, _, wgt, _ = lk.lutkan_forward_trace(layer, xg)
+        expect = (1 << k.long()).double() * (l0.double() + wgt.double())
+        # (the running sums carry 2^-24, so a value below 2^-126 * 2^24 -- a weight next to the knot at 0 -- may be flushed)
+        flushed = (expect < 2.0 ** -102) & (y.double().abs() <= expect)
+        assert torch.equal(torch.where(flushed, expect, y.double()), expect.expand(-1, width))

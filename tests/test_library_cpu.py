@@ -709,6 +709,29 @@ def test_m0_is_only_touched_by_the_lds_dma_helper(tmp_path):
     assert kernels > 50                                              # every LUT and B-spline tiled variant was seen
 
 
+def test_m0_is_only_touched_by_the_lds_dma_helper_in_the_narrow_kernels(tmp_path):
+    """The same check for the one-launch kernels of narrow layers, which stage their slices with the same helper."""
+    import subprocess
+    from paper_2601_03332_amd import build as lib_build
+    out = tmp_path / "narrow.s"
+    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + lib_build.HIPCC_FLAGS + \
+          ["-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2601_03332_amd", "csrc"), "-x", "hip",
+           "--cuda-device-only", "-S", os.path.join(ROOT, "paper_2601_03332_amd", "csrc", "lutkan_narrow.hip"), "-o", str(out)]
+    subprocess.run(cmd, check=True, capture_output=True)
+    kernels, inside_asm, current = 0, False, None
+    for line in open(out):
+        text = line.strip()
+        if re.match(r"_Z\S*narrow_kernel\S*:", text):
+            current, kernels = text.split(":")[0], kernels + 1
+        elif text.startswith(".Lfunc_end"):
+            current = None
+        elif text.startswith(";;#ASM"):
+            inside_asm = text.startswith(";;#ASMSTART")
+        elif current and not text.startswith(";") and re.search(r"\bm0\b", text.split(";")[0]):
+            assert inside_asm, f"compiler-generated use of m0 in {current}: {text}"
+    assert kernels > 50
+
+
 def test_host_compile_matches_the_oracle_on_random_shapes():
     """Forty layers with random shapes, grids, table sizes and options: codes, parameters and knots bit-identical to
     the oracle's, rebuilt artifacts byte-identical to compiled ones."""
