@@ -43,9 +43,9 @@ typedef enum { LUTKAN_CLIP_X = 0, LUTKAN_ZERO_SPLINE = 1 } lutkan_oob;          
  * from global memory and splits the inputs over the GPU.  AUTO: tiled when a slice fits LDS, except for batches of so
  * few rows that they touch less than the whole table (then gather), and except for a small narrow layer (one column
  * tile, d * jt <= 4096) at up to 10000 / (0.30 + 0.00053 d jt) rows (30000 for a 16x2 layer, 4000 for 256x16), which
- * lutkan_forward runs as a one-layer launch of the fused chain kernel, and except for a layer of one column tile of at most
- * 32 columns whose batch has outgrown that: lutkan_forward runs it in one launch that locates and sums (no records), where
- * the launch planning prices that below locate + tiled kernel;
+ * lutkan_forward runs as a one-layer launch of the fused chain kernel, and except where lutkan_forward needs no records because
+ * one launch locates, gathers and sums and the launch planning prices that lower: a few rows (up to some hundred) of a
+ * layer whose table is at most 128 MiB, and a layer of one column tile of at most 32 columns whose batch has outgrown both;
  * results agree to rounding, not bit for bit.  TILED (and AUTO) take the table's wide form, where the layer holds one
  * (lutkan_wide_table_build), when the launch planning prices it lower; TILED_WIDE takes it whatever the price and is
  * an error for a layer without one or a call it does not serve (16-bit codes with 16-byte records).  LUT layers only. */
@@ -64,7 +64,8 @@ typedef enum { LUTKAN_SPAN_DOMAIN = 0, LUTKAN_SPAN_EXTENDED = 1 } lutkan_knot_sp
 const char *lutkan_last_error(void);
 const char *lutkan_version(void);
 /* What the last forward call of this thread launched, for logs and tests: one clause per kernel launch -- except that "locate;
- * tiled np=1 split=1 one_launch waves=16; " is a narrow layer whose tiled kernel locates its inputs itself --, e.g.
+ * tiled np=1 split=1 one_launch waves=16; " is a narrow layer whose tiled kernel locates its inputs itself; "rows wpr=16; " is a
+ * few rows in one launch --, e.g.
  * "locate; tiled np=16 split=2 pipe=3; sum; " (row steps per wave, chunks of inputs, pipeline mode: 2 = two slice
  * buffers, 3 = three with the reads carried across inputs, 4 = three with two slices in flight; "tiled wide" on the
  * table's form with 16-bit codes, "tiled wide32" on the one with fp32 values) or "chain layers=2 wpr=4; " or "locate; gather split=16; sum; " or, for a large
@@ -287,7 +288,7 @@ int lutkan_forward_static_scratch(const lutkan_dev_layer *layer, const float *x,
  *                           fills the workspace with the lookup records (and adds to stats, nullable)
  *   lutkan_forward_edges    step 5 (Eq. 10, 17), Sec. 5.4 and the sum of Eq. 1 from the records in the workspace
  * Calling locate then edges on one stream with the same layer, B and workspace equals lutkan_forward, to rounding where
- * lutkan_forward runs a narrow layer in one launch (lutkan_algo). */
+ * lutkan_forward needs no records (lutkan_algo). */
 int lutkan_forward_locate(const lutkan_dev_layer *layer, const float *x, int64_t B, lutkan_oob_stats *stats,
                           void *workspace, size_t workspace_bytes, void *hip_stream);
 int lutkan_forward_edges(const lutkan_dev_layer *layer, int64_t B, float *y,

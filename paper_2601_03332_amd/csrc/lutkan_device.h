@@ -107,7 +107,7 @@ __device__ __forceinline__ void stage_slice(const unsigned char *gsrc, unsigned 
 
 // Sums the n_split partial outputs of the tiled kernels in ascending chunk order (deterministic): y = sum_s part[s],
 // or y = y + sum_s part[s] with `accumulate` (y then already holds the base branch of the layer).
-__global__ __launch_bounds__(256) void sum_partials_kernel(const float *part, float *y, int64_t n, int n_split, int accumulate) {
+[[maybe_unused]] __global__ __launch_bounds__(256) void sum_partials_kernel(const float *part, float *y, int64_t n, int n_split, int accumulate) {
   const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (e + 3 < n && (n & 3) == 0) {                   // 16-byte path needs every chunk's base aligned
     f32x4 acc = *reinterpret_cast<const f32x4 *>(part + e);

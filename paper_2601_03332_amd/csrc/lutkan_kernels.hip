@@ -11,7 +11,7 @@
 //                      "tiled" variant: a work-group owns (row tile) x (column tile), walks the inputs, and
 //                      stages each input's table slice in LDS;  "gather" variant: codes straight from global
 //                      memory (used for table slices too large for LDS and for the code trace).
-//   (narrow layers at large batches: 1. and 2. in one kernel, lutkan_narrow.hip)
+//   (narrow layers at large batches and a few rows on any layer: 1. and 2. in one kernel, lutkan_narrow.hip, lutkan_rows.hip)
 //   3. chain kernel    both steps for every layer of a narrow network in one launch, activations in LDS (small
 //                      batches, where the launches of 1. and 2. per layer cost more than the arithmetic).
 // The file is compiled with -ffp-contract=off; every fused multiply-add below is written out as fmaf().
@@ -19,6 +19,7 @@
 #include "lutkan_locate.h"
 #include "lutkan_narrow.h"
 #include "lutkan_pieces.h"
+#include "lutkan_rows.h"
 
 namespace {
 
@@ -1143,11 +1144,20 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   uint16_t *w_pieces = reinterpret_cast<uint16_t *>(ws_bytes + records_end);
   float *const partials = reinterpret_cast<float *>(ws_bytes + records_end + (with_base ? lutkan::base_product_workspace_bytes(l->d, l->m) : 0));
 
-  // A narrow layer in one launch, where its plan is priced below the tiled kernel's plus the locate pass (about 5 us and its
-  // 12 bytes per (row, input) at the rate of a large copy).  Both phases in one call only: it leaves no records.
-  if (l->algo == LUTKAN_ALGO_AUTO && tiled && phases == (kLocate | kEdges) && !trace) {
-    const lutkan::NarrowPlan np = lutkan::narrow_plan(l, B, need);
-    if (np.waves && np.cost < tp.cost + 5.0 + (double)B * l->d * 12.0 / 4.7e6) {
+  // One launch that needs no records, where one of the two is priced below the passes: a few rows on a table that the caches
+  // hold (beyond 128 MiB every call fetches its rows from HBM, which the passes spread over more work-groups), or a narrow
+  // layer.  Both phases in one call only.  The passes: locate, about 5 us and its 12 bytes per (row, input) at the rate of a
+  // large copy, then the tiled plan or the gather kernel (measured as above) and its summing pass.
+  if (l->algo == LUTKAN_ALGO_AUTO && phases == (kLocate | kEdges) && !trace && !q01_out) {
+    const double table = (double)l->n_tiles * l->d * l->blob_bytes;
+    const double passes = 5.0 + (double)B * l->d * 12.0 / 4.7e6 + (tiled ? (wide ? tpw.cost : tp.cost) : 10.0 + (double)B * l->d * l->n_tiles * (2.0 * l->jt + lay.param_row_bytes) / 9.4e6);
+    const lutkan::RowsPlan rp = table <= 128.0 * 1024 * 1024 ? lutkan::rows_plan(l, B) : lutkan::RowsPlan{0, 1e300};
+    const lutkan::NarrowPlan np = tiled ? lutkan::narrow_plan(l, B, need) : lutkan::NarrowPlan{0, 1, l->d, 0, 1e300};
+    if (rp.waves_per_row && rp.cost < std::min(passes, np.cost)) {
+      if (int rc = lutkan::rows_forward(l, rp, x, B, y, hip_stream)) return rc;
+      return stats ? count_oob(l, x, B, stats, s) : LUTKAN_OK;
+    }
+    if (np.waves && np.cost < passes) {
       if (int rc = lutkan::narrow_forward(l, np, x, B, y, workspace, hip_stream)) return rc;
       return stats ? count_oob(l, x, B, stats, s) : LUTKAN_OK;
     }

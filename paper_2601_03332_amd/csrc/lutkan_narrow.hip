@@ -47,42 +47,6 @@ struct NarrowArgs {
   float knots[LUTKAN_MAX_K + 1];
 };
 
-// Steps 1-4 of Sec. 4.5 for VEC inputs side by side: the arithmetic of locate_one (same operations, same roundings) without
-// its branches.  In(x) is t0 <= x <= tKs under either boundary mode.  The knots above x' are counted by the sign of x' - T
-// (exact; +inf past the last knot), shifted into a word: two instructions a knot and no condition register.  Ten segments
-// are searched without a loop, their knots in scalar registers; more in steps of eight.
-template <int VEC>
-__device__ __forceinline__ void locate_side_by_side(const NarrowArgs &a, const float *s_knots, const float x[VEC], int k[VEC], int l0[VEC], float w[VEC]) {
-  constexpr int kFirst = 9;
-  float xc[VEC];
-#pragma unroll
-  for (int v = 0; v < VEC; ++v) {
-    xc[v] = __builtin_amdgcn_fmed3f(x[v], a.t0, a.tKs) + 0.0f;   // (a NaN comes out inside and is put back in w; -0 becomes
-    unsigned above = 0;                                            // +0, whose difference from a knot at 0 has no sign bit)
-#pragma unroll
-    for (int q = 0; q < kFirst; ++q) above = __builtin_amdgcn_alignbit(above, __float_as_uint(xc[v] - a.inner[q]), 31);
-    k[v] = kFirst - __popc(above);
-  }
-#pragma unroll 1
-  for (int g = kFirst; g < a.K - 1; g += 8) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const float knot = a.inner[min(g + q, LUTKAN_MAX_K - 1)];
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) k[v] += (knot <= xc[v]) ? 1 : 0;
-    }
-  }
-#pragma unroll
-  for (int v = 0; v < VEC; ++v) {
-    const float tk = s_knots[k[v]], tk1 = s_knots[k[v] + 1];
-    const float u = __fdiv_rn(__fsub_rn(xc[v], tk), __fsub_rn(tk1, tk));             // Eq. 15, correctly rounded
-    const float z = __fmul_rn(u, (float)(a.L - 1));                                    // Eq. 16; 0 <= u <= 1
-    const float below = floorf(z);
-    l0[v] = (int)below;
-    w[v] = (x[v] != x[v]) ? __builtin_nanf("") : __fsub_rn(z, below);
-  }
-}
-
 // lane `from` of every group of LPR lanes, to all lanes of the group (LPR = 1, 2, 4, 8)
 template <int LPR, int from>
 __device__ __forceinline__ unsigned from_lane(unsigned v) {

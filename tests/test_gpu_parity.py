@@ -1403,3 +1403,46 @@ def test_narrow_layer_locates_bit_exactly():
         # (the running sums carry 2^-24, so a value below 2^-126 * 2^24 -- a weight next to the knot at 0 -- may be flushed)
         flushed = (expect < 2.0 ** -102) & (y.double().abs() <= expect)
         assert torch.equal(torch.where(flushed, expect, y.double()), expect.expand(-1, width))
+
+
+# ---------------------------------------------------------------- a few rows in one launch
+ROWS_CASES = [
+    # seed, d, m, G, L, scheme, boundary, oob, B, with_base, fp16, per_input: every tile width; one and several rounds of inputs
+    (951, 256, 256, 8, 64, SYM_INT8, CLOSED, CLIP_X, 1, False, False, False),
+    (952, 257, 300, 7, 48, ASYM_UINT8, HALF_OPEN, ZERO_SPLINE, 30, False, True, False),     # one input over a round
+    (953, 2048, 33, 5, 16, SYM_INT8, CLOSED, ZERO_SPLINE, 17, False, False, False),        # the most inputs
+    (954, 65, 70, 13, 32, ASYM_UINT8, CLOSED, CLIP_X, 500, True, False, False),            # four rows per work-group; 13 segments
+    (955, 300, 128, 5, 32, SYM_INT8, HALF_OPEN, CLIP_X, 203, False, False, True),          # one knot vector per input
+    (956, 1500, 3, 6, 16, ASYM_UINT8, HALF_OPEN, ZERO_SPLINE, 9, True, False, False),      # 4-column tile
+    (957, 1100, 30, 5, 64, SYM_INT8, CLOSED, CLIP_X, 20, False, True, False),              # binary16 parameter rows
+    (958, 600, 10, 64, 4, ASYM_UINT8, CLOSED, ZERO_SPLINE, 33, False, True, True),
+    (959, 1030, 6, 5, 32, SYM_INT8, HALF_OPEN, ZERO_SPLINE, 5, False, False, False),       # 8-column tile
+]
+
+
+@pytest.mark.parametrize("case", ROWS_CASES, ids=lambda c: f"seed{c[0]}")
+def test_few_rows_in_one_launch(case):
+    """Against the oracle and its OOB counters, with NaN, infinite and zero (of both signs) inputs."""
+    seed, d, m, G, L, scheme, boundary, oob, B, with_base, fp16, per_input = case
+    make = per_input_layer if per_input else random_layer
+    w = make(seed, d, m, G, L, scheme, boundary, oob, B, with_base=with_base)
+    s, x = w.layers[0], w.x
+    if B > 8:
+        x[1, :] = -0.0
+        x[2, 0] = np.nan
+        if not with_base:                                  # (an infinite base branch: only its class is defined)
+            x[3, d - 1] = np.inf
+            x[B - 1, d // 2] = -np.inf
+    art, ora = _compile_both(s, fp16)
+    layer = _device_layer(art, s)
+    _say(f"case rows d={d} m={m} K={G} L={L} scheme={scheme} boundary={boundary} oob={oob} B={B} base={with_base} fp16={fp16} per_input={per_input}")
+    xg = torch.from_numpy(x).to(DEV)
+    stats = torch.zeros(2, dtype=torch.int64, device=DEV)
+    y = lk.lutkan_forward(layer, xg, stats=stats)
+    assert lk.lutkan_last_plan().startswith("rows wpr="), lk.lutkan_last_plan()
+    y_again = lk.lutkan_forward(layer, xg)
+    torch.cuda.synchronize()
+    ref = oracle.lut_forward(ora, s.boundary, s.oob, x, trace=True, edge_scalars=s.edge_scales)
+    _assert_close(y.cpu().numpy(), ref, f"rows {w.name}")
+    assert np.array_equal(y.cpu().numpy(), y_again.cpu().numpy(), equal_nan=True)
+    assert stats.cpu().tolist() == [ref.oob_count, ref.oob_any_rows]
