@@ -1465,14 +1465,23 @@ extern "C" int lutkan_forward_trace(const lutkan_dev_layer *layer, const float *
                       workspace_bytes, hip_stream, "lutkan_forward_trace");
 }
 
+namespace {
+// Workspace of a chain: two activation buffers of *act bytes, then *scratch bytes for the layer that needs most.
+size_t model_workspace(const lutkan_dev_layer *layers, int32_t n_layers, int64_t B, size_t *act, size_t *scratch) {
+  *act = 0;
+  *scratch = 0;
+  for (int l = 0; l < n_layers; ++l) {
+    if (l + 1 < n_layers) *act = std::max(*act, (size_t)round_up((int64_t)layers[l].m * B * 4, 256));
+    *scratch = std::max(*scratch, lutkan_forward_workspace_bytes(&layers[l], B));
+  }
+  return 2 * *act + *scratch;
+}
+}  // namespace
+
 extern "C" size_t lutkan_model_workspace_bytes(const lutkan_dev_layer *layers, int32_t n_layers, int64_t B) {
   if (!layers || n_layers < 1 || B <= 0) return 0;
-  size_t act = 0, scratch = 0;
-  for (int l = 0; l < n_layers; ++l) {
-    if (l + 1 < n_layers) act = std::max(act, (size_t)round_up((int64_t)layers[l].m * B * 4, 256));
-    scratch = std::max(scratch, lutkan_forward_workspace_bytes(&layers[l], B));
-  }
-  return 2 * act + scratch;
+  size_t act, scratch;
+  return model_workspace(layers, n_layers, B, &act, &scratch);
 }
 
 extern "C" int lutkan_chain_forward(const lutkan_dev_layer *layers, int32_t n_layers, const float *x, int64_t B, float *y,
@@ -1492,14 +1501,10 @@ extern "C" int lutkan_model_forward(const lutkan_dev_layer *layers, int32_t n_la
     if (layers[l].m != layers[l + 1].d) return fail(LUTKAN_ESHAPE, "%s: layer %d has m=%d but layer %d has d=%d", who, l, layers[l].m, l + 1, layers[l + 1].d);
   if (B < 0) return fail(LUTKAN_EINVAL, "%s: B < 0", who);
   if (B == 0) return LUTKAN_OK;
-  const size_t need = lutkan_model_workspace_bytes(layers, n_layers, B);
+  size_t act, scratch;
+  const size_t need = model_workspace(layers, n_layers, B, &act, &scratch);
   if (!workspace || workspace_bytes < need) return fail(LUTKAN_ESHAPE, "%s: workspace of %zu bytes, need %zu", who, workspace_bytes, need);
   if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return fail(LUTKAN_EINVAL, "%s: workspace must be 256-byte aligned", who);
-  size_t act = 0, scratch = 0;
-  for (int l = 0; l < n_layers; ++l) {
-    if (l + 1 < n_layers) act = std::max(act, (size_t)round_up((int64_t)layers[l].m * B * 4, 256));
-    scratch = std::max(scratch, lutkan_forward_workspace_bytes(&layers[l], B));
-  }
   // Every layer would run as its own launch of the chain kernel: run them as one launch of it instead.  The
   // arithmetic per layer is the same, so the result is bit-identical to the layer-by-layer calls.
   bool all_small = (n_layers <= kChainMaxLayers);

@@ -1446,3 +1446,27 @@ def test_few_rows_in_one_launch(case):
     _assert_close(y.cpu().numpy(), ref, f"rows {w.name}")
     assert np.array_equal(y.cpu().numpy(), y_again.cpu().numpy(), equal_nan=True)
     assert stats.cpu().tolist() == [ref.oob_count, ref.oob_any_rows]
+
+
+def test_calls_run_on_torchs_current_stream():
+    """The stream handle that a call gets is the current stream's, on the default stream and on others, and work queued
+    there before the call is seen by it."""
+    from paper_2601_03332_amd import binding
+    dev = torch.empty(1, device=DEV).device
+    assert binding._stream(dev) == torch.cuda.current_stream(dev).cuda_stream
+    w = random_layer(971, 40, 70, 5, 16, SYM_INT8, CLOSED, CLIP_X, 64)
+    layer = _device_layer(_compile_both(w.layers[0])[0], w.layers[0])
+    xg = torch.from_numpy(w.x).to(DEV)
+    expect = lk.lutkan_forward(layer, xg)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream(dev)
+    with torch.cuda.stream(side):
+        assert binding._stream(dev) == side.cuda_stream == torch.cuda.current_stream(dev).cuda_stream
+        late = torch.zeros_like(xg)
+        for _ in range(20):
+            late.add_(1.0)
+        late.copy_(xg)
+        y = lk.lutkan_forward(layer, late)
+    side.synchronize()
+    assert binding._stream(dev) == torch.cuda.current_stream(dev).cuda_stream
+    assert torch.equal(y, expect)
