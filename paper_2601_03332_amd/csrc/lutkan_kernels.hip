@@ -32,9 +32,11 @@ struct LocateArgs {
   int64_t B, Bp;
   int32_t d, K, L;
   int32_t closed, zero_spline;
-  float tKs;             // safe upper clip value
+  float t0, tKs;         // the clip range: first knot, safe upper clip value
+  float masked_below, masked_above;      // zero_spline: inputs outside contribute nothing; clip_x: -inf, +inf
+  float inner[LUTKAN_MAX_K];             // the inner knots T[1] .. T[K-1], +inf past the last
   float knots[LUTKAN_MAX_K + 1];
-  const float *input_knots;    // [d][K+1]: one knot vector per input (then knots and tKs are not used)
+  const float *input_knots;    // [d][K+1]: one knot vector per input (then the knots and bounds above are not used)
   int32_t *k_out, *l0_out;     // nullable trace outputs, [B][d]
   uint8_t *in_out;
   float *w_out;
@@ -42,19 +44,22 @@ struct LocateArgs {
                                // operand of the base branch when it runs as a matrix product of its own
 };
 
-constexpr int kLocTile = 2048;  // (row, input) pairs per block of the LUT locate kernel: 256 threads x 8
-
-// One block locates a tile of ROWS rows x COLS inputs (ROWS * COLS = 2048; COLS = 64, 32 or 16 so that narrow layers
-// do not idle most lanes): x is read along inputs (coalesced), every thread locates eight elements, the records are
+// One block locates a tile of ROWS rows x COLS inputs (COLS = 64, 32 or 16 so that narrow layers do not idle most lanes;
+// ROWS * COLS = 256 E): x is read along inputs (coalesced), every thread locates E elements side by side, the records are
 // transposed through LDS and written along rows (coalesced): records are stored [input][row].
-// blockIdx.x = row tile, blockIdx.y = input tile, so small batches still fill the GPU.
+// blockIdx.x = row tile, blockIdx.y = input tile, so small batches still fill the GPU: E = 8 where that makes at least two
+// blocks per compute unit, else 2 (256 rows of 1024 inputs: 9.3 -> 5.0 us, with a plan's own padding instead of 1024 rows; 1000
+// rows of 200 inputs with knots of their own 8.7 -> 4.4).
+// Bound: HBM (4 bytes read, 8 or 16 written per element) at large sizes: 32768 rows of 1024 inputs 86 -> 75 us, 5.4 TB/s, 16384 of
+// 256 16.4 -> 13.4, against a knot loop of one compare, add and branch at a time, whose vector work (0.66 - 0.8 of the issue
+// slots) no longer hid behind the copies.
 // BASE: value_repr = spline_component, the record also carries SiLU(x).
 // PERIN: one knot vector per input; the block keeps the vectors of its COLS inputs in LDS (odd row stride, so lanes
 // that read the same knot index of different inputs hit different banks).
-template <bool BASE, int COLS, bool PERIN>
+template <bool BASE, int COLS, bool PERIN, int E>
 __global__ __launch_bounds__(256) void lutkan_locate_kernel(const LocateArgs a) {
   typedef typename std::conditional<BASE, u32x4, u32x2>::type rec_t;
-  constexpr int ROWS = kLocTile / COLS;
+  constexpr int ROWS = 256 * E / COLS;
   constexpr int ROW_GROUPS = 256 / COLS;                 // rows handled side by side in phase 1
   constexpr int KSTRIDE = LUTKAN_MAX_K + 1;
   static_assert(KSTRIDE % 2 == 1, "odd stride between the knot rows");
@@ -75,56 +80,71 @@ __global__ __launch_bounds__(256) void lutkan_locate_kernel(const LocateArgs a) 
   const unsigned masked_index = (unsigned)(a.K * a.L) | ((unsigned)a.K << 16);
   const int il = tid % COLS;
   const int i = i0 + il;
-  float xv[8];
+  float xv[E];
 #pragma unroll
-  for (int p = 0; p < 8; ++p) {                          // all eight loads in flight before the first is used
+  for (int p = 0; p < E; ++p) {                          // all loads in flight before the first is used
     const int64_t b = b0 + p * ROW_GROUPS + tid / COLS;
     xv[p] = (b < a.B && i < a.d) ? a.x[b * a.d + i] : 0.0f;
   }
   __syncthreads();                                       // s_knots is filled
+  // table row, segment, weight and mask of every element; the trace takes its outputs from the one-element form, which
+  // also keeps the sign of a zero weight
+  unsigned index[E];
+  float weight[E];
+  if (PERIN || a.k_out) {
 #pragma unroll
-  for (int p = 0; p < 8; ++p) {
-    const int bl = p * ROW_GROUPS + tid / COLS;
-    const int64_t b = b0 + bl;
-    rec_t rec = {};
-    rec.x = masked_index;
-    if (b < a.B && i < a.d) {
-      const float x = xv[p];
-      const Located o = locate_one<PERIN>(a, s_knots + (PERIN ? il * KSTRIDE : 0), x);
+    for (int p = 0; p < E; ++p) {
+      const Located o = locate_one<PERIN>(a, s_knots + (PERIN ? il * KSTRIDE : 0), xv[p]);
       const bool masked = a.zero_spline && !o.inside && !o.is_nan;
-      if (!masked) {
-        rec.x = (unsigned)(o.k * a.L + o.l0) | ((unsigned)o.k << 16);
-        rec.y = __float_as_uint(o.is_nan ? __builtin_nanf("") : o.w);
-      }
-      // base branch b(x) = SiLU(x) = x / (1 + exp(-x)) at the RAW input (Eq. 2); it is never masked (Sec. 5.4)
-      if constexpr (BASE) rec.z = __float_as_uint(__fdiv_rn(x, 1.0f + expf(-x)));
-      else if (a.silu_pieces) {
-        unsigned h, m, lo;
-        lutkan_cut3(__fdiv_rn(x, 1.0f + expf(-x)), h, m, lo);
-        uint16_t *dst = a.silu_pieces + b * a.d + i;
-        dst[0] = (uint16_t)h;
-        dst[a.Bp * a.d] = (uint16_t)m;
-        dst[2 * a.Bp * a.d] = (uint16_t)lo;
-      }
-      if (a.k_out) {
+      index[p] = masked ? masked_index : ((unsigned)(o.k * a.L + o.l0) | ((unsigned)o.k << 16));
+      weight[p] = masked ? 0.0f : o.is_nan ? __builtin_nanf("") : o.w;
+      const int64_t b = b0 + p * ROW_GROUPS + tid / COLS;
+      if (a.k_out && b < a.B && i < a.d) {
         a.k_out[b * a.d + i] = o.k;
         a.l0_out[b * a.d + i] = o.l0;
         a.in_out[b * a.d + i] = o.inside ? 1 : 0;
         a.w_out[b * a.d + i] = o.w;
       }
     }
-    else if (!BASE && a.silu_pieces && i < a.d) {          // a padding row: zero pieces, so that the product needs no row checks
-      uint16_t *dst = a.silu_pieces + b * a.d + i;
-      dst[0] = 0;
-      dst[a.Bp * a.d] = 0;
-      dst[2 * a.Bp * a.d] = 0;
+  } else {
+    int k[E], l0[E];
+    locate_side_by_side<E>(a, s_knots, xv, k, l0, weight);
+#pragma unroll
+    for (int p = 0; p < E; ++p) {
+      const bool masked = (xv[p] < a.masked_below) | (xv[p] > a.masked_above);
+      unsigned located = (unsigned)(k[p] * a.L + l0[p]) | ((unsigned)k[p] << 16);
+      asm("" : "+v"(located));             // (computed for every lane: a select, not a branch)
+      index[p] = masked ? masked_index : located;
+      weight[p] = masked ? 0.0f : weight[p];
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < E; ++p) {
+    const int bl = p * ROW_GROUPS + tid / COLS;
+    const int64_t b = b0 + bl;
+    const bool live = b < a.B && i < a.d;
+    rec_t rec = {};
+    rec.x = live ? index[p] : masked_index;
+    rec.y = live ? __float_as_uint(weight[p]) : 0u;
+    // base branch b(x) = SiLU(x) = x / (1 + exp(-x)) at the RAW input (Eq. 2); it is never masked (Sec. 5.4)
+    if constexpr (BASE) {
+      rec.z = live ? __float_as_uint(__fdiv_rn(xv[p], 1.0f + expf(-xv[p]))) : 0u;
+    } else if (a.silu_pieces && i < a.d) {                 // (a padding row: zero pieces, so that the product needs no row checks)
+      unsigned h = 0, m = 0, lo = 0;
+      if (b < a.B) lutkan_cut3(__fdiv_rn(xv[p], 1.0f + expf(-xv[p])), h, m, lo);
+      if (b < a.Bp) {
+        uint16_t *dst = a.silu_pieces + b * a.d + i;
+        dst[0] = (uint16_t)h;
+        dst[a.Bp * a.d] = (uint16_t)m;
+        dst[2 * a.Bp * a.d] = (uint16_t)lo;
+      }
     }
     s_rec[il][bl] = rec;
   }
   __syncthreads();
   const int bl2 = tid % ROWS;
 #pragma unroll
-  for (int p = 0; p < 8; ++p) {
+  for (int p = 0; p < E; ++p) {
     const int il2 = p * (256 / ROWS) + tid / ROWS;
     const int i2 = i0 + il2;
     if (i2 < a.d && b0 + bl2 < a.Bp) rec_out[(int64_t)i2 * a.Bp + b0 + bl2] = s_rec[il2][bl2];
@@ -1002,11 +1022,25 @@ bool tiled_supported(int jt, int blob_bytes, int value_repr) {
 }
 
 
+template <bool BASE, bool PERIN, int E>
+void launch_locate_tile(int cols, dim3 grid, hipStream_t s, const LocateArgs &la) {
+  if (cols == 64) hipLaunchKernelGGL((lutkan_locate_kernel<BASE, 64, PERIN, E>), grid, dim3(256), 0, s, la);
+  else if (cols == 32) hipLaunchKernelGGL((lutkan_locate_kernel<BASE, 32, PERIN, E>), grid, dim3(256), 0, s, la);
+  else hipLaunchKernelGGL((lutkan_locate_kernel<BASE, 16, PERIN, E>), grid, dim3(256), 0, s, la);
+}
+
 template <bool BASE, bool PERIN>
-void launch_locate(int cols, dim3 grid, hipStream_t s, const LocateArgs &la) {
-  if (cols == 64) hipLaunchKernelGGL((lutkan_locate_kernel<BASE, 64, PERIN>), grid, dim3(256), 0, s, la);
-  else if (cols == 32) hipLaunchKernelGGL((lutkan_locate_kernel<BASE, 32, PERIN>), grid, dim3(256), 0, s, la);
-  else hipLaunchKernelGGL((lutkan_locate_kernel<BASE, 16, PERIN>), grid, dim3(256), 0, s, la);
+int launch_locate(hipStream_t s, const LocateArgs &la, const char *who) {
+  // inputs per block: the width in {64, 32, 16} that pads d least (the widest on ties: longer runs of x)
+  int cols = 64;
+  for (int c = 32; c >= 16; c >>= 1)
+    if ((la.d + c - 1) / c * c < (la.d + cols - 1) / cols * cols) cols = c;
+  const unsigned col_tiles = (unsigned)((la.d + cols - 1) / cols);
+  if (col_tiles > 65535u) return fail(LUTKAN_EUNSUPPORTED, "%s: d too large", who);
+  const int64_t row_tiles = (la.Bp + 2048 / cols - 1) / (2048 / cols);
+  if (row_tiles * col_tiles >= 512) launch_locate_tile<BASE, PERIN, 8>(cols, dim3((unsigned)row_tiles, col_tiles), s, la);
+  else launch_locate_tile<BASE, PERIN, 2>(cols, dim3((unsigned)((la.Bp + 512 / cols - 1) / (512 / cols)), col_tiles), s, la);
+  return check_launch("lutkan_locate_kernel");
 }
 
 // The fused chain: validation, kernel arguments and launch (the body of lutkan_chain_forward; lutkan_forward also
@@ -1104,7 +1138,6 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   if (phases == (kLocate | kEdges) && !trace && !q01_out && small_layer_runs_as_chain(l, B))
     return chain_impl(l, 1, x, B, y, nullptr, stats, hip_stream, who);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  const int64_t Bp = padded_rows(B);
   const lutkan::BlobLayout lay = lutkan::blob_layout(l->K, l->L, l->jt, l->scheme, l->value_repr, l->param_dtype);
 
   // Which edge kernel runs, and how the base branch of a spline_component layer is evaluated, follow from the layer
@@ -1136,6 +1169,9 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   const bool wide = can_wide && ((tpw.cost < tp.cost && (wide_cb == 4 || l->scheme == LUTKAN_SYM_INT8)) || l->algo == LUTKAN_ALGO_TILED_WIDE);
   if (l->algo == LUTKAN_ALGO_TILED_WIDE && !wide)
     return fail(LUTKAN_EUNSUPPORTED, "%s: algo TILED_WIDE on a layer %s", who, l->wide_table ? "whose base branch runs inside the edge kernel (16-byte records: fp32 values of at most 64 KiB per slice only)" : "without a wide table");
+  // Rows that get records: whole row tiles of the edge kernel that follows (256 of the gather kernels), and of the product's
+  // 128; at most padded_rows(B), which the workspace has room for.
+  const int64_t Bp = round_up(B, tiled ? std::max(128, kTileWaves * (64 / (l->jt / 4)) * (wide ? tpw.np : tp.np)) : 256);
   // workspace: [records: room for 16 bytes each with the base branch; 8-byte records leave room for the 6 bytes per
   // (row, input) of the SiLU pieces behind them] [pieces of s_out*s_base, spline_component only] [partial sums]
   char *const ws_bytes = static_cast<char *>(workspace);
@@ -1171,24 +1207,18 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   la.closed = (l->boundary == LUTKAN_CLOSED);
   la.zero_spline = (l->oob == LUTKAN_ZERO_SPLINE);
   la.tKs = la.closed ? l->knots[l->K] : std::nextafterf(l->knots[l->K], -INFINITY);
+  la.t0 = l->knots[0];
+  la.masked_below = la.zero_spline ? la.t0 : -INFINITY;
+  la.masked_above = la.zero_spline ? la.tKs : INFINITY;
   for (int k = 0; k <= l->K; ++k) la.knots[k] = l->knots[k];
+  for (int k = 0; k < LUTKAN_MAX_K; ++k) la.inner[k] = (k + 1 < l->K) ? l->knots[k + 1] : INFINITY;
   la.input_knots = l->knots_per_input ? l->input_knots : nullptr;
   la.k_out = trace ? k_out : nullptr; la.l0_out = l0_out; la.in_out = in_out; la.w_out = w_out;
   if (phases & kLocate) {
-    // inputs per block: the width in {64, 32, 16} that pads d least (the widest on ties: longer runs of x)
-    int cols = 64;
-    for (int c = 32; c >= 16; c >>= 1)
-      if ((l->d + c - 1) / c * c < (l->d + cols - 1) / cols * cols) cols = c;
-    const dim3 lgrid((unsigned)(Bp / (kLocTile / cols)), (unsigned)((l->d + cols - 1) / cols));
-    if (lgrid.y > 65535u) return fail(LUTKAN_EUNSUPPORTED, "%s: d too large", who);
-    if (l->knots_per_input) {
-      if (rec_bytes == 16) launch_locate<true, true>(cols, lgrid, s, la);
-      else launch_locate<false, true>(cols, lgrid, s, la);
-    } else {
-      if (rec_bytes == 16) launch_locate<true, false>(cols, lgrid, s, la);
-      else launch_locate<false, false>(cols, lgrid, s, la);
-    }
-    if (int rc = check_launch("lutkan_locate_kernel")) return rc;
+    int rc;
+    if (l->knots_per_input) rc = rec_bytes == 16 ? launch_locate<true, true>(s, la, who) : launch_locate<false, true>(s, la, who);
+    else rc = rec_bytes == 16 ? launch_locate<true, false>(s, la, who) : launch_locate<false, false>(s, la, who);
+    if (rc) return rc;
     lutkan::plan_note("locate; ");
     if (stats) {
       if (int rc = count_oob(l, x, B, stats, s)) return rc;

@@ -288,7 +288,7 @@ NarrowPlan narrow_plan(const lutkan_dev_layer *l, int64_t B, size_t workspace_by
   if (!stage) return best;
   const int lpr = l->jt / 4, vec = kBlock / lpr;
   const double instructions = (l->scheme == LUTKAN_ASYM_UINT8 ? 150 : 132) + 45 * vec + (lpr == 8 ? 56 : 0) + (base ? 60 + 25 * vec : 0);
-  for (int waves = 16; waves >= 4; waves -= 12) {
+  for (int waves = 4; waves <= 16; waves += 12) {          // (fewer on a tie: their barriers hold up less; 64 -> 8 at 131072 rows 30 against 33)
     const int64_t groups = (B + (int64_t)waves * (64 / lpr) - 1) / ((int64_t)waves * (64 / lpr));
     const int resident = (int)std::min<size_t>(32 / waves, kMaxTiledLds / narrow_lds_bytes(stage, l->blob_bytes));
     for (int want = 1; want <= 64; ++want) {
