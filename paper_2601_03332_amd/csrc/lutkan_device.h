@@ -60,12 +60,17 @@ __device__ __forceinline__ float next_float_below(float t) {
 // 1.3 % slower on the widest layer).
 constexpr bool kLdsDmaPreservesM0 = false;
 
+// ONCE: the data is read by this work-group alone and never again in the launch: the load is marked non-temporal, so that it
+// does not push what others keep (and dirty lines that must be written back) out of the caches.
+template <bool ONCE = false>
 __device__ __forceinline__ void copy16_global_to_lds_at(const void *uniform_base, unsigned lane_byte_offset, void *lds_dst) {
   const unsigned dst = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)lds_dst);
   if constexpr (kLdsDmaPreservesM0) {
     unsigned saved;
     asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
                  : "=&s"(saved) : "s"(dst), "v"(lane_byte_offset), "s"(uniform_base) : "memory");
+  } else if constexpr (ONCE) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(dst), "v"(lane_byte_offset), "s"(uniform_base) : "m0", "memory");
   } else {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane_byte_offset), "s"(uniform_base) : "m0", "memory");
   }
@@ -97,12 +102,12 @@ __device__ __forceinline__ void lds_barrier() {
 // Copies n16 16-byte vectors from gsrc (wave-uniform) to lds_dst with all NW waves of the work-group, 1 KiB per wave
 // step: wave w takes the whole chunks w, w + NW, ...; the last, partial chunk goes to the wave whose turn it is.
 // lane_off = 16 * lane.
-template <int NW>
+template <int NW, bool ONCE = false>
 __device__ __forceinline__ void stage_slice(const unsigned char *gsrc, unsigned char *lds_dst, int n16, int wave, int lane, unsigned lane_off) {
   const int whole = n16 >> 6;
-  for (int c = wave; c < whole; c += NW) copy16_global_to_lds_at(gsrc + c * 1024, lane_off, lds_dst + c * 1024);
+  for (int c = wave; c < whole; c += NW) copy16_global_to_lds_at<ONCE>(gsrc + c * 1024, lane_off, lds_dst + c * 1024);
   const int tail = n16 & 63;
-  if (tail != 0 && wave == (whole % NW) && lane < tail) copy16_global_to_lds_at(gsrc + whole * 1024, lane_off, lds_dst + whole * 1024);
+  if (tail != 0 && wave == (whole % NW) && lane < tail) copy16_global_to_lds_at<ONCE>(gsrc + whole * 1024, lane_off, lds_dst + whole * 1024);
 }
 
 // Sums the n_split partial outputs of the tiled kernels in ascending chunk order (deterministic): y = sum_s part[s],
@@ -170,6 +175,7 @@ struct TilePlan {
   int np, n_split, chunk;
   double cost;       // the model's estimate for the launch (and its summing pass), microseconds
   bool hbm_bound;    // the estimate is the time the table takes to stream from HBM, not the work-groups' own time
+  bool reads_once;   // one row tile on a table that the last-level cache (256 MiB) does not hold: every slice is read once
 };
 
 // code_bytes: 1 for the table as compiled; 2 or 4 when the slices are those of a wide form of the table, whose row
@@ -178,7 +184,7 @@ inline double row_step_us(int code_bytes) { return code_bytes == 4 ? 0.070 : cod
 TilePlan plan_tiles(int64_t B, int d, int m, int n_tiles, int rps, int slice_bytes, int code_bytes = 1) {
   const int np_max = std::min(16, 64 / rps);
   const int max_split = std::max(1, std::min(128, d / 8));
-  TilePlan best{np_max, 1, d, 1e300, false};
+  TilePlan best{np_max, 1, d, 1e300, false, false};
   double best_cost = 1e300;
   // a table beyond what the caches hold streams from HBM once per launch: about 21 GB/s per streaming work-group,
   // 5.3 TB/s for the whole chip
@@ -214,7 +220,7 @@ TilePlan plan_tiles(int64_t B, int d, int m, int n_tiles, int rps, int slice_byt
         cost = std::max(cost, stream) + 0.01 * np;
       }
       if (split > 1) cost += 4.0 + (double)split * (double)B * m * 4.0 / 3e6;
-      if (cost < best_cost) { best_cost = cost; best = TilePlan{np, split, chunk, cost, hbm_bound}; }
+      if (cost < best_cost) { best_cost = cost; best = TilePlan{np, split, chunk, cost, hbm_bound, B <= rows && table_bytes > 256.0 * 1024 * 1024}; }
     }
   }
   return best;

@@ -207,6 +207,7 @@ struct EdgeArgs {
   int32_t accumulate;      // tiled kernel writing y itself (one chunk): add to what y holds (the base branch) instead of overwriting
   int32_t wide;            // tiled kernel: 2 or 4 when table, blob_bytes and the offsets describe a wide form (bytes per code), else 0
   int32_t deep;            // tiled kernel: the launch waits for the table to stream from HBM; keep two slices in flight
+  int32_t reads_once;      // tiled kernel, deep: every slice is read by one work-group only, from HBM; its copies are marked non-temporal
   int32_t asym;            // the layer's scheme is asymmetric uint8 (a second parameter plane)
 };
 
@@ -487,7 +488,13 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
 
   // copies slice (t, i) and this wave's records of input i into buffer `buf`
   auto stage_input = [&](int i, int buf) {
-    stage_slice<NW>(src + (size_t)i * a.blob_bytes, lds + buf * a.blob_bytes, nvec, wave, lane, lane_off);
+    // a table that streams from HBM for one row tile alone: 1024x1024 (686 MiB) at 256 rows 136 -> 121 us, 6.5 TB/s; with the
+    // caches full of written data 191 -> 126.  Where several row tiles share the slices through the L2s it costs 3 - 5 %
+    // (1024x700 at 1000 rows), and a table of up to 256 MiB may still lie in the last-level cache from the call before
+    // (512x512, 187 MiB, at 256 rows 42 -> 48): there the copies are ordinary.  (In PIPE 3 the choice alone cost 1.5 % of
+    // the widest layer at 32768 rows.)
+    if (DEEP && a.reads_once) stage_slice<NW, true>(src + (size_t)i * a.blob_bytes, lds + buf * a.blob_bytes, nvec, wave, lane, lane_off);
+    else stage_slice<NW>(src + (size_t)i * a.blob_bytes, lds + buf * a.blob_bytes, nvec, wave, lane, lane_off);
     if (lane < REC_LANES) copy16_global_to_lds_at(rec_src + (int64_t)i * a.Bp * RB, lane_off, rec_area + buf * (RW * RB));
   };
   stage_input(i_begin, 0);
@@ -927,7 +934,8 @@ int validate_layer(const lutkan_dev_layer *l, const char *who) {
 // (up to 128 MiB): when the bytes the lanes request (per row, input and column tile two code rows and one parameter
 // row) stay below the table's (measured: 256x256 near 128 rows).  A larger table streams from HBM on every tiled
 // launch, and scattered reads of it pay off for longer: the gather kernel is priced at 8 us plus the requested bytes
-// at 9.4 TB/s, the tiled launch at the estimate of its launch planning (measured: 1024x1024 between 128 and 256 rows).
+// at 9.4 TB/s, the tiled launch at the estimate of its launch planning, 0.84 of it where it reads every slice once (measured:
+// 1024x1024 between 130 rows, gather 110 us, tiled 121, and 200, 154 and 121).
 bool prefer_gather_for_small_batch(const lutkan_dev_layer *l, int64_t B, double tiled_cost_us) {
   const lutkan::BlobLayout lay = lutkan::blob_layout(l->K, l->L, l->jt, l->scheme, l->value_repr, l->param_dtype);
   const double touched = (double)B * l->d * l->n_tiles * (2.0 * l->jt + (double)lay.param_row_bytes);
@@ -1145,8 +1153,8 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   const bool with_base = (l->value_repr == LUTKAN_REPR_SPLINE_COMPONENT);
   bool tiled = tiled_supported(l->jt, l->blob_bytes, l->value_repr) && !q01_out;
   if (l->algo == LUTKAN_ALGO_GATHER) tiled = false;
-  const TilePlan tp = tiled ? plan_tiles(B, l->d, l->m, l->n_tiles, 64 / (l->jt / 4), l->blob_bytes) : TilePlan{1, 1, l->d, 0.0, false};
-  if (l->algo == LUTKAN_ALGO_AUTO && tiled && prefer_gather_for_small_batch(l, B, tp.cost)) tiled = false;
+  const TilePlan tp = tiled ? plan_tiles(B, l->d, l->m, l->n_tiles, 64 / (l->jt / 4), l->blob_bytes) : TilePlan{1, 1, l->d, 0.0, false, false};
+  if (l->algo == LUTKAN_ALGO_AUTO && tiled && prefer_gather_for_small_batch(l, B, tp.hbm_bound && tp.reads_once ? 0.84 * tp.cost : tp.cost)) tiled = false;
   const bool tiled_asked_for = (l->algo == LUTKAN_ALGO_TILED || l->algo == LUTKAN_ALGO_TILED_WIDE);
   if (tiled_asked_for && !tiled) return fail(LUTKAN_EUNSUPPORTED, "%s: tiled kernel needs a table slice <= 72 KiB (64 KiB with the base branch)%s", who, q01_out ? " and writes no code trace" : "");
   // Base branch as a matrix product of its own (SiLU(X) times the s_out*s_base of the table's base rows, into y) with
@@ -1237,6 +1245,7 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   ea.accumulate = 0;
   ea.wide = 0;
   ea.deep = 0;
+  ea.reads_once = 0;
   ea.asym = (l->scheme == LUTKAN_ASYM_UINT8);
   ea.chunk = l->d;
   ea.split_stride = 0;
@@ -1257,6 +1266,7 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
     }
     ea.chunk = plan.chunk;
     ea.deep = plan.hbm_bound ? 1 : 0;
+    ea.reads_once = plan.reads_once ? 1 : 0;
     if (plan.n_split > 1) { ea.y = partials; ea.split_stride = B * l->m; }
     ea.accumulate = (base_by_product && plan.n_split == 1) ? 1 : 0;     // with chunks, the summing pass adds to y instead
     const int rc = (l->scheme == LUTKAN_SYM_INT8) ? launch_tiled_jt<LUTKAN_SYM_INT8>(ea, plan.np, s) : launch_tiled_jt<LUTKAN_ASYM_UINT8>(ea, plan.np, s);
