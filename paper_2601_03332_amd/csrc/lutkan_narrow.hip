@@ -22,7 +22,7 @@
 // lane locates, at 6.2 cycles per instruction and SIMD with four waves (the 16-byte code rows of 16 rows collide in the
 // LDS banks).  Whole layers, locate + tiled + sum -> this kernel, microseconds: 78 -> 16, uint8 codes, L = 64, at 65536 rows
 // 49 -> 33; 16 -> 2 at 131072 rows 24 -> 11; 64 -> 8 at 131072 rows, L = 32, 51 -> 30, with spline_component 68 -> 42; 1000 -> 4 at
-// 20000 rows 109 -> 73; 100 -> 30 at 65536 rows 81 -> 66; 300 -> 10 at 1000 rows 19 -> 14.
+// 20000 rows 109 -> 73; 100 -> 30 at 65536 rows 81 -> 56; 300 -> 10 at 1000 rows 19 -> 14.
 // The file is compiled with -ffp-contract=off; every fused multiply-add is written out as fmaf().
 #include "lutkan_device.h"
 #include "lutkan_locate.h"
@@ -278,30 +278,37 @@ int launch_narrow_width(const NarrowArgs &na, int stage, bool base, bool half_pa
 namespace lutkan {
 
 // The launch shape by a cost model (microseconds, constants from 16 -> 2 ... 1000 -> 4 layers at 1000 to 131072 rows): a block
-// of 8 inputs costs a SIMD 6.2 cycles for each of its waves' instructions, at least 13 for each of one wave's (alone on its
-// SIMD a wave waits for its own results: 1000 -> 4 at 65536 rows) and 2000 a stage (the slices' way from L2); a work-group 3 us
-// of fill; as many work-groups share a compute unit as the LDS holds; chunks of inputs add the summing pass.
+// of 8 inputs costs a SIMD 6.2 cycles for each of its waves' instructions (5.2 with the 32-byte code rows, which collide less
+// in the LDS banks: 5.1 to 5.4 measured on 100 -> 30, 128 -> 32 and 200 -> 24; 4.7 if symmetric and eight waves share the
+// SIMD), at least 13 for each of one wave's (alone on its SIMD a wave waits for its own results: 1000 -> 4 at 65536 rows) and
+// 2000 a stage (the slices' way from L2); a work-group 3 us of fill; as many work-groups share a compute unit as the LDS
+// holds; chunks of inputs add the summing pass.  Half the stage where that lets a second symmetric work-group of 32-byte rows
+// share the unit: 100 -> 30, L = 32, at 131072 rows 99 us against 118, at 65536 54 against 60 (unsymmetric codes lose: 128 -> 32
+// 83 against 75).
 NarrowPlan narrow_plan(const lutkan_dev_layer *l, int64_t B, size_t workspace_bytes) {
   NarrowPlan best{0, 1, l->d, 0, 1e300};
-  const bool base = (l->value_repr == LUTKAN_REPR_SPLINE_COMPONENT);
-  const int stage = narrow_stage(l, base);
-  if (!stage) return best;
+  const bool base = (l->value_repr == LUTKAN_REPR_SPLINE_COMPONENT), symmetric = (l->scheme == LUTKAN_SYM_INT8);
+  const int widest = narrow_stage(l, base);
+  if (!widest) return best;
   const int lpr = l->jt / 4, vec = kBlock / lpr;
-  const double instructions = (l->scheme == LUTKAN_ASYM_UINT8 ? 150 : 132) + 45 * vec + (lpr == 8 ? 56 : 0) + (base ? 60 + 25 * vec : 0);
+  const double instructions = (symmetric ? 132 : 150) + 45 * vec + (lpr == 8 ? 56 : 0) + (base ? 60 + 25 * vec : 0);
   for (int waves = 4; waves <= 16; waves += 12) {          // (fewer on a tie: their barriers hold up less; 64 -> 8 at 131072 rows 30 against 33)
     const int64_t groups = (B + (int64_t)waves * (64 / lpr) - 1) / ((int64_t)waves * (64 / lpr));
-    const int resident = (int)std::min<size_t>(32 / waves, kMaxTiledLds / narrow_lds_bytes(stage, l->blob_bytes));
-    for (int want = 1; want <= 64; ++want) {
-      const int chunk = (int)round_up((l->d + want - 1) / want, kBlock);
-      const int split = (l->d + chunk - 1) / chunk;
-      if (split > 1 && (size_t)split * (size_t)B * (size_t)l->m * 4 > workspace_bytes) break;
-      const double per_unit = (double)((groups * split + 255) / 256);                // work-groups per compute unit
-      const double together = std::min((double)resident, per_unit);
-      const double block = std::max(std::max(2000.0 * kBlock / stage, 13.0 * instructions), 6.2 * instructions * together * waves / 4.0) / 2400.0;
-      double cost = std::ceil(per_unit / together) * (3.0 + chunk / kBlock * block);
-      if (split > 1) cost += 4.0 + (double)split * (double)B * l->m * 4.0 / 3e6;
-      if (cost < best.cost) best = NarrowPlan{waves, split, chunk, stage, cost};
-      if (chunk <= kBlock) break;
+    for (int stage = widest; stage >= (symmetric && lpr == 8 && waves == 16 ? 4 : widest); stage -= 4) {
+      const int resident = (int)std::min<size_t>(32 / waves, kMaxTiledLds / narrow_lds_bytes(stage, l->blob_bytes));
+      for (int want = 1; want <= 64; ++want) {
+        const int chunk = (int)round_up((l->d + want - 1) / want, kBlock);
+        const int split = (l->d + chunk - 1) / chunk;
+        if (split > 1 && (size_t)split * (size_t)B * (size_t)l->m * 4 > workspace_bytes) break;
+        const double per_unit = (double)((groups * split + 255) / 256);              // work-groups per compute unit
+        const double together = std::min((double)resident, per_unit);
+        const double cycles = lpr < 8 ? 6.2 : symmetric && together * waves >= 32 ? 4.7 : stage == 4 ? 5.6 : 5.2;
+        const double block = std::max(std::max(2000.0 * kBlock / stage, 13.0 * instructions), cycles * instructions * together * waves / 4.0) / 2400.0;
+        double cost = std::ceil(per_unit / together) * (3.0 + chunk / kBlock * block);
+        if (split > 1) cost += 4.0 + (double)split * (double)B * l->m * 4.0 / 3e6;
+        if (cost < best.cost) best = NarrowPlan{waves, split, chunk, stage, cost};
+        if (chunk <= kBlock) break;
+      }
     }
   }
   return best;

@@ -1348,6 +1348,8 @@ NARROW_CASES = [
     (938, 133, 32, 8, 64, SYM_INT8, CLOSED, CLIP_X, 20000, False, False),
     (939, 131, 15, 30, 8, ASYM_UINT8, CLOSED, CLIP_X, 25000, True, False),         # segments searched in steps of eight
     (940, 300, 10, 64, 4, SYM_INT8, HALF_OPEN, ZERO_SPLINE, 3000, False, False),   # the most segments
+    (941, 100, 30, 8, 32, SYM_INT8, CLOSED, ZERO_SPLINE, 40001, False, False),     # half stages, two work-groups on a unit
+    (942, 100, 30, 8, 32, SYM_INT8, CLOSED, CLIP_X, 40001, False, True),           # the same with binary16 parameters
 ]
 
 
