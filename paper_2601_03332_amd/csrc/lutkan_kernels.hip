@@ -752,6 +752,7 @@ constexpr int kChainWaves = 4;          // the sum over the waves below is writt
 constexpr int kChainMaxLayers = 8;
 constexpr int kChainMaxInputs = 1024;     // widest layer input: its records must fit the LDS record buffer
 constexpr int kChainMaxColumns = 64;      // widest layer output: one lane per column
+constexpr int kChainSplitRows = 1024;     // up to this many rows a whole work-group carries a row, beyond a single wave
 
 struct ChainLayer {
   const unsigned char *table;
@@ -1085,8 +1086,8 @@ int chain_impl(const lutkan_dev_layer *layers, int32_t n_layers, const float *x,
   if (B < 0) return fail(LUTKAN_EINVAL, "%s: B < 0", who);
   if (B == 0) return LUTKAN_OK;
   if (!x || !y || x == y) return fail(LUTKAN_EINVAL, "%s: null or aliased x / y", who);
-  // up to 1024 rows a whole work-group carries a row (the shortest path through a layer); beyond, one wave does
-  const int wpr = (B <= 1024) ? kChainWaves : 1;
+  // a whole work-group is the shortest path through a layer while the chip has room for one per row
+  const int wpr = (B <= kChainSplitRows) ? kChainWaves : 1;
   const int rows_per_group = kChainWaves / wpr;
   const int64_t groups = (B + rows_per_group - 1) / rows_per_group;
   if (groups > 0x7fffffff) return fail(LUTKAN_EUNSUPPORTED, "%s: B too large", who);
@@ -1111,10 +1112,22 @@ int chain_impl(const lutkan_dev_layer *layers, int32_t n_layers, const float *x,
 // few enough rows.  Measured on 16x2 ... 256x16 layers between 8192 and 131072 rows: the chain kernel takes about
 // 4 us + (0.35 + 0.00088 d jt) us per 1000 rows, locate + tiled kernel + summing pass about 17 us + (0.05 + 0.00035 d jt)
 // us per 1000 rows; the chain kernel wins below their crossing, taken a little low (16x2: up to 30000 rows, 78x16:
-// 10000, 64x32: 7000, 256x16: 4000).
+// 10000, 64x32: 7000, 256x16: 4000).  Beyond kChainSplitRows rows, where a single wave walks all inputs of its row, the
+// one-launch kernels that share the walk take the layer where they are priced 3.3 us lower -- what a launch of its own costs
+// it, should the other layers of its network have been one launch with it (microseconds, chain -> those: 100 -> 30 at 1500
+// rows 14.4 -> 8.7, at 5000 22 -> 13; 200 -> 16 at 5000 24 -> 13.5; 1000 -> 4 at 3500 52 -> 22; 78 -> 16 at 10000 19 -> 12.7, at 2000
+// 9.1 against 9.0, left alone).
 bool small_layer_runs_as_chain(const lutkan_dev_layer *l, int64_t B) {
   if (l->algo != LUTKAN_ALGO_AUTO || l->n_tiles != 1 || l->jt > kChainMaxColumns || l->d * l->jt > 4096) return false;
-  return (double)B * (0.30 + 0.00053 * l->d * l->jt) <= 10000.0;
+  if ((double)B * (0.30 + 0.00053 * l->d * l->jt) > 10000.0) return false;
+  if (B <= kChainSplitRows) return true;
+  // a wave's walk: 0.17 us per 64 columns' edges, 0.8 per 64 inputs located; one round of waves up to 1500 rows
+  const double walk = 0.17 * l->d * l->jt / 64 + 0.8 * ((l->d + 63) / 64);
+  const double chain = 3.3 + walk * std::max(1.0, 0.58 + 0.28e-3 * (double)B);
+  double other = lutkan::rows_plan(l, B).cost;
+  if (tiled_supported(l->jt, l->blob_bytes, l->value_repr))
+    other = std::min(other, lutkan::narrow_plan(l, B, lutkan_forward_workspace_bytes(l, B)).cost);
+  return chain <= other + 3.3;
 }
 
 // The OOB counters of a layer's inputs, added to `stats`.
@@ -1545,19 +1558,20 @@ extern "C" int lutkan_model_forward(const lutkan_dev_layer *layers, int32_t n_la
   const size_t need = model_workspace(layers, n_layers, B, &act, &scratch);
   if (!workspace || workspace_bytes < need) return fail(LUTKAN_ESHAPE, "%s: workspace of %zu bytes, need %zu", who, workspace_bytes, need);
   if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return fail(LUTKAN_EINVAL, "%s: workspace must be 256-byte aligned", who);
-  // Every layer would run as its own launch of the chain kernel: run them as one launch of it instead.  The
+  // Consecutive layers that would each run as a launch of the chain kernel run as one launch of it instead.  The
   // arithmetic per layer is the same, so the result is bit-identical to the layer-by-layer calls.
-  bool all_small = (n_layers <= kChainMaxLayers);
-  for (int l = 0; l < n_layers && all_small; ++l) all_small = small_layer_runs_as_chain(&layers[l], B);
-  if (all_small && n_layers > 1) return chain_impl(layers, n_layers, x, B, y, nullptr, stats, hip_stream, who);
   char *base = static_cast<char *>(workspace);
   float *ping[2] = {reinterpret_cast<float *>(base), reinterpret_cast<float *>(base + act)};
   void *rec = base + 2 * act;
   const float *in = x;
-  for (int l = 0; l < n_layers; ++l) {
-    float *out = (l + 1 == n_layers) ? y : ping[l & 1];
-    int rc = forward_impl(&layers[l], in, B, out, stats ? stats + l : nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, false, rec,
-                          scratch, hip_stream, who);
+  for (int l = 0, end; l < n_layers; l = end) {
+    for (end = l; end < n_layers && end - l < kChainMaxLayers && small_layer_runs_as_chain(&layers[end], B);) ++end;
+    const bool fused = end > l + 1;
+    if (!fused) end = l + 1;
+    float *out = (end == n_layers) ? y : (in == ping[0]) ? ping[1] : ping[0];
+    lutkan_oob_stats *const st = stats ? stats + l : nullptr;
+    const int rc = fused ? chain_impl(layers + l, end - l, in, B, out, nullptr, st, hip_stream, who)
+                         : forward_impl(&layers[l], in, B, out, st, nullptr, nullptr, nullptr, nullptr, nullptr, false, rec, scratch, hip_stream, who);
     if (rc) return rc;
     in = out;
   }

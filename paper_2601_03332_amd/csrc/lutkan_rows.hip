@@ -24,6 +24,7 @@ namespace {
 
 constexpr int kRowsWaves = 16;
 constexpr int kRowsMaxInputs = 2048;     // records of four rows in LDS
+constexpr int64_t kRowsMaxBatch = 6144; // beyond, the passes win: 40 -> 60 -> 60 -> 10 at 5000 rows 44 us (48 by passes), at 7500 64 (62)
 
 struct RowsArgs {
   const float *x;                        // [B][d]
@@ -196,7 +197,7 @@ namespace lutkan {
 // of a wave's walk over its inputs, whichever is longer.
 RowsPlan rows_plan(const lutkan_dev_layer *l, int64_t B) {
   RowsPlan best{0, 1e300};
-  if (l->d > kRowsMaxInputs) return best;
+  if (l->d > kRowsMaxInputs || B > kRowsMaxBatch) return best;
   const BlobLayout lay = blob_layout(l->K, l->L, l->jt, l->scheme, l->value_repr, l->param_dtype);
   const double bytes = (double)B * l->n_tiles * l->d * (std::max(128, 2 * l->jt) + std::max(128, lay.param_row_bytes) + (lay.params_off ? std::max(128, lay.params_off) : 0));
   for (int wpr = 16; wpr >= 4; wpr -= 12) {

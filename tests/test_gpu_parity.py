@@ -1350,6 +1350,7 @@ NARROW_CASES = [
     (940, 300, 10, 64, 4, SYM_INT8, HALF_OPEN, ZERO_SPLINE, 3000, False, False),   # the most segments
     (941, 100, 30, 8, 32, SYM_INT8, CLOSED, ZERO_SPLINE, 40001, False, False),     # half stages, two work-groups on a unit
     (942, 100, 30, 8, 32, SYM_INT8, CLOSED, CLIP_X, 40001, False, True),           # the same with binary16 parameters
+    (943, 200, 16, 8, 64, ASYM_UINT8, CLOSED, CLIP_X, 2049, False, False),         # too many rows for one wave to walk each
 ]
 
 
