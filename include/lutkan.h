@@ -44,8 +44,9 @@ typedef enum { LUTKAN_CLIP_X = 0, LUTKAN_ZERO_SPLINE = 1 } lutkan_oob;          
  * few rows that they touch less than the whole table (then gather), and except for a small narrow layer (one column
  * tile, d * jt <= 4096) at up to 10000 / (0.30 + 0.00053 d jt) rows (30000 for a 16x2 layer, 4000 for 256x16), which
  * lutkan_forward runs as a one-layer launch of the fused chain kernel, and except where lutkan_forward needs no records because
- * one launch locates, gathers and sums and the launch planning prices that lower: a few rows (up to some hundred) of a
- * layer whose table is at most 128 MiB, and a layer of one column tile of at most 32 columns whose batch has outgrown both;
+ * one launch locates, gathers and sums and the launch planning prices that lower (beyond 1024 rows also lower than the chain
+ * kernel, by 3.3 us): a few rows (up to some thousand) of a layer whose table is at most 128 MiB, and a layer of one column
+ * tile of at most 32 columns;
  * results agree to rounding, not bit for bit.  TILED (and AUTO) take the table's wide form, where the layer holds one
  * (lutkan_wide_table_build), when the launch planning prices it lower; TILED_WIDE takes it whatever the price and is
  * an error for a layer without one or a call it does not serve (16-bit codes with 16-byte records).  LUT layers only. */
@@ -322,8 +323,8 @@ int bspline_forward_edges(const bspline_dev_layer *layer, int64_t B, float *y,
 /* Per-layer chaining (Sec. 5.1: intermediate activations feed the next layer and may leave its domain):
  * y of layer l is x of layer l+1.  The workspace holds two ping-pong activation buffers plus the largest
  * per-layer scratch.  layers[l].m must equal layers[l+1].d.  stats (nullable) points to n_layers entries.
- * The result is bit-identical to calling lutkan_forward layer by layer; when every layer is one that lutkan_forward
- * runs as a launch of the chain kernel (see lutkan_algo), the whole network runs as ONE launch of it. */
+ * The result is bit-identical to calling lutkan_forward layer by layer; consecutive layers that lutkan_forward
+ * would each run as a launch of the chain kernel (see lutkan_algo), or the whole network, run as ONE launch of it. */
 size_t lutkan_model_workspace_bytes(const lutkan_dev_layer *layers, int32_t n_layers, int64_t B);
 int lutkan_model_forward(const lutkan_dev_layer *layers, int32_t n_layers, const float *x, int64_t B, float *y,
                          lutkan_oob_stats *stats, void *workspace, size_t workspace_bytes, void *hip_stream);
