@@ -289,7 +289,9 @@ int lutkan_forward_static_scratch(const lutkan_dev_layer *layer, const float *x,
  *                           fills the workspace with the lookup records (and adds to stats, nullable)
  *   lutkan_forward_edges    step 5 (Eq. 10, 17), Sec. 5.4 and the sum of Eq. 1 from the records in the workspace
  * Calling locate then edges on one stream with the same layer, B and workspace equals lutkan_forward, to rounding where
- * lutkan_forward needs no records (lutkan_algo). */
+ * lutkan_forward needs no records (lutkan_algo).  A phi layer's records serve any edge phase for B rows: algo and the wide
+ * table may change in between.  With spline_component both phases need the layer as it was (algo and the table forms decide
+ * where the base branch is evaluated, and that decides what a record holds). */
 int lutkan_forward_locate(const lutkan_dev_layer *layer, const float *x, int64_t B, lutkan_oob_stats *stats,
                           void *workspace, size_t workspace_bytes, void *hip_stream);
 int lutkan_forward_edges(const lutkan_dev_layer *layer, int64_t B, float *y,

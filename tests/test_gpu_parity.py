@@ -1451,6 +1451,47 @@ def test_few_rows_in_one_launch(case):
     assert stats.cpu().tolist() == [ref.oob_count, ref.oob_any_rows]
 
 
+# ---------------------------------------------------------------- the two phases as separate calls
+TWO_PHASE_CASES = [
+    # seed, d, m, G, L, scheme, B, with_base: batches whose launch plans read fewer rows than records are laid out for
+    (981, 40, 70, 5, 16, SYM_INT8, 70, False),
+    (982, 33, 130, 8, 32, ASYM_UINT8, 300, False),
+    (983, 300, 64, 6, 16, SYM_INT8, 1, False),
+    (984, 65, 20, 7, 32, ASYM_UINT8, 1300, False),
+    (985, 40, 70, 5, 16, ASYM_UINT8, 257, True),
+]
+
+
+@pytest.mark.parametrize("case", TWO_PHASE_CASES, ids=lambda c: f"seed{c[0]}")
+def test_locate_and_edges_as_separate_calls(case):
+    """locate, then edges, against the oracle, and bit for bit what one call on the same kernels returns.  Where a record lies
+    follows from B alone: a phi layer's records serve edge phases of every algo and table form."""
+    seed, d, m, G, L, scheme, B, with_base = case
+    w = random_layer(seed, d, m, G, L, scheme, HALF_OPEN, ZERO_SPLINE, B, uniform=False, with_base=with_base)
+    s, x = w.layers[0], w.x
+    art, ora = _compile_both(s)
+    xg = torch.from_numpy(x).to(DEV)
+    ref = oracle.lut_forward(ora, s.boundary, s.oob, x, trace=True, edge_scalars=s.edge_scales)
+    forms = [("auto", _device_layer(art, s)), ("gather", _device_layer(art, s, lk.ALGO_GATHER)), ("tiled", _device_layer(art, s, lk.ALGO_TILED))]
+    if art.info.jt == 64 and not with_base:
+        forms += [(f"wide{cb}", _device_layer(art, s, lk.ALGO_TILED_WIDE, wide=cb)) for cb in (2, 4)]
+    nbytes = max(lk.lutkan_forward_workspace_bytes(layer, B) for _, layer in forms)
+    for first, located in forms:
+        for second, summed in forms:
+            if with_base and first != second:          # (what a record holds then depends on algo)
+                continue
+            _say(f"case two phases d={d} m={m} L={L} scheme={scheme} B={B} base={with_base}: {first} then {second}")
+            ws = torch.zeros(nbytes, dtype=torch.uint8, device=DEV)
+            y = torch.empty((B, m), dtype=torch.float32, device=DEV)
+            lk.lutkan_forward_locate(located, xg, ws)
+            lk.lutkan_forward_edges(summed, B, y, ws)
+            whole = lk.lutkan_forward(summed, xg)
+            torch.cuda.synchronize()
+            _assert_close(y.cpu().numpy(), ref, f"{first} then {second}")
+            if second != "auto":
+                assert torch.equal(y, whole)
+
+
 def test_calls_run_on_torchs_current_stream():
     """The stream handle that a call gets is the current stream's, on the default stream and on others, and work queued
     there before the call is seen by it."""
