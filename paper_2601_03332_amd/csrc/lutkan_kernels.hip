@@ -1109,18 +1109,23 @@ int chain_impl(const lutkan_dev_layer *layers, int32_t n_layers, const float *x,
   return check_launch("lutkan_chain_kernel");
 }
 
-// The layers that AUTO runs as a launch of the chain kernel (see forward_impl): one column tile, d * jt <= 4096, and
+// The layers that AUTO can run as a launch of the chain kernel (see forward_impl): one column tile, d * jt <= 4096, and
 // few enough rows.  Measured on 16x2 ... 256x16 layers between 8192 and 131072 rows: the chain kernel takes about
 // 4 us + (0.35 + 0.00088 d jt) us per 1000 rows, locate + tiled kernel + summing pass about 17 us + (0.05 + 0.00035 d jt)
 // us per 1000 rows; the chain kernel wins below their crossing, taken a little low (16x2: up to 30000 rows, 78x16:
-// 10000, 64x32: 7000, 256x16: 4000).  Beyond kChainSplitRows rows, where a single wave walks all inputs of its row, the
+// 10000, 64x32: 7000, 256x16: 4000).
+bool small_layer_suits_chain(const lutkan_dev_layer *l, int64_t B) {
+  if (l->algo != LUTKAN_ALGO_AUTO || l->n_tiles != 1 || l->jt > kChainMaxColumns || l->d * l->jt > 4096) return false;
+  return (double)B * (0.30 + 0.00053 * l->d * l->jt) <= 10000.0;
+}
+
+// Those that it does run so: beyond kChainSplitRows rows, where a single wave walks all inputs of its row, the
 // one-launch kernels that share the walk take the layer where they are priced 3.3 us lower -- what a launch of its own costs
 // it, should the other layers of its network have been one launch with it (microseconds, chain -> those: 100 -> 30 at 1500
 // rows 14.4 -> 8.7, at 5000 22 -> 13; 200 -> 16 at 5000 24 -> 13.5; 1000 -> 4 at 3500 52 -> 22; 78 -> 16 at 10000 19 -> 12.7, at 2000
 // 9.1 against 9.0, left alone).
 bool small_layer_runs_as_chain(const lutkan_dev_layer *l, int64_t B) {
-  if (l->algo != LUTKAN_ALGO_AUTO || l->n_tiles != 1 || l->jt > kChainMaxColumns || l->d * l->jt > 4096) return false;
-  if ((double)B * (0.30 + 0.00053 * l->d * l->jt) > 10000.0) return false;
+  if (!small_layer_suits_chain(l, B)) return false;
   if (B <= kChainSplitRows) return true;
   // a wave's walk: 0.17 us per 64 columns' edges, 0.8 per 64 inputs located; one round of waves up to 1500 rows
   const double walk = 0.17 * l->d * l->jt / 64 + 0.8 * ((l->d + 63) / 64);
@@ -1561,6 +1566,10 @@ extern "C" int lutkan_model_forward(const lutkan_dev_layer *layers, int32_t n_la
   const size_t need = model_workspace(layers, n_layers, B, &act, &scratch);
   if (!workspace || workspace_bytes < need) return fail(LUTKAN_ESHAPE, "%s: workspace of %zu bytes, need %zu", who, workspace_bytes, need);
   if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return fail(LUTKAN_EINVAL, "%s: workspace must be 256-byte aligned", who);
+  // A network of small layers may run as one launch that writes y while it reads x: x == y is refused for all of them, those
+  // of which a layer leaves the chain included, so that the answer does not follow the pricing of launches.
+  if (x == y && n_layers <= kChainMaxLayers && std::all_of(layers, layers + n_layers, [B](const lutkan_dev_layer &l) { return small_layer_suits_chain(&l, B); }))
+    return fail(LUTKAN_EINVAL, "%s: x and y alias", who);
   // Consecutive layers that would each run as a launch of the chain kernel run as one launch of it instead.  The
   // arithmetic per layer is the same, so the result is bit-identical to the layer-by-layer calls.
   char *base = static_cast<char *>(workspace);

@@ -276,6 +276,24 @@ def test_binding_refuses_tensors_of_the_wrong_shape_dtype_or_device():
     assert lk.lutkan_last_plan() == ""                          # nothing reached a launch
 
 
+def test_model_forward_refuses_aliased_x_and_y_of_a_small_network_at_every_batch():
+    """A network of layers that are small enough for the fused launch is refused with x == y whether or not a layer leaves
+    that launch for a kernel of its own (1000 -> 4 does beyond 1024 rows)."""
+    lib = lk.load_library()
+    layers = (binding._DevLayer * 2)()
+    keep = []
+    for n, (d, m) in enumerate(((1000, 4), (4, 4))):
+        w = random_layer(61 + n, d, m, 5, 16, SYM_INT8, CLOSED, CLIP_X, 4)
+        art, _ = _both(w.layers[0])
+        keep.append(art)
+        lib.lutkan_dev_layer_init(art._h, C.byref(layers[n]))
+        layers[n].table = 4096
+    for B in (16, 1024, 2000, 3500, 4000):
+        need = lib.lutkan_model_workspace_bytes(layers, 2, B)
+        assert lib.lutkan_model_forward(layers, 2, 4096, B, 4096, None, 4096, need, None) == -1, B
+        assert "alias" in lk.lutkan_last_error()
+
+
 def test_stored_symmetric_artifact_with_an_offset_is_refused():
     """Eq. 11 fixes y_min = 0 for symmetric int8 and the device table of that scheme carries no y_min plane: stored
     arrays that say otherwise are refused instead of silently losing the offset."""
