@@ -394,7 +394,8 @@ int bspline_impl(const bspline_dev_layer *l, const float *x, int64_t B, float *y
   // where the gather kernel reads a third of it: 1024 -> 1024, G = 10 (54 MB) at 1 / 4 / 8 rows 24 / 29 / 38 us against 35;
   // 512 -> 512, G = 5 (8 MB) 17 / 18 / 21 against 14.
   const bool few_rows_of_a_large_table = B < 8 && (double)l->n_tiles * l->d * l->coef_blob_bytes > 32.0 * 1024 * 1024;
-  if (l->algo == LUTKAN_ALGO_AUTO && phases == (kLocate | kEdges) && !few_rows_of_a_large_table && lutkan::bspline_matrix_fits(l))
+  if (l->algo == LUTKAN_ALGO_AUTO && phases == (kLocate | kEdges) && !few_rows_of_a_large_table && !overlap(x, B * l->d, y, B * l->m) &&
+      lutkan::bspline_matrix_fits(l))
     return lutkan::bspline_matrix_forward(l, x, B, y, workspace, need, hip_stream);
 
   SplineLocateArgs la;

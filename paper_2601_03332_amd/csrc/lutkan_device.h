@@ -141,6 +141,13 @@ inline int64_t padded_rows(int64_t B) { return round_up(B, kMaxTileRows); }
 inline int lut_record_bytes(int value_repr) { return value_repr == LUTKAN_REPR_SPLINE_COMPONENT ? 16 : 8; }
 inline size_t record_bytes(int d, int64_t Bp, int bytes_per_record) { return (size_t)round_up((int64_t)d * Bp * bytes_per_record, 256); }
 
+// A kernel that reads x while it writes y cannot serve a y that lies partly over x; the passes can: the locate kernel has
+// read all of x before the edge kernel starts.
+inline bool overlap(const float *x, int64_t n_x, const float *y, int64_t n_y) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(x), b = reinterpret_cast<uintptr_t>(y);
+  return a < b + (uintptr_t)n_y * 4 && b < a + (uintptr_t)n_x * 4;
+}
+
 int check_launch(const char *what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LUTKAN_EHIP, "%s: %s", what, hipGetErrorString(e));

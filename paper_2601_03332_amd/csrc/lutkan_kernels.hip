@@ -1211,9 +1211,9 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
 
   // One launch that needs no records, where one of the two is priced below the passes: a few rows on a table that the caches
   // hold (beyond 128 MiB every call fetches its rows from HBM, which the passes spread over more work-groups), or a narrow
-  // layer.  Both phases in one call only.  The passes: locate, about 5 us and its 12 bytes per (row, input) at the rate of a
+  // layer.  Both phases in one call only, and y apart from x.  The passes: locate, about 5 us and its 12 bytes per (row, input) at the rate of a
   // large copy, then the tiled plan or the gather kernel (measured as above) and its summing pass.
-  if (l->algo == LUTKAN_ALGO_AUTO && phases == (kLocate | kEdges) && !trace && !q01_out) {
+  if (l->algo == LUTKAN_ALGO_AUTO && phases == (kLocate | kEdges) && !trace && !q01_out && !overlap(x, B * l->d, y, B * l->m)) {
     const double table = (double)l->n_tiles * l->d * l->blob_bytes;
     const double passes = 5.0 + (double)B * l->d * 12.0 / 4.7e6 + (tiled ? (wide ? tpw.cost : tp.cost) : 10.0 + (double)B * l->d * l->n_tiles * (2.0 * l->jt + lay.param_row_bytes) / 9.4e6);
     const lutkan::RowsPlan rp = table <= 128.0 * 1024 * 1024 ? lutkan::rows_plan(l, B) : lutkan::RowsPlan{0, 1e300};

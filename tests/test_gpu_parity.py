@@ -1492,6 +1492,36 @@ def test_locate_and_edges_as_separate_calls(case):
                 assert torch.equal(y, whole)
 
 
+@pytest.mark.parametrize("case", [(991, 256, 200, 64), (992, 300, 10, 3000), (993, 64, 8, 70000), (994, 70, 300, 30)], ids=lambda c: f"seed{c[0]}")
+def test_outputs_that_lie_partly_over_the_inputs(case):
+    """y starts inside x, or x inside y: every kernel of such a call has read what it needs before y is written.  The same
+    layers apart run in one launch that reads x to its end."""
+    seed, d, m, B = case
+    w = random_layer(seed, d, m, 5, 16, SYM_INT8, CLOSED, ZERO_SPLINE, B)
+    s, x = w.layers[0], w.x
+    art, ora = _compile_both(s)
+    layer, spline = _device_layer(art, s), art.bspline_to_device(DEV)
+    ref = oracle.lut_forward(ora, s.boundary, s.oob, x, trace=True)
+    refb = oracle.bspline_forward(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.boundary, s.oob, x)
+    xg = torch.from_numpy(x).to(DEV)
+    lk.lutkan_forward(layer, xg)
+    assert "rows" in lk.lutkan_last_plan() or "one_launch" in lk.lutkan_last_plan()
+    for what, at_x, at_y in (("y in x", 0, B * d // 2 & ~3), ("x in y", B * m // 2 & ~3, 0), ("one row apart", 0, 4)):
+        _say(f"case overlap {what}: d={d} m={m} B={B}")
+        buf = torch.zeros(max(at_x + B * d, at_y + B * m), dtype=torch.float32, device=DEV)
+        xv, yv = buf[at_x:at_x + B * d].view(B, d), buf[at_y:at_y + B * m].view(B, m)
+        xv.copy_(xg)
+        stats = torch.zeros(2, dtype=torch.int64, device=DEV)
+        lk.lutkan_forward(layer, xv, yv, stats=stats)
+        torch.cuda.synchronize()
+        _assert_close(yv.cpu().numpy(), ref, what)
+        assert stats.cpu().tolist() == [ref.oob_count, ref.oob_any_rows]
+        xv.copy_(xg)
+        lk.bspline_kan_forward(spline, xv, yv)
+        torch.cuda.synchronize()
+        _assert_close(yv.cpu().numpy(), refb, "bspline " + what)
+
+
 def test_calls_run_on_torchs_current_stream():
     """The stream handle that a call gets is the current stream's, on the default stream and on others, and work queued
     there before the call is seen by it."""
