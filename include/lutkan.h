@@ -309,9 +309,10 @@ int lutkan_forward_trace(const lutkan_dev_layer *layer, const float *x, int64_t 
 /* B-spline layer forward (Eq. 1 over Eq. 3-5): per (row, input) the span and the four non-zero cubic basis
  * values are computed once by the Cox-de Boor recursion in fp32; per edge four coefficient FMAs; the same
  * boundary_mode / oob_policy as the LUT layer is applied to x first.  With algo = AUTO a phi layer of at most 13 segments on
- * its domain grid with one knot vector runs as a dense product on the matrix cores, every fp32 operand cut exactly into
- * three bf16 pieces (relative error per term <= 2^-23), the basis as cubic polynomials per segment; the results agree with
- * the other kernels' to rounding. */
+ * its domain grid with one knot vector, neighbouring gaps within a factor of about 3 of each other, runs as a dense product on the matrix cores, every fp32 operand cut exactly into
+ * three bf16 pieces (relative error per term <= 2^-23), the basis as one cubic per segment and
+ * function (relative error of each value below 1e-6, however small it is); the results agree with the other kernels' to
+ * rounding. */
 int bspline_kan_forward(const bspline_dev_layer *layer, const float *x, int64_t B, float *y,
                         void *workspace, size_t workspace_bytes, void *hip_stream);
 

@@ -2,7 +2,7 @@
 // the LUT layer (lutkan_kernels.hip) -- per (row, input) the span and the four non-zero cubic basis values, then
 // per edge four coefficient FMAs -- with the same tiling, staging and launch planning.  Layers whose basis fits 16 slots
 // run on the matrix cores instead (bspline_matrix.hip); the kernels here serve the others (spline_component, more than
-// 13 segments, one knot vector per input), the two separate phases, and algo = GATHER / TILED.
+// 13 segments, one knot vector per input, strongly uneven knots), the two separate phases, and algo = GATHER / TILED.
 // The file is compiled with -ffp-contract=off; every fused multiply-add below is written out as fmaf().
 #include "bspline_matrix.h"
 #include "lutkan_device.h"

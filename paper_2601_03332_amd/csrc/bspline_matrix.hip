@@ -44,7 +44,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kMxWaves = 8;
 constexpr int kMxMaxSegments = 13;       // R = G + 3 <= 16
-constexpr int kMxSegStride = 20;         // floats per segment in LDS: 16 polynomial coefficients, middle, 1/width; 80-byte rows spread the banks
+constexpr int kMxSegFloats = 14;         // of a segment: 8 polynomial coefficients, its ends, middle and scale, the two outer factors
+constexpr int kMxSegStride = 20;         // ... in LDS: 80-byte rows spread the banks
 
 struct SplineMatrixArgs {
   const float *x;            // [B][d]
@@ -59,69 +60,73 @@ struct SplineMatrixArgs {
   float t0, tKs;             // the clip range
   float masked_below, masked_above;      // zero_spline: inputs outside contribute nothing; clip_x: -inf, +inf
   float knots[kMxMaxSegments - 1];       // the inner knots, +inf past the last
-  float segment[kMxMaxSegments][18];     // per segment: v^3, v^2, v, 1 coefficients of its four basis functions, middle, 1/width
+  float segment[kMxMaxSegments][kMxSegFloats];     // see segment_constants
 };
 
-// Where an input lies: its segment (a.segments for one that contributes nothing) and the local coordinate
-// v = (x' - middle) / width in it, |v| <= 1/2, NaN for a NaN input.
+// Where an input lies: the clipped x' (NaN for a NaN input) and its segment, a.segments for one that contributes nothing.
 struct Position {
-  float v;
+  float x;
   int segment;
 };
 
 // SLOTS - 4 inner knots at most.  `dead`: an input past the work-group's last, x finite.
 template <int SLOTS>
-__device__ __forceinline__ Position locate(const SplineMatrixArgs &a, const float *s_seg, float x, bool dead) {
+__device__ __forceinline__ Position locate(const SplineMatrixArgs &a, float x, bool dead) {
   const float xc = __builtin_amdgcn_fmed3f(x, a.t0, a.tKs);
   int k = 0;
 #pragma unroll
   for (int kappa = 0; kappa < SLOTS - 4; ++kappa) k += (a.knots[kappa] <= xc) ? 1 : 0;
   const bool masked = dead || x < a.masked_below || x > a.masked_above;
   k = masked ? a.segments : k;
-  const f32x2 mr = *reinterpret_cast<const f32x2 *>(s_seg + k * kMxSegStride + 16);
-  const float v = __fmul_rn(__fsub_rn(xc, mr.x), mr.y);
-  return Position{(x != x) ? __builtin_nanf("") : v, k};
+  return Position{(x != x) ? __builtin_nanf("") : xc, k};
 }
 
-// The four non-zero cubics as polynomials in v, coefficients rounded once from 64 bits: against the Cox-de Boor recursion
-// in fp32 a quarter of the instructions and half the error (rms 2.0e-8 against 3.6e-8 of the two middle functions on
-// uniform knots).  The segment a.segments of s_seg is all zero.
+// The four non-zero cubics, each with a small error relative to itself.  The two outer ones have a triple zero at an end of
+// the segment and are a factor times the cube of the distance from that end; a polynomial about the middle would cancel there
+// (values below 1e-3 came out with a median relative error of 5e-6 and more, some negative).  The two middle ones stay
+// away from zero (bspline_matrix_fits) and are polynomials about the middle, coefficients rounded once from 64 bits.
+// Distances are scaled by a power of two, which rounds nothing.  Against the Cox-de Boor recursion in fp32 a third of the
+// instructions; root of the summed squares of the four errors on uniform knots, G = 5 / 8 / 10: 2.4e-8 / 2.5e-8 / 2.4e-8
+// (recursion 5.5e-8 / 2.8e-8 / 4.1e-8), largest relative error 3.6e-7 (3.8e-7).  The segment a.segments of s_seg is all zero.
 __device__ __forceinline__ void basis_of(const float *s_seg, const Position &at, float n[4]) {
   const float *seg = s_seg + at.segment * kMxSegStride;
-  const f32x4 p3 = *reinterpret_cast<const f32x4 *>(seg), p2 = *reinterpret_cast<const f32x4 *>(seg + 4);
-  const f32x4 p1 = *reinterpret_cast<const f32x4 *>(seg + 8), p0 = *reinterpret_cast<const f32x4 *>(seg + 12);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) n[e] = fmaf(fmaf(fmaf(p3[e], at.v, p2[e]), at.v, p1[e]), at.v, p0[e]);
+  const f32x4 p32 = *reinterpret_cast<const f32x4 *>(seg), p10 = *reinterpret_cast<const f32x4 *>(seg + 4);
+  const f32x4 place = *reinterpret_cast<const f32x4 *>(seg + 8);                     // left end, right end, middle, scale
+  const f32x2 outer = *reinterpret_cast<const f32x2 *>(seg + 12);
+  const float from_right = __fmul_rn(__fsub_rn(place.y, at.x), place.w);
+  const float from_left = __fmul_rn(__fsub_rn(at.x, place.x), place.w);
+  const float v = __fmul_rn(__fsub_rn(at.x, place.z), place.w);
+  n[0] = __fmul_rn(__fmul_rn(__fmul_rn(from_right, from_right), from_right), outer.x);
+  n[1] = fmaf(fmaf(fmaf(p32.x, v, p32.z), v, p10.x), v, p10.z);
+  n[2] = fmaf(fmaf(fmaf(p32.y, v, p32.w), v, p10.y), v, p10.w);
+  n[3] = __fmul_rn(__fmul_rn(__fmul_rn(from_left, from_left), from_left), outer.y);
 }
 
 __device__ __forceinline__ void fill_segments(const SplineMatrixArgs &a, float *s_seg, int tid, int threads) {
-  for (int q = tid; q < (a.segments + 1) * 18; q += threads) {
-    const int s = q / 18, e = q - s * 18;
+  for (int q = tid; q < (a.segments + 1) * kMxSegFloats; q += threads) {
+    const int s = q / kMxSegFloats, e = q - s * kMxSegFloats;
     s_seg[s * kMxSegStride + e] = (s < a.segments) ? a.segment[s][e] : 0.0f;
   }
 }
 
-// The separate locate pass of a layer with many column tiles: 8-byte records {v, segment} [input][row], a tile of
+// The separate locate pass of a layer with many column tiles: 8-byte records {x', segment} [input][row], a tile of
 // 32 rows x 64 inputs per block, transposed through LDS as in the LUT layer's locate kernel.
 template <int SLOTS>
 __global__ __launch_bounds__(256) void bspline_matrix_locate_kernel(const SplineMatrixArgs a) {
   constexpr int ROWS = 32, COLS = 64;
   __shared__ u32x2 s_rec[COLS][ROWS + 1];
-  __shared__ __align__(16) float s_seg[(kMxMaxSegments + 1) * kMxSegStride];
   const int tid = threadIdx.x;
   const int64_t b0 = (int64_t)blockIdx.x * ROWS;
   const int i0 = blockIdx.y * COLS;
-  fill_segments(a, s_seg, tid, 256);
   const int il = tid & (COLS - 1);
   const int i = min(i0 + il, a.d - 1);
   float xv[8];
 #pragma unroll
   for (int p = 0; p < 8; ++p) xv[p] = a.x[min(b0 + p * 4 + tid / COLS, a.B - 1) * a.d + i];
-  __syncthreads();
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
-    const Position at = locate<SLOTS>(a, s_seg, xv[p], false);
-    s_rec[il][p * 4 + tid / COLS] = u32x2{__float_as_uint(at.v), (unsigned)at.segment};
+    const Position at = locate<SLOTS>(a, xv[p], false);
+    s_rec[il][p * 4 + tid / COLS] = u32x2{__float_as_uint(at.x), (unsigned)at.segment};
   }
   __syncthreads();
   const int bl = tid & (ROWS - 1);
@@ -274,7 +279,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
   int cur = 0;
   for (int i0 = i_begin; i0 < i_end; i0 += IS) {
     const bool more = i0 + IS < i_end;
-    // the inputs of this stage; one past the work-group's last takes the all-zero segment (and a finite v)
+    // the inputs of this stage; one past the work-group's last takes the all-zero segment (and a finite x)
     float xc[RT][4];
     Position rec[RT][4];
     bool dead[4];
@@ -299,7 +304,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
           Position at;
-          if constexpr (RECORDS) at = rec[rt][s]; else at = locate<SLOTS>(a, s_seg, xc[rt][s], dead[s]);
+          if constexpr (RECORDS) at = rec[rt][s]; else at = locate<SLOTS>(a, xc[rt][s], dead[s]);
           float n[4];
           basis_of(s_seg, at, n);
           slots_of<SLOTS>(n, at.segment, half, af[rt]);
@@ -344,9 +349,16 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
     }
 }
 
-// Coefficients in v = (x - middle) / width of the four cubics that are non-zero on the span [tau[mu], tau[mu+1]) (de Boor's
-// triangle on polynomials, 64 bits).  out: v^3 of the four functions, then v^2, v, 1.
-void segment_polynomials(const float *tau, int mu, double mid, double width, float out[16]) {
+// What the kernel knows of the span [tau[mu], tau[mu+1]): the two middle ones of its four cubics as polynomials in
+// v = (x - middle) * scale (de Boor's triangle on polynomials, 64 bits) -- v^3 of both, v^2 of both, v, 1 --, its ends, middle
+// and scale (the power of two that takes its width into [1, 2)), and the factors of the two outer ones' cubed distances.
+void segment_constants(const float *tau, int mu, float out[kMxSegFloats]) {
+  const double left = tau[mu], right = tau[mu + 1];
+  int exponent;
+  (void)std::frexp(right - left, &exponent);
+  const double scale = std::ldexp(1.0, 1 - exponent), width = 1.0 / scale;
+  const float middle = (float)(0.5 * (left + right));
+  const double mid = middle;
   double n[4][4] = {{1.0, 0.0, 0.0, 0.0}};               // n[e][deg]
   for (int q = 1; q <= 3; ++q) {
     double saved[4] = {0.0, 0.0, 0.0, 0.0};
@@ -365,8 +377,14 @@ void segment_polynomials(const float *tau, int mu, double mid, double width, flo
     }
     for (int g = 0; g < 4; ++g) n[q][g] = saved[g];
   }
-  for (int g = 0; g < 4; ++g)
-    for (int e = 0; e < 4; ++e) out[(3 - g) * 4 + e] = (float)n[e][g];
+  for (int g = 0; g < 4; ++g) {
+    out[(3 - g) * 2] = (float)n[1][g];
+    out[(3 - g) * 2 + 1] = (float)n[2][g];
+  }
+  out[8] = (float)left; out[9] = (float)right; out[10] = middle; out[11] = (float)scale;
+  // N = (right - x)^3 / ((tau[mu+1] - tau[mu-2]) (tau[mu+1] - tau[mu-1]) (tau[mu+1] - tau[mu])), and its mirror image
+  out[12] = (float)(width / (right - tau[mu - 2]) * (width / (right - tau[mu - 1])) * (width / (right - left)));
+  out[13] = (float)(width / (tau[mu + 3] - left) * (width / (tau[mu + 2] - left)) * (width / (right - left)));
 }
 
 struct MatrixPlan {
@@ -444,14 +462,7 @@ int bspline_matrix_forward(const bspline_dev_layer *l, const float *x, int64_t B
   ma.masked_below = (l->oob == LUTKAN_ZERO_SPLINE) ? ma.t0 : -INFINITY;
   ma.masked_above = (l->oob == LUTKAN_ZERO_SPLINE) ? ma.tKs : INFINITY;
   for (int k = 0; k < kMxMaxSegments - 1; ++k) ma.knots[k] = (k + 1 < l->G) ? T[k + 1] : INFINITY;
-  for (int k = 0; k < l->G; ++k) {
-    const float mid = (float)(0.5 * ((double)T[k] + (double)T[k + 1]));
-    const double width = (double)T[k + 1] - (double)T[k];
-    const float rcp = (float)(1.0 / width);
-    segment_polynomials(l->ext_knots, 3 + k, (double)mid, 1.0 / (double)rcp, ma.segment[k]);
-    ma.segment[k][16] = mid;
-    ma.segment[k][17] = rcp;
-  }
+  for (int k = 0; k < l->G; ++k) segment_constants(l->ext_knots, 3 + k, ma.segment[k]);
   const int slots = (ma.R <= 8) ? 8 : 16;
   const int nt = ma.jt >= 128 ? 4 : ma.jt >= 64 ? 2 : 1;
   // With 16 slots and four or more column tiles the inputs are located once, into records, instead of once per column
@@ -482,9 +493,18 @@ bool bspline_matrix_fits(const bspline_dev_layer *l) {
   if (l->value_repr != LUTKAN_REPR_PHI || l->knot_span != LUTKAN_SPAN_DOMAIN || l->knots_per_input) return false;
   if (l->G > kMxMaxSegments) return false;
   // segments far narrower or wider than any grid in use: their polynomial coefficients could leave fp32's range
+  double gap[LUTKAN_MAX_K + 6];
   for (int r = 0; r < l->G + 6; ++r) {
-    const double gap = (double)l->ext_knots[r + 1] - (double)l->ext_knots[r];
-    if (!(gap > 1e-30 && gap < 1e30)) return false;
+    gap[r] = (double)l->ext_knots[r + 1] - (double)l->ext_knots[r];
+    if (!(gap[r] > 1e-30 && gap[r] < 1e30)) return false;
+  }
+  // The two middle functions of a segment, as polynomials about its middle, have an error of some 3e-8; they are smallest at
+  // the segment's ends, where they are an outer function of the neighbour at its inner end.  1/6 on uniform knots, 1/28 where
+  // gaps differ by a factor of 3; on a grid that takes one below 1/32 it would be lost from the sixth digit on: the kernels with
+  // the recursion serve that layer.
+  for (int r = 3; r <= l->G + 2; ++r) {
+    const double around = gap[r - 1] + gap[r] + gap[r + 1];
+    if (32.0 * gap[r + 1] * gap[r + 1] < (gap[r] + gap[r + 1]) * around || 32.0 * gap[r - 1] * gap[r - 1] < (gap[r - 1] + gap[r]) * around) return false;
   }
   return true;
 }

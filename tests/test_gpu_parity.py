@@ -1335,6 +1335,71 @@ def test_bspline_layers_outside_the_matrix_kernel_keep_their_kernels():
     assert lk.lutkan_last_plan().startswith("bspline_matrix ")
 
 
+def _basis64(tau, x, G):
+    """All G+3 cubic basis values [len(x), G+3] in extended precision by the Cox-de Boor recursion, positive terms only."""
+    tau, x = tau.astype(np.longdouble), x.astype(np.longdouble)
+    span = np.clip(np.searchsorted(tau[4:G + 3], x, side="right"), 0, G - 1) + 3
+    n = [np.ones_like(x)]
+    for q in (1, 2, 3):
+        saved, level = np.zeros_like(x), []
+        for r in range(q):
+            hi, lo = tau[span + r + 1], tau[span + 1 - q + r]
+            t = n[r] / (hi - lo)
+            level.append(saved + (hi - x) * t)
+            saved = (x - lo) * t
+        n = level + [saved]
+    out = np.zeros((len(x), G + 3), np.longdouble)
+    for e in range(4):
+        out[np.arange(len(x)), span - 3 + e] = n[e]
+    return out
+
+
+@pytest.mark.parametrize("case", [(5, "uniform", -1.0, 1.0), (8, "uniform", -3.0, 3.0), (10, "uniform", 99.0, 101.0), (13, "uneven", -1.0, 1.0),
+                                  (5, "uneven", -2.0, 1.0), (7, "steep", -1.0, 1.0)], ids=lambda c: f"G{c[0]}_{c[1]}")
+def test_bspline_layer_keeps_small_basis_values(case):
+    """One input and an identity of coefficients return the basis itself: every value, down to those next to the end of a
+    function's support, is right relative to itself.  7 roundings of half a unit for the outer functions (each of the three
+    factors a subtraction, two products, the factor and its product): 4.2e-7; the middle ones, at least 1/32, have an absolute error
+    of 3e-8: 1e-6.  Then coefficients of twelve orders of magnitude: the error stays below 1.3e-6 of the sum of the
+    terms' magnitudes (1e-6, and the rounding of four products and their sums)."""
+    G, kind, lo, hi = case
+    rng = np.random.Generator(np.random.PCG64(G))
+    r = np.arange(G + 7) - 3
+    tau = (lo + r * ((hi - lo) / G)).astype(np.float32)
+    if kind != "uniform":
+        gaps = rng.uniform(0.5, 1.5, G + 6) if kind == "uneven" else 10.0 ** rng.uniform(-3.0, 0.0, G + 6)
+        grid = np.concatenate([[0.0], np.cumsum(gaps)])
+        tau = (lo + (grid - grid[3]) * ((hi - lo) / (grid[3 + G] - grid[3]))).astype(np.float32)
+    T = tau[3:3 + G + 1]
+    x = [rng.uniform(T[0], T[-1], 4000)]
+    for k in range(G):                                    # both ends of every segment, ever closer
+        step = (T[k + 1] - T[k]) * 10.0 ** rng.uniform(-6.0, 0.0, 1000)
+        x += [T[k] + step, T[k + 1] - step]
+    x = np.clip(np.concatenate(x).astype(np.float32), T[0], T[-1])
+    expect = _basis64(tau, x, G)
+    xg = torch.from_numpy(x[:, None].copy()).to(DEV)
+    _say(f"case small basis values G={G} {kind} [{lo}, {hi}] B={len(x)}")
+
+    def forward(coef):
+        art = lk.lutkan_compile(1, coef.shape[1], G, 3, tau, coef, 2, SYM_INT8, CLOSED, CLIP_X)
+        y = lk.bspline_kan_forward(art.bspline_to_device(DEV), xg)
+        plan = lk.lutkan_last_plan()
+        assert ("slots" in plan) == (kind != "steep"), plan             # strongly uneven knots stay with the recursion
+        torch.cuda.synchronize()
+        return y.cpu().numpy().astype(np.longdouble)
+
+    y = forward(np.eye(G + 3, dtype=np.float32)[None])
+    live = expect > 1e-30
+    assert np.all(y[expect == 0.0] == 0.0)
+    worst = float(np.max(np.abs(y - expect)[live] / expect[live]))
+    assert worst <= 1e-6, worst
+    coef = (rng.choice([-1.0, 1.0], size=(1, 40, G + 3)) * 10.0 ** rng.uniform(-6.0, 6.0, size=(1, 40, G + 3))).astype(np.float32)
+    y = forward(coef)
+    c = coef[0].astype(np.longdouble).T
+    worst = float(np.max(np.abs(y - expect @ c) / (expect @ np.abs(c))))
+    assert worst <= 1.3e-6, worst
+
+
 # ---------------------------------------------------------------- narrow layers in one launch
 NARROW_CASES = [
     # seed, d, m, G, L, scheme, boundary, oob, B, with_base, fp16: tiles of 4, 8, 16, 32 columns; stages of 8 and of 4 slices
