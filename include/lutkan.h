@@ -264,7 +264,7 @@ size_t bspline_forward_workspace_bytes(const bspline_dev_layer *layer, int64_t B
  * value_repr = spline_component (Eq. 2): the base branch s_out * s_base * SiLU(x), summed over the inputs, is evaluated
  * inside the edge kernel or, from 5e8 edge evaluations per call (d a multiple of 32, m >= 64, tiled kernel), as one
  * [B, d] x [d, m] product on the matrix cores with every fp32 operand cut exactly into three bf16 pieces (relative error
- * per term <= 2^-23), on top of which the edge kernel adds the spline branch; the two ways agree to rounding.  With
+ * per term <= 2^-24, of either sign), on top of which the edge kernel adds the spline branch; the two ways agree to rounding.  With
  * the product a row that contains an infinite input comes out NaN (edge by edge it may be +-inf).
  * Errors: EINVAL for null/ill-formed arguments, ESHAPE for a short workspace, EHIP if a launch fails. */
 int lutkan_forward(const lutkan_dev_layer *layer, const float *x, int64_t B, float *y,
@@ -310,7 +310,7 @@ int lutkan_forward_trace(const lutkan_dev_layer *layer, const float *x, int64_t 
  * values are computed once by the Cox-de Boor recursion in fp32; per edge four coefficient FMAs; the same
  * boundary_mode / oob_policy as the LUT layer is applied to x first.  With algo = AUTO a phi layer of at most 13 segments on
  * its domain grid with one knot vector, neighbouring gaps within a factor of about 3 of each other, runs as a dense product on the matrix cores, every fp32 operand cut exactly into
- * three bf16 pieces (relative error per term <= 2^-23), the basis as one cubic per segment and
+ * three bf16 pieces (relative error per term <= 2^-24, of either sign), the basis as one cubic per segment and
  * function (relative error of each value below 1e-6, however small it is); the results agree with the other kernels' to
  * rounding. */
 int bspline_kan_forward(const bspline_dev_layer *layer, const float *x, int64_t B, float *y,

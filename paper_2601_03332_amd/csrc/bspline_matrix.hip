@@ -7,7 +7,8 @@
 // The basis is evaluated where it is consumed, so the pass that writes and reads 32 bytes per (row, input) falls away.
 //
 // fp32 accuracy from bf16 matrix instructions, as in lutkan_base_gemm.hip: every fp32 operand is cut exactly into three
-// bf16 pieces and the six piece products that are not below 2^-24 of the product are accumulated in fp32.  The products
+// bf16 pieces and six of the nine piece products are accumulated in fp32; the other three are at most 2^-24 of the product
+// together (lutkan_pieces.h).  The products
 // of the two high pieces have an accumulator of their own, apart from the five small ones: with one accumulator for all
 // six, every small product rounds the large sum once more and the layer came out 1.2 - 1.8 times further from a 64-bit
 // evaluation than the tiled kernel; apart, it is nearer than that kernel (64 -> 128 at 131072 rows 1.6e-7 against 3.0e-7,
@@ -36,6 +37,7 @@
 // The file is compiled with -ffp-contract=off; fused multiply-adds are written out as fmaf().
 #include "bspline_matrix.h"
 #include "lutkan_device.h"
+#include "lutkan_pieces.h"
 
 namespace {
 
@@ -137,30 +139,19 @@ __global__ __launch_bounds__(256) void bspline_matrix_locate_kernel(const Spline
   }
 }
 
-// the three bf16 pieces of a finite fp32 value as the upper halves of h, m, l (a NaN stays one)
-__device__ __forceinline__ void cut_pieces(float a, unsigned p[3]) {
-  const unsigned h = __float_as_uint(a) & 0xffff0000u;
-  const float r = a - __uint_as_float(h);
-  const unsigned m = __float_as_uint(r) & 0xffff0000u;
-  p[0] = h;
-  p[1] = m;
-  p[2] = __float_as_uint(r - __uint_as_float(m));
-}
-__device__ __forceinline__ unsigned pack_upper(unsigned lo, unsigned hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
-
 union Slots { u32x4 u; bf16x8 h; };
 
 // a lane's 8 slots of one (row, input), three pieces
 template <int SLOTS>
 __device__ __forceinline__ void slots_of(const float n[4], int first, int half, Slots out[3]) {
   if constexpr (SLOTS == 8) {
-    unsigned p[4][3];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) cut_pieces(n[e], p[e]);
+    unsigned p01[3], p23[3];
+    lutkan_cut3_pair<false>(n[0], n[1], p01);
+    lutkan_cut3_pair<false>(n[2], n[3], p23);
     const int up = 16 * first;                              // first = 0 .. 4
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      const unsigned long long v = ((unsigned long long)pack_upper(p[2][q], p[3][q]) << 32) | pack_upper(p[0][q], p[1][q]);
+      const unsigned long long v = ((unsigned long long)p23[q] << 32) | p01[q];
       const unsigned long long lo = (first == 4 ? 0ull : v) << (up & 63);
       const unsigned long long hi = (first == 0 ? 0ull : v) >> ((64 - up) & 63);
       out[q].u = u32x4{(unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32)};
@@ -169,14 +160,12 @@ __device__ __forceinline__ void slots_of(const float n[4], int first, int half, 
     // rows first .. first+3; this lane holds those of parity `half`: two of them, in slots at and at + 1
     const bool same = ((first ^ half) & 1) == 0;
     const int at = (first + (same ? 0 : 1) - half) >> 1;    // 0 .. 6
-    unsigned p[2][3];
-    cut_pieces(same ? n[0] : n[1], p[0]);
-    cut_pieces(same ? n[2] : n[3], p[1]);
+    unsigned p[3];
+    lutkan_cut3_pair<false>(same ? n[0] : n[1], same ? n[2] : n[3], p);
     const int up = (at & 1) * 16, word = at >> 1;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      const unsigned w = pack_upper(p[0][q], p[1][q]);
-      const unsigned d0 = w << up, d1 = (w >> 16) & (up ? 0xffffu : 0u);
+      const unsigned d0 = p[q] << up, d1 = (p[q] >> 16) & (up ? 0xffffu : 0u);
       out[q].u = u32x4{word == 0 ? d0 : 0u, word == 1 ? d0 : (word == 0 ? d1 : 0u), word == 2 ? d0 : (word == 1 ? d1 : 0u),
                        word == 3 ? d0 : (word == 2 ? d1 : 0u)};
     }
@@ -229,13 +218,11 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
       const int id = tid + q * kThreads;
       if (kUnits < kThreads && id >= kUnits) break;
       const int u = id / BN, c = id % BN;
-      unsigned p[8][3];
+      unsigned p[4][3];
 #pragma unroll
-      for (int r = 0; r < 8; ++r) cut_pieces(cf[q][r], p[r]);
+      for (int r = 0; r < 4; ++r) lutkan_cut3_pair<true>(cf[q][2 * r], cf[q][2 * r + 1], p[r]);
 #pragma unroll
-      for (int w = 0; w < 3; ++w)
-        *reinterpret_cast<u32x4 *>(buf + ((u * 3 + w) * BN + c) * 16) =
-            u32x4{pack_upper(p[0][w], p[1][w]), pack_upper(p[2][w], p[3][w]), pack_upper(p[4][w], p[5][w]), pack_upper(p[6][w], p[7][w])};
+      for (int w = 0; w < 3; ++w) *reinterpret_cast<u32x4 *>(buf + ((u * 3 + w) * BN + c) * 16) = u32x4{p[0][w], p[1][w], p[2][w], p[3][w]};
     }
   };
 

@@ -3,9 +3,9 @@
 // a gather: a [B, d] x [d, m] product.  The LUT edge kernel then adds the spline branch on top of Y0.
 //
 // fp32 accuracy from bf16 matrix instructions: every fp32 operand is cut, exactly, into three bf16 pieces of eight
-// significand bits each (a = a_h + a_m + a_l by truncation, nothing is lost), and the product is accumulated in fp32
-// from the six piece products that are not below 2^-24 of it (h*h, h*m, m*h, m*m, h*l, l*h).  bf16 has the exponent
-// range of fp32, so no scaling is needed.  A non-finite SiLU(x) keeps its class in the high piece; its row comes out
+// significand bits each (a = a_h + a_m + a_l, nothing is lost), and the product is accumulated in fp32 from the six piece
+// products h*h, h*m, m*h, m*m, h*l, l*h; the other three are at most 2^-24 of it together (lutkan_pieces.h).  bf16 has the
+// exponent range of fp32, so no scaling is needed.  A non-finite SiLU(x) keeps its class in the high piece; its row comes out
 // non-finite (NaN where an edge-by-edge evaluation may give +-inf).
 //
 // Both operands arrive already cut: SiLU(x) by the locate kernel (lutkan_cut3 below, three planes [piece][row][input]),

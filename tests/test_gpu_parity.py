@@ -1335,6 +1335,59 @@ def test_bspline_layers_outside_the_matrix_kernel_keep_their_kernels():
     assert lk.lutkan_last_plan().startswith("bspline_matrix ")
 
 
+def _adversarial_factors(rng, n):
+    """fp32 values whose lower 16 significand bits weigh most when they are cut off, the largest and very small ones, and random ones."""
+    special = [1 + 2.0 ** -7 - 2.0 ** -23, 1 + 2.0 ** -8 - 2.0 ** -23, 1 + 2.0 ** -8 + 2.0 ** -16 + 2.0 ** -17, 1 + 2.0 ** -7 - 2.0 ** -16, 2 - 2.0 ** -23,
+               1 + 2.0 ** -15 - 2.0 ** -23, 3.4028234e38, -3.39e38, 1e-25, -1.0, 1.5]
+    return np.concatenate([special, rng.normal(size=n - len(special))]).astype(np.float32)
+
+
+def _assert_products_like_fp32(got, a, b, last_sum, what):
+    """got = a * b for exactly known fp32 a (rows) and b (columns): the dropped piece products (2^-24), the rounding of the five
+    small ones' sum (2^-7 of a rounding each) and the result's last sum make (1.1 + last_sum) * 2^-24: 1 where it is an
+    addition of the vector ALU, 2 where the matrix unit's accumulator does it, whose rounding mode is not specified (one unit in
+    the last place; 2.7 in all is measured, 9.2 with pieces cut by truncation).  Over random factors the errors
+    cancel (their mean would be -0.7 * 2^-24 with pieces cut by truncation; 3e5 products leave a deviation of 0.002 * 2^-24)."""
+    exact = a.astype(np.float64)[:, None] * b.astype(np.float64)[None, :]
+    normal = (np.abs(exact) > 1e-30) & (np.abs(exact) < 3.4e38)
+    rel = np.where(normal, got.astype(np.float64) / np.where(normal, exact, 1.0) - 1.0, 0.0) * 2.0 ** 24
+    _say(f"case {what}: {int(normal.sum())} products, largest relative error {np.abs(rel).max():.3f} * 2^-24, mean {rel[normal].mean():+.4f}")
+    assert np.abs(rel).max() <= 1.1 + last_sum and abs(rel[normal].mean()) <= 0.02
+
+
+def test_the_pieces_of_products_on_the_matrix_cores_b_spline_layer():
+    """A single coefficient c makes the layer's output c times a basis value; the column with c = 1 returns that value as it is."""
+    for G, r in ((5, 4), (10, 6)):
+        rng = np.random.Generator(np.random.PCG64(40 + G))
+        c = np.concatenate([[1.0], _adversarial_factors(rng, 127)]).astype(np.float32)
+        coef = np.zeros((1, len(c), G + 3), np.float32)
+        coef[0, :, r] = c
+        tau = (-1.0 + (np.arange(G + 7) - 3) * (2.0 / G)).astype(np.float32)
+        x = rng.uniform(-1.0, 1.0, (6000, 1)).astype(np.float32)
+        art = lk.lutkan_compile(1, len(c), G, 3, tau, coef, 2, SYM_INT8, CLOSED, CLIP_X)
+        y = lk.bspline_kan_forward(art.bspline_to_device(DEV), torch.from_numpy(x).to(DEV))
+        assert "slots" in lk.lutkan_last_plan()
+        y = y.cpu().numpy()
+        assert np.isfinite(y).all()
+        _assert_products_like_fp32(y[:, 1:], y[:, 0], c[1:], 1.0, f"B-spline G={G}")
+
+
+def test_the_pieces_of_products_on_the_matrix_cores_base_branch():
+    """The base product of a layer whose spline branch is zero and whose first input alone has a base weight."""
+    d, m, B = 32, 64, 250000
+    rng = np.random.Generator(np.random.PCG64(47))
+    c = np.concatenate([[1.0], _adversarial_factors(rng, m - 1)]).astype(np.float32)
+    scales = [np.zeros((d, m), np.float32), np.ones((d, m), np.float32), np.ones((d, m), np.float32)]
+    scales[0][0] = c
+    tau = (-1.0 + (np.arange(12) - 3) * 0.4).astype(np.float32)
+    art = lk.lutkan_compile(d, m, 5, 3, tau, np.zeros((d, m, 8), np.float32), 16, SYM_INT8, CLOSED, CLIP_X, edge_scales=tuple(scales))
+    x = rng.normal(size=(B, d)).astype(np.float32)
+    y = lk.lutkan_forward(art.to_device(DEV), torch.from_numpy(x).to(DEV))
+    assert "base_product; " in lk.lutkan_last_plan()
+    y = y[:5000].cpu().numpy()
+    _assert_products_like_fp32(y[:, 1:], y[:, 0], c[1:], 2.0, "base product")
+
+
 def _basis64(tau, x, G):
     """All G+3 cubic basis values [len(x), G+3] in extended precision by the Cox-de Boor recursion, positive terms only."""
     tau, x = tau.astype(np.longdouble), x.astype(np.longdouble)
