@@ -48,6 +48,7 @@ constexpr int kMxWaves = 8;
 constexpr int kMxMaxSegments = 13;       // R = G + 3 <= 16
 constexpr int kMxSegFloats = 14;         // of a segment: 8 polynomial coefficients, its ends, middle and scale, the two outer factors
 constexpr int kMxSegStride = 20;         // ... in LDS: 80-byte rows spread the banks
+constexpr int kMxLdsTail = (kMxMaxSegments + 1) * kMxSegStride * 4 + 16;      // behind the stages in LDS: the segments, a flag
 
 struct SplineMatrixArgs {
   const float *x;            // [B][d]
@@ -146,8 +147,8 @@ template <int SLOTS>
 __device__ __forceinline__ void slots_of(const float n[4], int first, int half, Slots out[3]) {
   if constexpr (SLOTS == 8) {
     unsigned p01[3], p23[3];
-    lutkan_cut3_pair<false>(n[0], n[1], p01);
-    lutkan_cut3_pair<false>(n[2], n[3], p23);
+    lutkan_cut3_pair(n[0], n[1], p01);
+    lutkan_cut3_pair(n[2], n[3], p23);
     const int up = 16 * first;                              // first = 0 .. 4
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -161,7 +162,7 @@ __device__ __forceinline__ void slots_of(const float n[4], int first, int half, 
     const bool same = ((first ^ half) & 1) == 0;
     const int at = (first + (same ? 0 : 1) - half) >> 1;    // 0 .. 6
     unsigned p[3];
-    lutkan_cut3_pair<false>(same ? n[0] : n[1], same ? n[2] : n[3], p);
+    lutkan_cut3_pair(same ? n[0] : n[1], same ? n[2] : n[3], p);
     const int up = (at & 1) * 16, word = at >> 1;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -182,6 +183,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
   constexpr int kStageBytes = 8 * 3 * BN * 16;
   extern __shared__ __align__(16) unsigned char lds[];
   float *const s_seg = reinterpret_cast<float *>(lds + 2 * kStageBytes);
+  int *const s_uncut = reinterpret_cast<int *>(s_seg + (kMxMaxSegments + 1) * kMxSegStride);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -193,10 +195,12 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
   const int i_end = min(a.d, i_begin + a.chunk);
 
   fill_segments(a, s_seg, tid, kThreads);
+  if (tid == 0) *s_uncut = 0;
 
   // this thread's coefficient columns of a stage: unit u = (input u) resp. (input u & 3, parity u >> 2)
   const float *tile = a.coef_table + (size_t)t * a.d * a.R * a.jt;
   float cf[UPT][8];
+  float largest = 0.0f;                                    // of the magnitudes this thread staged; NaN if one was
   auto load_coefs = [&](int i0) {
 #pragma unroll
     for (int q = 0; q < UPT; ++q) {
@@ -220,7 +224,10 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
       const int u = id / BN, c = id % BN;
       unsigned p[4][3];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) lutkan_cut3_pair<true>(cf[q][2 * r], cf[q][2 * r + 1], p[r]);
+      for (int r = 0; r < 4; ++r) {
+        lutkan_cut3_pair(cf[q][2 * r], cf[q][2 * r + 1], p[r]);
+        largest = __builtin_elementwise_maximum(__builtin_elementwise_maximum(largest, fabsf(cf[q][2 * r])), fabsf(cf[q][2 * r + 1]));
+      }
 #pragma unroll
       for (int w = 0; w < 3; ++w) *reinterpret_cast<u32x4 *>(buf + ((u * 3 + w) * BN + c) * 16) = u32x4{p[0][w], p[1][w], p[2][w], p[3][w]};
     }
@@ -315,6 +322,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
       }
     }
     if (more) store_coefs(lds + (cur ^ 1) * kStageBytes);   // (everyone left that buffer before the last barrier)
+    else if (!(largest <= kLargestBf16)) *s_uncut = 1;
     __syncthreads();
     cur ^= 1;
   }
@@ -334,6 +342,29 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
         if (b < a.B && c < width && j < a.m) yout[b * a.m + j] = acc[rt][ct][v] + low[rt][ct][v];
       }
     }
+  // A coefficient that is not finite (in a table that its owner wrote: the compiler refuses them), or has no bf16 value above it,
+  // makes every row of the product NaN, by 0 * inf.  It belongs to the rows on its support: the work-group sums its outputs
+  // again, term by term.
+  if (*s_uncut == 0) return;
+#pragma unroll 1
+  for (int e = 0; e < RT * NT * 16; ++e) {
+    const int rt = e / (NT * 16), c = (e / 16 % NT) * 32 + col, v = e % 16;
+    const int j = t * a.jt + c;
+    const int64_t b = row0 + rt * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+    if (b >= a.B || c >= width || j >= a.m) continue;
+    float sum = 0.0f;
+#pragma unroll 1
+    for (int i = i_begin; i < i_end; ++i) {
+      const Position at = locate<SLOTS>(a, a.x[b * a.d + i], false);
+      if (at.segment == a.segments) continue;
+      float n[4];
+      basis_of(s_seg, at, n);
+      const float *src = tile + ((size_t)i * a.R + at.segment) * a.jt + c;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sum = fmaf(n[q], src[q * a.jt], sum);
+    }
+    yout[b * a.m + j] = sum;
+  }
 }
 
 // What the kernel knows of the span [tau[mu], tau[mu+1]): the two middle ones of its four cubics as polynomials in
@@ -411,7 +442,7 @@ int launch_matrix(const SplineMatrixArgs &ma, int n_split, hipStream_t s) {
   constexpr int kRows = kMxWaves * 32 * RT;
   const int64_t groups = (ma.B + kRows - 1) / kRows * ma.n_tiles;
   if (groups > 0x7fffffffLL) return fail(LUTKAN_EUNSUPPORTED, "bspline_matrix_kernel: B * m too large for one launch");
-  const size_t lds = 2 * (size_t)(8 * 3 * 32 * NT * 16) + (size_t)(kMxMaxSegments + 1) * kMxSegStride * 4;
+  const size_t lds = 2 * (size_t)(8 * 3 * 32 * NT * 16) + kMxLdsTail;
   static LdsCap raised;
   if (int rc = raise_lds_cap(bspline_matrix_kernel<SLOTS, RT, NT, RECORDS>, &raised, "bspline_matrix_kernel")) return rc;
   hipLaunchKernelGGL((bspline_matrix_kernel<SLOTS, RT, NT, RECORDS>), dim3((unsigned)groups, (unsigned)n_split), dim3(kMxWaves * 64), lds, s, ma);

@@ -19,20 +19,19 @@ __device__ __forceinline__ unsigned lutkan_round_bf16_pair(float a0, float a1) {
   return c.u;
 }
 
-// The pieces of two values, packed (a0 in the lower halves): p[0] = h, p[1] = m, p[2] = l.  LARGE: a value may lie beyond the
-// largest bf16 value (3.39e38), where rounding up would be infinite; then h is that value and the rest is still exact.
-// An infinity or NaN leaves a NaN or infinity among its pieces.
-template <bool LARGE>
+constexpr float kLargestBf16 = 3.3895313892515355e38f;
+
+// The pieces of two values, packed (a0 in the lower halves): p[0] = h, p[1] = m, p[2] = l.  A value beyond the largest bf16 value
+// may round to an infinite h; it, an infinity and a NaN leave an infinity or a NaN among the pieces.
 __device__ __forceinline__ void lutkan_cut3_pair(float a0, float a1, unsigned p[3]) {
-  constexpr float kLargest = 3.3895313892515355e38f;
-  p[0] = LARGE ? lutkan_round_bf16_pair(__builtin_amdgcn_fmed3f(a0, -kLargest, kLargest), __builtin_amdgcn_fmed3f(a1, -kLargest, kLargest))
-               : lutkan_round_bf16_pair(a0, a1);
+  p[0] = lutkan_round_bf16_pair(a0, a1);
   const float r0 = a0 - __uint_as_float(p[0] << 16), r1 = a1 - __uint_as_float(p[0] & 0xffff0000u);
   p[1] = lutkan_round_bf16_pair(r0, r1);
   p[2] = lutkan_round_bf16_pair(r0 - __uint_as_float(p[1] << 16), r1 - __uint_as_float(p[1] & 0xffff0000u));
 }
 
-// One value's pieces as bit patterns.  inf and NaN keep their class in the high piece, the other two are zero.
+// One value's pieces as bit patterns.  Beyond the largest bf16 value h is that value and the rest is still exact; inf and NaN
+// keep their class in the high piece, the other two are zero.
 __device__ __forceinline__ void lutkan_cut3(float a, unsigned &h, unsigned &m, unsigned &l) {
   const unsigned ab = __float_as_uint(a);
   if ((ab & 0x7f800000u) == 0x7f800000u) {
@@ -40,9 +39,8 @@ __device__ __forceinline__ void lutkan_cut3(float a, unsigned &h, unsigned &m, u
     m = l = 0u;
     return;
   }
-  unsigned p[3];
-  lutkan_cut3_pair<true>(a, 0.0f, p);
-  h = p[0] & 0xffffu;
-  m = p[1] & 0xffffu;
-  l = p[2] & 0xffffu;
+  h = lutkan_round_bf16_pair(__builtin_amdgcn_fmed3f(a, -kLargestBf16, kLargestBf16), 0.0f) & 0xffffu;
+  const float r = a - __uint_as_float(h << 16);
+  m = lutkan_round_bf16_pair(r, 0.0f) & 0xffffu;
+  l = lutkan_round_bf16_pair(r - __uint_as_float(m << 16), 0.0f) & 0xffffu;
 }

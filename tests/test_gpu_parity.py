@@ -1335,10 +1335,42 @@ def test_bspline_layers_outside_the_matrix_kernel_keep_their_kernels():
     assert lk.lutkan_last_plan().startswith("bspline_matrix ")
 
 
+@pytest.mark.parametrize("case", [(995, 37, 70, 5, 300), (996, 130, 200, 10, 90), (997, 9, 6, 5, 5000), (998, 512, 400, 7, 5003)], ids=lambda c: f"seed{c[0]}")
+def test_coefficients_that_are_not_finite_reach_the_rows_on_their_support_only(case):
+    """The compiler refuses such coefficients; a device table that its owner writes may hold them.  The matrix product multiplies
+    every coefficient with every row: 0 * inf must not show.  Against the gather kernel on the same table."""
+    seed, d, m, G, B = case
+    w = random_layer(seed, d, m, G, 2, SYM_INT8, CLOSED, CLIP_X, B)
+    s = w.layers[0]
+    art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.L, s.scheme, s.boundary, s.oob)
+    layer, other = art.bspline_to_device(DEV), art.bspline_to_device(DEV, lk.ALGO_GATHER)
+    xg = torch.from_numpy(w.x).to(DEV)
+    clean = lk.bspline_kan_forward(layer, xg)
+    info, R = art.info, G + 3
+    for held in (layer, other):
+        table = held.coef_table.view(torch.float32).view(info.coef_n_tiles, d, R, info.coef_jt)
+        table[0, d // 2, 1, 3 % m] = float("inf")
+        table[0, 0, R - 2, 1] = float("nan")
+        table[-1, d - 1, 2, 0] = float("-inf")
+    _say(f"case not finite d={d} m={m} G={G} B={B}")
+    y = lk.bspline_kan_forward(layer, xg)
+    assert "slots" in lk.lutkan_last_plan()
+    expect = lk.bspline_kan_forward(other, xg)
+    torch.cuda.synchronize()
+    y, expect, clean = y.cpu().numpy(), expect.cpu().numpy(), clean.cpu().numpy()
+    assert np.array_equal(np.isfinite(y), np.isfinite(expect)) and 0 < (~np.isfinite(y)).sum() < 3 * B
+    assert np.array_equal(y[~np.isfinite(y)], expect[~np.isfinite(expect)], equal_nan=True)
+    live = np.isfinite(y)
+    assert np.all(np.abs(y - clean)[live] <= 1e-5 * np.sqrt(d) * 4 + 1e-6)
+
+
+LARGEST_FACTORS = [3.4028234e38, -3.39e38]                 # beyond the largest bf16 value
+
+
 def _adversarial_factors(rng, n):
-    """fp32 values whose lower 16 significand bits weigh most when they are cut off, the largest and very small ones, and random ones."""
+    """fp32 values whose lower 16 significand bits weigh most when they are cut off, very small ones, and random ones."""
     special = [1 + 2.0 ** -7 - 2.0 ** -23, 1 + 2.0 ** -8 - 2.0 ** -23, 1 + 2.0 ** -8 + 2.0 ** -16 + 2.0 ** -17, 1 + 2.0 ** -7 - 2.0 ** -16, 2 - 2.0 ** -23,
-               1 + 2.0 ** -15 - 2.0 ** -23, 3.4028234e38, -3.39e38, 1e-25, -1.0, 1.5]
+               1 + 2.0 ** -15 - 2.0 ** -23, 1e-25, -1.0, 1.5]
     return np.concatenate([special, rng.normal(size=n - len(special))]).astype(np.float32)
 
 
@@ -1356,10 +1388,11 @@ def _assert_products_like_fp32(got, a, b, last_sum, what):
 
 
 def test_the_pieces_of_products_on_the_matrix_cores_b_spline_layer():
-    """A single coefficient c makes the layer's output c times a basis value; the column with c = 1 returns that value as it is."""
-    for G, r in ((5, 4), (10, 6)):
+    """A single coefficient c makes the layer's output c times a basis value; the column with c = 1 returns that value as it is.
+    A table with coefficients beyond the largest bf16 value is summed term by term."""
+    for G, r, largest in ((5, 4, []), (10, 6, []), (10, 6, LARGEST_FACTORS)):
         rng = np.random.Generator(np.random.PCG64(40 + G))
-        c = np.concatenate([[1.0], _adversarial_factors(rng, 127)]).astype(np.float32)
+        c = np.concatenate([[1.0], largest, _adversarial_factors(rng, 127 - len(largest))]).astype(np.float32)
         coef = np.zeros((1, len(c), G + 3), np.float32)
         coef[0, :, r] = c
         tau = (-1.0 + (np.arange(G + 7) - 3) * (2.0 / G)).astype(np.float32)
@@ -1376,7 +1409,7 @@ def test_the_pieces_of_products_on_the_matrix_cores_base_branch():
     """The base product of a layer whose spline branch is zero and whose first input alone has a base weight."""
     d, m, B = 32, 64, 250000
     rng = np.random.Generator(np.random.PCG64(47))
-    c = np.concatenate([[1.0], _adversarial_factors(rng, m - 1)]).astype(np.float32)
+    c = np.concatenate([[1.0], LARGEST_FACTORS, _adversarial_factors(rng, m - 1 - len(LARGEST_FACTORS))]).astype(np.float32)
     scales = [np.zeros((d, m), np.float32), np.ones((d, m), np.float32), np.ones((d, m), np.float32)]
     scales[0][0] = c
     tau = (-1.0 + (np.arange(12) - 3) * 0.4).astype(np.float32)
