@@ -48,7 +48,7 @@ constexpr int kMxWaves = 8;
 constexpr int kMxMaxSegments = 13;       // R = G + 3 <= 16
 constexpr int kMxSegFloats = 14;         // of a segment: 8 polynomial coefficients, its ends, middle and scale, the two outer factors
 constexpr int kMxSegStride = 20;         // ... in LDS: 80-byte rows spread the banks
-constexpr int kMxLdsTail = (kMxMaxSegments + 1) * kMxSegStride * 4 + 16;      // behind the stages in LDS: the segments, a flag
+constexpr int kMxLdsTail = (kMxMaxSegments + 1) * (kMxSegStride * 4 + 2 * 16) + 16;      // behind the stages in LDS: segments, places, a flag
 
 struct SplineMatrixArgs {
   const float *x;            // [B][d]
@@ -142,34 +142,45 @@ __global__ __launch_bounds__(256) void bspline_matrix_locate_kernel(const Spline
 
 union Slots { u32x4 u; bf16x8 h; };
 
+// Where the four non-zero values of a segment go in a lane's 8 slots: for each of their four words the byte permute that takes
+// it out of the packed values (SLOTS 8: {n0, n1} and {n2, n3}, moved up by `first` slots; SLOTS 16: the two of the lane's
+// parity, moved to slot `at`).  One 16-byte LDS read and a permute per word and piece, in place of shifts and selects.
+template <int SLOTS>
+__device__ __forceinline__ void fill_places(u32x4 *s_place, int segments, int tid) {
+  constexpr unsigned kNone = 0x0c0cu, kValue[4] = {0x0100u, 0x0302u, 0x0504u, 0x0706u};      // two bytes of zero; value 0 .. 3
+  if (tid >= 2 * (segments + 1)) return;
+  const int first = tid >> 1, half = tid & 1;
+  const int at = (SLOTS == 8) ? first : (first + ((first ^ half) & 1) - half) >> 1, n = (SLOTS == 8) ? 4 : 2;
+  unsigned w[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int lo = 2 * q - at, hi = lo + 1;                // which of the packed values lands in slots 2q and 2q + 1
+    w[q] = ((lo >= 0 && lo < n) ? kValue[lo & 3] : kNone) | ((hi >= 0 && hi < n) ? kValue[hi & 3] : kNone) << 16;
+  }
+  s_place[tid] = u32x4{w[0], w[1], w[2], w[3]};
+}
+
 // a lane's 8 slots of one (row, input), three pieces
 template <int SLOTS>
-__device__ __forceinline__ void slots_of(const float n[4], int first, int half, Slots out[3]) {
+__device__ __forceinline__ void slots_of(const u32x4 *s_place, const float n[4], int first, int half, Slots out[3]) {
+  const u32x4 place = s_place[2 * first + half];
   if constexpr (SLOTS == 8) {
     unsigned p01[3], p23[3];
     lutkan_cut3_pair(n[0], n[1], p01);
     lutkan_cut3_pair(n[2], n[3], p23);
-    const int up = 16 * first;                              // first = 0 .. 4
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const unsigned long long v = ((unsigned long long)p23[q] << 32) | p01[q];
-      const unsigned long long lo = (first == 4 ? 0ull : v) << (up & 63);
-      const unsigned long long hi = (first == 0 ? 0ull : v) >> ((64 - up) & 63);
-      out[q].u = u32x4{(unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32)};
-    }
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) out[q].u[w] = __builtin_amdgcn_perm(p23[q], p01[q], place[w]);
   } else {
-    // rows first .. first+3; this lane holds those of parity `half`: two of them, in slots at and at + 1
+    // rows first .. first+3; this lane holds those of parity `half`
     const bool same = ((first ^ half) & 1) == 0;
-    const int at = (first + (same ? 0 : 1) - half) >> 1;    // 0 .. 6
     unsigned p[3];
     lutkan_cut3_pair(same ? n[0] : n[1], same ? n[2] : n[3], p);
-    const int up = (at & 1) * 16, word = at >> 1;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const unsigned d0 = p[q] << up, d1 = (p[q] >> 16) & (up ? 0xffffu : 0u);
-      out[q].u = u32x4{word == 0 ? d0 : 0u, word == 1 ? d0 : (word == 0 ? d1 : 0u), word == 2 ? d0 : (word == 1 ? d1 : 0u),
-                       word == 3 ? d0 : (word == 2 ? d1 : 0u)};
-    }
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) out[q].u[w] = __builtin_amdgcn_perm(p[q], p[q], place[w]);
   }
 }
 
@@ -183,7 +194,8 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
   constexpr int kStageBytes = 8 * 3 * BN * 16;
   extern __shared__ __align__(16) unsigned char lds[];
   float *const s_seg = reinterpret_cast<float *>(lds + 2 * kStageBytes);
-  int *const s_uncut = reinterpret_cast<int *>(s_seg + (kMxMaxSegments + 1) * kMxSegStride);
+  u32x4 *const s_place = reinterpret_cast<u32x4 *>(s_seg + (kMxMaxSegments + 1) * kMxSegStride);
+  int *const s_uncut = reinterpret_cast<int *>(s_place + 2 * (kMxMaxSegments + 1));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -195,6 +207,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
   const int i_end = min(a.d, i_begin + a.chunk);
 
   fill_segments(a, s_seg, tid, kThreads);
+  fill_places<SLOTS>(s_place, a.segments, tid);
   if (tid == 0) *s_uncut = 0;
 
   // this thread's coefficient columns of a stage: unit u = (input u) resp. (input u & 3, parity u >> 2)
@@ -301,7 +314,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
           if constexpr (RECORDS) at = rec[rt][s]; else at = locate<SLOTS>(a, xc[rt][s], dead[s]);
           float n[4];
           basis_of(s_seg, at, n);
-          slots_of<SLOTS>(n, at.segment, half, af[rt]);
+          slots_of<SLOTS>(s_place, n, at.segment, half, af[rt]);
         }
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
