@@ -464,12 +464,14 @@ int launch_matrix(const SplineMatrixArgs &ma, int n_split, hipStream_t s) {
 
 template <int SLOTS>
 int launch_matrix_slots(const SplineMatrixArgs &ma, int rt, int nt, int n_split, bool records, hipStream_t s) {
-  if (records) {
-    const dim3 grid((unsigned)(ma.Bp / 32), (unsigned)((ma.d + 63) / 64));
-    if (grid.y > 65535u) return fail(LUTKAN_EUNSUPPORTED, "bspline_matrix_locate_kernel: d too large");
-    hipLaunchKernelGGL(bspline_matrix_locate_kernel<SLOTS>, grid, dim3(256), 0, s, ma);
-    if (int rc = check_launch("bspline_matrix_locate_kernel")) return rc;
-    return launch_matrix<SLOTS, 1, 4, true>(ma, n_split, s);         // (many column tiles: the table is 128 columns wide)
+  if constexpr (SLOTS == 16) {                             // (with 8 slots a call never locates into records)
+    if (records) {
+      const dim3 grid((unsigned)(ma.Bp / 32), (unsigned)((ma.d + 63) / 64));
+      if (grid.y > 65535u) return fail(LUTKAN_EUNSUPPORTED, "bspline_matrix_locate_kernel: d too large");
+      hipLaunchKernelGGL(bspline_matrix_locate_kernel<SLOTS>, grid, dim3(256), 0, s, ma);
+      if (int rc = check_launch("bspline_matrix_locate_kernel")) return rc;
+      return launch_matrix<SLOTS, 1, 4, true>(ma, n_split, s);       // (many column tiles: the table is 128 columns wide)
+    }
   }
   if (nt == 4) return launch_matrix<SLOTS, 1, 4, false>(ma, n_split, s);
   if (nt == 2) return rt == 2 ? launch_matrix<SLOTS, 2, 2, false>(ma, n_split, s) : launch_matrix<SLOTS, 1, 2, false>(ma, n_split, s);
