@@ -93,20 +93,19 @@ def kernel_costs(info, spec, B, plan):
     last_split = 1
     for clause in [c.strip() for c in plan.split(";") if c.strip()]:
         nums = [int(v) for v in re.findall(r"=(\d+)", clause)]
-        if clause == "locate" and "one_launch" in plan:                     # located inside the kernel of the next clause
-            out.append(dict(kernel="lutkan_narrow_kernel", hbm=4 * B * d, l2=0, lds=0, valu=45 * B * d))
-        elif clause == "locate":
+        if clause == "locate":
             # about 30 + K vector instructions per (row, input): domain test, clip, K-1 compares, divide, floor, record
             silu_plane = 4 * B * d if (info.value_repr == 1 and "base_product" in plan) else 0
             out.append(dict(kernel="lutkan_locate_kernel", hbm=4 * B * d + rec * Bp * d + silu_plane, l2=0, lds=2 * rec * Bp * d,
                             valu=(30 + K) * B * d))
-        elif clause.startswith("tiled"):
-            np_, last_split = nums[:2]                                   # (the third number is the pipeline mode)
+        elif clause.startswith(("tiled", "narrow")):
+            # tiled: row steps per wave, chunks, pipeline mode.  narrow: chunks, waves; no records, inputs located in the kernel
+            narrow = clause.startswith("narrow")
+            np_, last_split = (1, nums[0]) if narrow else nums[:2]
             # a wide form of the table: 16-bit codes (code rows twice as long), or fp32 values (four times, no parameter rows)
             wide = 4 if clause.startswith("tiled wide32") else 2 if clause.startswith("tiled wide") else 0
-            one_launch = "one_launch" in clause                              # a narrow layer: no records, the third number its waves
-            rec_bytes = 0 if one_launch else rec * Bp * d
-            rows_per_group = (nums[2] if one_launch else 16) * (64 // (info.jt // 4)) * np_
+            rec_bytes = 0 if narrow else rec * Bp * d
+            rows_per_group = (nums[1] if narrow else 16) * (64 // (info.jt // 4)) * np_
             code_bytes_all = info.n_tiles * d * (K * info.L + 2) * info.jt
             param_bytes_all = info.n_tiles * d * (K + 1) * info.jt * (8 if asym else 4)
             table_bytes = info.table_bytes + (3 * code_bytes_all - param_bytes_all if wide == 4 else code_bytes_all if wide else 0)
@@ -120,8 +119,10 @@ def kernel_costs(info, spec, B, plan):
             # on fp32 values all but the address instruction are two-operand fp32 instructions on registers, which
             # issue about twice as fast as the rest: counted apart (valu2) and priced at their own rate
             valu2 = edges / 4 * 12 if wide == 4 else 0
-            out.append(dict(kernel="lutkan_narrow_kernel" if one_launch else "lutkan_tiled_kernel", hbm=table_bytes + rec_bytes + 4 * B * m * last_split,
-                            l2=staged, lds=edges / 4 * lds_per4 + staged, valu=edges / 4 * per4 - valu2, valu2=valu2))
+            inputs = B * d if narrow else 0
+            out.append(dict(kernel="lutkan_narrow_kernel" if narrow else "lutkan_tiled_kernel",
+                            hbm=table_bytes + rec_bytes + 4 * inputs + 4 * B * m * last_split, l2=staged, lds=edges / 4 * lds_per4 + staged,
+                            valu=edges / 4 * per4 - valu2 + 45 * inputs, valu2=valu2))
         elif clause.startswith("gather"):
             last_split = nums[0]
             touched = min(info.table_bytes, B * d * info.n_tiles * info.jt * (2 + prm))
@@ -269,7 +270,7 @@ def run_workload(rig, name, steps, warmup, batch=None, bspline=True, cpu_baselin
         lk.lutkan_forward(layer, acts[li], acts[li + 1], workspace=ws)
         plan = lk.lutkan_last_plan()
         costs += kernel_costs(art.info, spec, B, plan)
-        if plan.startswith("chain") or "one_launch" in plan:      # the whole call is the kernel (and its summing pass)
+        if plan.startswith(("chain", "narrow")):                  # the whole call is the kernel (and its summing pass)
             evs = [rig.events() for _ in range(n_ev)]
             for a, b in evs:
                 a.record()

@@ -64,15 +64,16 @@ typedef enum { LUTKAN_SPAN_DOMAIN = 0, LUTKAN_SPAN_EXTENDED = 1 } lutkan_knot_sp
 
 const char *lutkan_last_error(void);
 const char *lutkan_version(void);
-/* What the last forward call of this thread launched, for logs and tests: one clause per kernel launch -- except that "locate;
- * tiled np=1 split=1 one_launch waves=16; " is a narrow layer whose tiled kernel locates its inputs itself; "rows wpr=16; " is a
- * few rows in one launch --, e.g.
+/* What the last forward call of this thread launched, for logs and tests: one clause per kernel launch, in the order of
+ * the launches, e.g.
  * "locate; tiled np=16 split=2 pipe=3; sum; " (row steps per wave, chunks of inputs, pipeline mode: 2 = two slice
  * buffers, 3 = three with the reads carried across inputs, 4 = three with two slices in flight; "tiled wide" on the
- * table's form with 16-bit codes, "tiled wide32" on the one with fp32 values) or "chain layers=2 wpr=4; " or "locate; gather split=16; sum; " or, for a large
- * spline_component layer, "locate; base_product; tiled np=16 split=1 pipe=3; " or, for a B-spline layer on the matrix cores, "bspline_matrix np=1
- * split=2 slots=8; sum; " (model_forward: the clauses of all its
- * layers).  Thread-local, overwritten by the next forward call, never null. */
+ * table's form with 16-bit codes, "tiled wide32" on the one with fp32 values) or "chain layers=2 wpr=4; " or "locate; gather split=16; sum; " or, where
+ * one launch locates, gathers and sums, "rows wpr=16; " (a few rows; waves per row) or "narrow split=1 waves=16; " (a layer of at
+ * most 32 columns; chunks of inputs, waves per work-group) or, for a large spline_component layer, "locate; base_product; tiled
+ * np=16 split=1 pipe=3; " (base_product cuts the base rows into pieces in a launch of its own) or, for a B-spline layer on the
+ * matrix cores, "bspline_matrix np=1 split=2 slots=8; sum; ", after "bspline_matrix_locate; " where its inputs are located once
+ * into records (model_forward: the clauses of all its layers).  Thread-local, overwritten by the next forward call, never null. */
 const char *lutkan_last_plan(void);
 
 /* ------------------------------------------------------------------------------------------------

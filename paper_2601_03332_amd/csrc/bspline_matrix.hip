@@ -513,8 +513,8 @@ int bspline_matrix_forward(const bspline_dev_layer *l, const float *x, int64_t B
   if (mp.n_split > 1) { ma.y = partials; ma.split_stride = B * l->m; }
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   if (int rc = slots == 8 ? launch_matrix_slots<8>(ma, mp.rt, nt, mp.n_split, records, s) : launch_matrix_slots<16>(ma, mp.rt, nt, mp.n_split, records, s)) return rc;
-  if (records) plan_note("bspline_locate; bspline_tiled np=%d split=%d matrix slots=%d; ", mp.rt, mp.n_split, slots);
-  else plan_note("bspline_matrix np=%d split=%d slots=%d; ", mp.rt, mp.n_split, slots);
+  if (records) plan_note("bspline_matrix_locate; ");
+  plan_note("bspline_matrix np=%d split=%d slots=%d; ", mp.rt, mp.n_split, slots);
   if (mp.n_split == 1) return LUTKAN_OK;
   const int64_t n = B * l->m;
   hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s, partials, y, n, mp.n_split, 0);

@@ -339,7 +339,7 @@ int narrow_forward(const lutkan_dev_layer *l, const NarrowPlan &plan, const floa
     rc = plan.waves == 16 ? launch_narrow_width<LUTKAN_ASYM_UINT8, 16>(na, plan.stage, base, half_params, plan.n_split, s)
                           : launch_narrow_width<LUTKAN_ASYM_UINT8, 4>(na, plan.stage, base, half_params, plan.n_split, s);
   if (rc) return rc;
-  plan_note("locate; tiled np=1 split=%d one_launch waves=%d; ", plan.n_split, plan.waves);
+  plan_note("narrow split=%d waves=%d; ", plan.n_split, plan.waves);
   if (plan.n_split == 1) return LUTKAN_OK;
   const int64_t n = B * l->m;
   hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s, partials, y, n, plan.n_split, 0);

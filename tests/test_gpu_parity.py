@@ -1219,7 +1219,7 @@ def test_last_plan_reports_what_auto_dispatch_launched():
     lk.lutkan_forward(layer, xg, stats=stats)
     assert lk.lutkan_last_plan() == plan.replace("locate; ", "locate; oob; ")   # the counters add one launch, nothing else
     lk.bspline_kan_forward(art.bspline_to_device(DEV), xg)
-    assert lk.lutkan_last_plan().startswith("bspline_locate; bspline_tiled np=")
+    assert re.fullmatch(r"bspline_matrix_locate; bspline_matrix np=1 split=\d+ slots=16; (sum; )?", lk.lutkan_last_plan()), lk.lutkan_last_plan()
     _say("case last plan: cfg2 at 300, 5000, 20000 and 40000 rows")
     w2 = cfg2(B=40000)
     layers = []
@@ -1237,10 +1237,10 @@ def test_last_plan_reports_what_auto_dispatch_launched():
     assert lk.lutkan_last_plan() == "chain layers=1 wpr=4; "                   # a single small layer runs as a one-layer chain
     lk.lutkan_model_forward(layers, x2[:20000])
     plan = lk.lutkan_last_plan()                                               # 78x16 has outgrown the chain kernel, 16x2 has not yet
-    assert plan.count("locate; tiled np=") == 1 and plan.endswith("chain layers=1 wpr=1; "), plan
+    assert re.fullmatch(r"narrow split=\d+ waves=\d+; (sum; )?chain layers=1 wpr=1; ", plan), plan
     lk.lutkan_model_forward(layers, x2)
     plan = lk.lutkan_last_plan()
-    assert plan.count("locate; tiled np=") == 2 and "chain" not in plan, plan  # large batches: locate + tiled kernel per layer
+    assert re.fullmatch(r"(narrow split=\d+ waves=\d+; (sum; )?){2}", plan), plan     # large batches: the narrow kernel per layer
     torch.cuda.synchronize()
 
 
@@ -1305,7 +1305,7 @@ def test_bspline_layer_on_the_matrix_cores(case):
     xg = torch.from_numpy(x).to(DEV)
     y = lk.bspline_kan_forward(layer, xg)
     plan = lk.lutkan_last_plan()
-    assert f"slots={8 if G <= 5 else 16}; " in plan and plan.startswith("bspline_locate; " if seed == 911 else "bspline_matrix "), plan
+    assert f"slots={8 if G <= 5 else 16}; " in plan and plan.startswith("bspline_matrix_locate; bspline_matrix " if seed == 911 else "bspline_matrix "), plan
     shifted = torch.empty(B * d + 1, dtype=torch.float32, device=DEV)[1:].view(B, d).copy_(xg)      # rows off the 16-byte grid
     y_shifted = lk.bspline_kan_forward(layer, shifted)
     torch.cuda.synchronize()
@@ -1525,7 +1525,7 @@ def test_narrow_layer_in_one_launch(case):
     xg = torch.from_numpy(x).to(DEV)
     stats = torch.zeros(2, dtype=torch.int64, device=DEV)
     y = lk.lutkan_forward(layer, xg, stats=stats)
-    assert "one_launch" in lk.lutkan_last_plan(), lk.lutkan_last_plan()
+    assert lk.lutkan_last_plan().startswith("narrow split="), lk.lutkan_last_plan()
     shifted = torch.empty(B * d + 1, dtype=torch.float32, device=DEV)[1:].view(B, d).copy_(xg)
     y_shifted = lk.lutkan_forward(layer, shifted)
     torch.cuda.synchronize()
@@ -1551,7 +1551,7 @@ def test_narrow_layer_locates_bit_exactly():
         layer = art.to_device(DEV)
         xg = torch.from_numpy(x).to(DEV)
         y = lk.lutkan_forward(layer, xg)
-        assert "one_launch" in lk.lutkan_last_plan(), lk.lutkan_last_plan()
+        assert lk.lutkan_last_plan().startswith("narrow split="), lk.lutkan_last_plan()
         _, k, l0, _, wgt, _ = lk.lutkan_forward_trace(layer, xg)
         expect = (1 << k.long()).double() * (l0.double() + wgt.double())
         # (the running sums carry 2^-24, so a value below 2^-126 * 2^24 -- a weight next to the knot at 0 -- may be flushed)
@@ -1656,7 +1656,7 @@ def test_outputs_that_lie_partly_over_the_inputs(case):
     refb = oracle.bspline_forward(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.boundary, s.oob, x)
     xg = torch.from_numpy(x).to(DEV)
     lk.lutkan_forward(layer, xg)
-    assert "rows" in lk.lutkan_last_plan() or "one_launch" in lk.lutkan_last_plan()
+    assert lk.lutkan_last_plan().startswith(("rows ", "narrow "))
     for what, at_x, at_y in (("y in x", 0, B * d // 2 & ~3), ("x in y", B * m // 2 & ~3, 0), ("one row apart", 0, 4)):
         _say(f"case overlap {what}: d={d} m={m} B={B}")
         buf = torch.zeros(max(at_x + B * d, at_y + B * m), dtype=torch.float32, device=DEV)
