@@ -74,6 +74,22 @@ def make_workload(name, batch=None):
 
 
 # ------------------------------------------------------------------------------------------------ cost model
+ONE_LAUNCH_KERNELS = {"chain": "lutkan_chain_kernel", "narrow": "lutkan_narrow_kernel", "rows": "lutkan_rows_kernel"}
+
+
+def one_launch_kernel(plan):
+    """The kernel that runs a whole lutkan_forward call (but for a summing pass) without records, or None when the call
+    is the locate kernel and an edge kernel, which can be timed as two phases."""
+    return ONE_LAUNCH_KERNELS.get(plan.split()[0].rstrip(";"))
+
+
+def rows_with_records(info, B, plan):
+    """Rows that the locate kernel of a call fills: whole row tiles of its tiled kernel (and of the base product's 128), or 256."""
+    mt = re.search(r"tiled[a-z0-9 ]* np=(\d+)", plan)
+    unit = max(128, 16 * (64 // (info.jt // 4)) * int(mt.group(1))) if mt else 256
+    return -(-B // unit) * unit
+
+
 def kernel_costs(info, spec, B, plan):
     """What each kernel launch of one lutkan_forward call must move and compute, from the layer's shape and the launch
     plan the library reports (lutkan_last_plan): a list of dicts {kernel, hbm, l2, lds, valu[, valu2]} in bytes resp. vector
@@ -87,7 +103,7 @@ def kernel_costs(info, spec, B, plan):
     base = (info.value_repr == 1) and not base_product         # ... else inside the edge kernel
     rec = 16 if base else 8
     prm = (8 if asym else 4) + (4 if base else 0)               # parameter bytes per edge
-    Bp = -(-B // 1024) * 1024
+    Bp = rows_with_records(info, B, plan)
     edges = B * d * m
     out = []
     last_split = 1
@@ -114,8 +130,8 @@ def kernel_costs(info, spec, B, plan):
             # differences, four interpolations, four scalings [, four y_min] [, four base products]; on fp32 values one
             # address, four differences, four interpolations, four additions
             per4 = (13 if wide == 4 else (16 if asym else 12) if wide else (20 if asym else 18)) + (4 if base else 0)
-            # record, two code rows, alpha (+ y_min) per lane
-            lds_per4 = (12 if base else 8) + (32 if wide == 4 else (16 if wide else 8) + (32 if asym else 16))
+            # record (not in the narrow kernel), two code rows, alpha (+ y_min) per lane
+            lds_per4 = (4 if base else 0) + (0 if narrow else 8) + (32 if wide == 4 else (16 if wide else 8) + (32 if asym else 16))
             # on fp32 values all but the address instruction are two-operand fp32 instructions on registers, which
             # issue about twice as fast as the rest: counted apart (valu2) and priced at their own rate
             valu2 = edges / 4 * 12 if wide == 4 else 0
@@ -140,6 +156,14 @@ def kernel_costs(info, spec, B, plan):
             touched = min(info.table_bytes, B * d * info.jt * (2 + prm))
             out.append(dict(kernel="lutkan_chain_kernel", hbm=touched + 4 * B * (d + m), l2=edges * (2 + prm),
                             lds=16 * B * d * (1 + max(1, m)), valu=edges * 14 + (30 + K) * B * d))
+        elif clause.startswith("rows"):
+            # every column tile locates its row's inputs again; 16-byte records in LDS, read once per lane of four columns
+            columns = info.n_tiles * info.jt
+            touched = min(info.table_bytes, B * d * columns * (2 + prm))
+            out.append(dict(kernel="lutkan_rows_kernel", hbm=touched + 4 * B * (d + m), l2=B * d * columns * (2 + prm),
+                            lds=16 * B * d * (info.n_tiles + columns / 4), valu=B * d * (columns * 14 + 45 * info.n_tiles)))
+        elif clause != "oob":                                             # (the counters are not part of a timed call)
+            raise ValueError(f"bench.py: launch plan clause {clause!r} has no cost model")
     return out
 
 
@@ -270,14 +294,14 @@ def run_workload(rig, name, steps, warmup, batch=None, bspline=True, cpu_baselin
         lk.lutkan_forward(layer, acts[li], acts[li + 1], workspace=ws)
         plan = lk.lutkan_last_plan()
         costs += kernel_costs(art.info, spec, B, plan)
-        if plan.startswith(("chain", "narrow")):                  # the whole call is the kernel (and its summing pass)
+        if one_launch_kernel(plan):                               # the whole call is the kernel (and its summing pass)
             evs = [rig.events() for _ in range(n_ev)]
             for a, b in evs:
                 a.record()
                 lk.lutkan_forward(layer, acts[li], acts[li + 1], workspace=ws)
                 b.record()
             torch.cuda.synchronize()
-            kernels.append({"layer": li, "kernel": "lutkan_chain_kernel" if plan.startswith("chain") else "lutkan_narrow_kernel", "ms": sum(a.elapsed_time(b) for a, b in evs) / n_ev,
+            kernels.append({"layer": li, "kernel": one_launch_kernel(plan), "ms": sum(a.elapsed_time(b) for a, b in evs) / n_ev,
                             "plan": plan.strip()})
             continue
         evs = [[torch.cuda.Event(enable_timing=True) for _ in range(3)] for _ in range(n_ev)]

@@ -1673,6 +1673,17 @@ def test_outputs_that_lie_partly_over_the_inputs(case):
         _assert_close(yv.cpu().numpy(), refb, "bspline " + what)
 
 
+@pytest.mark.parametrize("workload,batch", [("cfg3_L64_sym", 256), ("cfg2", 20000), ("cfg5_closed_clip_x", 64)])
+def test_bench_times_the_calls_that_run_in_one_launch(workload, batch):
+    """bench.py takes a call apart into its phases only where it has two; the layers of these workloads run on the rows, narrow
+    and chain kernels."""
+    import bench
+    rec = bench.run_workload(bench.Rig(probes=False), workload, steps=2, warmup=1, batch=batch, bspline=False, cpu_baseline=False)
+    named = [k["kernel"] for k in rec["kernels"]]
+    assert any(k in ("lutkan_rows_kernel", "lutkan_narrow_kernel") for k in named), named
+    assert all(k["ms"] > 0 for k in rec["kernels"]) and rec["roofline"]["terms"]["work"]["hbm"] > 0
+
+
 def test_calls_run_on_torchs_current_stream():
     """The stream handle that a call gets is the current stream's, on the default stream and on others, and work queued
     there before the call is seen by it."""

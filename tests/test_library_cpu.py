@@ -294,6 +294,29 @@ def test_model_forward_refuses_aliased_x_and_y_of_a_small_network_at_every_batch
         assert "alias" in lk.lutkan_last_error()
 
 
+def test_bench_prices_every_launch_that_a_plan_can_name():
+    """Each clause of a launch plan has a kernel and a cost in bench.py's model; one that it does not know is an error, not zero
+    work.  Kernels that run a whole call are timed as one."""
+    import bench
+    w = random_layer(71, 256, 256, 8, 64, SYM_INT8, CLOSED, CLIP_X, 4)
+    s = w.layers[0]
+    art, _ = _both(s)
+    for plan, kernels in (("rows wpr=16; ", ["lutkan_rows_kernel"]), ("chain layers=1 wpr=4; ", ["lutkan_chain_kernel"]),
+                          ("narrow split=2 waves=4; sum; ", ["lutkan_narrow_kernel", "sum_partials_kernel"]),
+                          ("locate; gather split=16; sum; ", ["lutkan_locate_kernel", "lutkan_gather_kernel", "sum_partials_kernel"]),
+                          ("locate; oob; tiled wide np=4 split=1 pipe=2; ", ["lutkan_locate_kernel", "lutkan_tiled_kernel"]),
+                          ("locate; base_product; tiled np=16 split=1 pipe=3; ", ["lutkan_locate_kernel", "lutkan_base_gemm_kernel", "lutkan_tiled_kernel"])):
+        costs = bench.kernel_costs(art.info, s, 300, plan)
+        assert [c["kernel"] for c in costs] == kernels
+        assert all(c["hbm"] > 0 and c["valu"] > 0 for c in costs)
+        assert bench.one_launch_kernel(plan) == (kernels[0] if kernels[0] != "lutkan_locate_kernel" else None)
+    with pytest.raises(ValueError, match="a_new_kernel"):
+        bench.kernel_costs(art.info, s, 300, "a_new_kernel np=1; ")
+    assert bench.rows_with_records(art.info, 300, "locate; gather split=16; sum; ") == 512
+    assert bench.rows_with_records(art.info, 300, "tiled wide32 np=4 split=1 pipe=2; ") == 512
+    assert bench.rows_with_records(art.info, 300, "tiled np=1 split=1 pipe=2; ") == 384
+
+
 def test_stored_symmetric_artifact_with_an_offset_is_refused():
     """Eq. 11 fixes y_min = 0 for symmetric int8 and the device table of that scheme carries no y_min plane: stored
     arrays that say otherwise are refused instead of silently losing the offset."""
