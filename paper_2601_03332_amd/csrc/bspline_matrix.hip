@@ -52,10 +52,9 @@ constexpr int kMxLdsTail = (kMxMaxSegments + 1) * (kMxSegStride * 4 + 2 * 16) + 
 
 struct SplineMatrixArgs {
   const float *x;            // [B][d]
-  u32x2 *rec;                // [d][Bp] records of the separate locate pass
   const float *coef_table;   // [t][i][R][jt]
   float *y;
-  int64_t B, Bp;
+  int64_t B;
   int32_t d, m, R, segments, jt, n_tiles;
   int32_t x_vec4;            // rows of x are whole aligned 16-byte vectors
   int32_t chunk;             // inputs per work-group (blockIdx.y), a multiple of 8
@@ -112,34 +111,6 @@ __device__ __forceinline__ void fill_segments(const SplineMatrixArgs &a, float *
   }
 }
 
-// The separate locate pass of a layer with many column tiles: 8-byte records {x', segment} [input][row], a tile of
-// 32 rows x 64 inputs per block, transposed through LDS as in the LUT layer's locate kernel.
-template <int SLOTS>
-__global__ __launch_bounds__(256) void bspline_matrix_locate_kernel(const SplineMatrixArgs a) {
-  constexpr int ROWS = 32, COLS = 64;
-  __shared__ u32x2 s_rec[COLS][ROWS + 1];
-  const int tid = threadIdx.x;
-  const int64_t b0 = (int64_t)blockIdx.x * ROWS;
-  const int i0 = blockIdx.y * COLS;
-  const int il = tid & (COLS - 1);
-  const int i = min(i0 + il, a.d - 1);
-  float xv[8];
-#pragma unroll
-  for (int p = 0; p < 8; ++p) xv[p] = a.x[min(b0 + p * 4 + tid / COLS, a.B - 1) * a.d + i];
-#pragma unroll
-  for (int p = 0; p < 8; ++p) {
-    const Position at = locate<SLOTS>(a, xv[p], false);
-    s_rec[il][p * 4 + tid / COLS] = u32x2{__float_as_uint(at.x), (unsigned)at.segment};
-  }
-  __syncthreads();
-  const int bl = tid & (ROWS - 1);
-#pragma unroll
-  for (int p = 0; p < 8; ++p) {
-    const int il2 = p * 8 + tid / ROWS;
-    if (i0 + il2 < a.d && b0 + bl < a.Bp) a.rec[(int64_t)(i0 + il2) * a.Bp + b0 + bl] = s_rec[il2][bl];
-  }
-}
-
 union Slots { u32x4 u; bf16x8 h; };
 
 // Where the four non-zero values of a segment go in a lane's 8 slots: for each of their four words the byte permute that takes
@@ -184,7 +155,7 @@ __device__ __forceinline__ void slots_of(const u32x4 *s_place, const float n[4],
   }
 }
 
-template <int SLOTS, int RT, int NT, bool RECORDS>
+template <int SLOTS, int RT, int NT>
 __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const SplineMatrixArgs a) {
   constexpr int BN = 32 * NT;
   constexpr int IS = (SLOTS == 8) ? 8 : 4;                // inputs per stage: 8 units of 8 slots, 4 k steps
@@ -252,15 +223,11 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) row[rt] = min(row0 + rt * 32 + col, a.B - 1);
   float xv[RT][4];
-  u32x2 rv[RT][4];
   auto load_inputs = [&](int i0) {
     const int i = i0 + lane_input;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-      if constexpr (RECORDS) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) rv[rt][s] = a.rec[min(i + s, a.d - 1) * a.Bp + row[rt]];
-      } else if (a.x_vec4) {
+      if (a.x_vec4) {
         const f32x4 v = *reinterpret_cast<const f32x4 *>(a.x + row[rt] * a.d + min(i, a.d - 4));
         xv[rt][0] = v.x; xv[rt][1] = v.y; xv[rt][2] = v.z; xv[rt][3] = v.w;
       } else {
@@ -288,16 +255,12 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
     const bool more = i0 + IS < i_end;
     // the inputs of this stage; one past the work-group's last takes the all-zero segment (and a finite x)
     float xc[RT][4];
-    Position rec[RT][4];
     bool dead[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       dead[s] = i0 + lane_input + s >= i_end;
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        if constexpr (RECORDS) rec[rt][s] = Position{dead[s] ? 0.0f : __uint_as_float(rv[rt][s].x), dead[s] ? a.segments : (int)rv[rt][s].y};
-        else xc[rt][s] = dead[s] ? a.t0 : xv[rt][s];
-      }
+      for (int rt = 0; rt < RT; ++rt) xc[rt][s] = dead[s] ? a.t0 : xv[rt][s];
     }
     if (more) {                                            // the next stage travels while this one multiplies
       load_coefs(i0 + IS);
@@ -310,8 +273,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
         Slots af[RT][3];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          Position at;
-          if constexpr (RECORDS) at = rec[rt][s]; else at = locate<SLOTS>(a, xc[rt][s], dead[s]);
+          const Position at = locate<SLOTS>(a, xc[rt][s], dead[s]);
           float n[4];
           basis_of(s_seg, at, n);
           slots_of<SLOTS>(s_place, n, at.segment, half, af[rt]);
@@ -450,32 +412,23 @@ MatrixPlan plan_matrix(int64_t B, int d, int m, int n_tiles, int nt, int slots, 
   return best;
 }
 
-template <int SLOTS, int RT, int NT, bool RECORDS>
+template <int SLOTS, int RT, int NT>
 int launch_matrix(const SplineMatrixArgs &ma, int n_split, hipStream_t s) {
   constexpr int kRows = kMxWaves * 32 * RT;
   const int64_t groups = (ma.B + kRows - 1) / kRows * ma.n_tiles;
   if (groups > 0x7fffffffLL) return fail(LUTKAN_EUNSUPPORTED, "bspline_matrix_kernel: B * m too large for one launch");
   const size_t lds = 2 * (size_t)(8 * 3 * 32 * NT * 16) + kMxLdsTail;
   static LdsCap raised;
-  if (int rc = raise_lds_cap(bspline_matrix_kernel<SLOTS, RT, NT, RECORDS>, &raised, "bspline_matrix_kernel")) return rc;
-  hipLaunchKernelGGL((bspline_matrix_kernel<SLOTS, RT, NT, RECORDS>), dim3((unsigned)groups, (unsigned)n_split), dim3(kMxWaves * 64), lds, s, ma);
+  if (int rc = raise_lds_cap(bspline_matrix_kernel<SLOTS, RT, NT>, &raised, "bspline_matrix_kernel")) return rc;
+  hipLaunchKernelGGL((bspline_matrix_kernel<SLOTS, RT, NT>), dim3((unsigned)groups, (unsigned)n_split), dim3(kMxWaves * 64), lds, s, ma);
   return check_launch("bspline_matrix_kernel");
 }
 
 template <int SLOTS>
-int launch_matrix_slots(const SplineMatrixArgs &ma, int rt, int nt, int n_split, bool records, hipStream_t s) {
-  if constexpr (SLOTS == 16) {                             // (with 8 slots a call never locates into records)
-    if (records) {
-      const dim3 grid((unsigned)(ma.Bp / 32), (unsigned)((ma.d + 63) / 64));
-      if (grid.y > 65535u) return fail(LUTKAN_EUNSUPPORTED, "bspline_matrix_locate_kernel: d too large");
-      hipLaunchKernelGGL(bspline_matrix_locate_kernel<SLOTS>, grid, dim3(256), 0, s, ma);
-      if (int rc = check_launch("bspline_matrix_locate_kernel")) return rc;
-      return launch_matrix<SLOTS, 1, 4, true>(ma, n_split, s);       // (many column tiles: the table is 128 columns wide)
-    }
-  }
-  if (nt == 4) return launch_matrix<SLOTS, 1, 4, false>(ma, n_split, s);
-  if (nt == 2) return rt == 2 ? launch_matrix<SLOTS, 2, 2, false>(ma, n_split, s) : launch_matrix<SLOTS, 1, 2, false>(ma, n_split, s);
-  return rt == 2 ? launch_matrix<SLOTS, 2, 1, false>(ma, n_split, s) : launch_matrix<SLOTS, 1, 1, false>(ma, n_split, s);
+int launch_matrix_slots(const SplineMatrixArgs &ma, int rt, int nt, int n_split, hipStream_t s) {
+  if (nt == 4) return launch_matrix<SLOTS, 1, 4>(ma, n_split, s);
+  if (nt == 2) return rt == 2 ? launch_matrix<SLOTS, 2, 2>(ma, n_split, s) : launch_matrix<SLOTS, 1, 2>(ma, n_split, s);
+  return rt == 2 ? launch_matrix<SLOTS, 2, 1>(ma, n_split, s) : launch_matrix<SLOTS, 1, 1>(ma, n_split, s);
 }
 
 }  // namespace
@@ -498,22 +451,13 @@ int bspline_matrix_forward(const bspline_dev_layer *l, const float *x, int64_t B
   for (int k = 0; k < l->G; ++k) segment_constants(l->ext_knots, 3 + k, ma.segment[k]);
   const int slots = (ma.R <= 8) ? 8 : 16;
   const int nt = ma.jt >= 128 ? 4 : ma.jt >= 64 ? 2 : 1;
-  // With 16 slots and four or more column tiles the inputs are located once, into records, instead of once per column
-  // tile, from 1e9 edges on: 512 -> 512 at 8192 rows, G = 8, 362 -> 338 us, 1024 -> 1024 at 4096 rows, G = 10, 664 -> 633; the
-  // further launch costs more below (512 -> 512 at 500 rows 39 -> 42), and with 8 slots, whose search is short, everywhere
-  // (512 -> 512 at 8192 rows, G = 5, 184 -> 190; 1024 -> 1024 at 32768 2507 -> 2580).
-  const bool records = slots == 16 && l->n_tiles >= 4 && (double)B * l->d * l->m >= 1e9;
-  ma.Bp = padded_rows(B);
-  ma.rec = static_cast<u32x2 *>(workspace);
-  const size_t rec_bytes = records ? record_bytes(l->d, ma.Bp, 8) : 0;
-  float *const partials = reinterpret_cast<float *>(static_cast<char *>(workspace) + rec_bytes);
-  const MatrixPlan mp = plan_matrix(B, l->d, l->m, l->n_tiles, nt, slots, workspace_bytes - rec_bytes);
+  float *const partials = static_cast<float *>(workspace);
+  const MatrixPlan mp = plan_matrix(B, l->d, l->m, l->n_tiles, nt, slots, workspace_bytes);
   ma.chunk = mp.chunk;
   ma.y = y;
   if (mp.n_split > 1) { ma.y = partials; ma.split_stride = B * l->m; }
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  if (int rc = slots == 8 ? launch_matrix_slots<8>(ma, mp.rt, nt, mp.n_split, records, s) : launch_matrix_slots<16>(ma, mp.rt, nt, mp.n_split, records, s)) return rc;
-  if (records) plan_note("bspline_matrix_locate; ");
+  if (int rc = slots == 8 ? launch_matrix_slots<8>(ma, mp.rt, nt, mp.n_split, s) : launch_matrix_slots<16>(ma, mp.rt, nt, mp.n_split, s)) return rc;
   plan_note("bspline_matrix np=%d split=%d slots=%d; ", mp.rt, mp.n_split, slots);
   if (mp.n_split == 1) return LUTKAN_OK;
   const int64_t n = B * l->m;

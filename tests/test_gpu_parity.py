@@ -1219,7 +1219,7 @@ def test_last_plan_reports_what_auto_dispatch_launched():
     lk.lutkan_forward(layer, xg, stats=stats)
     assert lk.lutkan_last_plan() == plan.replace("locate; ", "locate; oob; ")   # the counters add one launch, nothing else
     lk.bspline_kan_forward(art.bspline_to_device(DEV), xg)
-    assert re.fullmatch(r"bspline_matrix_locate; bspline_matrix np=1 split=\d+ slots=16; (sum; )?", lk.lutkan_last_plan()), lk.lutkan_last_plan()
+    assert re.fullmatch(r"bspline_matrix np=1 split=\d+ slots=16; (sum; )?", lk.lutkan_last_plan()), lk.lutkan_last_plan()
     _say("case last plan: cfg2 at 300, 5000, 20000 and 40000 rows")
     w2 = cfg2(B=40000)
     layers = []
@@ -1285,7 +1285,7 @@ MATRIX_CASES = [
     (908, 130, 300, 10, HALF_OPEN, ZERO_SPLINE, 700, False),
     (909, 64, 8, 5, CLOSED, CLIP_X, 140000, True),            # two row tiles per wave on narrow columns
     (910, 68, 64, 12, HALF_OPEN, CLIP_X, 70001, False),
-    (911, 512, 400, 7, CLOSED, ZERO_SPLINE, 5003, False),     # located once into records (four column tiles, 1e9 edges)
+    (911, 512, 400, 7, CLOSED, ZERO_SPLINE, 5003, False),     # four column tiles, 1e9 edges
 ]
 
 
@@ -1305,7 +1305,7 @@ def test_bspline_layer_on_the_matrix_cores(case):
     xg = torch.from_numpy(x).to(DEV)
     y = lk.bspline_kan_forward(layer, xg)
     plan = lk.lutkan_last_plan()
-    assert f"slots={8 if G <= 5 else 16}; " in plan and plan.startswith("bspline_matrix_locate; bspline_matrix " if seed == 911 else "bspline_matrix "), plan
+    assert f"slots={8 if G <= 5 else 16}; " in plan and plan.startswith("bspline_matrix "), plan
     shifted = torch.empty(B * d + 1, dtype=torch.float32, device=DEV)[1:].view(B, d).copy_(xg)      # rows off the 16-byte grid
     y_shifted = lk.bspline_kan_forward(layer, shifted)
     torch.cuda.synchronize()
