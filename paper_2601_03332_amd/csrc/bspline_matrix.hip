@@ -11,7 +11,7 @@
 // together (lutkan_pieces.h).  The products
 // of the two high pieces have an accumulator of their own, apart from the five small ones: with one accumulator for all
 // six, every small product rounds the large sum once more and the layer came out 1.2 - 1.8 times further from a 64-bit
-// evaluation than the tiled kernel; apart, it is nearer than that kernel (64 -> 128 at 131072 rows 1.6e-7 against 3.0e-7,
+// evaluation than the tiled kernel; apart, it is nearer than that kernel (64 -> 128 at 131072 rows 1.5e-7 against 3.0e-7,
 // 1024 -> 1024 at 4096 rows, G = 10, 4.8e-7 against 5.7e-7).
 //
 // Operand A without LDS: in v_mfma_f32_32x32x16_bf16 a lane holds 8 consecutive k of one row, and k may be numbered
@@ -28,12 +28,14 @@
 // SIMD, so that one's vector work (basis, pieces) overlaps the other's matrix instructions.
 //
 // Bound: the matrix cores at the clock they leave the chip.  96 (SLOTS 16: 192) flop per edge; 1024 -> 1024 at 32768 rows,
-// G = 5: 3.3 PFLOP in 2.50 ms = 1.3 PFLOP/s (a bf16 library product of 8192^3 reaches 1.22 on the same card) against 5.82 ms
-// on the tiled kernel; the matrix pipes are 0.59 busy at 1.7 GHz, vector issue 0.41, LDS 0.24.
-// Whole layers, tiled -> matrix, microseconds: 128 -> 128 at 131072 rows, G = 5, 629 -> 174; 64 -> 8 165 -> 36; 256 -> 256 at
-// 16384 rows 289 -> 102 (G = 5), 289 -> 198 (G = 8); 1024 -> 1024 at 4096 rows, G = 10, 856 -> 633; 128 -> 128 at 64 rows
-// 19 -> 14.  Exchanging lanes so that each half of a wave evaluates the basis of every other input only (SLOTS 16) gave
-// nothing: the vector work is hidden.
+// G = 5: 3.30 TFLOP in 2.70 ms = 1.22 PFLOP/s, what a bf16 library product of 8192^3 reaches on such a card, against 6.16 ms on
+// the tiled kernel.  In one run under counters 2.88 ms at 1.83 GHz: matrix pipes 0.60 busy (1.15 PFLOP/s), vector issue 0.41, LDS
+// 0.24.
+// Whole layers, tiled -> matrix, microseconds (one run; boards and runs differ by 5 %): 128 -> 128 at 131072 rows, G = 5,
+// 587 -> 182; 64 -> 8 162 -> 34; 256 -> 256 at 16384 rows 273 -> 104 (G = 5), 272 -> 183 (G = 8); 1024 -> 1024, G = 10, at 4096 rows
+// 790 -> 684, at 32768 6290 -> 5250; 128 -> 128 at 64 rows 19 -> 13.  Exchanging lanes so that each half of a wave evaluates the
+// basis of every other input only (SLOTS 16) gave nothing, nor did records from a locate pass of its own (1024 -> 1024 at 4096
+// rows 634 against 635).
 // The file is compiled with -ffp-contract=off; fused multiply-adds are written out as fmaf().
 #include "bspline_matrix.h"
 #include "lutkan_device.h"

@@ -936,8 +936,11 @@ int validate_layer(const lutkan_dev_layer *l, const char *who) {
 // (up to 128 MiB): when the bytes the lanes request (per row, input and column tile two code rows and one parameter
 // row) stay below the table's (measured: 256x256 near 128 rows).  A larger table streams from HBM on every tiled
 // launch, and scattered reads of it pay off for longer: the gather kernel is priced at 8 us plus the requested bytes
-// at 9.4 TB/s, the tiled launch at the estimate of its launch planning, 0.84 of it where it reads every slice once (measured:
-// 1024x1024 between 130 rows, gather 110 us, tiled 121, and 200, 154 and 121).
+// at 9.4 TB/s, the tiled launch at the estimate of its launch planning, 0.84 of it where it reads every slice once.  Measured on
+// byte tables of 370 to 686 MiB at 48 to 400 rows, gather / tiled in us on either side of the line: 1024x1024, G = 10, 160 rows
+// 119 / 120, 192 rows 136 / 121; 2048x512 160 rows 121 / 126, 192 rows 136 / 126; 600x2048, G = 8, 128 rows 112 / 116, 144 rows
+// 122 / 119; 700x1024, uint8, L = 48, 80 rows 65 / 70, 96 rows 77 / 70; 1024x1024, G = 5, uint8, 48 rows 50 / 69, but 64 rows
+// (tiled) 62 / 69.
 bool prefer_gather_for_small_batch(const lutkan_dev_layer *l, int64_t B, double tiled_cost_us) {
   const lutkan::BlobLayout lay = lutkan::blob_layout(l->K, l->L, l->jt, l->scheme, l->value_repr, l->param_dtype);
   const double touched = (double)B * l->d * l->n_tiles * (2.0 * l->jt + (double)lay.param_row_bytes);

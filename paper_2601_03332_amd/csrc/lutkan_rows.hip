@@ -12,9 +12,10 @@
 // No workspace, no partial sums in memory, bit-reproducible; nearer to a 64-bit evaluation than the passes (short sums).
 //
 // Bound: dependent reads up to about a hundred rows, then the table bytes the lanes request (12 - 15 TB/s through the L2s).
-// Whole layers, passes -> this kernel, microseconds (about 11 of either are the host's): 256 -> 256, L = 64, at 1 / 64 / 256 / 512
-// rows 18 / 21 / 26 / 30 -> 11 / 12 / 11 / 17 (33 -> 33 at 1000); 1024 -> 64 at 128 rows 33 -> 14; 512 -> 512, L = 32, at 32 rows
-// 25 -> 12; 30 -> 1000 with spline_component at 128 rows 19 -> 11; 700 -> 130 at 128 rows 32 -> 18.
+// Whole layers replayed from a HIP graph, passes -> this kernel, microseconds: 256 -> 256, L = 64, at 1 / 64 / 256 / 512 rows
+// 11.4 / 20.4 / 26 / 29 -> 4.1 / 4.7 / 10.0 / 17.8 (at 1000 the passes run); 1024 -> 64 at 128 rows 30 -> 9.3; 512 -> 512, L = 32, at
+// 32 rows 24.5 -> 6.2; 30 -> 1000 with spline_component at 128 rows 16.8 -> 7.9; 700 -> 130 at 128 rows 30 -> 17.8.  Called one by one
+// the small ones take 7 to 8, the host's share.
 // The file is compiled with -ffp-contract=off; every fused multiply-add is written out as fmaf().
 #include "lutkan_device.h"
 #include "lutkan_locate.h"
