@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void lutkan_base_pieces_kernel(const BasePiece
 }
 
 struct BaseGemmArgs {
-  const uint16_t *a_pieces;          // [3][Bp][d]: SiLU(x) cut into pieces, rows from B to the next multiple of 128 zero (Bp, rows between planes, is one)
+  const uint16_t *a_pieces;          // [3][Bp][d]: SiLU(x) cut into pieces, rows B .. Bp-1 zero (Bp a multiple of 128)
   const uint16_t *w_pieces;          // [3][m_pad][d]
   float *y;                          // [B][m]
   int64_t B, Bp;

@@ -89,8 +89,7 @@ int choose_coef_jt(int m);
 
 // The base branch of a spline_component layer as one product on the matrix cores (lutkan_base_gemm.hip):
 // y[B][m] = SiLU(x)[B][d] x (s_out*s_base)[d][m], both operands as three bf16 pieces per fp32 value.
-//   silu_pieces  [3][Bp][d] bf16 bit patterns written by the locate kernel, rows from B to the next multiple of 128 zero;
-//                Bp, the rows between two planes, is a multiple of 128
+//   silu_pieces  [3][Bp][d] bf16 bit patterns written by the locate kernel, rows B .. Bp-1 zero, Bp a multiple of 128
 //   w_pieces     scratch of base_product_workspace_bytes(d, m) bytes, filled from the base rows of `table` by the call
 // base_product_fits: the shapes the product exists for (d a multiple of 32, at least 64 columns); for other shapes the
 // scratch size is 0.

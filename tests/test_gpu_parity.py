@@ -1615,8 +1615,8 @@ TWO_PHASE_CASES = [
 
 @pytest.mark.parametrize("case", TWO_PHASE_CASES, ids=lambda c: f"seed{c[0]}")
 def test_locate_and_edges_as_separate_calls(case):
-    """locate, then edges, against the oracle, and bit for bit what one call on the same kernels returns.  Where a record lies
-    follows from B alone: a phi layer's records serve edge phases of every algo and table form."""
+    """locate, then edges, against the oracle, and bit for bit what one call on the same kernels returns.  Where a record
+    of a separate phase lies follows from B alone: a phi layer's records serve edge phases of every algo and table form."""
     seed, d, m, G, L, scheme, B, with_base = case
     w = random_layer(seed, d, m, G, L, scheme, HALF_OPEN, ZERO_SPLINE, B, uniform=False, with_base=with_base)
     s, x = w.layers[0], w.x
