@@ -1,10 +1,10 @@
 // The B-spline layer as a dense contraction on the matrix cores:
 //     y[b][j] = sum_i sum_r N_r(x[b][i]) * c[i][r][j]
-// with the R = G + 3 basis values of an input as contraction index (four of them are non-zero).  The tiled kernel
-// (bspline_kernels.hip) spends four multiply-adds per edge and is bound by the 16 bytes of coefficients per edge that it
+// with the R = G + 3 basis values of an input as contraction index, four neighbouring ones of which are non-zero.  The tiled
+// kernel (bspline_kernels.hip) spends four multiply-adds per edge and is bound by the 16 bytes of coefficients per edge that it
 // reads from LDS at a row's own offset; here the coefficients are the second operand of a matrix instruction, read from
-// LDS once per 32 rows, and the price is the zeros: R (padded to 8 or 16 slots) products per edge instead of 4.
-// The basis is evaluated where it is consumed, so the pass that writes and reads 32 bytes per (row, input) falls away.
+// LDS once per 32 rows.  The basis is evaluated where it is consumed, so the pass that writes and reads 32 bytes per (row, input)
+// falls away.
 //
 // fp32 accuracy from bf16 matrix instructions, as in lutkan_base_gemm.hip: every fp32 operand is cut exactly into three
 // bf16 pieces and six of the nine piece products are accumulated in fp32; the other three are at most 2^-24 of the product
@@ -14,28 +14,34 @@
 // evaluation than the tiled kernel; apart, it is nearer than that kernel (64 -> 128 at 131072 rows 1.5e-7 against 3.0e-7,
 // 1024 -> 1024 at 4096 rows, G = 10, 4.8e-7 against 5.7e-7).
 //
-// Operand A without LDS: in v_mfma_f32_32x32x16_bf16 a lane holds 8 consecutive k of one row, and k may be numbered
-// freely as long as both operands agree, so k is numbered such that a lane's 8 slots belong to ONE input of its row:
-//   SLOTS = 8   (R <= 8)   a k step covers two inputs, the lower lanes' and the upper lanes' one; a lane's slots are the
-//                          input's 8 coefficient rows
-//   SLOTS = 16  (R <= 16)  a k step covers one input; the lower lanes hold its even coefficient rows, the upper lanes
-//                          the odd ones (two of the four non-zero values each)
-// A lane thus locates its (row, input), evaluates the four cubics and shifts their pieces into its slots in registers.
-// Operand B (coefficients): a work-group stages 8 (SLOTS 16: 4) inputs at a time, cut into pieces on the way into LDS, as
-// [unit][piece][column][8 slots]; unit = input (SLOTS 16: input and parity), k step s reads units s and s + 4.
+// Operand A, sparse and without LDS: v_smfmac_f32_32x32x32_bf16 takes operand A with two stored values of every four
+// consecutive k (a group) and two bits each for where they stand, and does twice the dense instruction's k in the same time (55.8
+// cycles at 2.4 GHz against 54.1, both at the clock that random operands leave the chip).  A basis always fits: coefficient row r
+// goes to group r % GRP of its input, so four neighbouring rows put at most two values into a group.  GRP groups per input:
+//   GRP = 2   R <= 8: two values in each group, nothing stored is zero
+//   GRP = 3   R <= 12: two, one and one
+//   GRP = 4   R <= 16: one in each
+// A lane holds 8 stored values of one row, four groups, and k may be numbered freely as long as both operands agree, so a lane's
+// groups are those of its own inputs: the lower lanes take the first half of a stage's inputs, the upper lanes the second, and
+// every basis value is evaluated once per wave.  A lane locates its (row, input), evaluates the four cubics, cuts them and moves
+// the pieces into its groups by byte permutes.
+// Operand B (coefficients): a work-group stages 8 (GRP 4: 4) inputs at a time, cut into pieces on the way into LDS, as
+// [unit][piece][column][8 slots]; a unit is two groups of an input half.  What a lane stores at e = 0 .. 3 meets operand B of the
+// lower lanes, at e = 4 .. 7 that of the upper lanes, in elements 0 .. 7 (a lower lane's) or 8 .. 15 (an upper lane's).
 //
 // A work-group is 8 waves of 32*RT rows x 32*NT columns (one column tile of the coefficient table); two waves share a
 // SIMD, so that one's vector work (basis, pieces) overlaps the other's matrix instructions.
 //
-// Bound: the matrix cores at the clock they leave the chip.  96 (SLOTS 16: 192) flop per edge; 1024 -> 1024 at 32768 rows,
-// G = 5: 3.30 TFLOP in 2.70 ms = 1.22 PFLOP/s, what a bf16 library product of 8192^3 reaches on such a card, against 6.16 ms on
-// the tiled kernel.  In one run under counters 2.88 ms at 1.83 GHz: matrix pipes 0.60 busy (1.15 PFLOP/s), vector issue 0.41, LDS
-// 0.24.
-// Whole layers, tiled -> matrix, microseconds (one run; boards and runs differ by 5 %): 128 -> 128 at 131072 rows, G = 5,
-// 587 -> 182; 64 -> 8 162 -> 34; 256 -> 256 at 16384 rows 273 -> 104 (G = 5), 272 -> 183 (G = 8); 1024 -> 1024, G = 10, at 4096 rows
-// 790 -> 684, at 32768 6290 -> 5250; 128 -> 128 at 64 rows 19 -> 13.  Exchanging lanes so that each half of a wave evaluates the
-// basis of every other input only (SLOTS 16) gave nothing, nor did records from a locate pass of its own (1024 -> 1024 at 4096
-// rows 634 against 635).
+// Bound: matrix and vector issue, at the clock they leave the chip.  48 / 72 / 96 sparse flop per edge; 1024 -> 1024, G = 10, at 4096
+// rows: matrix pipes 0.41 busy, vector issue 0.39, LDS 0.30, 1.9 GHz.  One such instruction of each of two waves and the 7 vector
+// instructions that go with it take 64 cycles at 2.4 GHz when nothing else does, here 83: vector instructions hide behind a matrix
+// instruction only up to about four.  (Spreading them between the matrix instructions by hand, evaluating a step ahead: 4 %
+// faster with 128 columns, 4 - 10 % slower with 64 and fewer, whose registers then spill; four waves of 64 rows x 128 columns:
+// 13 % slower.)
+// Whole layers, dense matrix instructions -> sparse, microseconds (one run each): 64 -> 128 at 131072 rows, G = 5, 111 -> 84;
+// 128 -> 128 190 -> 142; 128 -> 128, G = 8, 338 -> 191; 256 -> 256 at 16384 rows, G = 8, 189 -> 110; 1024 -> 1024 at 4096 rows, G = 5 /
+// 8 / 10, 348 / 658 / 658 -> 255 / 350 / 441; 64 -> 8 at 131072 rows 36 -> 31.  The tiled kernel takes 587 for 128 -> 128 (G = 5), 790
+// for 1024 -> 1024 (G = 10).
 // The file is compiled with -ffp-contract=off; fused multiply-adds are written out as fmaf().
 #include "bspline_matrix.h"
 #include "lutkan_device.h"
@@ -44,13 +50,14 @@
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kMxWaves = 8;
 constexpr int kMxMaxSegments = 13;       // R = G + 3 <= 16
 constexpr int kMxSegFloats = 14;         // of a segment: 8 polynomial coefficients, its ends, middle and scale, the two outer factors
 constexpr int kMxSegStride = 20;         // ... in LDS: 80-byte rows spread the banks
-constexpr int kMxLdsTail = (kMxMaxSegments + 1) * (kMxSegStride * 4 + 2 * 16) + 16;      // behind the stages in LDS: segments, places, a flag
+constexpr int kMxLdsTail = (kMxMaxSegments + 1) * (kMxSegStride * 4 + 16 + 4) + 16;      // behind the stages in LDS: segments, places, indices, a flag
 
 struct SplineMatrixArgs {
   const float *x;            // [B][d]
@@ -73,13 +80,13 @@ struct Position {
   int segment;
 };
 
-// SLOTS - 4 inner knots at most.  `dead`: an input past the work-group's last, x finite.
-template <int SLOTS>
+// 4 GRP - 4 inner knots at most.  `dead`: an input past the work-group's last, x finite.
+template <int GRP>
 __device__ __forceinline__ Position locate(const SplineMatrixArgs &a, float x, bool dead) {
   const float xc = __builtin_amdgcn_fmed3f(x, a.t0, a.tKs);
   int k = 0;
 #pragma unroll
-  for (int kappa = 0; kappa < SLOTS - 4; ++kappa) k += (a.knots[kappa] <= xc) ? 1 : 0;
+  for (int kappa = 0; kappa < 4 * GRP - 4; ++kappa) k += (a.knots[kappa] <= xc) ? 1 : 0;
   const bool masked = dead || x < a.masked_below || x > a.masked_above;
   k = masked ? a.segments : k;
   return Position{(x != x) ? __builtin_nanf("") : xc, k};
@@ -113,62 +120,49 @@ __device__ __forceinline__ void fill_segments(const SplineMatrixArgs &a, float *
   }
 }
 
-union Slots { u32x4 u; bf16x8 h; };
+union Sparse { u32x4 u; bf16x8 h; };          // a lane's 8 values of operand A: two of each of its four groups of slots
+union Dense { u32x4 u[2]; bf16x16 h; };       // a lane's 16 values of operand B
 
-// Where the four non-zero values of a segment go in a lane's 8 slots: for each of their four words the byte permute that takes
-// it out of the packed values (SLOTS 8: {n0, n1} and {n2, n3}, moved up by `first` slots; SLOTS 16: the two of the lane's
-// parity, moved to slot `at`).  One 16-byte LDS read and a permute per word and piece, in place of shifts and selects.
-template <int SLOTS>
-__device__ __forceinline__ void fill_places(u32x4 *s_place, int segments, int tid) {
+// Where the four non-zero values of a segment go.  Coefficient row r is slot r / GRP of group r % GRP, so the rows first ..
+// first+3 lie in every group once (GRP 4), once or twice (3) or twice (2).  place[g]: the byte permute that takes group g's two
+// values out of the packed {n0, n1} and {n2, n3}, in the order of their slots; bits 4g .. 4g+3 of the index: those two slots, the
+// lower one first (a group with one value has a zero beside it).  The entry of a.segments places nothing.
+template <int GRP>
+__device__ __forceinline__ void fill_places(u32x4 *s_place, unsigned *s_index, int segments, int tid) {
   constexpr unsigned kNone = 0x0c0cu, kValue[4] = {0x0100u, 0x0302u, 0x0504u, 0x0706u};      // two bytes of zero; value 0 .. 3
-  if (tid >= 2 * (segments + 1)) return;
-  const int first = tid >> 1, half = tid & 1;
-  const int at = (SLOTS == 8) ? first : (first + ((first ^ half) & 1) - half) >> 1, n = (SLOTS == 8) ? 4 : 2;
-  unsigned w[4];
+  if (tid > segments) return;
+  unsigned w[4] = {0u, 0u, 0u, 0u}, index = 0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int lo = 2 * q - at, hi = lo + 1;                // which of the packed values lands in slots 2q and 2q + 1
-    w[q] = ((lo >= 0 && lo < n) ? kValue[lo & 3] : kNone) | ((hi >= 0 && hi < n) ? kValue[hi & 3] : kNone) << 16;
+  for (int g = 0; g < GRP; ++g) {
+    const int n = (g + 2 * GRP * 4 - tid) % GRP;          // the first of the window's values in this group, from row tid + n
+    const int slot = (tid + n) / GRP;
+    unsigned lo = kValue[n & 3], hi = (n + GRP < 4) ? kValue[(n + GRP) & 3] : kNone;
+    int at = slot;
+    if (slot == 3) { hi = lo; lo = kNone; at = 2; }        // (the last slot: a single value, after an empty one)
+    if (tid == segments) { lo = hi = kNone; at = 0; }
+    w[g] = lo | (hi << 16);
+    index |= (unsigned)(at | ((at + 1) << 2)) << (4 * g);
   }
   s_place[tid] = u32x4{w[0], w[1], w[2], w[3]};
+  s_index[tid] = index;
 }
 
-// a lane's 8 slots of one (row, input), three pieces
-template <int SLOTS>
-__device__ __forceinline__ void slots_of(const u32x4 *s_place, const float n[4], int first, int half, Slots out[3]) {
-  const u32x4 place = s_place[2 * first + half];
-  if constexpr (SLOTS == 8) {
-    unsigned p01[3], p23[3];
-    lutkan_cut3_pair(n[0], n[1], p01);
-    lutkan_cut3_pair(n[2], n[3], p23);
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) out[q].u[w] = __builtin_amdgcn_perm(p23[q], p01[q], place[w]);
-  } else {
-    // rows first .. first+3; this lane holds those of parity `half`
-    const bool same = ((first ^ half) & 1) == 0;
-    unsigned p[3];
-    lutkan_cut3_pair(same ? n[0] : n[1], same ? n[2] : n[3], p);
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) out[q].u[w] = __builtin_amdgcn_perm(p[q], p[q], place[w]);
-  }
-}
-
-template <int SLOTS, int RT, int NT>
+template <int GRP, int RT, int NT>
 __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const SplineMatrixArgs a) {
   constexpr int BN = 32 * NT;
-  constexpr int IS = (SLOTS == 8) ? 8 : 4;                // inputs per stage: 8 units of 8 slots, 4 k steps
+  constexpr int IPL = (GRP == 4) ? 2 : 4;                 // inputs a lane evaluates per stage
+  constexpr int IS = 2 * IPL;                             // inputs per stage
+  constexpr int STEPS = IPL * GRP / 4;                    // matrix k steps per stage, four groups of a lane each
   constexpr int kThreads = kMxWaves * 64;
-  constexpr int kUnits = 8 * BN;                          // (unit, column) pairs of a stage, one thread cuts 8 coefficients of each
-  constexpr int UPT = (kUnits + kThreads - 1) / kThreads;
-  constexpr int kStageBytes = 8 * 3 * BN * 16;
+  constexpr int kUnits = 4 * STEPS;                       // of 8 slots of a column: what a lane reads of operand B per step and half of the inputs
+  constexpr int kPairs = kUnits * BN;                     // (unit, column) pairs of a stage, one thread cuts 8 coefficients of each
+  constexpr int UPT = (kPairs + kThreads - 1) / kThreads;
+  constexpr int kStageBytes = kUnits * 3 * BN * 16;
   extern __shared__ __align__(16) unsigned char lds[];
   float *const s_seg = reinterpret_cast<float *>(lds + 2 * kStageBytes);
   u32x4 *const s_place = reinterpret_cast<u32x4 *>(s_seg + (kMxMaxSegments + 1) * kMxSegStride);
-  int *const s_uncut = reinterpret_cast<int *>(s_place + 2 * (kMxMaxSegments + 1));
+  unsigned *const s_index = reinterpret_cast<unsigned *>(s_place + (kMxMaxSegments + 1));
+  int *const s_uncut = reinterpret_cast<int *>(s_index + (kMxMaxSegments + 1));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -180,10 +174,11 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
   const int i_end = min(a.d, i_begin + a.chunk);
 
   fill_segments(a, s_seg, tid, kThreads);
-  fill_places<SLOTS>(s_place, a.segments, tid);
+  fill_places<GRP>(s_place, s_index, a.segments, tid);
   if (tid == 0) *s_uncut = 0;
 
-  // this thread's coefficient columns of a stage: unit u = (input u) resp. (input u & 3, parity u >> 2)
+  // This thread's coefficient columns of a stage.  Unit u = (h * STEPS + step) * 2 + p: the groups 4 step + 2p and the next one
+  // of the lanes of half h, whose groups are those of its inputs one after the other.
   const float *tile = a.coef_table + (size_t)t * a.d * a.R * a.jt;
   float cf[UPT][8];
   float largest = 0.0f;                                    // of the magnitudes this thread staged; NaN if one was
@@ -192,21 +187,25 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
     for (int q = 0; q < UPT; ++q) {
       const int id = tid + q * kThreads;
       const int c = (id % BN) & (a.jt - 1);                // a column past the tile: a valid address, not stored
-      // the unit of a wave's 64 threads (two neighbouring ones with 32 columns, of one parity)
-      const int u = (BN >= 64) ? __builtin_amdgcn_readfirstlane((id / BN) & 7) : (id / BN) & 7;
-      const int parity = (SLOTS == 8) ? 0 : __builtin_amdgcn_readfirstlane(u >> 2);
-      const int i = min(i0 + (SLOTS == 8 ? u : (u & 3)), a.d - 1);       // past the last input: its basis is zero
-      const float *src = tile + (size_t)i * a.R * a.jt + c;
+      // the unit of a wave's 64 threads (with 32 columns two neighbouring ones; past the last one, where not stored)
+      const int u = min((BN >= 64) ? __builtin_amdgcn_readfirstlane(id / BN) : id / BN, kUnits - 1);
+      const int h = u / (2 * STEPS), group = 4 * ((u >> 1) - h * STEPS) + 2 * (u & 1);
 #pragma unroll
-      for (int r = 0; r < 8; ++r)                          // slots past the last coefficient row: their basis is zero, any row will do
-        cf[q][r] = src[min(SLOTS == 8 ? r : parity + 2 * r, a.R - 1) * a.jt];
+      for (int e = 0; e < 2; ++e) {
+        const int of = (group + e) / GRP, g = (group + e) - of * GRP;
+        const int i = min(i0 + h * IPL + of, a.d - 1);     // past the last input: its basis is zero
+        const float *src = tile + (size_t)i * a.R * a.jt + c;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)                        // slots past the last coefficient row: no value goes there, any row will do
+          cf[q][4 * e + r] = src[min(g + GRP * r, a.R - 1) * a.jt];
+      }
     }
   };
   auto store_coefs = [&](unsigned char *buf) {
 #pragma unroll
     for (int q = 0; q < UPT; ++q) {
       const int id = tid + q * kThreads;
-      if (kUnits < kThreads && id >= kUnits) break;
+      if (kPairs % kThreads != 0 && id >= kPairs) break;
       const int u = id / BN, c = id % BN;
       unsigned p[4][3];
 #pragma unroll
@@ -219,22 +218,27 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
     }
   };
 
-  // this lane's inputs of a stage: four consecutive ones of its row (the upper lanes' follow the lower lanes' with SLOTS 8)
-  const int lane_input = (SLOTS == 8) ? 4 * half : 0;
+  // this lane's inputs of a stage: consecutive ones of its row, the upper lanes' after the lower lanes'
+  const int lane_input = IPL * half;
   int64_t row[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) row[rt] = min(row0 + rt * 32 + col, a.B - 1);
-  float xv[RT][4];
+  float xv[RT][IPL];
   auto load_inputs = [&](int i0) {
     const int i = i0 + lane_input;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       if (a.x_vec4) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(a.x + row[rt] * a.d + min(i, a.d - 4));
-        xv[rt][0] = v.x; xv[rt][1] = v.y; xv[rt][2] = v.z; xv[rt][3] = v.w;
+        if constexpr (IPL == 4) {
+          const f32x4 v = *reinterpret_cast<const f32x4 *>(a.x + row[rt] * a.d + min(i, a.d - 4));
+          xv[rt][0] = v.x; xv[rt][1] = v.y; xv[rt][2] = v.z; xv[rt][3] = v.w;
+        } else {
+          const f32x2 v = *reinterpret_cast<const f32x2 *>(a.x + row[rt] * a.d + min(i, a.d - 2));
+          xv[rt][0] = v.x; xv[rt][1] = v.y;
+        }
       } else {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) xv[rt][s] = a.x[row[rt] * a.d + min(i + s, a.d - 1)];
+        for (int s = 0; s < IPL; ++s) xv[rt][s] = a.x[row[rt] * a.d + min(i + s, a.d - 1)];
       }
     }
   };
@@ -256,10 +260,10 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
   for (int i0 = i_begin; i0 < i_end; i0 += IS) {
     const bool more = i0 + IS < i_end;
     // the inputs of this stage; one past the work-group's last takes the all-zero segment (and a finite x)
-    float xc[RT][4];
-    bool dead[4];
+    float xc[RT][IPL];
+    bool dead[IPL];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int s = 0; s < IPL; ++s) {
       dead[s] = i0 + lane_input + s >= i_end;
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) xc[rt][s] = dead[s] ? a.t0 : xv[rt][s];
@@ -269,32 +273,54 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
       if (wave_live) load_inputs(i0 + IS);
     }
     if (wave_live) {
-      const unsigned char *buf = lds + cur * kStageBytes + half * (4 * 3 * BN * 16) + col * 16;
+      const unsigned char *buf = lds + cur * kStageBytes + half * (3 * BN * 16) + col * 16;
+      unsigned value[RT][3][IPL * GRP], index[RT][IPL];    // per piece the lane's groups, two values each; where they belong
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        Slots af[RT][3];
+      for (int s = 0; s < STEPS; ++s) {
+#pragma unroll
+        for (int of = (s == 0) ? 0 : (4 * s + GRP - 1) / GRP; of < (4 * s + 4 + GRP - 1) / GRP; ++of)      // the inputs this step is the first to need
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            const Position at = locate<GRP>(a, xc[rt][of], dead[of]);
+            float n[4];
+            basis_of(s_seg, at, n);
+            const u32x4 place = s_place[at.segment];
+            index[rt][of] = s_index[at.segment];
+            unsigned p01[3], p23[3];
+            lutkan_cut3_pair(n[0], n[1], p01);
+            lutkan_cut3_pair(n[2], n[3], p23);
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+              for (int g = 0; g < GRP; ++g) value[rt][q][of * GRP + g] = __builtin_amdgcn_perm(p23[q], p01[q], place[g]);
+          }
+        Sparse af[RT][3];
+        int slots[RT];                                     // bits 4g .. 4g+3: the slots of the step's group g
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          const Position at = locate<SLOTS>(a, xc[rt][s], dead[s]);
-          float n[4];
-          basis_of(s_seg, at, n);
-          slots_of<SLOTS>(s_place, n, at.segment, half, af[rt]);
+          if constexpr (GRP == 4) slots[rt] = (int)index[rt][s];
+          else if constexpr (GRP == 2) slots[rt] = (int)(index[rt][2 * s] | (index[rt][2 * s + 1] << 8));
+          else slots[rt] = (int)((index[rt][s] >> (4 * s)) | (index[rt][s + 1] << (12 - 4 * s)));
+#pragma unroll
+          for (int q = 0; q < 3; ++q) af[rt][q].u = u32x4{value[rt][q][4 * s], value[rt][q][4 * s + 1], value[rt][q][4 * s + 2], value[rt][q][4 * s + 3]};
         }
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
-          Slots wf[3];
+          Dense wf[3];
 #pragma unroll
-          for (int q = 0; q < 3; ++q) wf[q].u = *reinterpret_cast<const u32x4 *>(buf + ((s * 3 + q) * BN + ct * 32) * 16);
+          for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) wf[q].u[h] = *reinterpret_cast<const u32x4 *>(buf + (((h * STEPS + s) * 6 + q) * BN + ct * 32) * 16);
           // the six piece products, the small ones first
           constexpr int kPieceOfA[5] = {2, 0, 1, 1, 0}, kPieceOfW[5] = {0, 2, 1, 0, 1};
 #pragma unroll
           for (int p = 0; p < 5; ++p)
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
-              low[rt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rt][kPieceOfA[p]].h, wf[kPieceOfW[p]].h, low[rt][ct], 0, 0, 0);
+              low[rt][ct] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(af[rt][kPieceOfA[p]].h, wf[kPieceOfW[p]].h, low[rt][ct], slots[rt], 0, 0);
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt)
-            acc[rt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rt][0].h, wf[0].h, acc[rt][ct], 0, 0, 0);
+            acc[rt][ct] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(af[rt][0].h, wf[0].h, acc[rt][ct], slots[rt], 0, 0);
         }
       }
     }
@@ -332,7 +358,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
     float sum = 0.0f;
 #pragma unroll 1
     for (int i = i_begin; i < i_end; ++i) {
-      const Position at = locate<SLOTS>(a, a.x[b * a.d + i], false);
+      const Position at = locate<GRP>(a, a.x[b * a.d + i], false);
       if (at.segment == a.segments) continue;
       float n[4];
       basis_of(s_seg, at, n);
@@ -389,17 +415,17 @@ struct MatrixPlan {
 
 // Launch shape: 32-row tiles per wave (rt) and chunks of inputs, by the same kind of cost model as the tiled kernels
 // (microseconds): a stage costs a SIMD's two waves their matrix instructions (32 cycles each, 0.8 of the time) or their
-// vector work, whichever is more, and 1000 cycles of barrier and latency, at the 1.7 GHz of a chip under matrix load
-// (128 -> 128 at 131072 rows: 5.2 us per stage of 8 inputs); a work-group adds its fill; the launch runs in rounds of 256
+// vector work, whichever is more, and 1000 cycles of barrier and latency, at 1.45 GHz (128 -> 128 at 131072 rows: 3.4 us per stage
+// of 8 inputs with two groups each, 5.1 with three; 1024 -> 1024: 3.3 per stage of 4 with four groups); a work-group adds its fill; the launch runs in rounds of 256
 // work-groups; chunks add the summing pass and are as many as the caller's workspace holds sums for.  Two accumulators
 // of 64 rows x 128 columns would not fit the registers of two waves per SIMD: rt = 1 there.
-MatrixPlan plan_matrix(int64_t B, int d, int m, int n_tiles, int nt, int slots, size_t partial_bytes) {
-  const int is = (slots == 8) ? 8 : 4;
+MatrixPlan plan_matrix(int64_t B, int d, int m, int n_tiles, int nt, int grp, size_t partial_bytes) {
+  const int is = (grp == 4) ? 4 : 8, steps = is * grp / 8;
   MatrixPlan best{1, 1, d, 1e300};
   for (int rt = 1; rt <= (nt == 4 ? 1 : 2); ++rt) {
     const int64_t groups = (B + kMxWaves * 32 * rt - 1) / (kMxWaves * 32 * rt) * n_tiles;
-    const double matrix = 2.0 * 4 * rt * nt * 6 * 32 * 1.25, vector = 2.0 * (4 * rt * 80 + 45 * nt) * 4.0;
-    const double stage = (std::max(matrix, vector) + 1000.0) / 1700.0;
+    const double matrix = 2.0 * steps * rt * nt * 6 * 32 * 1.25, vector = 2.0 * (is / 2 * rt * 80 + 45 * nt) * 4.0;
+    const double stage = (std::max(matrix, vector) + 1000.0) / 1450.0;
     for (int want = 1; want <= 64; ++want) {
       const int chunk = (int)round_up((d + want - 1) / want, 8);
       const int split = (d + chunk - 1) / chunk;
@@ -414,23 +440,23 @@ MatrixPlan plan_matrix(int64_t B, int d, int m, int n_tiles, int nt, int slots, 
   return best;
 }
 
-template <int SLOTS, int RT, int NT>
+template <int GRP, int RT, int NT>
 int launch_matrix(const SplineMatrixArgs &ma, int n_split, hipStream_t s) {
   constexpr int kRows = kMxWaves * 32 * RT;
   const int64_t groups = (ma.B + kRows - 1) / kRows * ma.n_tiles;
   if (groups > 0x7fffffffLL) return fail(LUTKAN_EUNSUPPORTED, "bspline_matrix_kernel: B * m too large for one launch");
-  const size_t lds = 2 * (size_t)(8 * 3 * 32 * NT * 16) + kMxLdsTail;
+  const size_t lds = 2 * (size_t)((GRP == 3 ? 12 : 8) * 3 * 32 * NT * 16) + kMxLdsTail;
   static LdsCap raised;
-  if (int rc = raise_lds_cap(bspline_matrix_kernel<SLOTS, RT, NT>, &raised, "bspline_matrix_kernel")) return rc;
-  hipLaunchKernelGGL((bspline_matrix_kernel<SLOTS, RT, NT>), dim3((unsigned)groups, (unsigned)n_split), dim3(kMxWaves * 64), lds, s, ma);
+  if (int rc = raise_lds_cap(bspline_matrix_kernel<GRP, RT, NT>, &raised, "bspline_matrix_kernel")) return rc;
+  hipLaunchKernelGGL((bspline_matrix_kernel<GRP, RT, NT>), dim3((unsigned)groups, (unsigned)n_split), dim3(kMxWaves * 64), lds, s, ma);
   return check_launch("bspline_matrix_kernel");
 }
 
-template <int SLOTS>
-int launch_matrix_slots(const SplineMatrixArgs &ma, int rt, int nt, int n_split, hipStream_t s) {
-  if (nt == 4) return launch_matrix<SLOTS, 1, 4>(ma, n_split, s);
-  if (nt == 2) return rt == 2 ? launch_matrix<SLOTS, 2, 2>(ma, n_split, s) : launch_matrix<SLOTS, 1, 2>(ma, n_split, s);
-  return rt == 2 ? launch_matrix<SLOTS, 2, 1>(ma, n_split, s) : launch_matrix<SLOTS, 1, 1>(ma, n_split, s);
+template <int GRP>
+int launch_matrix_groups(const SplineMatrixArgs &ma, int rt, int nt, int n_split, hipStream_t s) {
+  if (nt == 4) return launch_matrix<GRP, 1, 4>(ma, n_split, s);
+  if (nt == 2) return rt == 2 ? launch_matrix<GRP, 2, 2>(ma, n_split, s) : launch_matrix<GRP, 1, 2>(ma, n_split, s);
+  return rt == 2 ? launch_matrix<GRP, 2, 1>(ma, n_split, s) : launch_matrix<GRP, 1, 1>(ma, n_split, s);
 }
 
 }  // namespace
@@ -451,16 +477,18 @@ int bspline_matrix_forward(const bspline_dev_layer *l, const float *x, int64_t B
   ma.masked_above = (l->oob == LUTKAN_ZERO_SPLINE) ? ma.tKs : INFINITY;
   for (int k = 0; k < kMxMaxSegments - 1; ++k) ma.knots[k] = (k + 1 < l->G) ? T[k + 1] : INFINITY;
   for (int k = 0; k < l->G; ++k) segment_constants(l->ext_knots, 3 + k, ma.segment[k]);
-  const int slots = (ma.R <= 8) ? 8 : 16;
+  const int grp = (ma.R <= 8) ? 2 : (ma.R <= 12) ? 3 : 4;
   const int nt = ma.jt >= 128 ? 4 : ma.jt >= 64 ? 2 : 1;
   float *const partials = static_cast<float *>(workspace);
-  const MatrixPlan mp = plan_matrix(B, l->d, l->m, l->n_tiles, nt, slots, workspace_bytes);
+  const MatrixPlan mp = plan_matrix(B, l->d, l->m, l->n_tiles, nt, grp, workspace_bytes);
   ma.chunk = mp.chunk;
   ma.y = y;
   if (mp.n_split > 1) { ma.y = partials; ma.split_stride = B * l->m; }
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  if (int rc = slots == 8 ? launch_matrix_slots<8>(ma, mp.rt, nt, mp.n_split, s) : launch_matrix_slots<16>(ma, mp.rt, nt, mp.n_split, s)) return rc;
-  plan_note("bspline_matrix np=%d split=%d slots=%d; ", mp.rt, mp.n_split, slots);
+  const int rc = grp == 2 ? launch_matrix_groups<2>(ma, mp.rt, nt, mp.n_split, s) : grp == 3 ? launch_matrix_groups<3>(ma, mp.rt, nt, mp.n_split, s)
+                                                                                : launch_matrix_groups<4>(ma, mp.rt, nt, mp.n_split, s);
+  if (rc) return rc;
+  plan_note("bspline_matrix np=%d split=%d slots=%d; ", mp.rt, mp.n_split, ma.R <= 8 ? 8 : 16);
   if (mp.n_split == 1) return LUTKAN_OK;
   const int64_t n = B * l->m;
   hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s, partials, y, n, mp.n_split, 0);

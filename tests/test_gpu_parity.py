@@ -1314,6 +1314,26 @@ def test_bspline_layer_on_the_matrix_cores(case):
     assert np.array_equal(y.cpu().numpy(), y_shifted.cpu().numpy(), equal_nan=True)
 
 
+@pytest.mark.parametrize("G", [1, 5, 6, 9, 10, 13])
+def test_every_input_of_a_stage_meets_its_own_coefficients(G):
+    """The grids at either end of two, three and four groups of slots per input; inputs short of, filling and past a stage of the
+    matrix kernel, whose lower lanes take one half of it and upper lanes the other.  All inputs at once, then each alone (the
+    others' coefficients are zero: a slot that met a neighbour's shows)."""
+    for d in (1, 2, 3, 4, 5, 7, 8, 9, 13, 17):
+        w = random_layer(700 + G, d, 5, G, 2, SYM_INT8, CLOSED, CLIP_X, 100, uniform=False)
+        s = w.layers[0]
+        xg = torch.from_numpy(w.x).to(DEV)
+        for only in [None] + list(range(d)):
+            coef = s.coef.copy()
+            if only is not None:
+                coef[np.arange(d) != only] = 0.0
+            art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, coef, s.L, s.scheme, s.boundary, s.oob)
+            y = lk.bspline_kan_forward(art.bspline_to_device(DEV), xg)
+            assert lk.lutkan_last_plan().startswith("bspline_matrix "), lk.lutkan_last_plan()
+            ref = oracle.bspline_forward(s.d, s.m, s.G, s.p, s.ext_knots, coef, s.boundary, s.oob, w.x)
+            _assert_close(y.cpu().numpy(), ref, f"G={G} d={d} only={only}")
+
+
 def test_bspline_layers_outside_the_matrix_kernel_keep_their_kernels():
     """What the matrix kernel does not serve, and the handful of rows on a large table that it is slower at."""
     for kw, what in ((dict(G=14), "14 segments"), (dict(with_base=True), "spline_component")):
