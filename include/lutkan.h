@@ -284,6 +284,13 @@ int lutkan_forward(const lutkan_dev_layer *layer, const float *x, int64_t B, flo
 int lutkan_forward_static_scratch(const lutkan_dev_layer *layer, const float *x, int64_t B, float *y,
                                   lutkan_oob_stats *stats, void *hip_stream);
 
+/* lutkan_forward for a caller that has no workspace at hand: a call that runs in one launch without one (a small narrow layer, a
+ * few rows, a narrow layer in one chunk; see lutkan_algo) is launched, and *workspace_bytes is 0.  Any other launches
+ * nothing, returns LUTKAN_OK and sets *workspace_bytes to lutkan_forward_workspace_bytes: the caller calls lutkan_forward with
+ * that much.  Route and result are those of lutkan_forward.  Errors as there; EINVAL for a null workspace_bytes. */
+int lutkan_forward_or_workspace(const lutkan_dev_layer *layer, const float *x, int64_t B, float *y,
+                                lutkan_oob_stats *stats, size_t *workspace_bytes, void *hip_stream);
+
 /* The two phases of lutkan_forward as separate calls, for callers that time or overlap them:
  *   lutkan_forward_locate   steps 1-4 of Sec. 4.5 and the domain test of Sec. 5.2 for every (row, input);
  *                           fills the workspace with the lookup records (and adds to stats, nullable)
@@ -331,6 +338,10 @@ int bspline_forward_edges(const bspline_dev_layer *layer, int64_t B, float *y,
 size_t lutkan_model_workspace_bytes(const lutkan_dev_layer *layers, int32_t n_layers, int64_t B);
 int lutkan_model_forward(const lutkan_dev_layer *layers, int32_t n_layers, const float *x, int64_t B, float *y,
                          lutkan_oob_stats *stats, void *workspace, size_t workspace_bytes, void *hip_stream);
+/* As lutkan_forward_or_workspace: a network that is one launch without a workspace is launched, for any other *workspace_bytes
+ * is set and nothing is launched. */
+int lutkan_model_forward_or_workspace(const lutkan_dev_layer *layers, int32_t n_layers, const float *x, int64_t B, float *y,
+                                      lutkan_oob_stats *stats, size_t *workspace_bytes, void *hip_stream);
 
 /* The same chain as lutkan_model_forward in ONE launch, for narrow networks at small batches (the batch-256 latency
  * setting of Sec. 8, where the per-layer launches cost more than the arithmetic): a work-group (up to 1024 rows) or a

@@ -76,6 +76,7 @@ EXPORTS = [
     "lutkan_model_workspace_bytes", "lutkan_model_forward", "lutkan_chain_forward", "lutkan_forward_locate", "lutkan_forward_edges",
     "bspline_forward_locate", "bspline_forward_edges", "lutkan_probe_launch", "lutkan_artifact_from_arrays",
     "lutkan_error_stats_workspace_bytes", "lutkan_error_stats", "lutkan_forward_static_scratch",
+    "lutkan_forward_or_workspace", "lutkan_model_forward_or_workspace",
     "lutkan_wide_table_bytes", "lutkan_wide_table_build",
 ]
 
@@ -118,6 +119,8 @@ def load_library():
     lib.bspline_forward_workspace_bytes.argtypes = [C.POINTER(_SplineDevLayer), i64]
     lib.bspline_forward_workspace_bytes.restype = sz
     lib.lutkan_forward.argtypes = [C.POINTER(_DevLayer), vp, i64, vp, vp, vp, sz, vp]
+    lib.lutkan_forward_or_workspace.argtypes = [C.POINTER(_DevLayer), vp, i64, vp, vp, C.POINTER(sz), vp]
+    lib.lutkan_model_forward_or_workspace.argtypes = [C.POINTER(_DevLayer), i32, vp, i64, vp, vp, C.POINTER(sz), vp]
     lib.lutkan_forward_static_scratch.argtypes = [C.POINTER(_DevLayer), vp, i64, vp, vp, vp]
     lib.lutkan_forward_trace.argtypes = [C.POINTER(_DevLayer), vp, i64, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.bspline_kan_forward.argtypes = [C.POINTER(_SplineDevLayer), vp, i64, vp, vp, sz, vp]
@@ -487,6 +490,13 @@ def lutkan_model_workspace_bytes(layers: Sequence[LutLayer], B: int) -> int:
     return int(load_library().lutkan_model_workspace_bytes(arr, len(layers), B))
 
 
+def _output(x, B, m):
+    """The [B, m] float32 output beside x (float32).  new_empty parses three arguments less than torch.empty (1.2 us against 1.7);
+    for a subclass of Tensor it would return one."""
+    torch = _torch()
+    return x.new_empty(B, m) if type(x) is torch.Tensor else torch.empty((B, m), dtype=torch.float32, device=x.device)
+
+
 def _workspace(nbytes, device, workspace):
     torch = _torch()
     if workspace is None:
@@ -497,14 +507,19 @@ def _workspace(nbytes, device, workspace):
 
 def lutkan_forward(layer: LutLayer, x, y=None, stats=None, workspace=None):
     """y[B,m] = LUT layer forward of x[B,d] on the current stream.  stats: optional int64[2] CUDA tensor (added to)."""
-    torch = _torch()
     B = _check_io("lutkan_forward", layer, x=x, y=y, workspace=workspace, stats=stats)
     if y is None:
-        y = torch.empty((B, layer.m), dtype=torch.float32, device=x.device)
-    ws = _workspace(lutkan_forward_workspace_bytes(layer, B), x.device, workspace)
-    _check(load_library().lutkan_forward(C.byref(layer.c), x.data_ptr(), B, y.data_ptr(),
-                                         stats.data_ptr() if stats is not None else None,
-                                         ws.data_ptr(), ws.numel(), _stream(x.device)))
+        y = _output(x, B, layer.m)
+    lib, stats_ptr, stream = load_library(), stats.data_ptr() if stats is not None else None, _stream(x.device)
+    if workspace is None:                        # most small calls need none: one call into the library, nothing allocated
+        need = C.c_size_t()
+        _check(lib.lutkan_forward_or_workspace(layer.c, x.data_ptr(), B, y.data_ptr(), stats_ptr, need, stream))
+        if need.value == 0:
+            return y
+        workspace = _workspace(need.value, x.device, None)
+    else:
+        _require(workspace, _torch().uint8, "workspace")
+    _check(lib.lutkan_forward(layer.c, x.data_ptr(), B, y.data_ptr(), stats_ptr, workspace.data_ptr(), workspace.numel(), stream))
     return y
 
 
@@ -576,10 +591,9 @@ def lutkan_forward_trace(layer: LutLayer, x, codes: bool = False, workspace=None
 
 
 def bspline_kan_forward(layer: BsplineLayer, x, y=None, workspace=None):
-    torch = _torch()
     B = _check_io("bspline_kan_forward", layer, x=x, y=y, workspace=workspace)
     if y is None:
-        y = torch.empty((B, layer.m), dtype=torch.float32, device=x.device)
+        y = _output(x, B, layer.m)
     ws = _workspace(bspline_forward_workspace_bytes(layer, B), x.device, workspace)
     _check(load_library().bspline_kan_forward(C.byref(layer.c), x.data_ptr(), B, y.data_ptr(), ws.data_ptr(),
                                               ws.numel(), _stream(x.device)))
@@ -588,17 +602,21 @@ def bspline_kan_forward(layer: BsplineLayer, x, y=None, workspace=None):
 
 def lutkan_model_forward(layers: List[LutLayer], x, y=None, stats=None, workspace=None):
     """Chained forward: layer l's output is layer l+1's input.  stats: optional int64[n_layers,2] CUDA tensor."""
-    torch = _torch()
     ends = _check_chain("lutkan_model_forward", layers)
     B = _check_io("lutkan_model_forward", ends, x=x, y=y, workspace=workspace, stats=stats, n_stats=len(layers))
     arr = (_DevLayer * len(layers))(*[l.c for l in layers])
     if y is None:
-        y = torch.empty((B, layers[-1].m), dtype=torch.float32, device=x.device)
-    need = int(load_library().lutkan_model_workspace_bytes(arr, len(layers), B))
-    ws = _workspace(need, x.device, workspace)
-    _check(load_library().lutkan_model_forward(arr, len(layers), x.data_ptr(), B, y.data_ptr(),
-                                               stats.data_ptr() if stats is not None else None,
-                                               ws.data_ptr(), ws.numel(), _stream(x.device)))
+        y = _output(x, B, layers[-1].m)
+    lib, stats_ptr, stream = load_library(), stats.data_ptr() if stats is not None else None, _stream(x.device)
+    if workspace is None:                        # as in lutkan_forward
+        need = C.c_size_t()
+        _check(lib.lutkan_model_forward_or_workspace(arr, len(layers), x.data_ptr(), B, y.data_ptr(), stats_ptr, need, stream))
+        if need.value == 0:
+            return y
+        workspace = _workspace(need.value, x.device, None)
+    else:
+        _require(workspace, _torch().uint8, "workspace")
+    _check(lib.lutkan_model_forward(arr, len(layers), x.data_ptr(), B, y.data_ptr(), stats_ptr, workspace.data_ptr(), workspace.numel(), stream))
     return y
 
 

@@ -188,7 +188,7 @@ struct TilePlan {
 // code_bytes: 1 for the table as compiled; 2 or 4 when the slices are those of a wide form of the table, whose row
 // steps take fewer instructions.
 inline double row_step_us(int code_bytes) { return code_bytes == 4 ? 0.070 : code_bytes == 2 ? 0.095 : 0.11; }
-TilePlan plan_tiles(int64_t B, int d, int m, int n_tiles, int rps, int slice_bytes, int code_bytes = 1) {
+[[maybe_unused]] TilePlan plan_tiles(int64_t B, int d, int m, int n_tiles, int rps, int slice_bytes, int code_bytes = 1) {
   const int np_max = std::min(16, 64 / rps);
   const int max_split = std::max(1, std::min(128, d / 8));
   TilePlan best{np_max, 1, d, 1e300, false, false};
@@ -210,8 +210,11 @@ TilePlan plan_tiles(int64_t B, int d, int m, int n_tiles, int rps, int slice_byt
     for (int c = 1; c <= 8; ++c) candidates[n_candidates++] = c;
     for (int rounds = 1; rounds <= 4; ++rounds) candidates[n_candidates++] = (int)std::min<int64_t>(max_split, (256 * rounds + groups - 1) / groups);
     candidates[n_candidates++] = max_split;
+    uint64_t priced[3] = {0, 0, 0};                      // counts 0 .. 128 that came up before (on small layers most of the list)
     for (int q = 0; q < n_candidates; ++q) {
       const int want = std::min(candidates[q], max_split);
+      if (priced[want >> 6] >> (want & 63) & 1) continue;
+      priced[want >> 6] |= 1ull << (want & 63);
       const int chunk = (d + want - 1) / want;
       const int split = (d + chunk - 1) / chunk;      // no empty trailing chunks
       const double rounds = (double)((groups * split + 255) / 256);
@@ -277,10 +280,10 @@ int launch_with_lds(Kern kern, LdsCap *cap, const dim3 &grid, size_t lds, hipStr
   return check_launch(what);
 }
 
-// Records for every (input, padded row), then room for the partial sums when the inputs are split into chunks.
-inline size_t tiled_workspace_bytes(int d, int m, int jt, int n_tiles, int64_t B, int bytes_per_record, int slice_bytes, int code_bytes = 1) {
+// Records for every (input, padded row), then room for the partial sums when the inputs are split into chunks (tp: the tiled
+// kernel's plan for the same rows and form of the table).
+inline size_t tiled_workspace_bytes(int d, int m, int jt, int n_tiles, int64_t B, int bytes_per_record, const TilePlan &tp) {
   size_t bytes = record_bytes(d, padded_rows(B), bytes_per_record);
-  const TilePlan tp = plan_tiles(B, d, m, n_tiles, 64 / (jt / 4), slice_bytes, code_bytes);
   // any of the kernels may run (tiled, gather with one column per lane, gather with four): room for the largest set
   const GatherPlan gp = plan_gather(B, d, m), gp4 = plan_gather(B, d, n_tiles * jt / 4);
   const int n_split = std::max(tp.n_split, std::max(gp.n_split, gp4.n_split));

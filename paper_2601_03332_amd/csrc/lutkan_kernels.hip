@@ -1149,23 +1149,46 @@ int count_oob(const lutkan_dev_layer *l, const float *x, int64_t B, lutkan_oob_s
   return LUTKAN_OK;
 }
 
+// What a forward call may need, and the plans of the tiled kernel for the byte table and the wide form that this follows from
+// (the same plans the call then runs on).
+size_t forward_workspace(const lutkan_dev_layer *l, int64_t B, TilePlan &byte_plan, TilePlan &wide_plan) {
+  const int rps = 64 / (l->jt / 4), rec_bytes = lut_record_bytes(l->value_repr);
+  byte_plan = plan_tiles(B, l->d, l->m, l->n_tiles, rps, l->blob_bytes);
+  size_t bytes = tiled_workspace_bytes(l->d, l->m, l->jt, l->n_tiles, B, rec_bytes, byte_plan);
+  wide_plan = byte_plan;
+  if (l->wide_table && l->wide_blob_bytes >= 1) {
+    wide_plan = plan_tiles(B, l->d, l->m, l->n_tiles, rps, l->wide_blob_bytes, l->wide_code_bytes);
+    bytes = std::max(bytes, tiled_workspace_bytes(l->d, l->m, l->jt, l->n_tiles, B, rec_bytes, wide_plan));
+  }
+  return bytes + (l->value_repr == LUTKAN_REPR_SPLINE_COMPONENT ? lutkan::base_product_workspace_bytes(l->d, l->m) : 0);
+}
+
+// needed (nullable): the call comes without a workspace.  If it needs none it runs and *needed is 0, else nothing is launched and
+// *needed is the size to come back with; the route is the same either way.
 int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y, lutkan_oob_stats *stats,
                  int32_t *k_out, int32_t *l0_out, uint8_t *in_out, float *w_out, int16_t *q01_out, bool trace,
-                 void *workspace, size_t workspace_bytes, void *hip_stream, const char *who, int phases = kLocate | kEdges) {
+                 void *workspace, size_t workspace_bytes, void *hip_stream, const char *who, int phases = kLocate | kEdges,
+                 size_t *needed = nullptr) {
+  if (needed) *needed = 0;
   if (int rc = validate_layer(l, who)) return rc;
   if (B < 0) return fail(LUTKAN_EINVAL, "%s: B < 0", who);
   if (B == 0) return LUTKAN_OK;
   if (((phases & kLocate) && !x) || ((phases & kEdges) && !y)) return fail(LUTKAN_EINVAL, "%s: null x or y", who);
   if (x == y) return fail(LUTKAN_EINVAL, "%s: x and y alias", who);
   if (trace && (!k_out || !l0_out || !in_out || !w_out)) return fail(LUTKAN_EINVAL, "%s: null trace output", who);
-  const size_t need = lutkan_forward_workspace_bytes(l, B);
-  if (!workspace || workspace_bytes < need) return fail(LUTKAN_ESHAPE, "%s: workspace of %zu bytes, need %zu", who, workspace_bytes, need);
-  if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return fail(LUTKAN_EINVAL, "%s: workspace must be 256-byte aligned", who);
+  TilePlan byte_plan, wide_plan;
+  size_t need = 0;
+  if (!needed) {
+    need = forward_workspace(l, B, byte_plan, wide_plan);
+    if (!workspace || workspace_bytes < need) return fail(LUTKAN_ESHAPE, "%s: workspace of %zu bytes, need %zu", who, workspace_bytes, need);
+    if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return fail(LUTKAN_EINVAL, "%s: workspace must be 256-byte aligned", who);
+  }
   // A small narrow layer at a moderate batch: the one-launch chain kernel with a single layer beats locate + edge
   // kernel (+ partial sums) by 1.4-2x (78x16, 128x8, 64x32 up to 8192 rows); with more inputs per output column the
   // per-row walk over the inputs gets too long for it (256x64, 1024x64: slower).
   if (phases == (kLocate | kEdges) && !trace && !q01_out && small_layer_runs_as_chain(l, B))
     return chain_impl(l, 1, x, B, y, nullptr, stats, hip_stream, who);
+  if (needed) need = forward_workspace(l, B, byte_plan, wide_plan);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const lutkan::BlobLayout lay = lutkan::blob_layout(l->K, l->L, l->jt, l->scheme, l->value_repr, l->param_dtype);
 
@@ -1174,7 +1197,7 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   const bool with_base = (l->value_repr == LUTKAN_REPR_SPLINE_COMPONENT);
   bool tiled = tiled_supported(l->jt, l->blob_bytes, l->value_repr) && !q01_out;
   if (l->algo == LUTKAN_ALGO_GATHER) tiled = false;
-  const TilePlan tp = tiled ? plan_tiles(B, l->d, l->m, l->n_tiles, 64 / (l->jt / 4), l->blob_bytes) : TilePlan{1, 1, l->d, 0.0, false, false};
+  const TilePlan tp = tiled ? byte_plan : TilePlan{1, 1, l->d, 0.0, false, false};
   if (l->algo == LUTKAN_ALGO_AUTO && tiled && prefer_gather_for_small_batch(l, B, tp.hbm_bound && tp.reads_once ? 0.84 * tp.cost : tp.cost)) tiled = false;
   const bool tiled_asked_for = (l->algo == LUTKAN_ALGO_TILED || l->algo == LUTKAN_ALGO_TILED_WIDE);
   if (tiled_asked_for && !tiled) return fail(LUTKAN_EUNSUPPORTED, "%s: tiled kernel needs a table slice <= 72 KiB (64 KiB with the base branch)%s", who, q01_out ? " and writes no code trace" : "");
@@ -1192,7 +1215,7 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   const int wide_cb = l->wide_code_bytes;
   const bool can_wide = tiled && l->wide_table != nullptr &&
                         (rec_bytes == 8 || (wide_cb == 4 && l->wide_blob_bytes <= lutkan::lds_slice_budget(LUTKAN_REPR_SPLINE_COMPONENT)));
-  const TilePlan tpw = can_wide ? plan_tiles(B, l->d, l->m, l->n_tiles, 64 / (l->jt / 4), l->wide_blob_bytes, wide_cb) : tp;
+  const TilePlan tpw = can_wide ? wide_plan : tp;
   // (with y_min the row step on 16-bit codes reads 56 bytes per lane from LDS and measured within 3 % of the byte form
   // either way on 256x256 and 128x128 layers: left to the byte form unless asked for)
   const bool wide = can_wide && ((tpw.cost < tp.cost && (wide_cb == 4 || l->scheme == LUTKAN_SYM_INT8)) || l->algo == LUTKAN_ALGO_TILED_WIDE);
@@ -1224,10 +1247,14 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
       if (int rc = lutkan::rows_forward(l, rp, x, B, y, hip_stream)) return rc;
       return stats ? count_oob(l, x, B, stats, s) : LUTKAN_OK;
     }
-    if (np.waves && np.cost < passes) {
+    if (np.waves && np.cost < passes && !(needed && np.n_split > 1)) {
       if (int rc = lutkan::narrow_forward(l, np, x, B, y, workspace, hip_stream)) return rc;
       return stats ? count_oob(l, x, B, stats, s) : LUTKAN_OK;
     }
+  }
+  if (needed) {
+    *needed = need;
+    return LUTKAN_OK;
   }
 
   LocateArgs la;
@@ -1355,10 +1382,8 @@ extern "C" size_t lutkan_forward_workspace_bytes(const lutkan_dev_layer *layer, 
   // would divide by zero in the launch planning)
   if (!layer || B <= 0 || layer->d < 1 || layer->m < 1 || layer->n_tiles < 1 || layer->blob_bytes < 1) return 0;
   if (layer->jt < 4 || layer->jt > 64 || (layer->jt & (layer->jt - 1))) return 0;
-  size_t bytes = tiled_workspace_bytes(layer->d, layer->m, layer->jt, layer->n_tiles, B, lut_record_bytes(layer->value_repr), layer->blob_bytes);
-  if (layer->wide_table && layer->wide_blob_bytes >= 1)
-    bytes = std::max(bytes, tiled_workspace_bytes(layer->d, layer->m, layer->jt, layer->n_tiles, B, lut_record_bytes(layer->value_repr), layer->wide_blob_bytes, layer->wide_code_bytes));
-  return bytes + (layer->value_repr == LUTKAN_REPR_SPLINE_COMPONENT ? lutkan::base_product_workspace_bytes(layer->d, layer->m) : 0);
+  TilePlan byte_plan, wide_plan;
+  return forward_workspace(layer, B, byte_plan, wide_plan);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1460,6 +1485,14 @@ extern "C" int lutkan_forward(const lutkan_dev_layer *layer, const float *x, int
                       workspace_bytes, hip_stream, "lutkan_forward");
 }
 
+extern "C" int lutkan_forward_or_workspace(const lutkan_dev_layer *layer, const float *x, int64_t B, float *y,
+                                           lutkan_oob_stats *stats, size_t *workspace_bytes, void *hip_stream) {
+  lutkan::plan_clear();
+  if (!workspace_bytes) return fail(LUTKAN_EINVAL, "lutkan_forward_or_workspace: null workspace_bytes");
+  return forward_impl(layer, x, B, y, stats, nullptr, nullptr, nullptr, nullptr, nullptr, false, nullptr, 0, hip_stream, "lutkan_forward",
+                      kLocate | kEdges, workspace_bytes);
+}
+
 // Device memory for lutkan_forward_static_scratch: one array per GPU that loads this library, held until the process
 // ends.  In host code the name is only a handle for hipGetSymbolAddress; what kernels and copies get is the address
 // that call returns on the current device.
@@ -1553,10 +1586,11 @@ extern "C" int lutkan_chain_forward(const lutkan_dev_layer *layers, int32_t n_la
   return chain_impl(layers, n_layers, x, B, y, hidden, stats, hip_stream, "lutkan_chain_forward");
 }
 
-extern "C" int lutkan_model_forward(const lutkan_dev_layer *layers, int32_t n_layers, const float *x, int64_t B, float *y,
-                                    lutkan_oob_stats *stats, void *workspace, size_t workspace_bytes, void *hip_stream) {
-  const char *who = "lutkan_model_forward";
-  lutkan::plan_clear();
+namespace {
+// needed: as in forward_impl
+int model_impl(const lutkan_dev_layer *layers, int32_t n_layers, const float *x, int64_t B, float *y, lutkan_oob_stats *stats,
+               void *workspace, size_t workspace_bytes, void *hip_stream, const char *who, size_t *needed) {
+  if (needed) *needed = 0;
   if (!layers || n_layers < 1 || n_layers > LUTKAN_MAX_LAYERS) return fail(LUTKAN_EINVAL, "%s: need 1..%d layers", who, LUTKAN_MAX_LAYERS);
   for (int l = 0; l < n_layers; ++l)                       // before anything is computed from a layer's fields
     if (int rc = validate_layer(&layers[l], who)) return rc;
@@ -1564,14 +1598,24 @@ extern "C" int lutkan_model_forward(const lutkan_dev_layer *layers, int32_t n_la
     if (layers[l].m != layers[l + 1].d) return fail(LUTKAN_ESHAPE, "%s: layer %d has m=%d but layer %d has d=%d", who, l, layers[l].m, l + 1, layers[l + 1].d);
   if (B < 0) return fail(LUTKAN_EINVAL, "%s: B < 0", who);
   if (B == 0) return LUTKAN_OK;
-  size_t act, scratch;
-  const size_t need = model_workspace(layers, n_layers, B, &act, &scratch);
-  if (!workspace || workspace_bytes < need) return fail(LUTKAN_ESHAPE, "%s: workspace of %zu bytes, need %zu", who, workspace_bytes, need);
-  if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return fail(LUTKAN_EINVAL, "%s: workspace must be 256-byte aligned", who);
+  size_t act = 0, scratch = 0;
+  if (!needed) {
+    const size_t need = model_workspace(layers, n_layers, B, &act, &scratch);
+    if (!workspace || workspace_bytes < need) return fail(LUTKAN_ESHAPE, "%s: workspace of %zu bytes, need %zu", who, workspace_bytes, need);
+    if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return fail(LUTKAN_EINVAL, "%s: workspace must be 256-byte aligned", who);
+  }
   // A network of small layers may run as one launch that writes y while it reads x: x == y is refused for all of them, those
   // of which a layer leaves the chain included, so that the answer does not follow the pricing of launches.
   if (x == y && n_layers <= kChainMaxLayers && std::all_of(layers, layers + n_layers, [B](const lutkan_dev_layer &l) { return small_layer_suits_chain(&l, B); }))
     return fail(LUTKAN_EINVAL, "%s: x and y alias", who);
+  if (needed) {                                            // one launch of the chain kernel, one layer, or activations to keep
+    if (n_layers == 1)
+      return forward_impl(layers, x, B, y, stats, nullptr, nullptr, nullptr, nullptr, nullptr, false, nullptr, 0, hip_stream, who, kLocate | kEdges, needed);
+    if (n_layers <= kChainMaxLayers && std::all_of(layers, layers + n_layers, [B](const lutkan_dev_layer &l) { return small_layer_runs_as_chain(&l, B); }))
+      return chain_impl(layers, n_layers, x, B, y, nullptr, stats, hip_stream, who);
+    *needed = model_workspace(layers, n_layers, B, &act, &scratch);
+    return LUTKAN_OK;
+  }
   // Consecutive layers that would each run as a launch of the chain kernel run as one launch of it instead.  The
   // arithmetic per layer is the same, so the result is bit-identical to the layer-by-layer calls.
   char *base = static_cast<char *>(workspace);
@@ -1590,4 +1634,18 @@ extern "C" int lutkan_model_forward(const lutkan_dev_layer *layers, int32_t n_la
     in = out;
   }
   return LUTKAN_OK;
+}
+}  // namespace
+
+extern "C" int lutkan_model_forward(const lutkan_dev_layer *layers, int32_t n_layers, const float *x, int64_t B, float *y,
+                                    lutkan_oob_stats *stats, void *workspace, size_t workspace_bytes, void *hip_stream) {
+  lutkan::plan_clear();
+  return model_impl(layers, n_layers, x, B, y, stats, workspace, workspace_bytes, hip_stream, "lutkan_model_forward", nullptr);
+}
+
+extern "C" int lutkan_model_forward_or_workspace(const lutkan_dev_layer *layers, int32_t n_layers, const float *x, int64_t B, float *y,
+                                                 lutkan_oob_stats *stats, size_t *workspace_bytes, void *hip_stream) {
+  lutkan::plan_clear();
+  if (!workspace_bytes) return fail(LUTKAN_EINVAL, "lutkan_model_forward_or_workspace: null workspace_bytes");
+  return model_impl(layers, n_layers, x, B, y, stats, nullptr, 0, hip_stream, "lutkan_model_forward", workspace_bytes);
 }

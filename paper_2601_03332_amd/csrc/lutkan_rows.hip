@@ -15,7 +15,7 @@
 // Whole layers replayed from a HIP graph, passes -> this kernel, microseconds: 256 -> 256, L = 64, at 1 / 64 / 256 / 512 rows
 // 11.4 / 20.4 / 26 / 29 -> 4.1 / 4.7 / 10.0 / 17.8 (at 1000 the passes run); 1024 -> 64 at 128 rows 30 -> 9.3; 512 -> 512, L = 32, at
 // 32 rows 24.5 -> 6.2; 30 -> 1000 with spline_component at 128 rows 16.8 -> 7.9; 700 -> 130 at 128 rows 30 -> 17.8.  Called one by one
-// the small ones take 7 to 8, the host's share.
+// the small ones take 6.5, the host's share.
 // The file is compiled with -ffp-contract=off; every fused multiply-add is written out as fmaf().
 #include "lutkan_device.h"
 #include "lutkan_locate.h"

@@ -1314,6 +1314,52 @@ def test_bspline_layer_on_the_matrix_cores(case):
     assert np.array_equal(y.cpu().numpy(), y_shifted.cpu().numpy(), equal_nan=True)
 
 
+# widths, rows, L, scheme, with stats, what runs: without a workspace (0) or with one (1)
+WITHOUT_WORKSPACE = [((10, 8), 1024, 64, SYM_INT8, False, 0), ((78, 16, 2), 256, 64, ASYM_UINT8, True, 0), ((78, 16, 2), 0, 64, ASYM_UINT8, False, 0),
+                     ((256, 256), 16, 64, SYM_INT8, True, 0), ((256, 256), 4000, 64, SYM_INT8, False, 1), ((78, 16), 65536, 64, ASYM_UINT8, True, 0),
+                     ((1000, 30), 9000, 16, SYM_INT8, False, 1), ((40, 60, 60, 10), 5000, 32, ASYM_UINT8, True, 1), ((200, 300), 1000, 48, ASYM_UINT8, True, 1)]
+
+
+@pytest.mark.parametrize("case", WITHOUT_WORKSPACE, ids=lambda c: "-".join(map(str, c[0])) + f"x{c[1]}")
+def test_forward_without_a_workspace(case):
+    """A call without a workspace either is the call with one, bit for bit on the same route, or launches nothing and says how
+    much it needs; the binding returns the same outputs and counters both ways."""
+    import ctypes as C
+    widths, B, L, scheme, with_stats, needs = case
+    layers, w = [], None
+    for n, (d, m) in enumerate(zip(widths[:-1], widths[1:])):
+        w = random_layer(640 + n, d, m, 5, L, scheme, CLOSED, CLIP_X, max(B, 1))
+        s = w.layers[0]
+        layers.append(lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.L, s.scheme, s.boundary, s.oob).to_device(DEV))
+        x = w.x if n == 0 else x
+    xg = torch.from_numpy(x[:B].copy()).to(DEV)
+    n, lib, need = len(layers), lk.load_library(), C.c_size_t(77)
+    arr = (type(layers[0].c) * n)(*[l.c for l in layers])
+    stats = [torch.zeros((n, 2), dtype=torch.int64, device=DEV) if with_stats else None for _ in range(3)]
+    ptr = [t.data_ptr() if t is not None else None for t in stats]
+    room = lk.lutkan_model_workspace_bytes(layers, B) if n > 1 else lk.lutkan_forward_workspace_bytes(layers[0], B)
+    ws = torch.empty(max(room, 256), dtype=torch.uint8, device=DEV)
+    y0, y1 = (torch.full((B, widths[-1]), -7.0, device=DEV) for _ in range(2))
+    _say(f"case without a workspace {widths} B={B}")
+    stream = torch.cuda.current_stream().cuda_stream
+    if n > 1:
+        assert lib.lutkan_model_forward(arr, n, xg.data_ptr(), B, y0.data_ptr(), ptr[0], ws.data_ptr(), ws.numel(), stream) == 0
+        plan = lk.lutkan_last_plan()
+        assert lib.lutkan_model_forward_or_workspace(arr, n, xg.data_ptr(), B, y1.data_ptr(), ptr[1], C.byref(need), stream) == 0
+    else:
+        assert lib.lutkan_forward(arr, xg.data_ptr(), B, y0.data_ptr(), ptr[0], ws.data_ptr(), ws.numel(), stream) == 0
+        plan = lk.lutkan_last_plan()
+        assert lib.lutkan_forward_or_workspace(arr, xg.data_ptr(), B, y1.data_ptr(), ptr[1], C.byref(need), stream) == 0
+    if needs:
+        assert need.value == room and lk.lutkan_last_plan() == "" and bool((y1 == -7.0).all())
+        assert stats[1] is None or int(stats[1].abs().sum()) == 0
+    else:
+        assert need.value == 0 and lk.lutkan_last_plan() == plan
+        assert torch.equal(y0, y1) and (stats[0] is None or torch.equal(stats[0], stats[1]))
+    y2 = lk.lutkan_model_forward(layers, xg, stats=stats[2]) if n > 1 else lk.lutkan_forward(layers[0], xg, stats=None if stats[2] is None else stats[2][0])
+    assert lk.lutkan_last_plan() == plan and torch.equal(y0, y2) and (stats[0] is None or torch.equal(stats[0], stats[2]))
+
+
 @pytest.mark.parametrize("G", [1, 5, 6, 9, 10, 13])
 def test_every_input_of_a_stage_meets_its_own_coefficients(G):
     """The grids at either end of two, three and four groups of slots per input; inputs short of, filling and past a stage of the

@@ -189,7 +189,15 @@ def test_forward_argument_validation_happens_before_any_launch():
     dl.L = s.L
     dl.knots[2] = dl.knots[1]
     assert lib.lutkan_forward(C.byref(dl), 16, 4, 32, None, 256, 1 << 20, None) == -1
+    need = C.c_size_t(5)
+    assert lib.lutkan_forward_or_workspace(C.byref(dl), 16, 4, 32, None, C.byref(need), None) == -1
+    dl.knots[2] = np.float32(0.5 * (dl.knots[1] + dl.knots[3]))
+    assert lib.lutkan_forward_or_workspace(C.byref(dl), 16, 4, 32, None, None, None) == -1
+    assert lib.lutkan_forward_or_workspace(C.byref(dl), 16, 4, 16, None, C.byref(need), None) == -1      # x == y
+    assert lib.lutkan_forward_or_workspace(C.byref(dl), 16, 0, 32, None, C.byref(need), None) == 0 and need.value == 0
+    dl.knots[2] = dl.knots[1]
     two = (binding._DevLayer * 2)(dl, dl)
+    assert lib.lutkan_model_forward_or_workspace(two, 2, 16, 4, 32, None, C.byref(need), None) == -1
     assert lib.lutkan_model_forward(two, 2, 16, 4, 32, None, 256, 1 << 20, None) == -1     # every layer is validated first
     # the fused chain: same checks, plus the shapes it cannot hold
     assert lib.lutkan_chain_forward(two, 2, 16, 4, 32, None, None, None) == -1             # the knots are still broken
