@@ -36,6 +36,7 @@ struct LocateArgs {
   float masked_below, masked_above;      // zero_spline: inputs outside contribute nothing; clip_x: -inf, +inf
   float inner[LUTKAN_MAX_K];             // the inner knots T[1] .. T[K-1], +inf past the last
   float knots[LUTKAN_MAX_K + 1];
+  uint32_t divided_below;      // see divided_below()
   const float *input_knots;    // [d][K+1]: one knot vector per input (then the knots and bounds above are not used)
   int32_t *k_out, *l0_out;     // nullable trace outputs, [B][d]
   uint8_t *in_out;
@@ -64,7 +65,8 @@ __global__ __launch_bounds__(256) void lutkan_locate_kernel(const LocateArgs a) 
   constexpr int KSTRIDE = LUTKAN_MAX_K + 1;
   static_assert(KSTRIDE % 2 == 1, "odd stride between the knot rows");
   __shared__ rec_t s_rec[COLS][ROWS + 1];
-  __shared__ float s_knots[(PERIN ? COLS : 1) * KSTRIDE];
+  __shared__ float s_knots[PERIN ? COLS * KSTRIDE : KSTRIDE];       // PERIN, or the trace of a shared vector
+  __shared__ f32x4 s_seg[PERIN ? 1 : LUTKAN_MAX_K];
   rec_t *const rec_out = static_cast<rec_t *>(a.rec);
   const int tid = threadIdx.x;
   const int64_t b0 = (int64_t)blockIdx.x * ROWS;
@@ -76,6 +78,7 @@ __global__ __launch_bounds__(256) void lutkan_locate_kernel(const LocateArgs a) 
     }
   } else {
     if (tid <= a.K) s_knots[tid] = a.knots[tid];
+    fill_segments(a, s_seg, tid);
   }
   const unsigned masked_index = (unsigned)(a.K * a.L) | ((unsigned)a.K << 16);
   const int il = tid % COLS;
@@ -108,7 +111,7 @@ __global__ __launch_bounds__(256) void lutkan_locate_kernel(const LocateArgs a) 
     }
   } else {
     int k[E], l0[E];
-    locate_side_by_side<E>(a, s_knots, xv, k, l0, weight);
+    locate_side_by_side<E>(a, s_seg, xv, k, l0, weight);
 #pragma unroll
     for (int p = 0; p < E; ++p) {
       const bool masked = (xv[p] < a.masked_below) | (xv[p] > a.masked_above);
@@ -1270,6 +1273,7 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   la.masked_above = la.zero_spline ? la.tKs : INFINITY;
   for (int k = 0; k <= l->K; ++k) la.knots[k] = l->knots[k];
   for (int k = 0; k < LUTKAN_MAX_K; ++k) la.inner[k] = (k + 1 < l->K) ? l->knots[k + 1] : INFINITY;
+  la.divided_below = l->knots_per_input ? 0u : divided_below(l->knots, l->K);
   la.input_knots = l->knots_per_input ? l->input_knots : nullptr;
   la.k_out = trace ? k_out : nullptr; la.l0_out = l0_out; la.in_out = in_out; la.w_out = w_out;
   if (phases & kLocate) {

@@ -49,36 +49,85 @@ __device__ __forceinline__ Located locate_one(const Args &a, const float *s_knot
   return o;
 }
 
-// Steps 1-4 of Sec. 4.5 for VEC inputs side by side: the arithmetic of locate_one (same operations, same roundings) without
-// its branches.  In(x) is t0 <= x <= tKs under either boundary mode.  The knots above x' are counted by the sign of x' - T
-// (exact; +inf past the last knot), shifted into a word: two instructions a knot and no condition register.  Ten segments
-// are searched without a loop, their knots in scalar registers; more in steps of eight.
+// Eq. 15 by a reciprocal that every segment keeps: num / den correctly rounded from y = RN(1/den) in five operations -- a
+// quotient within two units, one correction that makes it faithful, one that rounds it correctly (Markstein's theorem: q + r y,
+// rounded once, is the rounded a/b if r = a - b q is exact, q faithful and y = RN(1/b)) -- where the compiler's division takes
+// eleven and a hardware reciprocal.  r is exact while num >= 2^-90 and den lies in [2^-30, 2^30]; other pairs are divided.
+constexpr unsigned kPlainNumerator = 0x12800000u;      // 2^-90
+__device__ __forceinline__ float quotient(float num, float den, float y) {
+  const float q0 = __fmul_rn(num, y);
+  const float q1 = fmaf(fmaf(-q0, den, num), y, q0);
+  return fmaf(fmaf(-q1, den, num), y, q1);
+}
+
+// The rows that locate_side_by_side looks up, in LDS: of segment k its first knot, width (rounded as Eq. 15 rounds it) and the
+// width's reciprocal.  fill_segments covers segments 0 .. K-1 with the threads of a work-group.
+template <typename Args>
+__device__ __forceinline__ void fill_segments(const Args &a, f32x4 *s_seg, int tid) {
+  if (tid >= a.K) return;
+  const float tk = a.knots[tid], den = __fsub_rn(a.knots[tid + 1], tk);
+  s_seg[tid] = f32x4{tk, den, __fdiv_rn(1.0f, den), 0.0f};
+}
+// The bits below which a numerator is divided instead (0 counts as none: its bits - 1 wrap round); every one if a width is not plain.
+inline unsigned divided_below(const float *knots, int K) {
+  for (int k = 0; k < K; ++k) {
+    const float den = knots[k + 1] - knots[k];
+    if (!(den >= 0x1p-30f && den <= 0x1p30f)) return 0xffffffffu;
+  }
+  return kPlainNumerator - 1;
+}
+
+// Steps 1-4 of Sec. 4.5 for VEC inputs side by side: the arithmetic of locate_one (same results to the bit) without its
+// branches.  In(x) is t0 <= x <= tKs under either boundary mode.  The knots above x' are counted by the sign of x' - T
+// (exact; +inf past the last knot), shifted into a word: two instructions a knot and no condition register.  Up to five and up to
+// ten segments are searched without a loop, their knots in scalar registers; more in steps of eight.
 template <int VEC, typename Args>
-__device__ __forceinline__ void locate_side_by_side(const Args &a, const float *s_knots, const float x[VEC], int k[VEC], int l0[VEC], float w[VEC]) {
-  constexpr int kFirst = 9;
+__device__ __forceinline__ void locate_side_by_side(const Args &a, const f32x4 *s_seg, const float x[VEC], int k[VEC], int l0[VEC], float w[VEC]) {
+  constexpr int kFew = 4, kFirst = 9;
   float xc[VEC];
+  unsigned above[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) {
     xc[v] = __builtin_amdgcn_fmed3f(x[v], a.t0, a.tKs) + 0.0f;   // (a NaN comes out inside and is put back in w; -0 becomes
-    unsigned above = 0;                                            // +0, whose difference from a knot at 0 has no sign bit)
+    above[v] = 0;                                                  // +0, whose difference from a knot at 0 has no sign bit)
 #pragma unroll
-    for (int q = 0; q < kFirst; ++q) above = __builtin_amdgcn_alignbit(above, __float_as_uint(xc[v] - a.inner[q]), 31);
-    k[v] = kFirst - __popc(above);
+    for (int q = 0; q < kFew; ++q) above[v] = __builtin_amdgcn_alignbit(above[v], __float_as_uint(xc[v] - a.inner[q]), 31);
+    k[v] = kFew - __popc(above[v]);
   }
-#pragma unroll 1
-  for (int g = kFirst; g < a.K - 1; g += 8) {
+  if (a.K > kFew + 1) {                                  // uniform
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const float knot = a.inner[min(g + q, LUTKAN_MAX_K - 1)];
+    for (int v = 0; v < VEC; ++v) {
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) k[v] += (knot <= xc[v]) ? 1 : 0;
+      for (int q = kFew; q < kFirst; ++q) above[v] = __builtin_amdgcn_alignbit(above[v], __float_as_uint(xc[v] - a.inner[q]), 31);
+      k[v] = kFirst - __popc(above[v]);
     }
+#pragma unroll 1
+    for (int g = kFirst; g < a.K - 1; g += 8) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float knot = a.inner[min(g + q, LUTKAN_MAX_K - 1)];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) k[v] += (knot <= xc[v]) ? 1 : 0;
+      }
+    }
+  }
+  float num[VEC], den[VEC], u[VEC];
+  unsigned smallest = 0xffffffffu;
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) {
+    const f32x4 seg = s_seg[k[v]];
+    num[v] = __fsub_rn(xc[v], seg.x);
+    den[v] = seg.y;
+    u[v] = quotient(num[v], den[v], seg.z);                                          // Eq. 15, correctly rounded
+    smallest = min(smallest, __float_as_uint(num[v]) - 1u);
+  }
+  if (smallest < a.divided_below) {
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) u[v] = __fdiv_rn(num[v], den[v]);
   }
 #pragma unroll
   for (int v = 0; v < VEC; ++v) {
-    const float tk = s_knots[k[v]], tk1 = s_knots[k[v] + 1];
-    const float u = __fdiv_rn(__fsub_rn(xc[v], tk), __fsub_rn(tk1, tk));             // Eq. 15, correctly rounded
-    const float z = __fmul_rn(u, (float)(a.L - 1));                                    // Eq. 16; 0 <= u <= 1
+    const float z = __fmul_rn(u[v], (float)(a.L - 1));                                 // Eq. 16; 0 <= u <= 1
     const float below = floorf(z);
     l0[v] = (int)below;
     w[v] = (x[v] != x[v]) ? __builtin_nanf("") : __fsub_rn(z, below);

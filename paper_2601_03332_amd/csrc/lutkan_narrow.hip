@@ -43,6 +43,7 @@ struct NarrowArgs {
   int64_t split_stride;
   float t0, tKs;
   float masked_below, masked_above;      // zero_spline: inputs outside contribute nothing; clip_x: -inf, +inf
+  uint32_t divided_below;                // see divided_below()
   float inner[LUTKAN_MAX_K];             // the inner knots T[1] .. T[K-1], +inf past the last
   float knots[LUTKAN_MAX_K + 1];
 };
@@ -69,7 +70,7 @@ __global__ __launch_bounds__(NW * 64) void lutkan_narrow_kernel(const NarrowArgs
   constexpr int RPS = 64 / LPR;
   constexpr int PSZ = PH ? 8 : 16, PLANE = 4 * LPR * (PH ? 2 : 4), kParamRow = PLANE * (SCHEME == LUTKAN_ASYM_UINT8 ? 2 : 1);
   extern __shared__ __align__(16) unsigned char lds[];
-  float *const s_knots = reinterpret_cast<float *>(lds + 2 * S * a.blob_bytes);
+  f32x4 *const s_seg = reinterpret_cast<f32x4 *>(lds + 2 * S * a.blob_bytes);
   typedef const __attribute__((address_space(3))) unsigned char *lds_bytes;
   typedef const __attribute__((address_space(3))) unsigned *lds_u32;
   typedef const __attribute__((address_space(3))) u32x2 *lds_u32x2;
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(NW * 64) void lutkan_narrow_kernel(const NarrowArgs
   const int i_end = min(a.d, i_begin + a.chunk);
   const unsigned stage_bytes = S * a.blob_bytes;
   const unsigned lane_off = lane * 16;
-  if (tid <= a.K) s_knots[tid] = a.knots[tid];
+  fill_segments(a, s_seg, tid);
 
   // the slices of the up to S inputs from i on, one contiguous run
   auto stage = [&](int i, int buf) {
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(NW * 64) void lutkan_narrow_kernel(const NarrowArgs
     unsigned code_at[VEC], param_at[VEC], weight[VEC], silu[VEC];
     int k[VEC], l0[VEC];
     float w[VEC];
-    locate_side_by_side<VEC>(a, s_knots, xv, k, l0, w);
+    locate_side_by_side<VEC>(a, s_seg, xv, k, l0, w);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
       const int s = sub * VEC + v;
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(NW * 64) void lutkan_narrow_kernel(const NarrowArgs
   }
 }
 
-inline size_t narrow_lds_bytes(int stage, int blob_bytes) { return 2 * (size_t)stage * blob_bytes + (LUTKAN_MAX_K + 1) * 4; }
+inline size_t narrow_lds_bytes(int stage, int blob_bytes) { return 2 * (size_t)stage * blob_bytes + LUTKAN_MAX_K * 16; }
 
 // Inputs per stage: 8 or 4, as two stages fit the LDS; 0: this kernel does not serve the layer.  With the base branch 4: the
 // reads of eight inputs and their base rows together do not fit the registers of 16 waves.
@@ -326,6 +327,7 @@ int narrow_forward(const lutkan_dev_layer *l, const NarrowPlan &plan, const floa
   na.masked_above = (l->oob == LUTKAN_ZERO_SPLINE) ? na.tKs : INFINITY;
   for (int k = 0; k <= l->K; ++k) na.knots[k] = l->knots[k];
   for (int k = 0; k < LUTKAN_MAX_K; ++k) na.inner[k] = (k + 1 < l->K) ? l->knots[k + 1] : INFINITY;
+  na.divided_below = divided_below(l->knots, l->K);
   na.chunk = plan.chunk;
   float *const partials = static_cast<float *>(workspace);
   if (plan.n_split > 1) { na.y = partials; na.split_stride = B * l->m; }
