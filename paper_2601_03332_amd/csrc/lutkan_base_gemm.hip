@@ -11,26 +11,23 @@
 // Both operands arrive already cut: SiLU(x) by the locate kernel (lutkan_cut3 below, three planes [piece][row][input]),
 // s_out*s_base by lutkan_base_pieces_kernel from the base rows of the LUT device table (three planes
 // [piece][column][input]); in both the inputs are contiguous, which is the operand order of the matrix instruction
-// (a lane holds 8 consecutive k of one row resp. column).  One work-group of 256 threads computes a 128 x 128 tile of
-// Y0, its four waves 64 x 64 each as 2 x 2 tiles of v_mfma_f32_32x32x16_bf16; the inputs are walked 32 at a time: 48 KiB
-// of pieces go global -> registers -> LDS (the loads of the next step are in flight while this step multiplies), each
-// wave then reads its operands with 16-byte LDS reads.  Two work-groups fit a compute unit.
-#include <hip/hip_runtime.h>
-
-#include <cstdint>
-
-#include "lutkan_internal.h"
+// (a lane holds 8 consecutive k of one row resp. column).  One work-group of 512 threads computes a 128 x 128 tile of
+// Y0, its eight waves 64 x 32 each as two tiles of v_mfma_f32_32x32x16_bf16; the inputs are walked 32 at a time: 48 KiB
+// of pieces go global -> registers -> one of two LDS buffers (the loads of the next step are in flight while this step
+// multiplies, one barrier a step), each wave then reads its operands with 16-byte LDS reads.
+//
+// Bound: LDS and matrix issue, about 12 us each of 512 -> 512 at 8192 rows, and the barriers between: 32 us, 0.8 PFLOP/s.  With four
+// waves of 64 x 64 (one per SIMD where a launch has 256 tiles), one buffer and the column tiles of a row tile spread over the XCDs
+// 39; loads two steps ahead 32.  The layer 321 -> 316 us, 1024 -> 1024, G = 10, 1356 -> 1346, 512 -> 300 at 5000 rows 195 -> 190.
+#include "lutkan_device.h"
 #include "lutkan_pieces.h"
-
-using lutkan::fail;
 
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kBM = 128, kBN = 128, kBK = 32;
+constexpr int kBM = 128, kBN = 128, kBK = 32, kGemmWaves = 8;
 constexpr int kLdk = kBK + 8;            // bf16 elements per LDS row: 80 bytes, so that the 16 rows of a 16-byte read group fall into different banks
 constexpr int kVecPerStep = 3 * kBM * kBK * 2 / 16;      // 16-byte vectors of one operand per k step: 1536, six per thread
 
@@ -69,91 +66,104 @@ struct BaseGemmArgs {
   int32_t d, m, m_pad;
 };
 
-__global__ __launch_bounds__(256) void lutkan_base_gemm_kernel(const BaseGemmArgs a) {
+__global__ __launch_bounds__(kGemmWaves * 64) void lutkan_base_gemm_kernel(const BaseGemmArgs a) {
   static_assert(kBM == kBN, "both operand tiles share one LDS shape");
-  __shared__ __align__(16) uint16_t sA[3][kBM][kLdk];
-  __shared__ __align__(16) uint16_t sW[3][kBN][kLdk];
+  extern __shared__ __align__(16) uint16_t lds[];       // two buffers of [operand][piece][row or column][kLdk]
+  constexpr int kTile = 3 * kBM * kLdk, kBuffer = 2 * kTile, kThreads = kGemmWaves * 64, kPer = kVecPerStep / kThreads;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1;               // this wave's 64 x 64 quarter of the tile
-  const int64_t row0 = (int64_t)blockIdx.y * kBM;
-  const int col0 = blockIdx.x * kBN;
+  const int wr = wave >> 2, wc = wave & 3;               // this wave's 64 x 32 eighth of the tile
+  // The column tiles of a row tile run on one XCD (work-groups go to the eight in turn) and find its SiLU pieces in that L2: row
+  // tiles in groups of eight, the row tile the fastest of a group's indices.
+  const unsigned col_tiles = a.m_pad / kBN, row_tiles = (unsigned)((a.B + kBM - 1) / kBM);
+  const unsigned in_groups = row_tiles / 8 * 8 * col_tiles, rest = row_tiles % 8;
+  unsigned row_tile, col_tile;
+  if (blockIdx.x < in_groups) {
+    const unsigned in = blockIdx.x % (8 * col_tiles);
+    row_tile = blockIdx.x / (8 * col_tiles) * 8 + in % 8;
+    col_tile = in / 8;
+  } else {
+    row_tile = row_tiles - rest + (blockIdx.x - in_groups) % rest;
+    col_tile = (blockIdx.x - in_groups) / rest;
+  }
+  const int64_t row0 = (int64_t)row_tile * kBM;
+  const int col0 = (int)col_tile * kBN;
 
-  f32x16 acc[2][2];
+  f32x16 acc[2];
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[rt][ct][v] = 0.0f;
+    for (int v = 0; v < 16; ++v) acc[rt][v] = 0.0f;
 
-  // this thread's six vectors of each operand tile: vector v = tid + 256 q is piece v / 512, row (v % 512) / 4,
+  // this thread's vectors of each operand tile: vector v = tid + threads * q is piece v / 512, row (v % 512) / 4,
   // inputs 8 * (v % 4) .. + 7 of the step (four adjacent threads read the 64 contiguous bytes of one row)
-  const uint16_t *ga[6], *gw[6];
-  uint16_t *la[6], *lw[6];
+  static_assert(kVecPerStep % kThreads == 0, "whole vectors per thread and operand");
+  const uint16_t *ga[kPer], *gw[kPer];
+  int at[kPer];
 #pragma unroll
-  for (int q = 0; q < 6; ++q) {
-    const int v = tid + 256 * q;
+  for (int q = 0; q < kPer; ++q) {
+    const int v = tid + kThreads * q;
     const int piece = v >> 9, r = (v & 511) >> 2, k8 = (v & 3) * 8;
     ga[q] = a.a_pieces + ((size_t)piece * a.Bp + row0 + r) * a.d + k8;
     gw[q] = a.w_pieces + ((size_t)piece * a.m_pad + col0 + r) * a.d + k8;
-    la[q] = &sA[piece][r][k8];
-    lw[q] = &sW[piece][r][k8];
+    at[q] = (piece * kBM + r) * kLdk + k8;
   }
-  static_assert(kVecPerStep == 6 * 256, "six vectors per thread and operand");
-  u32x4 ra[6], rw[6];
+  u32x4 ra[kPer], rw[kPer];
+  auto load = [&](int k0) {
 #pragma unroll
-  for (int q = 0; q < 6; ++q) { ra[q] = *reinterpret_cast<const u32x4 *>(ga[q]); rw[q] = *reinterpret_cast<const u32x4 *>(gw[q]); }
+    for (int q = 0; q < kPer; ++q) { ra[q] = *reinterpret_cast<const u32x4 *>(ga[q] + k0); rw[q] = *reinterpret_cast<const u32x4 *>(gw[q] + k0); }
+  };
+  auto store = [&](uint16_t *buf) {
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) { *reinterpret_cast<u32x4 *>(buf + at[q]) = ra[q]; *reinterpret_cast<u32x4 *>(buf + kTile + at[q]) = rw[q]; }
+  };
+  load(0);
+  store(lds);
+  if (kBK < a.d) load(kBK);
+  __syncthreads();
 
+  int cur = 0;
   for (int k0 = 0; k0 < a.d; k0 += kBK) {
-#pragma unroll
-    for (int q = 0; q < 6; ++q) { *reinterpret_cast<u32x4 *>(la[q]) = ra[q]; *reinterpret_cast<u32x4 *>(lw[q]) = rw[q]; }
-    __syncthreads();
-    if (k0 + kBK < a.d) {                                // the next step's pieces travel while this step multiplies
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
-        ra[q] = *reinterpret_cast<const u32x4 *>(ga[q] + k0 + kBK);
-        rw[q] = *reinterpret_cast<const u32x4 *>(gw[q] + k0 + kBK);
-      }
-    }
+    const uint16_t *sA = lds + cur * kBuffer + (wr * 64 + (lane & 31)) * kLdk, *sW = lds + cur * kBuffer + kTile + (wc * 32 + (lane & 31)) * kLdk;
     // ---- 2 k sub-steps of 16: a lane holds 8 consecutive k of row resp. column lane % 32, k offset 8 * (lane / 32)
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       const int kk = ks * 16 + (lane >> 5) * 8;
-      bf16x8 af[2][3], wf[2][3];
+      bf16x8 af[2][3], wf[3];
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int p = 0; p < 3; ++p) {
+        wf[p] = *reinterpret_cast<const bf16x8 *>(sW + p * kBN * kLdk + kk);
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          af[t][p] = *reinterpret_cast<const bf16x8 *>(&sA[p][wr * 64 + t * 32 + (lane & 31)][kk]);
-          wf[t][p] = *reinterpret_cast<const bf16x8 *>(&sW[p][wc * 64 + t * 32 + (lane & 31)][kk]);
-        }
-      // the six piece products, the small ones first; the four accumulators take turns, so that no matrix instruction
-      // waits for the one before it
+        for (int t = 0; t < 2; ++t) af[t][p] = *reinterpret_cast<const bf16x8 *>(sA + (p * kBM + t * 32) * kLdk + kk);
+      }
+      // the six piece products, the small ones first; the two accumulators take turns
       constexpr int kPieceOfA[6] = {2, 0, 1, 1, 0, 0}, kPieceOfW[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
       for (int p = 0; p < 6; ++p)
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-          for (int ct = 0; ct < 2; ++ct)
-            acc[rt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rt][kPieceOfA[p]], wf[ct][kPieceOfW[p]], acc[rt][ct], 0, 0, 0);
+          acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rt][kPieceOfA[p]], wf[kPieceOfW[p]], acc[rt], 0, 0, 0);
     }
-    __syncthreads();                                     // everyone is done with this step's operands
+    if (k0 + kBK < a.d) {
+      store(lds + (cur ^ 1) * kBuffer);                  // (everyone left that buffer before the last barrier)
+      if (k0 + 2 * kBK < a.d) load(k0 + 2 * kBK);        // travels while the next step multiplies
+    }
+    // orders LDS traffic only: the loads stay in flight
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    cur ^= 1;
   }
 
   // ---- the accumulator of a 32 x 32 tile: element v of a lane is row 8*(v/4) + 4*(lane/32) + v%4, column lane%32
+  const int j = col0 + wc * 32 + (lane & 31);
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) {
-      const int j = col0 + wc * 64 + ct * 32 + (lane & 31);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t b = row0 + wr * 64 + rt * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (b < a.B && j < a.m) a.y[b * a.m + j] = acc[rt][ct][v];
-      }
+    for (int v = 0; v < 16; ++v) {
+      const int64_t b = row0 + wr * 64 + rt * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+      if (b < a.B && j < a.m) a.y[b * a.m + j] = acc[rt][v];
     }
 }
 
@@ -183,7 +193,10 @@ int launch_base_product(const uint16_t *silu_pieces, int64_t Bp, const void *tab
   BaseGemmArgs a;
   a.a_pieces = silu_pieces; a.w_pieces = w_pieces; a.y = y;
   a.B = B; a.Bp = Bp; a.d = d; a.m = m; a.m_pad = p.m_pad;
-  hipLaunchKernelGGL(lutkan_base_gemm_kernel, dim3((unsigned)(p.m_pad / kBN), (unsigned)((B + kBM - 1) / kBM)), dim3(256), 0, s, a);
+  constexpr size_t lds = 2 * 2 * 3 * kBM * kLdk * sizeof(uint16_t);
+  static LdsCap raised;
+  if (int rc = raise_lds_cap(lutkan_base_gemm_kernel, &raised, who)) return rc;
+  hipLaunchKernelGGL(lutkan_base_gemm_kernel, dim3((unsigned)(p.m_pad / kBN * ((B + kBM - 1) / kBM))), dim3(kGemmWaves * 64), lds, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LUTKAN_EHIP, "%s: base-branch product: %s", who, hipGetErrorString(e));
   return LUTKAN_OK;

@@ -148,7 +148,7 @@ inline bool overlap(const float *x, int64_t n_x, const float *y, int64_t n_y) {
   return a < b + (uintptr_t)n_y * 4 && b < a + (uintptr_t)n_x * 4;
 }
 
-int check_launch(const char *what) {
+[[maybe_unused]] int check_launch(const char *what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LUTKAN_EHIP, "%s: %s", what, hipGetErrorString(e));
   return LUTKAN_OK;
