@@ -200,10 +200,32 @@ inline double row_step_us(int code_bytes) { return code_bytes == 4 ? 0.070 : cod
   // a work-group's first slice arrives before it computes anything; the wide form's is twice as long (measured on a
   // 256x256 layer at 512 rows, 8 inputs per work-group: 0.030 -> 0.037 ms on the wide form)
   const double fill = 3.0 + (code_bytes > 1 ? 0.5 * slice_bytes / 21e3 : 0.0);
+  // prices one launch shape and keeps it if it is the cheapest so far, with chunks of at most `longest` inputs
+  auto price = [&](int np, int want, double per_input, int longest) {
+    const int64_t rows = (int64_t)kTileWaves * rps * np;
+    const int64_t groups = (B + rows - 1) / rows * n_tiles;
+    const int chunk = (d + want - 1) / want;
+    const int split = (d + chunk - 1) / chunk;      // no empty trailing chunks
+    if (chunk > longest) return;
+    const double rounds = (double)((groups * split + 255) / 256);
+    double cost = rounds * (fill + chunk * per_input);
+    bool hbm_bound = false;
+    if (streams_from_hbm) {         // ties go to the smaller row tile (fewer padding rows)
+      // within one round of work-groups: once per row tile (measured at a few hundred to a few thousand rows);
+      // over several rounds: once per round, the row tiles of a round walk the inputs together and share what
+      // they read through the caches
+      const double passes = rounds > 1.0 ? rounds : (double)(groups / n_tiles);
+      const double stream = passes * table_bytes / std::min(5.3e6, 21e3 * (double)std::min<int64_t>(256, groups * split));
+      hbm_bound = stream > cost;
+      cost = std::max(cost, stream) + 0.01 * np;
+    }
+    if (split > 1) cost += 4.0 + (double)split * (double)B * m * 4.0 / 3e6;
+    if (cost < best_cost) { best_cost = cost; best = TilePlan{np, split, chunk, cost, hbm_bound, B <= rows && table_bytes > 256.0 * 1024 * 1024}; }
+  };
+  auto per_input_us = [&](int np) { return std::max(0.55 + row_step_us(code_bytes) * np, slice_bytes / 100e3) + 0.1; };
   for (int np = np_max; np >= 1; np >>= 1) {
     const int64_t rows = (int64_t)kTileWaves * rps * np;
     const int64_t groups = (B + rows - 1) / rows * n_tiles;
-    const double per_input = std::max(0.55 + row_step_us(code_bytes) * np, slice_bytes / 100e3) + 0.1;
     // candidate chunk counts: 1 .. 8, then the counts that fill whole rounds of 256 work-groups, and the cap
     int candidates[16];
     int n_candidates = 0;
@@ -215,22 +237,24 @@ inline double row_step_us(int code_bytes) { return code_bytes == 4 ? 0.070 : cod
       const int want = std::min(candidates[q], max_split);
       if (priced[want >> 6] >> (want & 63) & 1) continue;
       priced[want >> 6] |= 1ull << (want & 63);
-      const int chunk = (d + want - 1) / want;
-      const int split = (d + chunk - 1) / chunk;      // no empty trailing chunks
-      const double rounds = (double)((groups * split + 255) / 256);
-      double cost = rounds * (fill + chunk * per_input);
-      bool hbm_bound = false;
-      if (streams_from_hbm) {         // ties go to the smaller row tile (fewer padding rows)
-        // within one round of work-groups: once per row tile (measured at a few hundred to a few thousand rows);
-        // over several rounds: once per round, the row tiles of a round walk the inputs together and share what
-        // they read through the caches
-        const double passes = rounds > 1.0 ? rounds : (double)(groups / n_tiles);
-        const double stream = passes * table_bytes / std::min(5.3e6, 21e3 * (double)std::min<int64_t>(256, groups * split));
-        hbm_bound = stream > cost;
-        cost = std::max(cost, stream) + 0.01 * np;
+      price(np, want, per_input_us(np), d);
+    }
+  }
+  // Where the column tiles do not divide 256, a count that fills a round begins the next one with its last few work-groups: the
+  // largest count that ends inside the round then, if it is priced a twentieth lower and its sums are at most an eighth longer than
+  // those of the shape found so far (a sum's error grows with its length).  Microseconds: 1024 -> 700 at 1000 rows, 24 chunks (264
+  // work-groups) -> 23 (253), 224 -> 162; 900 -> 900 at 600 rows 174 -> 158; 1000 -> 180 at 5000 rows 178 -> 165; not for
+  // fp32 values beyond the caches, whose price is too low (512 -> 600, 212 MB, at 1500 rows 103 -> 106).
+  if (256 % n_tiles != 0 && !(code_bytes == 4 && streams_from_hbm)) {
+    const int longest = best.chunk + best.chunk / 8;
+    best_cost *= 0.95;
+    for (int np = np_max; np >= 1; np >>= 1) {
+      const int64_t rows = (int64_t)kTileWaves * rps * np;
+      const int64_t groups = (B + rows - 1) / rows * n_tiles;
+      for (int rounds = 1; rounds <= 4; ++rounds) {
+        const int64_t want = 256 * rounds / groups;
+        if (want > 8 && want < max_split) price(np, (int)want, per_input_us(np), longest);
       }
-      if (split > 1) cost += 4.0 + (double)split * (double)B * m * 4.0 / 3e6;
-      if (cost < best_cost) { best_cost = cost; best = TilePlan{np, split, chunk, cost, hbm_bound, B <= rows && table_bytes > 256.0 * 1024 * 1024}; }
     }
   }
   return best;

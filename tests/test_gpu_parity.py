@@ -1314,6 +1314,24 @@ def test_bspline_layer_on_the_matrix_cores(case):
     assert np.array_equal(y.cpu().numpy(), y_shifted.cpu().numpy(), equal_nan=True)
 
 
+@pytest.mark.parametrize("case", [(641, 1000, 180, 6, 48, SYM_INT8, 5000), (642, 520, 330, 8, 64, SYM_INT8, 900), (643, 400, 700, 5, 48, ASYM_UINT8, 700)],
+                         ids=lambda c: f"seed{c[0]}")
+def test_chunks_of_column_tiles_that_do_not_divide_the_chip(case):
+    """The chunks of a layer of 3, 6 or 11 column tiles end inside a round of 256 work-groups, not a few work-groups into the next."""
+    import re
+    seed, d, m, G, L, scheme, B = case
+    w = random_layer(seed, d, m, G, L, scheme, CLOSED, CLIP_X, B)
+    s = w.layers[0]
+    art, ora = _compile_both(s)
+    layer = _device_layer(art, s)
+    _say(f"case chunks d={d} m={m} B={B}")
+    y = lk.lutkan_forward(layer, torch.from_numpy(w.x).to(DEV))
+    np_, split = map(int, re.search(r"tiled[^;]* np=(\d+) split=(\d+) ", lk.lutkan_last_plan()).groups())
+    groups = -(-B // (16 * np_ * (64 // (art.info.jt // 4)))) * art.info.n_tiles * split
+    assert groups % 256 == 0 or groups % 256 > 128, (groups, lk.lutkan_last_plan())
+    _assert_close(y.cpu().numpy(), oracle.lut_forward(ora, s.boundary, s.oob, w.x), f"chunks {w.name}")
+
+
 # widths, rows, L, scheme, with stats, what runs: without a workspace (0) or with one (1)
 WITHOUT_WORKSPACE = [((10, 8), 1024, 64, SYM_INT8, False, 0), ((78, 16, 2), 256, 64, ASYM_UINT8, True, 0), ((78, 16, 2), 0, 64, ASYM_UINT8, False, 0),
                      ((256, 256), 16, 64, SYM_INT8, True, 0), ((256, 256), 4000, 64, SYM_INT8, False, 1), ((78, 16), 65536, 64, ASYM_UINT8, True, 0),
