@@ -29,7 +29,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kBM = 128, kBN = 128, kBK = 32, kGemmWaves = 8;
 constexpr int kLdk = kBK + 8;            // bf16 elements per LDS row: 80 bytes, so that the 16 rows of a 16-byte read group fall into different banks
-constexpr int kVecPerStep = 3 * kBM * kBK * 2 / 16;      // 16-byte vectors of one operand per k step: 1536, six per thread
+constexpr int kVecPerStep = 3 * kBM * kBK * 2 / 16;      // 16-byte vectors of one operand per k step: 1536, three per thread
 
 struct BasePiecesArgs {
   const unsigned char *table;        // LUT device table: slice (t, i) starts with the jt floats s_out*s_base of its columns

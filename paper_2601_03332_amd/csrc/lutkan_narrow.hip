@@ -18,8 +18,8 @@
 // then over the blocks, which keeps them nearer to a 64-bit evaluation than the tiled kernel's chunks (78 -> 16 at 65536 rows
 // 1.1e-7 against 1.4e-7; as one running sum it was 2.4e-7).
 //
-// Bound: vector issue.  A block is about 150 instructions for its edges (132 with symmetric codes) and 45 for each input a
-// lane locates, at 6.2 cycles per instruction and SIMD with four waves (the 16-byte code rows of 16 rows collide in the
+// Bound: vector issue and waits.  A block is about 150 instructions for its edges (132 with symmetric codes) and 45 for each input a
+// lane locates (35 on grids of up to five segments; 66 before the segments' reciprocals, 78 -> 16 at 65536 rows 34.6 -> 31.1), at 6.2 cycles per instruction and SIMD with four waves (the 16-byte code rows of 16 rows collide in the
 // LDS banks).  Whole layers, locate + tiled + sum -> this kernel, microseconds: 78 -> 16, uint8 codes, L = 64, at 65536 rows
 // 49 -> 33; 16 -> 2 at 131072 rows 24 -> 11; 64 -> 8 at 131072 rows, L = 32, 51 -> 30, with spline_component 68 -> 42; 1000 -> 4 at
 // 20000 rows 109 -> 73; 100 -> 30 at 65536 rows 81 -> 56; 300 -> 10 at 1000 rows 19 -> 14.
