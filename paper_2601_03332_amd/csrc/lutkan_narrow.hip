@@ -225,15 +225,15 @@ __global__ __launch_bounds__(NW * 64) void lutkan_narrow_kernel(const NarrowArgs
   }
 }
 
-inline size_t narrow_lds_bytes(int stage, int blob_bytes) { return 2 * (size_t)stage * blob_bytes + LUTKAN_MAX_K * 16; }
+inline size_t narrow_lds_bytes(int stage, int blob_bytes, int K) { return 2 * (size_t)stage * blob_bytes + (size_t)K * 16; }
 
 // Inputs per stage: 8 or 4, as two stages fit the LDS; 0: this kernel does not serve the layer.  With the base branch 4: the
 // reads of eight inputs and their base rows together do not fit the registers of 16 waves.
 int narrow_stage(const lutkan_dev_layer *l, bool base) {
   if (l->n_tiles != 1 || l->jt > 32 || l->knots_per_input) return 0;
-  if (!base && narrow_lds_bytes(8, l->blob_bytes) <= (size_t)kMaxTiledLds) return 8;
+  if (!base && narrow_lds_bytes(8, l->blob_bytes, l->K) <= (size_t)kMaxTiledLds) return 8;
   if (!base && l->jt < 16) return 0;                       // (slices of 4 and 8 columns that long are not built for)
-  return narrow_lds_bytes(4, l->blob_bytes) <= (size_t)kMaxTiledLds ? 4 : 0;
+  return narrow_lds_bytes(4, l->blob_bytes, l->K) <= (size_t)kMaxTiledLds ? 4 : 0;
 }
 
 template <int SCHEME, int LPR, int S, int NW>
@@ -242,7 +242,7 @@ int launch_narrow(const NarrowArgs &na, bool base, bool half_params, int n_split
   const int64_t groups = (na.B + kRows - 1) / kRows;
   if (groups > 0x7fffffffLL) return fail(LUTKAN_EUNSUPPORTED, "lutkan_narrow_kernel: B too large for one launch");
   const dim3 grid((unsigned)groups, (unsigned)n_split);
-  const size_t lds = narrow_lds_bytes(S, na.blob_bytes);
+  const size_t lds = narrow_lds_bytes(S, na.blob_bytes, na.K);
 #define LUTKAN_LAUNCH_NARROW(BASE, PH)                                                                                            \
   do {                                                                                                                            \
     static LdsCap raised;                                                                                                         \
@@ -296,7 +296,7 @@ NarrowPlan narrow_plan(const lutkan_dev_layer *l, int64_t B, size_t workspace_by
   for (int waves = 4; waves <= 16; waves += 12) {          // (fewer on a tie: their barriers hold up less; 64 -> 8 at 131072 rows 30 against 33)
     const int64_t groups = (B + (int64_t)waves * (64 / lpr) - 1) / ((int64_t)waves * (64 / lpr));
     for (int stage = widest; stage >= (symmetric && lpr == 8 && waves == 16 ? 4 : widest); stage -= 4) {
-      const int resident = (int)std::min<size_t>(32 / waves, kMaxTiledLds / narrow_lds_bytes(stage, l->blob_bytes));
+      const int resident = (int)std::min<size_t>(32 / waves, kMaxTiledLds / narrow_lds_bytes(stage, l->blob_bytes, l->K));
       for (int want = 1; want <= 64; ++want) {
         const int chunk = (int)round_up((l->d + want - 1) / want, kBlock);
         const int split = (l->d + chunk - 1) / chunk;
