@@ -36,7 +36,7 @@ struct LocateArgs {
   float masked_below, masked_above;      // zero_spline: inputs outside contribute nothing; clip_x: -inf, +inf
   float inner[LUTKAN_MAX_K];             // the inner knots T[1] .. T[K-1], +inf past the last
   float knots[LUTKAN_MAX_K + 1];
-  uint32_t divided_below;      // see divided_below()
+  uint32_t last_divided;       // see last_divided()
   const float *input_knots;    // [d][K+1]: one knot vector per input (then the knots and bounds above are not used)
   int32_t *k_out, *l0_out;     // nullable trace outputs, [B][d]
   uint8_t *in_out;
@@ -1273,7 +1273,7 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   la.masked_above = la.zero_spline ? la.tKs : INFINITY;
   for (int k = 0; k <= l->K; ++k) la.knots[k] = l->knots[k];
   for (int k = 0; k < LUTKAN_MAX_K; ++k) la.inner[k] = (k + 1 < l->K) ? l->knots[k + 1] : INFINITY;
-  la.divided_below = l->knots_per_input ? 0u : divided_below(l->knots, l->K);
+  la.last_divided = l->knots_per_input ? 0u : last_divided(l->knots, l->K);
   la.input_knots = l->knots_per_input ? l->input_knots : nullptr;
   la.k_out = trace ? k_out : nullptr; la.l0_out = l0_out; la.in_out = in_out; la.w_out = w_out;
   if (phases & kLocate) {

@@ -68,13 +68,14 @@ __device__ __forceinline__ void fill_segments(const Args &a, f32x4 *s_seg, int t
   const float tk = a.knots[tid], den = __fsub_rn(a.knots[tid + 1], tk);
   s_seg[tid] = f32x4{tk, den, __fdiv_rn(1.0f, den), 0.0f};
 }
-// The bits below which a numerator is divided instead (0 counts as none: its bits - 1 wrap round); every one if a width is not plain.
-inline unsigned divided_below(const float *knots, int K) {
+// A numerator whose bits - 1 are at most this is divided instead: one below 2^-90 (0, whose bits - 1 wrap round, is not: its quotient
+// by a plain width is 0), or every one, 0 included, if a width is not plain: its reciprocal may be 0 or infinite.
+inline unsigned last_divided(const float *knots, int K) {
   for (int k = 0; k < K; ++k) {
     const float den = knots[k + 1] - knots[k];
     if (!(den >= 0x1p-30f && den <= 0x1p30f)) return 0xffffffffu;
   }
-  return kPlainNumerator - 1;
+  return kPlainNumerator - 2;
 }
 
 // Steps 1-4 of Sec. 4.5 for VEC inputs side by side: the arithmetic of locate_one (same results to the bit) without its
@@ -121,7 +122,7 @@ __device__ __forceinline__ void locate_side_by_side(const Args &a, const f32x4 *
     u[v] = quotient(num[v], den[v], seg.z);                                          // Eq. 15, correctly rounded
     smallest = min(smallest, __float_as_uint(num[v]) - 1u);
   }
-  if (smallest < a.divided_below) {
+  if (smallest <= a.last_divided) {
 #pragma unroll
     for (int v = 0; v < VEC; ++v) u[v] = __fdiv_rn(num[v], den[v]);
   }

@@ -43,7 +43,7 @@ struct NarrowArgs {
   int64_t split_stride;
   float t0, tKs;
   float masked_below, masked_above;      // zero_spline: inputs outside contribute nothing; clip_x: -inf, +inf
-  uint32_t divided_below;                // see divided_below()
+  uint32_t last_divided;                 // see last_divided()
   float inner[LUTKAN_MAX_K];             // the inner knots T[1] .. T[K-1], +inf past the last
   float knots[LUTKAN_MAX_K + 1];
 };
@@ -327,7 +327,7 @@ int narrow_forward(const lutkan_dev_layer *l, const NarrowPlan &plan, const floa
   na.masked_above = (l->oob == LUTKAN_ZERO_SPLINE) ? na.tKs : INFINITY;
   for (int k = 0; k <= l->K; ++k) na.knots[k] = l->knots[k];
   for (int k = 0; k < LUTKAN_MAX_K; ++k) na.inner[k] = (k + 1 < l->K) ? l->knots[k + 1] : INFINITY;
-  na.divided_below = divided_below(l->knots, l->K);
+  na.last_divided = last_divided(l->knots, l->K);
   na.chunk = plan.chunk;
   float *const partials = static_cast<float *>(workspace);
   if (plan.n_split > 1) { na.y = partials; na.split_stride = B * l->m; }

@@ -39,7 +39,7 @@ struct RowsArgs {
   float t0, tKs;
   float masked_below, masked_above;      // zero_spline: inputs outside contribute nothing; clip_x: -inf, +inf
   int32_t zero_spline;
-  uint32_t divided_below;                // see divided_below()
+  uint32_t last_divided;                 // see last_divided()
   float inner[LUTKAN_MAX_K];             // the inner knots T[1] .. T[K-1], +inf past the last
   float knots[LUTKAN_MAX_K + 1];
 };
@@ -229,7 +229,7 @@ int rows_forward(const lutkan_dev_layer *l, const RowsPlan &plan, const float *x
   ra.masked_above = ra.zero_spline ? ra.tKs : INFINITY;
   for (int k = 0; k <= l->K; ++k) ra.knots[k] = l->knots[k];
   for (int k = 0; k < LUTKAN_MAX_K; ++k) ra.inner[k] = (k + 1 < l->K) ? l->knots[k + 1] : INFINITY;
-  ra.divided_below = l->knots_per_input ? 0u : divided_below(l->knots, l->K);
+  ra.last_divided = l->knots_per_input ? 0u : last_divided(l->knots, l->K);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const int rc = (l->scheme == LUTKAN_SYM_INT8) ? launch_rows_width<LUTKAN_SYM_INT8>(ra, l->jt, plan.waves_per_row, s)
                                                 : launch_rows_width<LUTKAN_ASYM_UINT8>(ra, l->jt, plan.waves_per_row, s);

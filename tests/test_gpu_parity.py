@@ -1643,6 +1643,72 @@ def test_narrow_layer_locates_bit_exactly():
         assert torch.equal(torch.where(flushed, expect, y.double()), expect.expand(-1, width))
 
 
+# Shared grids whose segments are not all between 2^-30 and 2^30 wide, and one whose are.
+WIDTH_GRIDS = {
+    "subnormal": np.float32([1.0, 2.0, 3.0, 5.0, 9.0]) * np.float32(1e-39),                       # 1 / width is infinite
+    "below 2^-30": np.float32([-1.0, 0.0, 1.0, 3.0, 7.0]) * np.float32(2.0 ** -40),
+    "above 2^30": np.float32([-5.0, -1.0, 0.0, 2.0, 9.0]) * np.float32(2.0 ** 32),
+    "overflowing": np.float32([-3.0e38, 3.0e38, 3.2e38]),                                         # the first width is infinite
+    "one of each": np.float32([-3.0e38, -1.0, -1.0 + 2.0 ** -24, 0.0, 1e-39, 1.0, 3.0e38]),
+    "2^-30 to 2^30": np.float32([0.0, 2.0 ** -30, 2.0 ** -29, 1.0, 2.0 ** 30]),
+}
+
+
+@pytest.mark.parametrize("grid", WIDTH_GRIDS)
+def test_segments_of_any_width_locate_bit_exactly(grid):
+    """The revealing table (codes q[k][l] = l, alpha_k = 2^k: the output is 2^k (l0 + w)) on narrow and wide segments, in every kernel
+    that locates inputs: at the knots and below the first, where the numerator of Eq. 15 is zero, beside them, between them, and
+    with numerators around 2^-90.  Thousands of rows together hold one knot, so that all elements of a thread do."""
+    knots = WIDTH_GRIDS[grid]
+    K, L, B = knots.size - 1, 16, 70000
+    rng = np.random.Generator(np.random.PCG64(78))
+    k = rng.integers(0, K, size=B)
+    lo, hi = knots[k].astype(np.float64), knots[k + 1].astype(np.float64)
+    x = (lo + rng.uniform(size=B) * (hi - lo)).astype(np.float32)
+    x[:20000] = np.clip(knots[k[:20000]] + np.ldexp(rng.uniform(1.0, 2.0, size=20000), rng.integers(-100, -80, size=20000)).astype(np.float32), knots[0], knots[-1])
+    run = 40000 // (K + 2)
+    for n, v in enumerate([np.float32(-3.3e38)] + list(knots)):
+        x[20000 + n * run:20000 + (n + 1) * run] = v
+    near = np.concatenate([knots, np.nextafter(knots, np.float32(-np.inf)), np.nextafter(knots, np.float32(np.inf))])
+    x[:near.size] = near
+    with np.errstate(over="ignore"):
+        x[~np.isfinite(x - knots[0])] = knots[0]           # (inf / inf: not a number by Eq. 15 itself)
+    x = x.reshape(B, 1)
+    q = np.tile(np.arange(L, dtype=np.uint8), (1, K, 1))
+    scale = (2.0 ** np.arange(K)).astype(np.float32).reshape(1, K)
+    ora = SimpleNamespace(d=1, m=1, K=K, L=L, scheme=ASYM_UINT8, knots=knots, q=q, scale=scale, y_min=np.zeros((1, K), np.float32))
+    ref = oracle.lut_forward(ora, CLOSED, CLIP_X, x, trace=True)
+    z = ref.l0[:, 0].astype(np.float64) + ref.w[:, 0]
+    assert np.isfinite(z).all()
+    xg = torch.from_numpy(x).to(DEV)
+
+    def check(name, y, first=0):
+        assert lk.lutkan_last_plan().startswith(name), lk.lutkan_last_plan()
+        got, of = y.cpu().numpy().astype(np.float64), slice(first, first + y.shape[0])
+        expect = np.ldexp(z[of], ref.k[of, 0])[:, None]
+        # (the running sums carry 2^-24: a z below 2^-126 * 2^24 is subnormal there, flushed or a multiple of 2^-149 * 2^24)
+        wrong = (got != expect) & ~((z[of] < 2.0 ** -102)[:, None] & (np.abs(got) <= expect + np.ldexp(2.0 ** -125, ref.k[of, 0])[:, None]))
+        row = first + int(np.argmax(wrong.any(axis=1)))
+        assert not wrong.any(), f"{name} {y.shape[1]} columns, {grid}: x = {x[row, 0]!r} gives {got[row - first]}, not {expect[row - first]}"
+
+    def layer(m, algo):
+        return lk.lutkan_artifact_from_arrays(1, m, knots, np.tile(q, (m, 1, 1)), np.tile(scale, (m, 1)), np.zeros((m, K), np.float32), CLOSED,
+                                              CLIP_X).to_device(DEV, algo)
+
+    _say(f"case widths {grid}")
+    check("narrow ", lk.lutkan_forward(layer(4, lk.ALGO_AUTO), xg))
+    check("narrow ", lk.lutkan_forward(layer(16, lk.ALGO_AUTO), xg))
+    check("locate; tiled ", lk.lutkan_forward(layer(1, lk.ALGO_TILED), xg))
+    check("locate; gather ", lk.lutkan_forward(layer(1, lk.ALGO_GATHER), xg))
+    several = layer(130, lk.ALGO_AUTO)
+    for first in range(0, B, 1000):
+        check("rows ", lk.lutkan_forward(several, xg[first:first + 1000].contiguous()), first)
+    check("locate; tiled ", lk.lutkan_forward(layer(1, lk.ALGO_TILED), xg[:3000].contiguous()))
+    one = layer(1, lk.ALGO_AUTO)
+    check("chain ", lk.lutkan_chain_forward([one], xg))
+    check("locate; ", lk.lutkan_forward_trace(one, xg)[0])
+
+
 # ---------------------------------------------------------------- a few rows in one launch
 ROWS_CASES = [
     # seed, d, m, G, L, scheme, boundary, oob, B, with_base, fp16, per_input: every tile width; one and several rounds of inputs
