@@ -65,8 +65,9 @@ __global__ __launch_bounds__(256) void lutkan_locate_kernel(const LocateArgs a) 
   constexpr int KSTRIDE = LUTKAN_MAX_K + 1;
   static_assert(KSTRIDE % 2 == 1, "odd stride between the knot rows");
   __shared__ rec_t s_rec[COLS][ROWS + 1];
-  __shared__ float s_knots[PERIN ? COLS * KSTRIDE : KSTRIDE];       // PERIN, or the trace of a shared vector
-  __shared__ f32x4 s_seg[PERIN ? 1 : LUTKAN_MAX_K];
+  constexpr bool SEGMENTS = !PERIN && E > 2;             // eight elements a thread pay for the segments' reciprocals, two do not
+  __shared__ float s_knots[(PERIN ? COLS : 1) * KSTRIDE];
+  __shared__ f32x4 s_seg[SEGMENTS ? LUTKAN_MAX_K : 1];
   rec_t *const rec_out = static_cast<rec_t *>(a.rec);
   const int tid = threadIdx.x;
   const int64_t b0 = (int64_t)blockIdx.x * ROWS;
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(256) void lutkan_locate_kernel(const LocateArgs a) 
     }
   } else {
     if (tid <= a.K) s_knots[tid] = a.knots[tid];
-    fill_segments(a, s_seg, tid);
+    if constexpr (SEGMENTS) fill_segments(a, s_seg, tid);
   }
   const unsigned masked_index = (unsigned)(a.K * a.L) | ((unsigned)a.K << 16);
   const int il = tid % COLS;
@@ -111,7 +112,8 @@ __global__ __launch_bounds__(256) void lutkan_locate_kernel(const LocateArgs a) 
     }
   } else {
     int k[E], l0[E];
-    locate_side_by_side<E>(a, s_seg, xv, k, l0, weight);
+    if constexpr (SEGMENTS) locate_side_by_side<E>(a, s_seg, xv, k, l0, weight);
+    else locate_side_by_side<E>(a, s_knots, xv, k, l0, weight);
 #pragma unroll
     for (int p = 0; p < E; ++p) {
       const bool masked = (xv[p] < a.masked_below) | (xv[p] > a.masked_above);

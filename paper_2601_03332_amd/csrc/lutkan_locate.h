@@ -60,7 +60,7 @@ __device__ __forceinline__ float quotient(float num, float den, float y) {
   return fmaf(fmaf(-q1, den, num), y, q1);
 }
 
-// The rows that locate_side_by_side looks up, in LDS: of segment k its first knot, width (rounded as Eq. 15 rounds it) and the
+// The rows that the second locate_side_by_side looks up, in LDS: of segment k its first knot, width (rounded as Eq. 15 rounds it) and the
 // width's reciprocal.  fill_segments covers segments 0 .. K-1 with the threads of a work-group.
 template <typename Args>
 __device__ __forceinline__ void fill_segments(const Args &a, f32x4 *s_seg, int tid) {
@@ -80,26 +80,25 @@ inline unsigned last_divided(const float *knots, int K) {
 
 // Steps 1-4 of Sec. 4.5 for VEC inputs side by side: the arithmetic of locate_one (same results to the bit) without its
 // branches.  In(x) is t0 <= x <= tKs under either boundary mode.  The knots above x' are counted by the sign of x' - T
-// (exact; +inf past the last knot), shifted into a word: two instructions a knot and no condition register.  Up to five and up to
-// ten segments are searched without a loop, their knots in scalar registers; more in steps of eight.
-template <int VEC, typename Args>
-__device__ __forceinline__ void locate_side_by_side(const Args &a, const f32x4 *s_seg, const float x[VEC], int k[VEC], int l0[VEC], float w[VEC]) {
-  constexpr int kFew = 4, kFirst = 9;
-  float xc[VEC];
+// (exact; +inf past the last knot), shifted into a word: two instructions a knot and no condition register.  Ten segments are
+// searched without a loop, their knots in scalar registers; more in steps of eight.  FEW = 4: grids of up to five segments stop there.
+template <int VEC, int FEW, typename Args>
+__device__ __forceinline__ void clip_and_search(const Args &a, const float x[VEC], float xc[VEC], int k[VEC]) {
+  constexpr int kFirst = 9;
   unsigned above[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) {
     xc[v] = __builtin_amdgcn_fmed3f(x[v], a.t0, a.tKs) + 0.0f;   // (a NaN comes out inside and is put back in w; -0 becomes
     above[v] = 0;                                                  // +0, whose difference from a knot at 0 has no sign bit)
 #pragma unroll
-    for (int q = 0; q < kFew; ++q) above[v] = __builtin_amdgcn_alignbit(above[v], __float_as_uint(xc[v] - a.inner[q]), 31);
-    k[v] = kFew - __popc(above[v]);
+    for (int q = 0; q < FEW; ++q) above[v] = __builtin_amdgcn_alignbit(above[v], __float_as_uint(xc[v] - a.inner[q]), 31);
+    k[v] = FEW - __popc(above[v]);
   }
-  if (a.K > kFew + 1) {                                  // uniform
+  if (FEW == kFirst || a.K > FEW + 1) {                  // uniform
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
 #pragma unroll
-      for (int q = kFew; q < kFirst; ++q) above[v] = __builtin_amdgcn_alignbit(above[v], __float_as_uint(xc[v] - a.inner[q]), 31);
+      for (int q = FEW; q < kFirst; ++q) above[v] = __builtin_amdgcn_alignbit(above[v], __float_as_uint(xc[v] - a.inner[q]), 31);
       k[v] = kFirst - __popc(above[v]);
     }
 #pragma unroll 1
@@ -112,20 +111,10 @@ __device__ __forceinline__ void locate_side_by_side(const Args &a, const f32x4 *
       }
     }
   }
-  float num[VEC], den[VEC], u[VEC];
-  unsigned smallest = 0xffffffffu;
-#pragma unroll
-  for (int v = 0; v < VEC; ++v) {
-    const f32x4 seg = s_seg[k[v]];
-    num[v] = __fsub_rn(xc[v], seg.x);
-    den[v] = seg.y;
-    u[v] = quotient(num[v], den[v], seg.z);                                          // Eq. 15, correctly rounded
-    smallest = min(smallest, __float_as_uint(num[v]) - 1u);
-  }
-  if (smallest <= a.last_divided) {
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) u[v] = __fdiv_rn(num[v], den[v]);
-  }
+}
+
+template <int VEC, typename Args>
+__device__ __forceinline__ void round_down(const Args &a, const float x[VEC], const float u[VEC], int l0[VEC], float w[VEC]) {
 #pragma unroll
   for (int v = 0; v < VEC; ++v) {
     const float z = __fmul_rn(u[v], (float)(a.L - 1));                                 // Eq. 16; 0 <= u <= 1
@@ -133,6 +122,44 @@ __device__ __forceinline__ void locate_side_by_side(const Args &a, const f32x4 *
     l0[v] = (int)below;
     w[v] = (x[v] != x[v]) ? __builtin_nanf("") : __fsub_rn(z, below);
   }
+}
+
+// Eq. 15 divided, from the knots in LDS: for threads that locate one or two elements.  The segments' rows below cost a work-group a
+// division ahead of its first barrier, and FEW = 4 one more wait for the knots, which so few elements do not pay for: launches
+// replayed, with them -> so, microseconds: 11 -> 880 at 422 rows 17.12 -> 16.70, 9 -> 66 -> 249 at 805 25.9 -> 25.5, 10 -> 93 at 1104
+// 10.02 -> 9.84, 24 -> 243 at 2620 18.6 -> 18.4.
+template <int VEC, typename Args>
+__device__ __forceinline__ void locate_side_by_side(const Args &a, const float *s_knots, const float x[VEC], int k[VEC], int l0[VEC], float w[VEC]) {
+  float xc[VEC], u[VEC];
+  clip_and_search<VEC, 9>(a, x, xc, k);
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) {
+    const float tk = s_knots[k[v]], tk1 = s_knots[k[v] + 1];
+    u[v] = __fdiv_rn(__fsub_rn(xc[v], tk), __fsub_rn(tk1, tk));                        // correctly rounded
+  }
+  round_down<VEC>(a, x, u, l0, w);
+}
+
+// Eq. 15 by the segments' reciprocals: for threads that locate eight elements, or input after input (78 -> 16 at 65536 rows 34.6 ->
+// 31.1; a chain of three locate passes at 131072 rows 595 -> 592).
+template <int VEC, typename Args>
+__device__ __forceinline__ void locate_side_by_side(const Args &a, const f32x4 *s_seg, const float x[VEC], int k[VEC], int l0[VEC], float w[VEC]) {
+  float xc[VEC], num[VEC], den[VEC], u[VEC];
+  clip_and_search<VEC, 4>(a, x, xc, k);
+  unsigned smallest = 0xffffffffu;
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) {
+    const f32x4 seg = s_seg[k[v]];
+    num[v] = __fsub_rn(xc[v], seg.x);
+    den[v] = seg.y;
+    u[v] = quotient(num[v], den[v], seg.z);                                            // correctly rounded
+    smallest = min(smallest, __float_as_uint(num[v]) - 1u);
+  }
+  if (smallest <= a.last_divided) {
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) u[v] = __fdiv_rn(num[v], den[v]);
+  }
+  round_down<VEC>(a, x, u, l0, w);
 }
 
 // Eq. 17 on the four codes of a lane (one dword of table row l0, one of row l0+1) as t = (q0 + w * (q1 - q0)) * 2^-24: a byte

@@ -39,7 +39,6 @@ struct RowsArgs {
   float t0, tKs;
   float masked_below, masked_above;      // zero_spline: inputs outside contribute nothing; clip_x: -inf, +inf
   int32_t zero_spline;
-  uint32_t last_divided;                 // see last_divided()
   float inner[LUTKAN_MAX_K];             // the inner knots T[1] .. T[K-1], +inf past the last
   float knots[LUTKAN_MAX_K + 1];
 };
@@ -56,16 +55,16 @@ __global__ __launch_bounds__(kRowsWaves * 64) void lutkan_rows_kernel(const Rows
   const int t = blockIdx.x % a.n_tiles;
   const int64_t row = (int64_t)(blockIdx.x / a.n_tiles) * ROWS + rrow;
   const float *xrow = a.x + min(row, a.B - 1) * a.d;                      // (a row past the last repeats it and is not stored)
-  // LDS: sums of the waves [16][JT], records [ROWS][d], segments
+  // LDS: sums of the waves [16][JT], records [ROWS][d], knots
   f32x4 (*const s_part)[LPR] = reinterpret_cast<f32x4 (*)[LPR]>(lds);
   u32x4 *const s_rec_all = reinterpret_cast<u32x4 *>(lds + kRowsWaves * JT * 4);
   u32x4 *const s_rec = s_rec_all + (size_t)rrow * a.d;
-  f32x4 *const s_seg = reinterpret_cast<f32x4 *>(s_rec_all + (size_t)ROWS * a.d);
+  float *const s_knots = reinterpret_cast<float *>(s_rec_all + (size_t)ROWS * a.d);
   const int plane = JT * (a.param_fp16 ? 2 : 4);
   const int param_row = plane * (SCHEME == LUTKAN_ASYM_UINT8 ? 2 : 1);
 
-  float x0 = xrow[min(rtid, a.d - 1)];                                    // in flight while the segments are placed
-  if (!a.input_knots) fill_segments(a, s_seg, tid);
+  float x0 = xrow[min(rtid, a.d - 1)];                                    // in flight while the knots are placed
+  if (tid <= a.K) s_knots[tid] = a.knots[tid];
   __syncthreads();
   for (int i = rtid; i < a.d; i += WPR * 64) {
     const float x = (i == rtid) ? x0 : xrow[i];
@@ -82,7 +81,7 @@ __global__ __launch_bounds__(kRowsWaves * 64) void lutkan_rows_kernel(const Rows
       int k[1], l0[1];
       const float xs[1] = {x};
       float ws[1];
-      locate_side_by_side<1>(a, s_seg, xs, k, l0, ws);
+      locate_side_by_side<1>(a, s_knots, xs, k, l0, ws);
       masked = (x < a.masked_below) | (x > a.masked_above);
       row_at = (unsigned)(k[0] * a.L + l0[0]);
       segment = (unsigned)k[0];
@@ -165,7 +164,7 @@ int launch_rows(const RowsArgs &ra, int wpr, hipStream_t s) {
   const int rows = kRowsWaves / wpr;
   const int64_t groups = (ra.B + rows - 1) / rows * ra.n_tiles;
   if (groups > 0x7fffffffLL) return fail(LUTKAN_EUNSUPPORTED, "lutkan_rows_kernel: B * m too large for one launch");
-  const size_t lds = (size_t)kRowsWaves * 16 * LPR + (size_t)rows * ra.d * 16 + LUTKAN_MAX_K * 16;
+  const size_t lds = (size_t)kRowsWaves * 16 * LPR + (size_t)rows * ra.d * 16 + (LUTKAN_MAX_K + 1) * 4;
   if (wpr == 16) {
     static LdsCap raised;
     if (int rc = raise_lds_cap(lutkan_rows_kernel<SCHEME, LPR, 16>, &raised, "lutkan_rows_kernel")) return rc;
@@ -229,7 +228,6 @@ int rows_forward(const lutkan_dev_layer *l, const RowsPlan &plan, const float *x
   ra.masked_above = ra.zero_spline ? ra.tKs : INFINITY;
   for (int k = 0; k <= l->K; ++k) ra.knots[k] = l->knots[k];
   for (int k = 0; k < LUTKAN_MAX_K; ++k) ra.inner[k] = (k + 1 < l->K) ? l->knots[k + 1] : INFINITY;
-  ra.last_divided = l->knots_per_input ? 0u : last_divided(l->knots, l->K);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const int rc = (l->scheme == LUTKAN_SYM_INT8) ? launch_rows_width<LUTKAN_SYM_INT8>(ra, l->jt, plan.waves_per_row, s)
                                                 : launch_rows_width<LUTKAN_ASYM_UINT8>(ra, l->jt, plan.waves_per_row, s);
