@@ -242,10 +242,11 @@ inline double row_step_us(int code_bytes) { return code_bytes == 4 ? 0.070 : cod
   }
   // Where the column tiles do not divide 256, a count that fills a round begins the next one with its last few work-groups: the
   // largest count that ends inside the round then, if it is priced an eighth lower (the model is no better than that:
-  // 141 -> 161 at 3867 rows, priced 5 % lower, took 2 us more) and its sums are at most an eighth longer than
+  // 141 -> 161 at 3867 rows, priced 5 - 7 % lower, took 2 us more) and its sums are at most an eighth longer than
   // those of the shape found so far (a sum's error grows with its length).  Microseconds: 1024 -> 700 at 1000 rows, 24 chunks (264
   // work-groups) -> 23 (253), 224 -> 162; 900 -> 900 at 600 rows 174 -> 158; 1000 -> 180 at 5000 rows 178 -> 165; not for
-  // fp32 values beyond the caches, whose price is too low (512 -> 600, 212 MB, at 1500 rows 103 -> 106).
+  // fp32 values beyond the caches, whose price is too low (512 -> 600, 212 MB, at 1500 rows 103 -> 106).  Row tiles can leave the same
+  // few work-groups where the column tiles divide 256 (4 column tiles of 3 row tiles, 22 chunks: 264): not measured, and left as it is.
   if (256 % n_tiles != 0 && !(code_bytes == 4 && streams_from_hbm)) {
     const int longest = best.chunk + best.chunk / 8;
     best_cost *= 0.875;
