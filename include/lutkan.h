@@ -72,7 +72,7 @@ const char *lutkan_version(void);
  * one launch locates, gathers and sums, "rows wpr=16; " (a few rows; waves per row) or "narrow split=1 waves=16; " (a layer of at
  * most 32 columns; chunks of inputs, waves per work-group) or, for a large spline_component layer, "locate; base_product; tiled
  * np=16 split=1 pipe=3; " (base_product cuts the base rows into pieces in a launch of its own) or, for a B-spline layer on the
- * matrix cores, "bspline_matrix np=1 split=2 slots=8; sum; " (slots: up to 8 or up to 16 coefficient rows per input; model_forward: the clauses of all its layers).  Thread-local, overwritten by the next forward call, never null. */
+ * matrix cores, "bspline_matrix np=1 split=2 slots=8; sum; " (slots: up to 8, 12 or 16 coefficient rows per input; model_forward: the clauses of all its layers).  Thread-local, overwritten by the next forward call, never null. */
 const char *lutkan_last_plan(void);
 
 /* ------------------------------------------------------------------------------------------------

@@ -488,7 +488,7 @@ int bspline_matrix_forward(const bspline_dev_layer *l, const float *x, int64_t B
   const int rc = grp == 2 ? launch_matrix_groups<2>(ma, mp.rt, nt, mp.n_split, s) : grp == 3 ? launch_matrix_groups<3>(ma, mp.rt, nt, mp.n_split, s)
                                                                                 : launch_matrix_groups<4>(ma, mp.rt, nt, mp.n_split, s);
   if (rc) return rc;
-  plan_note("bspline_matrix np=%d split=%d slots=%d; ", mp.rt, mp.n_split, ma.R <= 8 ? 8 : 16);
+  plan_note("bspline_matrix np=%d split=%d slots=%d; ", mp.rt, mp.n_split, 4 * grp);
   if (mp.n_split == 1) return LUTKAN_OK;
   const int64_t n = B * l->m;
   hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s, partials, y, n, mp.n_split, 0);
