@@ -64,7 +64,7 @@ __global__ __launch_bounds__(kRowsWaves * 64) void lutkan_rows_kernel(const Rows
   const int param_row = plane * (SCHEME == LUTKAN_ASYM_UINT8 ? 2 : 1);
 
   float x0 = xrow[min(rtid, a.d - 1)];                                    // in flight while the knots are placed
-  if (tid <= a.K) s_knots[tid] = a.knots[tid];
+  if (!a.input_knots && tid <= a.K) s_knots[tid] = a.knots[tid];
   __syncthreads();
   for (int i = rtid; i < a.d; i += WPR * 64) {
     const float x = (i == rtid) ? x0 : xrow[i];
