@@ -11,8 +11,8 @@
 // together (lutkan_pieces.h).  The products
 // of the two high pieces have an accumulator of their own, apart from the five small ones: with one accumulator for all
 // six, every small product rounds the large sum once more and the layer came out 1.2 - 1.8 times further from a 64-bit
-// evaluation than the tiled kernel; apart, it is nearer than that kernel (64 -> 128 at 131072 rows 1.5e-7 against 3.0e-7,
-// 1024 -> 1024 at 4096 rows, G = 10, 4.8e-7 against 5.7e-7).
+// evaluation than the tiled kernel; apart, it is nearer than that kernel (64 -> 128 at 131072 rows 1.1e-7 against 3.0e-7,
+// 1024 -> 1024 at 4096 rows, G = 10, 4.0e-7 against 5.7e-7).
 //
 // Operand A, sparse and without LDS: v_smfmac_f32_32x32x32_bf16 takes operand A with two stored values of every four
 // consecutive k (a group) and two bits each for where they stand, and does twice the dense instruction's k in the same time (55.8

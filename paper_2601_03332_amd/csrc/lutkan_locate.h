@@ -126,8 +126,8 @@ __device__ __forceinline__ void round_down(const Args &a, const float x[VEC], co
 
 // Eq. 15 divided, from the knots in LDS: for threads that locate one or two elements.  The segments' rows below cost a work-group a
 // division ahead of its first barrier, and FEW = 4 one more wait for the knots, which so few elements do not pay for: launches
-// replayed, with them -> so, microseconds: 11 -> 880 at 422 rows 17.12 -> 16.70, 9 -> 66 -> 249 at 805 25.9 -> 25.5, 10 -> 93 at 1104
-// 10.02 -> 9.84, 24 -> 243 at 2620 18.6 -> 18.4.
+// replayed, with them -> so, microseconds: 11 -> 880 at 422 rows 17.12 -> 16.92, 9 -> 66 -> 249 at 805 25.9 -> 25.5, 10 -> 93 at 1104
+// 10.03 -> 9.88, 24 -> 243 at 2620 18.6 -> 18.4.
 template <int VEC, typename Args>
 __device__ __forceinline__ void locate_side_by_side(const Args &a, const float *s_knots, const float x[VEC], int k[VEC], int l0[VEC], float w[VEC]) {
   float xc[VEC], u[VEC];
