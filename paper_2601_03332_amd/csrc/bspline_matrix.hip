@@ -179,25 +179,55 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
 
   // This thread's coefficient columns of a stage.  Unit u = (h * STEPS + step) * 2 + p: the groups 4 step + 2p and the next one
   // of the lanes of half h, whose groups are those of its inputs one after the other.
+  // Where they lie from the stage's first slice on, in floats, is the same for every stage and (from 64 columns on) for a wave:
+  // computed once, in scalar registers.  With the addresses computed at every load a wave spent 190 scalar instructions a stage on
+  // them: 1024 -> 1024 at 4096 rows, G = 10, 432 -> 409 us, 128 -> 128 at 131072, G = 5 / 8, 126 -> 123 / 176 -> 170 (buffer
+  // loads with the offsets as their scalar operands: 417, 124, 168).
   const float *tile = a.coef_table + (size_t)t * a.d * a.R * a.jt;
   float cf[UPT][8];
   float largest = 0.0f;                                    // of the magnitudes this thread staged; NaN if one was
+  auto unit_of = [&](int q) {                              // (with 32 columns a wave has two; past the last one, where not stored)
+    const int id = tid + q * kThreads;
+    return min((BN >= 64) ? __builtin_amdgcn_readfirstlane(id / BN) : id / BN, kUnits - 1);
+  };
+  auto row_of = [&](int u, int e, int &of) {               // the first coefficient row of a unit's group e, and the input of the stage
+    const int h = u / (2 * STEPS), group = 4 * ((u >> 1) - h * STEPS) + 2 * (u & 1) + e;
+    of = h * IPL + group / GRP;
+    return group % GRP;
+  };
+  int offset[UPT][8];
+#pragma unroll
+  for (int q = 0; q < UPT; ++q)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      int of;
+      const int g = row_of(unit_of(q), e, of);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)                          // slots past the last coefficient row: no value goes there, any row will do
+        offset[q][4 * e + r] = (of * a.R + min(g + GRP * r, a.R - 1)) * a.jt;
+    }
   auto load_coefs = [&](int i0) {
+    if (BN >= 64 && i0 + IS <= a.d) {
+      const float *stage = tile + (size_t)i0 * a.R * a.jt;
+#pragma unroll
+      for (int q = 0; q < UPT; ++q) {
+        const unsigned c = (unsigned)((tid + q * kThreads) % BN) & (unsigned)(a.jt - 1);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) cf[q][r] = (stage + offset[q][r])[c];
+      }
+      return;
+    }
 #pragma unroll
     for (int q = 0; q < UPT; ++q) {
-      const int id = tid + q * kThreads;
-      const int c = (id % BN) & (a.jt - 1);                // a column past the tile: a valid address, not stored
-      // the unit of a wave's 64 threads (with 32 columns two neighbouring ones; past the last one, where not stored)
-      const int u = min((BN >= 64) ? __builtin_amdgcn_readfirstlane(id / BN) : id / BN, kUnits - 1);
-      const int h = u / (2 * STEPS), group = 4 * ((u >> 1) - h * STEPS) + 2 * (u & 1);
+      const int c = ((tid + q * kThreads) % BN) & (a.jt - 1);      // a column past the tile: a valid address, not stored
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        const int of = (group + e) / GRP, g = (group + e) - of * GRP;
-        const int i = min(i0 + h * IPL + of, a.d - 1);     // past the last input: its basis is zero
+        int of;
+        const int g = row_of(unit_of(q), e, of);
+        const int i = min(i0 + of, a.d - 1);               // past the last input: its basis is zero
         const float *src = tile + (size_t)i * a.R * a.jt + c;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)                        // slots past the last coefficient row: no value goes there, any row will do
-          cf[q][4 * e + r] = src[min(g + GRP * r, a.R - 1) * a.jt];
+        for (int r = 0; r < 4; ++r) cf[q][4 * e + r] = src[min(g + GRP * r, a.R - 1) * a.jt];
       }
     }
   };
