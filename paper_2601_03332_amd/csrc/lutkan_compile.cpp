@@ -55,6 +55,15 @@ int choose_jt(int m, int K, int L, int scheme, int value_repr, int param_dtype) 
   return jt < 32 ? jt : 32;   // no width fits: the gather kernel, which is fastest on 32-column tiles
 }
 
+// bspline_dev_layer's coef_range: 2^e is the power of two above the largest coefficient.  Exponents so far out that the products' scale
+// would leave fp32's normal range are not recorded.
+static int32_t coef_range(float largest, float smallest_edge) {
+  int e;
+  (void)std::frexp(largest, &e);
+  const bool even = std::isfinite(largest) && largest > 0.0f && smallest_edge >= std::ldexp(1.0f, e - 16);
+  return (even && e >= -60 && e <= 60) ? LUTKAN_COEF_RANGE_BIAS + e : 0;
+}
+
 int choose_coef_jt(int m) {
   int jt = 4;
   while (jt < m && jt < 128) jt *= 2;
@@ -321,10 +330,13 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
   nt = std::max(1, std::min(nt, 64));
   nt = (int)std::min<size_t>((size_t)nt, (size_t)d);
   std::atomic<long> unrepresentable{0};       // float16 parameters that overflowed
+  float largest_coef[64] = {}, smallest_edge[64];      // per thread: the largest magnitude, the least of the edges' own largest (zero edges aside)
+  std::fill(smallest_edge, smallest_edge + 64, INFINITY);
   const SlicePacker packer{lay, jt, L, scheme, device_params_are_half(repr, half_params ? LUTKAN_PARAM_FP16 : LUTKAN_PARAM_FP32, jt)};
   auto work = [&](int tid) {
     std::vector<float> v((size_t)L);
     std::vector<double> own_basis;
+    float layer_largest = 0.0f, least_edge = INFINITY;
     for (int i = tid; i < d; i += nt) {
       if (per_input) basis_table(i, own_basis);
       const std::vector<double> &basis = per_input ? own_basis : shared_basis;
@@ -345,7 +357,14 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
           cslice[cj] = base_gain;
           cslice += cjt;
         }
-        for (int r = 0; r < R; ++r) cslice[(size_t)r * cjt + cj] = with_base ? spline_gain * c[r] : c[r];
+        float largest = 0.0f;
+        for (int r = 0; r < R; ++r) {
+          const float held = with_base ? spline_gain * c[r] : c[r];
+          cslice[(size_t)r * cjt + cj] = held;
+          largest = std::max(largest, std::fabs(held));
+        }
+        layer_largest = std::max(layer_largest, largest);
+        if (largest > 0.0f) least_edge = std::min(least_edge, largest);
         for (int k = 0; k < K; ++k) {
           const int r0 = first_knot + k - P;               // coefficient of the span's first basis function
           auto coefficient = [&](int r) { return (r >= 0 && r < R) ? (double)c[r] : 0.0; };
@@ -375,6 +394,8 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
         }
       }
     }
+    largest_coef[tid] = layer_largest;
+    smallest_edge[tid] = least_edge;
   };
   if (nt == 1) {
     work(0);
@@ -390,6 +411,7 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
     return fail(LUTKAN_EUNSUPPORTED, "lutkan_compile: %ld segments have an alpha or y_min too large for float16", n);
   }
 
+  a->coef_range = coef_range(*std::max_element(largest_coef, largest_coef + nt), *std::min_element(smallest_edge, smallest_edge + nt));
   fill_info(a, d, m, K, L, G, scheme, desc->boundary, desc->oob, repr, desc->param_dtype, desc->knots_per_input, jt, n_tiles, lay, cjt, coef_blob);
   a->info.knot_span = desc->knot_span;
   *out = a;
@@ -523,6 +545,7 @@ extern "C" int bspline_dev_layer_init(const lutkan_artifact *a, bspline_dev_laye
   out->algo = LUTKAN_ALGO_AUTO;
   for (int r = 0; r < I.G + 2 * P + 1; ++r) out->ext_knots[r] = a->ext_knots[r];
   out->coef_table = nullptr;
+  out->coef_range = a->coef_range;
   out->knots_per_input = I.knots_per_input;
   out->input_ext_knots = nullptr;
   return LUTKAN_OK;

@@ -1385,6 +1385,58 @@ def test_forward_without_a_workspace(case):
     assert lk.lutkan_last_plan() == plan and torch.equal(y0, y2) and (stats[0] is None or torch.equal(stats[0], stats[2]))
 
 
+HALF_PIECE_CASES = [
+    # seed, d, m, G, boundary, oob, B: at least 120, 96, 80 inputs per work-group; 2, 3, 4 groups of slots; 128, 64 and 32 columns; inputs that end inside a stage
+    (951, 121, 129, 5, CLOSED, CLIP_X, 32513),
+    (952, 120, 64, 1, HALF_OPEN, ZERO_SPLINE, 66000),
+    (953, 123, 20, 4, CLOSED, ZERO_SPLINE, 120001),
+    (954, 97, 200, 6, HALF_OPEN, CLIP_X, 20001),
+    (955, 98, 40, 9, CLOSED, ZERO_SPLINE, 60001),
+    (956, 130, 30, 8, CLOSED, CLIP_X, 60000),
+    (957, 81, 128, 13, HALF_OPEN, ZERO_SPLINE, 65001),
+    (958, 84, 60, 10, CLOSED, CLIP_X, 65000),
+    (959, 83, 9, 11, HALF_OPEN, CLIP_X, 120000),
+]
+
+
+@pytest.mark.parametrize("case", HALF_PIECE_CASES, ids=lambda c: f"seed{c[0]}")
+def test_bspline_layer_on_two_binary16_pieces(case):
+    """Against the oracle in 300 rows, the ends of the batch and rows with a NaN and infinities among them, and no further from the
+    oracle's 64 bits than the three bf16 pieces, which the same layer without its recorded magnitudes runs on.  Then
+    tables that their owner scales by powers of two: within the pieces' range the outputs scale with them but for the smallest
+    coefficients' last bits (2^-36 of a coefficient that is up to 2^3 here); beyond it, and far below it, the outputs are summed
+    term by term and agree to the rounding of such a sum (2^-24 for each of its d steps at most)."""
+    seed, d, m, G, boundary, oob, B = case
+    w = random_layer(seed, d, m, G, 2, SYM_INT8, boundary, oob, B, uniform=True)
+    s, x = w.layers[0], w.x
+    x[3, d // 2] = np.nan
+    x[5, :] = np.inf
+    x[B - 1, 0] = -np.inf
+    art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.L, s.scheme, s.boundary, s.oob)
+    layer, other = art.bspline_to_device(DEV), art.bspline_to_device(DEV)
+    assert layer.c.coef_range != 0
+    other.c.coef_range = 0
+    xg = torch.from_numpy(x).to(DEV)
+    _say(f"case two pieces d={d} m={m} G={G} boundary={boundary} oob={oob} B={B}")
+    y, y_bf16 = lk.bspline_kan_forward(layer, xg), lk.bspline_kan_forward(other, xg)
+    torch.cuda.synchronize()
+    assert not torch.equal(y[6:B - 1], y_bf16[6:B - 1]), lk.lutkan_last_plan()
+    rng = np.random.Generator(np.random.PCG64(seed))
+    rows = np.unique(np.concatenate([np.arange(40), np.arange(B - 40, B), rng.integers(0, B, 300)]))
+    ref = oracle.bspline_forward(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.boundary, s.oob, x[rows])
+    _assert_close(y.cpu().numpy()[rows], ref, f"two pieces {w.name}")
+    live = np.isfinite(ref.y)
+    errors = [np.linalg.norm((v.cpu().numpy()[rows].astype(np.float64) - ref.y)[live]) for v in (y, y_bf16)]
+    assert errors[0] <= errors[1], errors
+    clean, held = y.cpu().numpy().astype(np.float64), layer.coef_table.clone()
+    live = np.isfinite(clean)
+    for exponent, steps in ((3, 1), (-9, 1), (20, d), (-30, d)):
+        layer.coef_table.copy_(held * 2.0 ** exponent)
+        scaled = lk.bspline_kan_forward(layer, xg).cpu().numpy().astype(np.float64) * 2.0 ** -exponent
+        assert np.array_equal(np.isfinite(scaled), live)
+        assert np.linalg.norm((scaled - clean)[live]) <= steps * 2.0 ** -24 * np.linalg.norm(clean[live]), exponent
+
+
 @pytest.mark.parametrize("G", [1, 5, 6, 9, 10, 13])
 def test_every_input_of_a_stage_meets_its_own_coefficients(G):
     """The grids at either end of two, three and four groups of slots per input; inputs short of, filling and past a stage of the
