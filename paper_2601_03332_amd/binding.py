@@ -1,4 +1,5 @@
-"""ctypes binding of include/lutkan.h.  Same entry-point names as the C ABI; argument marshalling only."""
+"""ctypes binding of include/lutkan.h.  Same entry-point names as the C ABI; argument marshalling only.  The forward calls without
+optional arguments go through the same steps in native code (csrc/lutkan_call.cpp)."""
 from __future__ import annotations
 
 import ctypes as C
@@ -138,6 +139,29 @@ def load_library():
     lib.lutkan_error_stats.argtypes = [vp, vp, i64, i32, vp, i32, C.c_float, C.c_float, vp, i32, vp, vp, sz, vp]
     _lib = lib
     return lib
+
+
+_native = None
+
+
+def _native_calls():
+    """The module of native forward calls, built first only when it does not exist.  Its functions return None for a call that takes
+    the general path."""
+    global _native
+    if _native is None:
+        import importlib.util
+        torch, lib = _torch(), load_library()
+        if not os.path.exists(_build.CALL):
+            _build.build_call()
+        spec = importlib.util.spec_from_file_location("_lutkan_call", _build.CALL)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        entries = (lib.lutkan_forward_or_workspace, lib.lutkan_forward, lib.lutkan_model_forward_or_workspace, lib.lutkan_model_forward,
+                   lib.bspline_forward_workspace_bytes, lib.bspline_kan_forward)
+        module.init(*[C.cast(f, C.c_void_p).value for f in entries], _DevLayer, _SplineDevLayer,
+                    getattr(torch._C, "_cuda_getCurrentRawStream", lambda index: torch.cuda.current_stream(index).cuda_stream))
+        _native = module
+    return _native
 
 
 def lutkan_last_error() -> str:
@@ -507,6 +531,10 @@ def _workspace(nbytes, device, workspace):
 
 def lutkan_forward(layer: LutLayer, x, y=None, stats=None, workspace=None):
     """y[B,m] = LUT layer forward of x[B,d] on the current stream.  stats: optional int64[2] CUDA tensor (added to)."""
+    if y is None and stats is None and workspace is None:
+        out = (_native or _native_calls()).lut_forward(layer, x)
+        if out is not None:
+            return out
     B = _check_io("lutkan_forward", layer, x=x, y=y, workspace=workspace, stats=stats)
     if y is None:
         y = _output(x, B, layer.m)
@@ -591,6 +619,10 @@ def lutkan_forward_trace(layer: LutLayer, x, codes: bool = False, workspace=None
 
 
 def bspline_kan_forward(layer: BsplineLayer, x, y=None, workspace=None):
+    if y is None and workspace is None:
+        out = (_native or _native_calls()).spline_forward(layer, x)
+        if out is not None:
+            return out
     B = _check_io("bspline_kan_forward", layer, x=x, y=y, workspace=workspace)
     if y is None:
         y = _output(x, B, layer.m)
@@ -602,6 +634,10 @@ def bspline_kan_forward(layer: BsplineLayer, x, y=None, workspace=None):
 
 def lutkan_model_forward(layers: List[LutLayer], x, y=None, stats=None, workspace=None):
     """Chained forward: layer l's output is layer l+1's input.  stats: optional int64[n_layers,2] CUDA tensor."""
+    if y is None and stats is None and workspace is None:
+        out = (_native or _native_calls()).lut_model_forward(layers, x)
+        if out is not None:
+            return out
     ends = _check_chain("lutkan_model_forward", layers)
     B = _check_io("lutkan_model_forward", ends, x=x, y=y, workspace=workspace, stats=stats, n_stats=len(layers))
     arr = (_DevLayer * len(layers))(*[l.c for l in layers])

@@ -1,4 +1,5 @@
-"""Builds liblutkan.so (host LUT compiler + gfx950 kernels) in-tree with hipcc."""
+"""Builds liblutkan.so (host LUT compiler + gfx950 kernels) in-tree with hipcc, and beside it the binding's forward calls as a
+CPython module (_lutkan_call.so, host code against torch's headers)."""
 from __future__ import annotations
 
 import os
@@ -9,6 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.environ.get("LUTKAN_LIBRARY", os.path.join(HERE, "liblutkan.so"))
+CALL = os.path.join(HERE, "_lutkan_call.so")
+CALL_SOURCE = os.path.join(CSRC, "lutkan_call.cpp")
 SOURCES = [os.path.join(CSRC, "lutkan_compile.cpp"), os.path.join(CSRC, "lutkan_kernels.hip"),
            os.path.join(CSRC, "bspline_kernels.hip"), os.path.join(CSRC, "lutkan_probes.hip"),
            os.path.join(CSRC, "lutkan_stats.hip"), os.path.join(CSRC, "lutkan_base_gemm.hip"),
@@ -37,6 +40,21 @@ def stale() -> bool:
     return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS)
 
 
+def build_call(verbose: bool = False) -> str:
+    """The CPython module.  torch's libraries are named, not searched for at run time: the binding imports torch before the module."""
+    import importlib.util
+    import sysconfig
+    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include")]
+    for path in (os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]):
+        cmd += ["-isystem", path]
+    cmd += [CALL_SOURCE, "-o", CALL, "-L" + os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALL
+
+
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -52,8 +70,10 @@ def build(verbose: bool = False) -> str:
         return obj
 
     # the translation units are independent: one compiler process each (lutkan_kernels.hip is the long one)
-    with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:
+    with ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, os.cpu_count() or 1, 8)) as pool:
+        call = pool.submit(build_call, verbose)
         objs = list(pool.map(compile_one, SOURCES))
+        call.result()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs + ["-lpthread"]
     if verbose:
         print(" ".join(cmd), flush=True)

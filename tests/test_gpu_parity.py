@@ -1915,3 +1915,55 @@ def test_calls_run_on_torchs_current_stream():
     side.synchronize()
     assert binding._stream(dev) == torch.cuda.current_stream(dev).cuda_stream
     assert torch.equal(y, expect)
+
+
+class _Intercepts(torch.overrides.TorchFunctionMode):
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        return func(*args, **(kwargs or {}))
+
+
+def test_native_calls_take_the_plain_case_and_leave_the_rest_to_the_general_path():
+    """A call without optional arguments in native code: bit for bit the general path's output, with and without a workspace, on the
+    current stream, for one layer, a network and the B-spline layer; None, with nothing done, for whatever is not plain."""
+    from paper_2601_03332_amd import binding
+    native = binding._native_calls()
+    w = random_layer(981, 40, 50, 5, 16, SYM_INT8, CLOSED, CLIP_X, 3000)
+    arts = [_compile_both(s)[0] for s in (w.layers[0], random_layer(982, 50, 7, 6, 16, SYM_INT8, CLOSED, CLIP_X, 1).layers[0])]
+    layers, spline = [a.to_device(DEV) for a in arts], arts[0].bspline_to_device(DEV)
+    x = torch.from_numpy(w.x).to(DEV)
+    side = torch.cuda.Stream()
+    for B in (0, 1, 60, 3000):
+        _say(f"case native calls B={B}")
+        xb = x[:B].clone()
+        side.wait_stream(torch.cuda.current_stream())
+        for call, general, held in ((native.lut_forward, lk.lutkan_forward, layers[0]), (native.lut_model_forward, lk.lutkan_model_forward, layers),
+                                    (native.spline_forward, lk.bspline_kan_forward, spline)):
+            m = held[-1].m if held is layers else held.m
+            expect = general(held, xb, y=torch.full((B, m), 7.0, device=DEV))
+            plan = lk.lutkan_last_plan()
+            assert torch.equal(call(held, xb), expect) and (B == 0 or lk.lutkan_last_plan() == plan)
+            with torch.cuda.stream(side):
+                y = general(held, xb)
+            side.synchronize()
+            assert torch.equal(y, expect) and not y.requires_grad
+            other = held if held is not layers else tuple(held)
+            assert torch.equal(call(other, torch.nn.Parameter(xb)), expect)
+            subclass = xb.as_subclass(type("Sub", (torch.Tensor,), {}))
+            with _Intercepts():
+                assert call(held, xb) is None and torch.equal(general(held, xb), expect)
+            for bad in (subclass, xb[:, 1:], xb.double(), xb.cpu(), xb.t(), xb[None], xb.numel(), None):
+                assert call(held, bad) is None
+            if B > 1:
+                strided = torch.empty(B, 2 * xb.shape[1], device=DEV)[:, ::2]
+                assert call(held, strided) is None
+                with pytest.raises(lk.LutKanError, match="contiguous"):
+                    general(held, strided)
+            with pytest.raises(lk.LutKanError, match="shape"):
+                general(held, xb[:, 1:])
+    assert native.lut_forward(spline, x) is None and native.spline_forward(layers[0], x) is None
+    assert native.lut_model_forward([], x) is None and native.lut_model_forward([layers[1], layers[0]], x) is None
+    broken = layers[0].with_contract(CLOSED, CLIP_X)
+    broken.c.d = 0                                         # the library refuses it: the general path says why
+    assert native.lut_forward(broken, x) is None
+    with pytest.raises(lk.LutKanError, match="lutkan_forward"):
+        lk.lutkan_forward(broken, x)
