@@ -418,8 +418,8 @@ constexpr double kBaseProductMinEdges = 5e8;      // batch * d * m from which th
 // on the stored values.
 //
 // PIPE: how the copies, the barrier and the LDS reads of consecutive inputs overlap.
-//   2  two buffers.  Every input ends in "wait for my copies of the next slice, barrier", and every wave then refills
-//      its read pipeline (record -> addresses -> codes and scales, two LDS round trips) at the same moment, with
+//   2  two buffers.  Every input ends in "wait for my copies of the next slice, read its first records, barrier", and every wave
+//      then refills its read pipeline (addresses -> codes and scales, an LDS round trip) at the same moment, with
 //      nothing else on the SIMD to cover it.
 //   3  three buffers, reads carried across inputs (no BASE, NP >= 2; where three buffers fit the LDS).  The slice of
 //      input i+2 is copied while input i is processed; the one barrier per input (before input i: "everyone has
@@ -567,12 +567,14 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
   };
 
   // The read pipeline: rcq[k] is the record of row step p+k, fq[k] the codes and parameters of row step p+k, for the
-  // current step p.  Carried from one input to the next (PIPE 3), else refilled at the top of every input.
+  // current step p.  Carried from one input to the next (PIPE 3; of PIPE 2 the records), else refilled at the top of every input.
   rec_t rcq[AHEAD + 1];
   Fetched fq[AHEAD];
-  auto fill_read_pipeline = [&](const unsigned char *rec_buf, unsigned col_codes, unsigned col_params) {
+  auto read_records = [&](const unsigned char *rec_buf) {
 #pragma unroll
     for (int k = 0; k <= AHEAD; ++k) rcq[k] = *reinterpret_cast<const rec_t *>(rec_buf + (k < NP ? k : NP - 1) * (RPS * RB));
+  };
+  auto read_codes = [&](unsigned col_codes, unsigned col_params) {
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k) fq[k] = fetch(rcq[k], col_codes, col_params);
   };
@@ -580,7 +582,10 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
   if (CARRY) {
     unsigned cc, cp;
     columns_of(0, cc, cp);
-    fill_read_pipeline(rec_area + hrow * RB, cc, cp);
+    read_records(rec_area + hrow * RB);
+    read_codes(cc, cp);
+  } else if (PIPE == 2) {
+    read_records(rec_area + hrow * RB);
   }
 
   for (int i = i_begin; i < i_end; ++i) {
@@ -615,7 +620,8 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
     if (CARRY) columns_of(ahead, ahead_codes, ahead_params);
     f32x4 base_gain = {0.f, 0.f, 0.f, 0.f};
     if (BASE) base_gain = *reinterpret_cast<const f32x4 *>(slice + sub * 16) * (VALUES ? 1.0f : kTwoToMinus24);   // (the sums on fp32 values are not scaled)
-    if (!CARRY) fill_read_pipeline(rec_buf, col_codes, col_params);
+    if (DEEP) read_records(rec_buf);
+    if (!CARRY) read_codes(col_codes, col_params);
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const Fetched f_cur = fq[0];
@@ -709,8 +715,16 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
       fq[AHEAD - 1] = f_new;
     }
     if (PIPE == 2) {
-      wait_all_vector_loads();                         // my share of the next slice has landed ...
-      lds_barrier();                                   // ... everyone's has, and everyone is done with this one
+      wait_all_vector_loads();                         // my share of the next slice and my records have landed ...
+      // The records of the next input's first row steps, the wave's own copies, are read ahead of the barrier (after the last input
+      // this one's again, unused) and the barrier is the bare instruction: one LDS round trip behind it instead of two.  Every read
+      // of this slice has returned, with the first touch of the last row step.  512 -> 256 on 16-bit codes at 5000 rows 128.2 -> 125.5
+      // us, 300 -> 200 with 16-byte records at 3000 78.3 -> 76.5, 256 -> 256 on 16-bit codes at 16384 169.2 -> 167.2, 1024 -> 1024,
+      // uint8, at 32768 5280 -> 5255.
+      __builtin_amdgcn_sched_barrier(0);
+      read_records(rec_area + (i + 1 < i_end ? nxt : cur) * (RW * RB) + hrow * RB);
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_barrier" ::: "memory");          // ... everyone's share has, and everyone is done with this slice
     }
     cur = nxt;
   }
