@@ -453,6 +453,10 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
   // not: the waves of the binary16 form spent 13 % of their cycles waiting for LDS reads, so they read two steps ahead.
   constexpr int AHEAD = (CB > 1) ? 2 : 1;
   static_assert(!CARRY || NP > AHEAD, "carried reads: the pipeline must fit into one input's row steps");
+  // Records are read one row step ahead of the reads they address, three where the byte form carries its reads from input to input:
+  // a step waits for its record, and everything older, at its start.  1024 -> 1024 at 32768 / 4096 rows, int8, 4765 / 629 -> 4713 / 622
+  // us (four ahead 4732 / 624; in PIPE 2 uint8 at 32768 rows 5240 -> 5353; the wide forms: nothing, 16-bit codes 1 % slower).
+  constexpr int LEAD = (CARRY && CB == 1 && NP > AHEAD + 2) ? 2 : 0, RECS = AHEAD + LEAD;
   extern __shared__ __align__(16) unsigned char lds[];
   constexpr int JT = 4 * LPR;
   constexpr int RPS = 64 / LPR;
@@ -568,11 +572,11 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
 
   // The read pipeline: rcq[k] is the record of row step p+k, fq[k] the codes and parameters of row step p+k, for the
   // current step p.  Carried from one input to the next (PIPE 3; of PIPE 2 the records), else refilled at the top of every input.
-  rec_t rcq[AHEAD + 1];
+  rec_t rcq[RECS + 1];
   Fetched fq[AHEAD];
   auto read_records = [&](const unsigned char *rec_buf) {
 #pragma unroll
-    for (int k = 0; k <= AHEAD; ++k) rcq[k] = *reinterpret_cast<const rec_t *>(rec_buf + (k < NP ? k : NP - 1) * (RPS * RB));
+    for (int k = 0; k <= RECS; ++k) rcq[k] = *reinterpret_cast<const rec_t *>(rec_buf + (k < NP ? k : NP - 1) * (RPS * RB));
   };
   auto read_codes = [&](unsigned col_codes, unsigned col_params) {
 #pragma unroll
@@ -627,15 +631,15 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
       const Fetched f_cur = fq[0];
       const rec_t rc_cur = rcq[0];
       Fetched f_new = fq[AHEAD - 1];
-      rec_t rc_new = rcq[AHEAD];
+      rec_t rc_new = rcq[RECS];
       // first touch of step p's data, and of the record whose addresses are computed next (everything older has
       // arrived then: LDS reads return in order)
       if (SCHEME == LUTKAN_ASYM_UINT8 || VALUES) asm volatile("" ::"v"(f_cur.pb.x));
       if (VALUES) asm volatile("" ::"v"(f_cur.pa.x), "v"(rcq[AHEAD].y));
       else asm volatile("" ::"v"(f_cur.pa.x), "v"(f_cur.c1), "v"(rcq[AHEAD].y));
       __builtin_amdgcn_sched_barrier(0);
-      if (p + AHEAD + 1 < NP) rc_new = *reinterpret_cast<const rec_t *>(rec_buf + (p + AHEAD + 1) * (RPS * RB));
-      else if (CARRY) rc_new = *reinterpret_cast<const rec_t *>(rec_ahead + (p + AHEAD + 1 - NP) * (RPS * RB));
+      if (p + RECS + 1 < NP) rc_new = *reinterpret_cast<const rec_t *>(rec_buf + (p + RECS + 1) * (RPS * RB));
+      else if (CARRY) rc_new = *reinterpret_cast<const rec_t *>(rec_ahead + (p + RECS + 1 - NP) * (RPS * RB));
       if (p + AHEAD < NP) f_new = fetch(rcq[AHEAD], col_codes, col_params);
       else if (CARRY) f_new = fetch(rcq[AHEAD], ahead_codes, ahead_params);
       __builtin_amdgcn_sched_barrier(0);
@@ -708,8 +712,8 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int k = 0; k < AHEAD; ++k) rcq[k] = rcq[k + 1];
-      rcq[AHEAD] = rc_new;
+      for (int k = 0; k < RECS; ++k) rcq[k] = rcq[k + 1];
+      rcq[RECS] = rc_new;
 #pragma unroll
       for (int k = 0; k + 1 < AHEAD; ++k) fq[k] = fq[k + 1];
       fq[AHEAD - 1] = f_new;
