@@ -816,14 +816,18 @@ __global__ __launch_bounds__(kChainWaves * 64) void lutkan_chain_kernel(const Ch
   float *s_part = s_act_all + ROWS * kChainMaxColumns;
   unsigned *s_outside = reinterpret_cast<unsigned *>(s_part + kChainWaves * kChainMaxColumns);
   float *s_knots = reinterpret_cast<float *>(s_outside + kChainWaves);
+  const int64_t row = (int64_t)blockIdx.x * ROWS + rrow;
+  const bool live = row < a.B;
+  const int64_t b = live ? row : a.B - 1;
+  // A row on four waves: its first input travels while the knots do (128 -> 32 at 256 rows 5.65 -> 5.48 us, 78 -> 16 -> 2 5.75 -> 5.69); with a
+  // wave per row the two registers cost an eighth of the occupancy (40 -> 8 at 8000 rows 6.8 -> 7.4).
+  constexpr bool EARLY = (WPR == kChainWaves);
+  const float x_first = (EARLY && rtid < a.layer[0].d) ? a.x[b * a.layer[0].d + rtid] : 0.0f;
   for (int q = tid; q < a.n_layers * (LUTKAN_MAX_K + 1); q += kChainWaves * 64) {
     const int l = q / (LUTKAN_MAX_K + 1), kappa = q - l * (LUTKAN_MAX_K + 1);
     s_knots[q] = (kappa <= a.layer[l].K) ? a.layer[l].knots[kappa] : 0.0f;
   }
   __syncthreads();
-  const int64_t row = (int64_t)blockIdx.x * ROWS + rrow;
-  const bool live = row < a.B;
-  const int64_t b = live ? row : a.B - 1;
   int64_t hidden_off = 0;
 
   for (int l = 0; l < a.n_layers; ++l) {
@@ -833,7 +837,7 @@ __global__ __launch_bounds__(kChainWaves * 64) void lutkan_chain_kernel(const Ch
     const unsigned masked_index = (unsigned)(Y.K * Y.L) | ((unsigned)Y.K << 16);
     unsigned outside = 0;
     for (int i = rtid; i < Y.d; i += WPR * 64) {
-      const float x = (l == 0) ? a.x[b * Y.d + i] : s_act[i];
+      const float x = (l != 0) ? s_act[i] : (EARLY && i == rtid) ? x_first : a.x[b * Y.d + i];
       const Located o = Y.input_knots ? locate_one<true>(Y, Y.input_knots + (int64_t)i * (Y.K + 1), x) : locate_one<false>(Y, T, x);
       u32x4 rec = {masked_index, 0u, 0u, 0u};
       const bool masked = Y.zero_spline && !o.inside && !o.is_nan;
@@ -865,9 +869,13 @@ __global__ __launch_bounds__(kChainWaves * 64) void lutkan_chain_kernel(const Ch
     const int S = 64 >> Y.jt_log2;
     const int g = wr * S + (lane >> Y.jt_log2);
     const int stride = WPR * S;
-    constexpr int U = 4;
     float acc = 0.0f;
-    for (int i0 = g; i0 < Y.d; i0 += U * stride) {
+    // Rounds of eight (a row on four waves, where the registers cost no occupancy), four, two and one inputs of every group, their table
+    // reads in flight together: in rounds of four only, the last one read its missing inputs' rows again.  Microseconds replayed,
+    // so -> with them: 78 -> 16 -> 2 at 256 rows 6.08 -> 5.77, 10 -> 8 with base at 1024 3.93 -> 3.78, 78 -> 32 -> 16 -> 1 with base at 256 9.00 ->
+    // 8.32, 16 -> 2 at 20000 11.2 -> 9.6, 40 -> 8 at 8000 7.8 -> 6.8, 64 -> 64 at 512 5.82 -> 5.75, 300 -> 8 at 900 the same.
+    auto round = [&](auto count, int i0) {
+      constexpr int U = decltype(count)::value;
       u32x4 rec[U];
       unsigned c0[U], c1[U];
       float al[U], ym[U], bg[U];
@@ -903,7 +911,18 @@ __global__ __launch_bounds__(kChainWaves * 64) void lutkan_chain_kernel(const Ch
           if (Y.with_base) acc = fmaf(bg[u], __uint_as_float(rec[u].z), acc);  // + s_out*s_base * SiLU(x)
         }
       }
+    };
+    int i0 = g, left = (Y.d - __builtin_amdgcn_readfirstlane(wr * S) + stride - 1) / stride;      // inputs of the wave's first group: no group has more
+    if constexpr (WPR == kChainWaves) {
+      for (; left >= 8; left -= 8, i0 += 8 * stride) round(std::integral_constant<int, 8>{}, i0);
     }
+    for (; left >= 4; left -= 4, i0 += 4 * stride) round(std::integral_constant<int, 4>{}, i0);
+    if (left >= 2) {
+      round(std::integral_constant<int, 2>{}, i0);
+      left -= 2;
+      i0 += 2 * stride;
+    }
+    if (left >= 1) round(std::integral_constant<int, 1>{}, i0);
     for (int off = jt; off < 64; off <<= 1) acc += __shfl_xor(acc, off, kWave);          // fixed order over a wave's groups
     if (lane < jt) s_part[wave * kChainMaxColumns + lane] = acc;
     __syncthreads();                                     // the waves' sums are in place; everyone is done with the records
