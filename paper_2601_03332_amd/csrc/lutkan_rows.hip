@@ -43,9 +43,12 @@ struct RowsArgs {
   float knots[LUTKAN_MAX_K + 1];
 };
 
-template <int SCHEME, int LPR, int WPR>
-__global__ __launch_bounds__(kRowsWaves * 64) void lutkan_rows_kernel(const RowsArgs a) {
-  constexpr int ROWS = kRowsWaves / WPR, JT = 4 * LPR, GROUPS = WPR * (64 / LPR), U = 4;
+// DEPTH: inputs of every group in a round, four or two, a kernel of its own each: 71 - 91 vector registers and one work-group per compute
+// unit, or at most 64 and two.  (Two also need at most 80 scalar registers, which the launch bounds ask for: with 82 100 -> 200 at 600
+// rows took 14.5 us instead of 11.1.)  See launch_rows_depth.
+template <int SCHEME, int LPR, int WPR, int DEPTH>
+__global__ __launch_bounds__(kRowsWaves * 64, DEPTH == 2 ? 8 : 4) void lutkan_rows_kernel(const RowsArgs a) {
+  constexpr int ROWS = kRowsWaves / WPR, JT = 4 * LPR, GROUPS = WPR * (64 / LPR);
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -99,7 +102,8 @@ __global__ __launch_bounds__(kRowsWaves * 64) void lutkan_rows_kernel(const Rows
   const int g = wr * (64 / LPR) + lane / LPR;
   const unsigned char *tile = a.table + (size_t)t * a.d * a.blob_bytes;
   float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int i0 = g; i0 < a.d; i0 += U * GROUPS) {
+  auto round = [&](auto count, int i0) {
+    constexpr int U = decltype(count)::value;
     u32x4 rec[U];
     unsigned c0[U], c1[U];
     f32x4 al[U], ym[U], bg[U];
@@ -141,6 +145,11 @@ __global__ __launch_bounds__(kRowsWaves * 64) void lutkan_rows_kernel(const Rows
         }
       }
     }
+  };
+  if (DEPTH == 2 && a.d <= GROUPS) {
+    round(std::integral_constant<int, 1>{}, g);
+  } else {
+    for (int i0 = g; i0 < a.d; i0 += DEPTH * GROUPS) round(std::integral_constant<int, DEPTH>{}, i0);
   }
 #pragma unroll
   for (int off = LPR; off < 64; off <<= 1) {
@@ -159,22 +168,33 @@ __global__ __launch_bounds__(kRowsWaves * 64) void lutkan_rows_kernel(const Rows
   }
 }
 
+template <int SCHEME, int LPR, int WPR, int DEPTH>
+int launch_rows_kernel(const RowsArgs &ra, hipStream_t s) {
+  constexpr int kRows = kRowsWaves / WPR;
+  const int64_t groups = (ra.B + kRows - 1) / kRows * ra.n_tiles;
+  if (groups > 0x7fffffffLL) return fail(LUTKAN_EUNSUPPORTED, "lutkan_rows_kernel: B * m too large for one launch");
+  const size_t lds = (size_t)kRowsWaves * 16 * LPR + (size_t)kRows * ra.d * 16 + (LUTKAN_MAX_K + 1) * 4;
+  static LdsCap raised;
+  if (int rc = raise_lds_cap(lutkan_rows_kernel<SCHEME, LPR, WPR, DEPTH>, &raised, "lutkan_rows_kernel")) return rc;
+  hipLaunchKernelGGL((lutkan_rows_kernel<SCHEME, LPR, WPR, DEPTH>), dim3((unsigned)groups), dim3(kRowsWaves * 64), lds, s, ra);
+  return check_launch("lutkan_rows_kernel");
+}
+
+// Two inputs a round where no group has more (a round reads the rows of the inputs that it lacks again), or where more work-groups of four
+// rows than compute units wait for one another: two run on a unit then, which is worth more than the longer rounds.  Replayed,
+// us, four -> two: 64 -> 1024 at 16 rows 3.75 -> 3.40, 30 -> 700 at 500 20.3 -> 12.2, 11 -> 880 at 422 16.7 -> 9.8; 100 -> 200 at 600 15.4 -> 11.1,
+// 64 -> 1000 at 300 17.6 -> 13.0, 450 -> 200 at 300 33.5 -> 29.4, 256 -> 256 at 400 16.4 -> 14.6, 64 -> 64 at 1500 7.3 -> 6.0; but 256 -> 256 at 200 rows
+// (200 work-groups) 8.8 -> 10.2, 450 -> 200 at 100 rows with 16 waves a row 11.6 -> 12.0.
+template <int SCHEME, int LPR, int WPR>
+int launch_rows_depth(const RowsArgs &ra, hipStream_t s) {
+  constexpr int kRows = kRowsWaves / WPR;
+  const bool two = ra.d <= 2 * WPR * (64 / LPR) || (WPR == 4 && (ra.B + kRows - 1) / kRows * ra.n_tiles > 256);
+  return two ? launch_rows_kernel<SCHEME, LPR, WPR, 2>(ra, s) : launch_rows_kernel<SCHEME, LPR, WPR, 4>(ra, s);
+}
+
 template <int SCHEME, int LPR>
 int launch_rows(const RowsArgs &ra, int wpr, hipStream_t s) {
-  const int rows = kRowsWaves / wpr;
-  const int64_t groups = (ra.B + rows - 1) / rows * ra.n_tiles;
-  if (groups > 0x7fffffffLL) return fail(LUTKAN_EUNSUPPORTED, "lutkan_rows_kernel: B * m too large for one launch");
-  const size_t lds = (size_t)kRowsWaves * 16 * LPR + (size_t)rows * ra.d * 16 + (LUTKAN_MAX_K + 1) * 4;
-  if (wpr == 16) {
-    static LdsCap raised;
-    if (int rc = raise_lds_cap(lutkan_rows_kernel<SCHEME, LPR, 16>, &raised, "lutkan_rows_kernel")) return rc;
-    hipLaunchKernelGGL((lutkan_rows_kernel<SCHEME, LPR, 16>), dim3((unsigned)groups), dim3(kRowsWaves * 64), lds, s, ra);
-  } else {
-    static LdsCap raised;
-    if (int rc = raise_lds_cap(lutkan_rows_kernel<SCHEME, LPR, 4>, &raised, "lutkan_rows_kernel")) return rc;
-    hipLaunchKernelGGL((lutkan_rows_kernel<SCHEME, LPR, 4>), dim3((unsigned)groups), dim3(kRowsWaves * 64), lds, s, ra);
-  }
-  return check_launch("lutkan_rows_kernel");
+  return wpr == 16 ? launch_rows_depth<SCHEME, LPR, 16>(ra, s) : launch_rows_depth<SCHEME, LPR, 4>(ra, s);
 }
 
 template <int SCHEME>

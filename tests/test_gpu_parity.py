@@ -1783,7 +1783,20 @@ ROWS_CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", ROWS_CASES, ids=lambda c: f"seed{c[0]}")
+ROUND_CASES = [
+    # as above: no group with more than one input, than two, one input over; more work-groups than compute units, odd numbers of rounds
+    (961, 64, 130, 8, 64, SYM_INT8, CLOSED, CLIP_X, 3, False, False, False),
+    (962, 128, 70, 5, 32, ASYM_UINT8, HALF_OPEN, ZERO_SPLINE, 5, True, False, False),
+    (963, 129, 70, 5, 32, SYM_INT8, CLOSED, ZERO_SPLINE, 5, False, True, False),
+    (964, 16, 300, 6, 48, ASYM_UINT8, CLOSED, CLIP_X, 703, False, False, False),
+    (965, 33, 200, 9, 32, SYM_INT8, HALF_OPEN, ZERO_SPLINE, 901, True, False, False),
+    (966, 100, 100, 5, 64, ASYM_UINT8, CLOSED, CLIP_X, 1021, False, True, False),
+    (967, 47, 260, 7, 16, SYM_INT8, HALF_OPEN, CLIP_X, 600, False, False, True),
+    (968, 1, 500, 5, 32, ASYM_UINT8, CLOSED, ZERO_SPLINE, 160, False, False, False),
+]
+
+
+@pytest.mark.parametrize("case", ROWS_CASES + ROUND_CASES, ids=lambda c: f"seed{c[0]}")
 def test_few_rows_in_one_launch(case):
     """Against the oracle and its OOB counters, with NaN, infinite and zero (of both signs) inputs."""
     seed, d, m, G, L, scheme, boundary, oob, B, with_base, fp16, per_input = case
