@@ -213,9 +213,12 @@ int launch_rows_width(const RowsArgs &ra, int jt, int wpr, hipStream_t s) {
 namespace lutkan {
 
 // The launch shape by a cost model (microseconds; constants from 30 -> 1000 ... 1024 -> 64 layers at 1 to 4000 rows): 3.5 for
-// launch, locate and sum; then 2.9 (3.2 with four rows) per round of 512 work-groups -- 3.5 more where every input has its own
+// launch, locate and sum; then 2.9 (3.2 with four rows, 1.6 where these are more than one work-group per compute unit and so run two
+// on a unit) per round of 512 work-groups -- 3.5 more where every input has its own
 // knots, read from memory -- and the table bytes a batch requests, in lines of 128, at 15 TB/s, or 1.3 per dependent round
 // of a wave's walk over its inputs, whichever is longer.
+// (1.6: the passes -> this kernel, replayed, 100 -> 200 at 1000 / 1500 rows 19.1 -> 14.1 / 20.3 -> 18.7, 150 -> 150 at 1000 25.3 -> 19.3, 32 -> 300 at 1500
+// 18.0 -> 16.5; with 1.4 for all launches of rounds of two 60 -> 100 at 300 rows 4.3 -> 6.6, 8 -> 600 at 1000 10.1 -> 14.7.)
 RowsPlan rows_plan(const lutkan_dev_layer *l, int64_t B) {
   RowsPlan best{0, 1e300};
   if (l->d > kRowsMaxInputs || B > kRowsMaxBatch) return best;
@@ -223,8 +226,9 @@ RowsPlan rows_plan(const lutkan_dev_layer *l, int64_t B) {
   const double bytes = (double)B * l->n_tiles * l->d * (std::max(128, 2 * l->jt) + std::max(128, lay.param_row_bytes) + (lay.params_off ? std::max(128, lay.params_off) : 0));
   for (int wpr = 16; wpr >= 4; wpr -= 12) {
     const int rows = kRowsWaves / wpr, inputs_per_round = 4 * wpr * (64 / (l->jt / 4));
-    const double rounds = std::max(1.0, (double)((B + rows - 1) / rows * l->n_tiles) / 512.0);
-    const double per_round = (wpr == 16 ? 2.9 : 3.2) + (l->knots_per_input ? 3.5 : 0.0);
+    const int64_t groups = (B + rows - 1) / rows * l->n_tiles;
+    const double rounds = std::max(1.0, (double)groups / 512.0);
+    const double per_round = (wpr == 16 ? 2.9 : groups > 256 ? 1.6 : 3.2) + (l->knots_per_input ? 3.5 : 0.0);
     const double cost = 3.5 + std::max(rounds * per_round + bytes / 15e6, 1.3 * ((l->d + inputs_per_round - 1) / inputs_per_round));
     if (cost < best.cost) best = RowsPlan{wpr, cost};
   }
