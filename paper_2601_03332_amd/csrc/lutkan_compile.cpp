@@ -13,6 +13,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
+#include <limits>
 #include <new>
 #include <thread>
 
@@ -267,8 +268,21 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
       if (!(tau_h[r] < tau_h[r + 1])) return fail(LUTKAN_EINVAL, "lutkan_compile: knots of vector %d not strictly increasing at %d", h, r);
   }
   const size_t E = (size_t)d * m;
-  for (size_t n = 0; n < E * R; ++n)
-    if (!std::isfinite(desc->coef[n])) return fail(LUTKAN_EINVAL, "lutkan_compile: coefficient %zu is not finite", n);
+  float largest_coef = 0.0f, smallest_edge = INFINITY;       // the largest magnitude, the least of the edges' own largest (zero edges aside)
+  for (size_t e = 0; e < E; ++e) {
+    const float *c = desc->coef + e * R;
+    float largest = 0.0f;
+    bool finite = true;
+    for (int r = 0; r < R; ++r) {
+      const float a = std::fabs(c[r]);
+      finite &= a <= std::numeric_limits<float>::max();
+      largest = a > largest ? a : largest;
+    }
+    for (int r = 0; !finite && r < R; ++r)
+      if (!std::isfinite(c[r])) return fail(LUTKAN_EINVAL, "lutkan_compile: coefficient %zu is not finite", e * R + r);
+    largest_coef = std::max(largest_coef, largest);
+    if (largest > 0.0f) smallest_edge = std::min(smallest_edge, largest);
+  }
   if (with_base)
     for (size_t e = 0; e < E; ++e)
       if (!std::isfinite(desc->edge_base_scale[e]) || !std::isfinite(desc->edge_spline_scale[e]) || !std::isfinite(desc->edge_out_scale[e]))
@@ -330,13 +344,10 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
   nt = std::max(1, std::min(nt, 64));
   nt = (int)std::min<size_t>((size_t)nt, (size_t)d);
   std::atomic<long> unrepresentable{0};       // float16 parameters that overflowed
-  float largest_coef[64] = {}, smallest_edge[64];      // per thread: the largest magnitude, the least of the edges' own largest (zero edges aside)
-  std::fill(smallest_edge, smallest_edge + 64, INFINITY);
   const SlicePacker packer{lay, jt, L, scheme, device_params_are_half(repr, half_params ? LUTKAN_PARAM_FP16 : LUTKAN_PARAM_FP32, jt)};
   auto work = [&](int tid) {
     std::vector<float> v((size_t)L);
     std::vector<double> own_basis;
-    float layer_largest = 0.0f, least_edge = INFINITY;
     for (int i = tid; i < d; i += nt) {
       if (per_input) basis_table(i, own_basis);
       const std::vector<double> &basis = per_input ? own_basis : shared_basis;
@@ -357,14 +368,7 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
           cslice[cj] = base_gain;
           cslice += cjt;
         }
-        float largest = 0.0f;
-        for (int r = 0; r < R; ++r) {
-          const float held = with_base ? spline_gain * c[r] : c[r];
-          cslice[(size_t)r * cjt + cj] = held;
-          largest = std::max(largest, std::fabs(held));
-        }
-        layer_largest = std::max(layer_largest, largest);
-        if (largest > 0.0f) least_edge = std::min(least_edge, largest);
+        for (int r = 0; r < R; ++r) cslice[(size_t)r * cjt + cj] = with_base ? spline_gain * c[r] : c[r];
         for (int k = 0; k < K; ++k) {
           const int r0 = first_knot + k - P;               // coefficient of the span's first basis function
           auto coefficient = [&](int r) { return (r >= 0 && r < R) ? (double)c[r] : 0.0; };
@@ -394,8 +398,6 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
         }
       }
     }
-    largest_coef[tid] = layer_largest;
-    smallest_edge[tid] = least_edge;
   };
   if (nt == 1) {
     work(0);
@@ -411,7 +413,7 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
     return fail(LUTKAN_EUNSUPPORTED, "lutkan_compile: %ld segments have an alpha or y_min too large for float16", n);
   }
 
-  a->coef_range = coef_range(*std::max_element(largest_coef, largest_coef + nt), *std::min_element(smallest_edge, smallest_edge + nt));
+  if (!with_base) a->coef_range = coef_range(largest_coef, smallest_edge);     // (with the base branch the table holds other products)
   fill_info(a, d, m, K, L, G, scheme, desc->boundary, desc->oob, repr, desc->param_dtype, desc->knots_per_input, jt, n_tiles, lay, cjt, coef_blob);
   a->info.knot_span = desc->knot_span;
   *out = a;
