@@ -61,7 +61,6 @@ typedef enum { LUTKAN_SPAN_DOMAIN = 0, LUTKAN_SPAN_EXTENDED = 1 } lutkan_knot_sp
 #define LUTKAN_MAX_K 64            /* segments per layer (the knot vector travels in the kernel arguments) */
 #define LUTKAN_MAX_ROWS 65535      /* K * L, table rows per input (a row index travels in 16 bits) */
 #define LUTKAN_MAX_LAYERS 16
-#define LUTKAN_COEF_RANGE_BIAS 128
 
 const char *lutkan_last_error(void);
 const char *lutkan_version(void);
@@ -214,9 +213,6 @@ typedef struct {
   float ext_knots[LUTKAN_MAX_K + 7];  /* host copy, entries 0..G+6 used */
   const float *coef_table;            /* device, lutkan_info.coef_table_bytes bytes, 16-byte aligned */
   int32_t knots_per_input;
-  int32_t coef_range;                 /* magnitudes of the coefficients, or 0 (not recorded): LUTKAN_COEF_RANGE_BIAS + e when every
-                                         coefficient is below 2^e and the largest of every edge at least 2^(e-16) (or the
-                                         edge is all zero); see bspline_kan_forward */
   const float *input_ext_knots;       /* device fp32 [d][G+2p+1], a copy of lutkan_artifact_ext_knots; NULL if shared */
 } bspline_dev_layer;
 
@@ -323,11 +319,7 @@ int lutkan_forward_trace(const lutkan_dev_layer *layer, const float *x, int64_t 
  * its domain grid with one knot vector, neighbouring gaps within a factor of about 3 of each other, runs as a dense product on the matrix cores, every fp32 operand cut exactly into
  * three bf16 pieces (relative error per term <= 2^-24, of either sign), the basis as one cubic per segment and
  * function (relative error of each value below 1e-6, however small it is); the results agree with the other kernels' to
- * rounding.  Where a work-group sums at least 80 inputs (96, 120 on grids of up to 9, 5 segments) and layer->coef_range is recorded, the operands are cut into two binary16
- * pieces instead (23 of 24 significand bits; basis values keep 20 bits down to 2^-30, coefficients down to 2^-20 of the largest)
- * and summed in blocks of 32 inputs, which leaves the sums nearer to 64 bits than the three pieces do.  A table that its owner
- * rewrites needs no new coef_range: coefficients beyond 16 times the recorded magnitude, or all below 2^-22 of it, are seen by the
- * kernel, which then sums those outputs term by term (slower). */
+ * rounding. */
 int bspline_kan_forward(const bspline_dev_layer *layer, const float *x, int64_t B, float *y,
                         void *workspace, size_t workspace_bytes, void *hip_stream);
 

@@ -64,7 +64,7 @@ class _SplineDevLayer(C.Structure):
     _fields_ = [(n, C.c_int32) for n in ("d", "m", "G", "degree", "boundary", "oob", "value_repr", "knot_span", "jt",
                                          "n_tiles", "coef_blob_bytes", "algo")] + \
                [("ext_knots", C.c_float * (MAX_K + 7)), ("coef_table", C.c_void_p), ("knots_per_input", C.c_int32),
-                ("coef_range", C.c_int32), ("input_ext_knots", C.c_void_p)]
+                ("input_ext_knots", C.c_void_p)]
 
 
 EXPORTS = [

@@ -14,16 +14,6 @@
 // evaluation than the tiled kernel; apart, it is nearer than that kernel (64 -> 128 at 131072 rows 1.1e-7 against 3.0e-7,
 // 1024 -> 1024 at 4096 rows, G = 10, 4.0e-7 against 5.7e-7).
 //
-// Two binary16 pieces and three products (HALF; lutkan_pieces.h): half of the matrix work, a third less of the rest, at 23 instead of 24
-// bits per operand, 8e-8 on a layer's outputs where the three pieces add 1e-8.  What a long sum loses by its own roundings is
-// more: the products of the high pieces are summed over 32 inputs at a time, and the blocks by the vector ALU in a third set of
-// registers.  Error against 64 bits (2-norm), three pieces -> two in blocks: 96 -> 128, G = 5 / 8 / 10, 1.38e-7 / 1.54e-7 / 1.74e-7 ->
-// 1.29e-7 / 1.34e-7 / 1.42e-7; 128 -> 128 1.54e-7 / 1.77e-7 / 2.03e-7 -> 1.30e-7 / 1.35e-7 / 1.46e-7; 1024 -> 1024 at 4096 rows,
-// G = 10, 4.0e-7 -> 1.6e-7; but 64 -> 128, G = 5, 1.14e-7 -> 1.18e-7, and 97 -> 129 with a seventh of the inputs clipped 3 % more:
-// so from 120, 96 and 80 inputs per work-group on (kHalfMinInputs).  Whole layers, microseconds: 128 -> 128 at 131072 rows, G = 5 / 8 / 10, 123 / 174 /
-// 220 -> 100 / 130 / 155; 1024 -> 1024 at 4096 rows, G = 5 / 8 / 10, 235 / 337 / 423 -> 186 / 240 / 295.  The products of the
-// lower pieces carry a factor of 2048 (kLowPieceScale) and have sums of their own.
-//
 // Operand A, sparse and without LDS: v_smfmac_f32_32x32x32_bf16 takes operand A with two stored values of every four
 // consecutive k (a group) and two bits each for where they stand, and does twice the dense instruction's k in the same time (55.8
 // cycles at 2.4 GHz against 54.1, both at the clock that random operands leave the chip).  A basis always fits: coefficient row r
@@ -48,7 +38,7 @@
 // instruction only up to about four.  (Spreading them between the matrix instructions by hand, evaluating a step ahead: 4 %
 // faster with 128 columns, 4 - 10 % slower with 64 and fewer, whose registers then spill; four waves of 64 rows x 128 columns:
 // 13 % slower.)
-// Whole layers, three pieces, dense matrix instructions -> sparse, microseconds (one run each): 64 -> 128 at 131072 rows, G = 5, 111 -> 84;
+// Whole layers, dense matrix instructions -> sparse, microseconds (one run each): 64 -> 128 at 131072 rows, G = 5, 111 -> 84;
 // 128 -> 128 190 -> 142; 128 -> 128, G = 8, 338 -> 191; 256 -> 256 at 16384 rows, G = 8, 189 -> 110; 1024 -> 1024 at 4096 rows, G = 5 /
 // 8 / 10, 348 / 658 / 658 -> 255 / 350 / 441; 64 -> 8 at 131072 rows 36 -> 31.  The tiled kernel takes 587 for 128 -> 128 (G = 5), 790
 // for 1024 -> 1024 (G = 10).
@@ -61,18 +51,13 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x16 __attribute__((ext_vector_type(16)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kMxWaves = 8;
 constexpr int kMxMaxSegments = 13;       // R = G + 3 <= 16
 constexpr int kMxSegFloats = 14;         // of a segment: 8 polynomial coefficients, its ends, middle and scale, the two outer factors
 constexpr int kMxSegStride = 20;         // ... in LDS: 80-byte rows spread the banks
-constexpr float kBasisScale = 32768.0f;  // of the basis values before they are cut into binary16 pieces
-constexpr int kHalfMinInputs[3] = {120, 96, 80};   // per work-group, with 2, 3 and 4 groups, from which two binary16 pieces are no further from 64 bits
-constexpr int kBlockInputs = 32;         // ... with the products of their high pieces summed over this many inputs at a time
-constexpr int kMxLdsTail = (kMxMaxSegments + 1) * (kMxSegStride * 4 + 16 + 4) + 16;      // behind the stages in LDS: segments, places, indices, flags
+constexpr int kMxLdsTail = (kMxMaxSegments + 1) * (kMxSegStride * 4 + 16 + 4) + 16;      // behind the stages in LDS: segments, places, indices, a flag
 
 struct SplineMatrixArgs {
   const float *x;            // [B][d]
@@ -86,10 +71,7 @@ struct SplineMatrixArgs {
   float t0, tKs;             // the clip range
   float masked_below, masked_above;      // zero_spline: inputs outside contribute nothing; clip_x: -inf, +inf
   float knots[kMxMaxSegments - 1];       // the inner knots, +inf past the last
-  float segment[kMxMaxSegments][kMxSegFloats];     // see segment_constants; times kBasisScale for two binary16 pieces
-  // two binary16 pieces: the power of two that takes the layer's coefficients below 2^12, its inverse over kBasisScale, the largest
-  // coefficient that has pieces, and the least that one of the work-group's must reach (or all are zero)
-  float coef_scale, out_scale, largest_coef, least_coef;
+  float segment[kMxMaxSegments][kMxSegFloats];     // see segment_constants
 };
 
 // Where an input lies: the clipped x' (NaN for a NaN input) and its segment, a.segments for one that contributes nothing.
@@ -138,8 +120,8 @@ __device__ __forceinline__ void fill_segments(const SplineMatrixArgs &a, float *
   }
 }
 
-union Sparse { u32x4 u; bf16x8 h; f16x8 f; };          // a lane's 8 values of operand A: two of each of its four groups of slots
-union Dense { u32x4 u[2]; bf16x16 h; f16x16 f; };       // a lane's 16 values of operand B
+union Sparse { u32x4 u; bf16x8 h; };          // a lane's 8 values of operand A: two of each of its four groups of slots
+union Dense { u32x4 u[2]; bf16x16 h; };       // a lane's 16 values of operand B
 
 // Where the four non-zero values of a segment go.  Coefficient row r is slot r / GRP of group r % GRP, so the rows first ..
 // first+3 lie in every group once (GRP 4), once or twice (3) or twice (2).  place[g]: the byte permute that takes group g's two
@@ -165,32 +147,22 @@ __device__ __forceinline__ void fill_places(u32x4 *s_place, unsigned *s_index, i
   s_index[tid] = index;
 }
 
-// Inputs that a lane evaluates per stage.  Two binary16 pieces hold a third set of sums: stages of half the length where the registers
-// of the full ones would spill (128 -> 128 at 131072 rows, G = 5: 113 -> 99 us).
-constexpr int inputs_per_lane(int grp, int nt, bool half) { return (grp == 4 || (half && grp == 2 && nt == 4)) ? 2 : 4; }
-
-// HALF: two binary16 pieces per operand and three products, else three bf16 pieces and six.
-template <int GRP, int RT, int NT, bool HALF>
+template <int GRP, int RT, int NT>
 __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const SplineMatrixArgs a) {
   constexpr int BN = 32 * NT;
-  constexpr int PC = HALF ? 2 : 3;                        // pieces of an operand
-  constexpr int IPL = inputs_per_lane(GRP, NT, HALF);
+  constexpr int IPL = (GRP == 4) ? 2 : 4;                 // inputs a lane evaluates per stage
   constexpr int IS = 2 * IPL;                             // inputs per stage
   constexpr int STEPS = IPL * GRP / 4;                    // matrix k steps per stage, four groups of a lane each
   constexpr int kThreads = kMxWaves * 64;
   constexpr int kUnits = 4 * STEPS;                       // of 8 slots of a column: what a lane reads of operand B per step and half of the inputs
   constexpr int kPairs = kUnits * BN;                     // (unit, column) pairs of a stage, one thread cuts 8 coefficients of each
   constexpr int UPT = (kPairs + kThreads - 1) / kThreads;
-  constexpr int kStageBytes = kUnits * PC * BN * 16;
-  // the coefficients of a stage are loaded and cut unit by unit between its steps, not all at once around them, where their
-  // registers would spill beside three sets of sums (128 -> 128 at 131072 rows, G = 8: 153 -> 143 us)
-  constexpr bool SPREAD = HALF && GRP == 3 && NT == 4;
-  static_assert(!SPREAD || (UPT == STEPS && BN >= 64), "a unit of the thread per step");
+  constexpr int kStageBytes = kUnits * 3 * BN * 16;
   extern __shared__ __align__(16) unsigned char lds[];
   float *const s_seg = reinterpret_cast<float *>(lds + 2 * kStageBytes);
   u32x4 *const s_place = reinterpret_cast<u32x4 *>(s_seg + (kMxMaxSegments + 1) * kMxSegStride);
   unsigned *const s_index = reinterpret_cast<unsigned *>(s_place + (kMxMaxSegments + 1));
-  int *const s_uncut = reinterpret_cast<int *>(s_index + (kMxMaxSegments + 1));      // then: a coefficient that is not zero, one of some size
+  int *const s_uncut = reinterpret_cast<int *>(s_index + (kMxMaxSegments + 1));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -203,7 +175,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
 
   fill_segments(a, s_seg, tid, kThreads);
   fill_places<GRP>(s_place, s_index, a.segments, tid);
-  if (tid < 3) s_uncut[tid] = 0;
+  if (tid == 0) *s_uncut = 0;
 
   // This thread's coefficient columns of a stage.  Unit u = (h * STEPS + step) * 2 + p: the groups 4 step + 2p and the next one
   // of the lanes of half h, whose groups are those of its inputs one after the other.
@@ -232,22 +204,10 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
       const int g = row_of(unit_of(q), e, of);
 #pragma unroll
       for (int r = 0; r < 4; ++r)                          // slots past the last coefficient row: no value goes there, any row will do
-        offset[q][4 * e + r] = ((SPREAD ? 0 : of * a.R) + min(g + GRP * r, a.R - 1)) * a.jt;
+        offset[q][4 * e + r] = (of * a.R + min(g + GRP * r, a.R - 1)) * a.jt;
     }
-  auto load_unit = [&](int i0, int q) {
-    const unsigned c = (unsigned)((tid + q * kThreads) % BN) & (unsigned)(a.jt - 1);     // a column past the tile: a valid address, not stored
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      int of;
-      const int g = row_of(unit_of(q), e, of);
-      const unsigned i = (unsigned)min(i0 + of, a.d - 1);  // past the last input: its basis is zero
-      const float *src = tile + (uint64_t)i * (unsigned)(a.R * a.jt);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) cf[q][4 * e + r] = (src + (SPREAD ? offset[q][4 * e + r] : min(g + GRP * r, a.R - 1) * a.jt))[c];
-    }
-  };
   auto load_coefs = [&](int i0) {
-    if (BN >= 64 && !SPREAD && i0 + IS <= a.d) {
+    if (BN >= 64 && i0 + IS <= a.d) {
       const float *stage = tile + (size_t)i0 * a.R * a.jt;
 #pragma unroll
       for (int q = 0; q < UPT; ++q) {
@@ -258,25 +218,34 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
       return;
     }
 #pragma unroll
-    for (int q = 0; q < UPT; ++q) load_unit(i0, q);
-  };
-  auto store_unit = [&](unsigned char *buf, int q) {
-    const int id = tid + q * kThreads;
-    if (kPairs % kThreads != 0 && id >= kPairs) return;
-    const int u = id / BN, c = id % BN;
-    unsigned p[4][PC];
+    for (int q = 0; q < UPT; ++q) {
+      const int c = ((tid + q * kThreads) % BN) & (a.jt - 1);      // a column past the tile: a valid address, not stored
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      if constexpr (HALF) lutkan_cut2_pair(cf[q][2 * r] * a.coef_scale, cf[q][2 * r + 1] * a.coef_scale, p[r]);
-      else lutkan_cut3_pair(cf[q][2 * r], cf[q][2 * r + 1], p[r]);
-      largest = __builtin_elementwise_maximum(__builtin_elementwise_maximum(largest, fabsf(cf[q][2 * r])), fabsf(cf[q][2 * r + 1]));
+      for (int e = 0; e < 2; ++e) {
+        int of;
+        const int g = row_of(unit_of(q), e, of);
+        const int i = min(i0 + of, a.d - 1);               // past the last input: its basis is zero
+        const float *src = tile + (size_t)i * a.R * a.jt + c;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) cf[q][4 * e + r] = src[min(g + GRP * r, a.R - 1) * a.jt];
+      }
     }
-#pragma unroll
-    for (int w = 0; w < PC; ++w) *reinterpret_cast<u32x4 *>(buf + ((u * PC + w) * BN + c) * 16) = u32x4{p[0][w], p[1][w], p[2][w], p[3][w]};
   };
   auto store_coefs = [&](unsigned char *buf) {
 #pragma unroll
-    for (int q = 0; q < UPT; ++q) store_unit(buf, q);
+    for (int q = 0; q < UPT; ++q) {
+      const int id = tid + q * kThreads;
+      if (kPairs % kThreads != 0 && id >= kPairs) break;
+      const int u = id / BN, c = id % BN;
+      unsigned p[4][3];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        lutkan_cut3_pair(cf[q][2 * r], cf[q][2 * r + 1], p[r]);
+        largest = __builtin_elementwise_maximum(__builtin_elementwise_maximum(largest, fabsf(cf[q][2 * r])), fabsf(cf[q][2 * r + 1]));
+      }
+#pragma unroll
+      for (int w = 0; w < 3; ++w) *reinterpret_cast<u32x4 *>(buf + ((u * 3 + w) * BN + c) * 16) = u32x4{p[0][w], p[1][w], p[2][w], p[3][w]};
+    }
   };
 
   // this lane's inputs of a stage: consecutive ones of its row, the upper lanes' after the lower lanes'
@@ -304,21 +273,20 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
     }
   };
 
-  f32x16 acc[RT][NT], low[RT][NT];       // the products of the high pieces, and the smaller ones (HALF: times kLowPieceScale)
-  [[maybe_unused]] f32x16 total[RT][NT];                   // HALF: the sums of acc's blocks of kBlockInputs inputs
+  f32x16 acc[RT][NT], low[RT][NT];       // the products of the high pieces, and the five smaller ones
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) { acc[rt][ct][v] = 0.0f; low[rt][ct][v] = 0.0f; total[rt][ct][v] = 0.0f; }
+      for (int v = 0; v < 16; ++v) { acc[rt][ct][v] = 0.0f; low[rt][ct][v] = 0.0f; }
 
   load_coefs(i_begin);
   if (wave_live) load_inputs(i_begin);
   store_coefs(lds);
   __syncthreads();
 
-  int cur = 0, stages_of_block = 0;
+  int cur = 0;
   for (int i0 = i_begin; i0 < i_end; i0 += IS) {
     const bool more = i0 + IS < i_end;
     // the inputs of this stage; one past the work-group's last takes the all-zero segment (and a finite x)
@@ -330,19 +298,13 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) xc[rt][s] = dead[s] ? a.t0 : xv[rt][s];
     }
-    const int i0_next = more ? i0 + IS : i0;
-    unsigned char *const next = lds + (cur ^ 1) * kStageBytes;     // (everyone left that buffer before the last barrier)
-    // the next stage travels while this one multiplies
-    if constexpr (SPREAD) {                                // (after the last stage its own again: nobody reads them)
-      if (wave_live) load_inputs(i0_next);
-      else { load_coefs(i0_next); store_coefs(next); }
-    } else if (more) {
-      load_coefs(i0_next);
-      if (wave_live) load_inputs(i0_next);
+    if (more) {                                            // the next stage travels while this one multiplies
+      load_coefs(i0 + IS);
+      if (wave_live) load_inputs(i0 + IS);
     }
     if (wave_live) {
-      const unsigned char *buf = lds + cur * kStageBytes + half * (PC * BN * 16) + col * 16;
-      unsigned value[RT][PC][IPL * GRP], index[RT][IPL];    // per piece the lane's groups, two values each; where they belong
+      const unsigned char *buf = lds + cur * kStageBytes + half * (3 * BN * 16) + col * 16;
+      unsigned value[RT][3][IPL * GRP], index[RT][IPL];    // per piece the lane's groups, two values each; where they belong
 #pragma unroll
       for (int s = 0; s < STEPS; ++s) {
 #pragma unroll
@@ -354,21 +316,15 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
             basis_of(s_seg, at, n);
             const u32x4 place = s_place[at.segment];
             index[rt][of] = s_index[at.segment];
-            unsigned p01[PC], p23[PC];
-            if constexpr (HALF) {
-              lutkan_cut2_pair(n[0], n[1], p01);
-              lutkan_cut2_pair(n[2], n[3], p23);
-            } else {
-              lutkan_cut3_pair(n[0], n[1], p01);
-              lutkan_cut3_pair(n[2], n[3], p23);
-            }
+            unsigned p01[3], p23[3];
+            lutkan_cut3_pair(n[0], n[1], p01);
+            lutkan_cut3_pair(n[2], n[3], p23);
 #pragma unroll
-            for (int q = 0; q < PC; ++q)
+            for (int q = 0; q < 3; ++q)
 #pragma unroll
               for (int g = 0; g < GRP; ++g) value[rt][q][of * GRP + g] = __builtin_amdgcn_perm(p23[q], p01[q], place[g]);
           }
-        if constexpr (SPREAD) load_unit(i0_next, s);
-        Sparse af[RT][PC];
+        Sparse af[RT][3];
         int slots[RT];                                     // bits 4g .. 4g+3: the slots of the step's group g
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
@@ -376,56 +332,30 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
           else if constexpr (GRP == 2) slots[rt] = (int)(index[rt][2 * s] | (index[rt][2 * s + 1] << 8));
           else slots[rt] = (int)((index[rt][s] >> (4 * s)) | (index[rt][s + 1] << (12 - 4 * s)));
 #pragma unroll
-          for (int q = 0; q < PC; ++q) af[rt][q].u = u32x4{value[rt][q][4 * s], value[rt][q][4 * s + 1], value[rt][q][4 * s + 2], value[rt][q][4 * s + 3]};
+          for (int q = 0; q < 3; ++q) af[rt][q].u = u32x4{value[rt][q][4 * s], value[rt][q][4 * s + 1], value[rt][q][4 * s + 2], value[rt][q][4 * s + 3]};
         }
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
-          Dense wf[PC];
+          Dense wf[3];
 #pragma unroll
-          for (int q = 0; q < PC; ++q)
+          for (int q = 0; q < 3; ++q)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) wf[q].u[h] = *reinterpret_cast<const u32x4 *>(buf + (((h * STEPS + s) * 2 * PC + q) * BN + ct * 32) * 16);
-          if constexpr (HALF) {
+            for (int h = 0; h < 2; ++h) wf[q].u[h] = *reinterpret_cast<const u32x4 *>(buf + (((h * STEPS + s) * 6 + q) * BN + ct * 32) * 16);
+          // the six piece products, the small ones first
+          constexpr int kPieceOfA[5] = {2, 0, 1, 1, 0}, kPieceOfW[5] = {0, 2, 1, 0, 1};
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-              low[rt][ct] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(af[rt][0].f, wf[1].f, low[rt][ct], slots[rt], 0, 0);
-              acc[rt][ct] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(af[rt][0].f, wf[0].f, acc[rt][ct], slots[rt], 0, 0);
-              low[rt][ct] = __builtin_amdgcn_smfmac_f32_32x32x32_f16(af[rt][1].f, wf[0].f, low[rt][ct], slots[rt], 0, 0);
-            }
-          } else {
-            // the six piece products, the small ones first
-            constexpr int kPieceOfA[5] = {2, 0, 1, 1, 0}, kPieceOfW[5] = {0, 2, 1, 0, 1};
-#pragma unroll
-            for (int p = 0; p < 5; ++p)
-#pragma unroll
-              for (int rt = 0; rt < RT; ++rt)
-                low[rt][ct] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(af[rt][kPieceOfA[p]].h, wf[kPieceOfW[p]].h, low[rt][ct], slots[rt], 0, 0);
+          for (int p = 0; p < 5; ++p)
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
-              acc[rt][ct] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(af[rt][0].h, wf[0].h, acc[rt][ct], slots[rt], 0, 0);
-          }
+              low[rt][ct] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(af[rt][kPieceOfA[p]].h, wf[kPieceOfW[p]].h, low[rt][ct], slots[rt], 0, 0);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            acc[rt][ct] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(af[rt][0].h, wf[0].h, acc[rt][ct], slots[rt], 0, 0);
         }
-        if constexpr (SPREAD) store_unit(next, s);
       }
     }
-    if (HALF && ++stages_of_block == kBlockInputs / IS) {
-      stages_of_block = 0;
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int ct = 0; ct < NT; ++ct)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) { total[rt][ct][v] += acc[rt][ct][v]; acc[rt][ct][v] = 0.0f; }
-    }
-    if (more) {
-      if (!SPREAD) store_coefs(next);
-    } else if constexpr (HALF) {
-      if (!(largest <= a.largest_coef)) s_uncut[0] = 1;
-      if (largest > 0.0f) s_uncut[1] = 1;
-      if (largest >= a.least_coef) s_uncut[2] = 1;
-    } else if (!(largest <= kLargestBf16)) {
-      s_uncut[0] = 1;
-    }
+    if (more) store_coefs(lds + (cur ^ 1) * kStageBytes);   // (everyone left that buffer before the last barrier)
+    else if (!(largest <= kLargestBf16)) *s_uncut = 1;
     __syncthreads();
     cur ^= 1;
   }
@@ -442,15 +372,13 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int64_t b = row0 + rt * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-        const float sum = HALF ? fmaf(low[rt][ct][v], 1.0f / kLowPieceScale, acc[rt][ct][v] + total[rt][ct][v]) * a.out_scale : acc[rt][ct][v] + low[rt][ct][v];
-        if (b < a.B && c < width && j < a.m) yout[b * a.m + j] = sum;
+        if (b < a.B && c < width && j < a.m) yout[b * a.m + j] = acc[rt][ct][v] + low[rt][ct][v];
       }
     }
   // A coefficient that is not finite (in a table that its owner wrote: the compiler refuses them), or has no bf16 value above it,
   // makes every row of the product NaN, by 0 * inf.  It belongs to the rows on its support: the work-group sums its outputs
-  // again, term by term.  HALF: likewise a table that its owner wrote with coefficients beyond or far below the magnitudes that the
-  // layer was made for.
-  if (s_uncut[0] == 0 && (!HALF || s_uncut[1] == s_uncut[2])) return;
+  // again, term by term.
+  if (*s_uncut == 0) return;
 #pragma unroll 1
   for (int e = 0; e < RT * NT * 16; ++e) {
     const int rt = e / (NT * 16), c = (e / 16 % NT) * 32 + col, v = e % 16;
@@ -466,7 +394,7 @@ __global__ __launch_bounds__(kMxWaves * 64, 2) void bspline_matrix_kernel(const 
       basis_of(s_seg, at, n);
       const float *src = tile + ((size_t)i * a.R + at.segment) * a.jt + c;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) sum = fmaf(HALF ? n[q] * (1.0f / kBasisScale) : n[q], src[q * a.jt], sum);
+      for (int q = 0; q < 4; ++q) sum = fmaf(n[q], src[q * a.jt], sum);
     }
     yout[b * a.m + j] = sum;
   }
@@ -521,22 +449,17 @@ struct MatrixPlan {
 // of 8 inputs with two groups each, 5.1 with three; 1024 -> 1024: 3.3 per stage of 4 with four groups); a work-group adds its fill; the launch runs in rounds of 256
 // work-groups; chunks add the summing pass and are as many as the caller's workspace holds sums for.  Two accumulators
 // of 64 rows x 128 columns would not fit the registers of two waves per SIMD: rt = 1 there.
-// Three sets of them (half) fit 32 rows from 64 columns on; a stage of that form: 128 -> 128 at 131072 rows, G = 5, 1.4 us per 4
-// inputs, G = 8 3.8 per 8, 1024 -> 1024, G = 10, 2.2 per 4, 128 -> 64, G = 5, 1.8 per 8.
-// `longest`: inputs in a chunk at most.
-MatrixPlan plan_matrix(int64_t B, int d, int m, int n_tiles, int nt, int grp, bool half, int longest, size_t partial_bytes) {
-  const int is = 2 * inputs_per_lane(grp, nt, half), steps = is * grp / 8;
+MatrixPlan plan_matrix(int64_t B, int d, int m, int n_tiles, int nt, int grp, size_t partial_bytes) {
+  const int is = (grp == 4) ? 4 : 8, steps = is * grp / 8;
   MatrixPlan best{1, 1, d, 1e300};
-  for (int rt = 1; rt <= (nt == 4 || (half && nt == 2) ? 1 : 2); ++rt) {
+  for (int rt = 1; rt <= (nt == 4 ? 1 : 2); ++rt) {
     const int64_t groups = (B + kMxWaves * 32 * rt - 1) / (kMxWaves * 32 * rt) * n_tiles;
-    const double matrix = 2.0 * steps * rt * nt * (half ? 3 : 6) * 32 * 1.25;
-    const double vector = 2.0 * (half ? is / 2 * rt * 31 + 31 * steps * nt : is / 2 * rt * 80 + 45 * nt) * 4.0;
-    const double stage = (std::max(matrix, vector) + (half ? 600.0 : 1000.0)) / 1450.0;
+    const double matrix = 2.0 * steps * rt * nt * 6 * 32 * 1.25, vector = 2.0 * (is / 2 * rt * 80 + 45 * nt) * 4.0;
+    const double stage = (std::max(matrix, vector) + 1000.0) / 1450.0;
     for (int want = 1; want <= 64; ++want) {
       const int chunk = (int)round_up((d + want - 1) / want, 8);
       const int split = (d + chunk - 1) / chunk;
       if (split > 1 && (size_t)split * (size_t)B * (size_t)m * 4 > partial_bytes) break;
-      if (chunk > longest) continue;
       const double rounds = (double)((groups * split + 255) / 256);
       double cost = rounds * (4.0 + (double)((chunk + is - 1) / is) * stage);
       if (split > 1) cost += 4.0 + (double)split * (double)B * m * 4.0 / 3e6;
@@ -547,29 +470,23 @@ MatrixPlan plan_matrix(int64_t B, int d, int m, int n_tiles, int nt, int grp, bo
   return best;
 }
 
-template <int GRP, int RT, int NT, bool HALF>
+template <int GRP, int RT, int NT>
 int launch_matrix(const SplineMatrixArgs &ma, int n_split, hipStream_t s) {
   constexpr int kRows = kMxWaves * 32 * RT;
   const int64_t groups = (ma.B + kRows - 1) / kRows * ma.n_tiles;
   if (groups > 0x7fffffffLL) return fail(LUTKAN_EUNSUPPORTED, "bspline_matrix_kernel: B * m too large for one launch");
-  const size_t lds = 2 * (size_t)(GRP * inputs_per_lane(GRP, NT, HALF) * (HALF ? 2 : 3) * 32 * NT * 16) + kMxLdsTail;
+  const size_t lds = 2 * (size_t)((GRP == 3 ? 12 : 8) * 3 * 32 * NT * 16) + kMxLdsTail;
   static LdsCap raised;
-  if (int rc = raise_lds_cap(bspline_matrix_kernel<GRP, RT, NT, HALF>, &raised, "bspline_matrix_kernel")) return rc;
-  hipLaunchKernelGGL((bspline_matrix_kernel<GRP, RT, NT, HALF>), dim3((unsigned)groups, (unsigned)n_split), dim3(kMxWaves * 64), lds, s, ma);
+  if (int rc = raise_lds_cap(bspline_matrix_kernel<GRP, RT, NT>, &raised, "bspline_matrix_kernel")) return rc;
+  hipLaunchKernelGGL((bspline_matrix_kernel<GRP, RT, NT>), dim3((unsigned)groups, (unsigned)n_split), dim3(kMxWaves * 64), lds, s, ma);
   return check_launch("bspline_matrix_kernel");
 }
 
-template <int GRP, bool HALF>
-int launch_matrix_groups(const SplineMatrixArgs &ma, int rt, int nt, int n_split, hipStream_t s) {
-  if (nt == 4) return launch_matrix<GRP, 1, 4, HALF>(ma, n_split, s);
-  if constexpr (!HALF) { if (nt == 2 && rt == 2) return launch_matrix<GRP, 2, 2, HALF>(ma, n_split, s); }
-  if (nt == 2) return launch_matrix<GRP, 1, 2, HALF>(ma, n_split, s);
-  return rt == 2 ? launch_matrix<GRP, 2, 1, HALF>(ma, n_split, s) : launch_matrix<GRP, 1, 1, HALF>(ma, n_split, s);
-}
-
 template <int GRP>
-int launch_matrix_pieces(const SplineMatrixArgs &ma, bool half, int rt, int nt, int n_split, hipStream_t s) {
-  return half ? launch_matrix_groups<GRP, true>(ma, rt, nt, n_split, s) : launch_matrix_groups<GRP, false>(ma, rt, nt, n_split, s);
+int launch_matrix_groups(const SplineMatrixArgs &ma, int rt, int nt, int n_split, hipStream_t s) {
+  if (nt == 4) return launch_matrix<GRP, 1, 4>(ma, n_split, s);
+  if (nt == 2) return rt == 2 ? launch_matrix<GRP, 2, 2>(ma, n_split, s) : launch_matrix<GRP, 1, 2>(ma, n_split, s);
+  return rt == 2 ? launch_matrix<GRP, 2, 1>(ma, n_split, s) : launch_matrix<GRP, 1, 1>(ma, n_split, s);
 }
 
 }  // namespace
@@ -593,28 +510,13 @@ int bspline_matrix_forward(const bspline_dev_layer *l, const float *x, int64_t B
   const int grp = (ma.R <= 8) ? 2 : (ma.R <= 12) ? 3 : 4;
   const int nt = ma.jt >= 128 ? 4 : ma.jt >= 64 ? 2 : 1;
   float *const partials = static_cast<float *>(workspace);
-  MatrixPlan mp = plan_matrix(B, l->d, l->m, l->n_tiles, nt, grp, false, INT32_MAX, workspace_bytes);
-  // Two binary16 pieces, where the layer's coefficients have them and the sums are long enough that summing in blocks gains more
-  // than the shorter operands lose, in chunks no longer than the other form's.
-  const bool half = l->coef_range != 0 && std::min(mp.chunk, ma.d) >= kHalfMinInputs[grp - 2];
-  if (half) {
-    mp = plan_matrix(B, l->d, l->m, l->n_tiles, nt, grp, true, mp.chunk, workspace_bytes);
-    const int exponent = l->coef_range - LUTKAN_COEF_RANGE_BIAS;
-    ma.coef_scale = std::ldexp(1.0f, 12 - exponent);
-    ma.out_scale = std::ldexp(1.0f / kBasisScale, exponent - 12);
-    ma.largest_coef = std::ldexp(kLargestBinary16, exponent - 12);
-    ma.least_coef = std::ldexp(1.0f, exponent - 12 - 10);
-    for (int k = 0; k < l->G; ++k)
-      for (int e = 0; e < kMxSegFloats; ++e)
-        if (e < 8 || e >= 12) ma.segment[k][e] *= kBasisScale;
-  }
+  const MatrixPlan mp = plan_matrix(B, l->d, l->m, l->n_tiles, nt, grp, workspace_bytes);
   ma.chunk = mp.chunk;
   ma.y = y;
   if (mp.n_split > 1) { ma.y = partials; ma.split_stride = B * l->m; }
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  const int rc = grp == 2   ? launch_matrix_pieces<2>(ma, half, mp.rt, nt, mp.n_split, s)
-                 : grp == 3 ? launch_matrix_pieces<3>(ma, half, mp.rt, nt, mp.n_split, s)
-                            : launch_matrix_pieces<4>(ma, half, mp.rt, nt, mp.n_split, s);
+  const int rc = grp == 2 ? launch_matrix_groups<2>(ma, mp.rt, nt, mp.n_split, s) : grp == 3 ? launch_matrix_groups<3>(ma, mp.rt, nt, mp.n_split, s)
+                                                                                : launch_matrix_groups<4>(ma, mp.rt, nt, mp.n_split, s);
   if (rc) return rc;
   plan_note("bspline_matrix np=%d split=%d slots=%d; ", mp.rt, mp.n_split, 4 * grp);
   if (mp.n_split == 1) return LUTKAN_OK;

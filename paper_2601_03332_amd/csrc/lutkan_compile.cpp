@@ -13,7 +13,6 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
-#include <limits>
 #include <new>
 #include <thread>
 
@@ -54,15 +53,6 @@ int choose_jt(int m, int K, int L, int scheme, int value_repr, int param_dtype) 
   while (fit > 4 && blob_layout(K, L, fit, scheme, value_repr, param_dtype).bytes > lds_slice_budget(value_repr)) fit /= 2;
   if (blob_layout(K, L, fit, scheme, value_repr, param_dtype).bytes <= lds_slice_budget(value_repr)) return fit;
   return jt < 32 ? jt : 32;   // no width fits: the gather kernel, which is fastest on 32-column tiles
-}
-
-// bspline_dev_layer's coef_range: 2^e is the power of two above the largest coefficient.  Exponents so far out that the products' scale
-// would leave fp32's normal range are not recorded.
-static int32_t coef_range(float largest, float smallest_edge) {
-  int e;
-  (void)std::frexp(largest, &e);
-  const bool even = std::isfinite(largest) && largest > 0.0f && smallest_edge >= std::ldexp(1.0f, e - 16);
-  return (even && e >= -60 && e <= 60) ? LUTKAN_COEF_RANGE_BIAS + e : 0;
 }
 
 int choose_coef_jt(int m) {
@@ -268,21 +258,8 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
       if (!(tau_h[r] < tau_h[r + 1])) return fail(LUTKAN_EINVAL, "lutkan_compile: knots of vector %d not strictly increasing at %d", h, r);
   }
   const size_t E = (size_t)d * m;
-  float largest_coef = 0.0f, smallest_edge = INFINITY;       // the largest magnitude, the least of the edges' own largest (zero edges aside)
-  for (size_t e = 0; e < E; ++e) {
-    const float *c = desc->coef + e * R;
-    float largest = 0.0f;
-    bool finite = true;
-    for (int r = 0; r < R; ++r) {
-      const float a = std::fabs(c[r]);
-      finite &= a <= std::numeric_limits<float>::max();
-      largest = a > largest ? a : largest;
-    }
-    for (int r = 0; !finite && r < R; ++r)
-      if (!std::isfinite(c[r])) return fail(LUTKAN_EINVAL, "lutkan_compile: coefficient %zu is not finite", e * R + r);
-    largest_coef = std::max(largest_coef, largest);
-    if (largest > 0.0f) smallest_edge = std::min(smallest_edge, largest);
-  }
+  for (size_t n = 0; n < E * R; ++n)
+    if (!std::isfinite(desc->coef[n])) return fail(LUTKAN_EINVAL, "lutkan_compile: coefficient %zu is not finite", n);
   if (with_base)
     for (size_t e = 0; e < E; ++e)
       if (!std::isfinite(desc->edge_base_scale[e]) || !std::isfinite(desc->edge_spline_scale[e]) || !std::isfinite(desc->edge_out_scale[e]))
@@ -413,7 +390,6 @@ extern "C" int lutkan_compile(const lutkan_layer_desc *desc, int32_t n_threads, 
     return fail(LUTKAN_EUNSUPPORTED, "lutkan_compile: %ld segments have an alpha or y_min too large for float16", n);
   }
 
-  if (!with_base) a->coef_range = coef_range(largest_coef, smallest_edge);     // (with the base branch the table holds other products)
   fill_info(a, d, m, K, L, G, scheme, desc->boundary, desc->oob, repr, desc->param_dtype, desc->knots_per_input, jt, n_tiles, lay, cjt, coef_blob);
   a->info.knot_span = desc->knot_span;
   *out = a;
@@ -547,7 +523,6 @@ extern "C" int bspline_dev_layer_init(const lutkan_artifact *a, bspline_dev_laye
   out->algo = LUTKAN_ALGO_AUTO;
   for (int r = 0; r < I.G + 2 * P + 1; ++r) out->ext_knots[r] = a->ext_knots[r];
   out->coef_table = nullptr;
-  out->coef_range = a->coef_range;
   out->knots_per_input = I.knots_per_input;
   out->input_ext_knots = nullptr;
   return LUTKAN_OK;

@@ -110,5 +110,4 @@ struct lutkan_artifact {
   std::vector<float> edge_base, edge_spline, edge_out;   // [E] each, empty for value_repr = phi
   std::vector<uint8_t> table;     // device LUT table, [t][i] slices
   std::vector<float> coef_table;  // device B-spline table, [t][i][R][jt]
-  int32_t coef_range = 0;         // see bspline_dev_layer
 };

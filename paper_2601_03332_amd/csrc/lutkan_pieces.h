@@ -19,24 +19,6 @@ __device__ __forceinline__ unsigned lutkan_round_bf16_pair(float a0, float a1) {
   return c.u;
 }
 
-// Two binary16 pieces instead of three bf16 ones: a = h + l / 2048, h rounded to binary16, l the scaled rest rounded to binary16.
-// 11 + 11 significand bits and the rest's sign hold 23 of the 24 bits: the rest is rounded in a quarter of all values, by
-// 2^-23 of a's binade (root mean square 4e-8).  The rest is scaled so that it keeps its bits down to a = 2^-12; below, the
-// two are off by 2^-36 at most.  The caller scales a into that range.  Three piece products, h h, h l and l h; the
-// dropped l l is at most 2^-22 of the product (root mean square 4e-8).
-typedef _Float16 lutkan_cut_f16x2 __attribute__((ext_vector_type(2)));
-constexpr float kLowPieceScale = 2048.0f;
-constexpr float kLargestBinary16 = 65504.0f;
-
-__device__ __forceinline__ void lutkan_cut2_pair(float a0, float a1, unsigned p[2]) {
-  union { lutkan_cut_f16x2 h; unsigned u; } high, low;
-  high.h = __builtin_convertvector(lutkan_cut_f32x2{a0, a1}, lutkan_cut_f16x2);
-  low.h = __builtin_convertvector(lutkan_cut_f32x2{fmaf((float)high.h.x, -kLowPieceScale, a0 * kLowPieceScale),
-                                                   fmaf((float)high.h.y, -kLowPieceScale, a1 * kLowPieceScale)}, lutkan_cut_f16x2);
-  p[0] = high.u;
-  p[1] = low.u;
-}
-
 constexpr float kLargestBf16 = 3.3895313892515355e38f;
 
 // The pieces of two values, packed (a0 in the lower halves): p[0] = h, p[1] = m, p[2] = l.  A value beyond the largest bf16 value

@@ -1385,8 +1385,8 @@ def test_forward_without_a_workspace(case):
     assert lk.lutkan_last_plan() == plan and torch.equal(y0, y2) and (stats[0] is None or torch.equal(stats[0], stats[2]))
 
 
-HALF_PIECE_CASES = [
-    # seed, d, m, G, boundary, oob, B: at least 120, 96, 80 inputs per work-group; 2, 3, 4 groups of slots; 128, 64 and 32 columns; inputs that end inside a stage
+LONG_SUM_CASES = [
+    # seed, d, m, G, boundary, oob, B: 80 inputs per work-group and more; 2, 3, 4 groups of slots; 128, 64 and 32 columns; inputs that end inside a stage
     (951, 121, 129, 5, CLOSED, CLIP_X, 32513),
     (952, 120, 64, 1, HALF_OPEN, ZERO_SPLINE, 66000),
     (953, 123, 20, 4, CLOSED, ZERO_SPLINE, 120001),
@@ -1396,16 +1396,22 @@ HALF_PIECE_CASES = [
     (957, 81, 128, 13, HALF_OPEN, ZERO_SPLINE, 65001),
     (958, 84, 60, 10, CLOSED, CLIP_X, 65000),
     (959, 83, 9, 11, HALF_OPEN, CLIP_X, 120000),
+    (960, 1001, 300, 10, CLOSED, ZERO_SPLINE, 2000),            # in chunks whose sums are added in a second pass
 ]
 
 
-@pytest.mark.parametrize("case", HALF_PIECE_CASES, ids=lambda c: f"seed{c[0]}")
-def test_bspline_layer_on_two_binary16_pieces(case):
-    """Against the oracle in 300 rows, the ends of the batch and rows with a NaN and infinities among them, and no further from the
-    oracle's 64 bits than the three bf16 pieces, which the same layer without its recorded magnitudes runs on.  Then
-    tables that their owner scales by powers of two: within the pieces' range the outputs scale with them but for the smallest
-    coefficients' last bits (2^-36 of a coefficient that is up to 2^3 here); beyond it, and far below it, the outputs are summed
-    term by term and agree to the rounding of such a sum (2^-24 for each of its d steps at most)."""
+def _long_sum_bound(d, G):
+    """Of the sum of the terms' magnitudes: 1.3e-6 for basis values, pieces and products (test_bspline_layer_keeps_small_basis_values), and a
+    unit in the last place for every addition: the matrix unit's, 8 inputs of one group of slots at a time, the two accumulators' and the chunks'."""
+    groups = 2 if G <= 5 else 3 if G <= 9 else 4
+    return 1.3e-6 + (d * groups / 8 + 16) * 2.0 ** -23
+
+
+@pytest.mark.parametrize("case", LONG_SUM_CASES, ids=lambda c: f"seed{c[0]}")
+def test_bspline_layer_of_many_inputs(case):
+    """Against the oracle in 300 rows, the ends of the batch and rows with a NaN and infinities among them.  Then tables that their owner
+    rewrites: scaled by powers of two, all of it or one column, every output is scaled likewise, to the bit; an infinite coefficient of
+    the last input shows in the rows on its support."""
     seed, d, m, G, boundary, oob, B = case
     w = random_layer(seed, d, m, G, 2, SYM_INT8, boundary, oob, B, uniform=True)
     s, x = w.layers[0], w.x
@@ -1413,28 +1419,63 @@ def test_bspline_layer_on_two_binary16_pieces(case):
     x[5, :] = np.inf
     x[B - 1, 0] = -np.inf
     art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.L, s.scheme, s.boundary, s.oob)
-    layer, other = art.bspline_to_device(DEV), art.bspline_to_device(DEV)
-    assert layer.c.coef_range != 0
-    other.c.coef_range = 0
+    layer = art.bspline_to_device(DEV)
     xg = torch.from_numpy(x).to(DEV)
-    _say(f"case two pieces d={d} m={m} G={G} boundary={boundary} oob={oob} B={B}")
-    y, y_bf16 = lk.bspline_kan_forward(layer, xg), lk.bspline_kan_forward(other, xg)
-    torch.cuda.synchronize()
-    assert not torch.equal(y[6:B - 1], y_bf16[6:B - 1]), lk.lutkan_last_plan()
+    _say(f"case many inputs d={d} m={m} G={G} boundary={boundary} oob={oob} B={B}")
+    y = lk.bspline_kan_forward(layer, xg)
+    plan = lk.lutkan_last_plan()
+    assert "slots" in plan and ("sum; " in plan) == (d == 1001), plan
     rng = np.random.Generator(np.random.PCG64(seed))
     rows = np.unique(np.concatenate([np.arange(40), np.arange(B - 40, B), rng.integers(0, B, 300)]))
     ref = oracle.bspline_forward(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.boundary, s.oob, x[rows])
-    _assert_close(y.cpu().numpy()[rows], ref, f"two pieces {w.name}")
-    live = np.isfinite(ref.y)
-    errors = [np.linalg.norm((v.cpu().numpy()[rows].astype(np.float64) - ref.y)[live]) for v in (y, y_bf16)]
-    assert errors[0] <= errors[1], errors
-    clean, held = y.cpu().numpy().astype(np.float64), layer.coef_table.clone()
-    live = np.isfinite(clean)
-    for exponent, steps in ((3, 1), (-9, 1), (20, d), (-30, d)):
+    _assert_close(y.cpu().numpy()[rows], ref, f"many inputs {w.name}")
+    held, bound = layer.coef_table.clone(), _long_sum_bound(d, G)
+    for exponent in (3, -9, 20, -30):
         layer.coef_table.copy_(held * 2.0 ** exponent)
-        scaled = lk.bspline_kan_forward(layer, xg).cpu().numpy().astype(np.float64) * 2.0 ** -exponent
-        assert np.array_equal(np.isfinite(scaled), live)
-        assert np.linalg.norm((scaled - clean)[live]) <= steps * 2.0 ** -24 * np.linalg.norm(clean[live]), exponent
+        scaled = lk.bspline_kan_forward(layer, xg)
+        assert torch.equal((scaled * 2.0 ** -exponent).nan_to_num(123.0), y.nan_to_num(123.0)), exponent
+    layer.coef_table.copy_(held)
+    table = layer.coef_table.view(art.info.coef_n_tiles, d, G + 3, art.info.coef_jt)
+    table[0, :, :, 1] *= 2.0 ** -40
+    scaled = lk.bspline_kan_forward(layer, xg)
+    scaled[:, 1] *= 2.0 ** 40
+    assert torch.equal(scaled.nan_to_num(123.0), y.nan_to_num(123.0))
+    layer.coef_table.copy_(held)
+    table[0, d - 1, 3, 1] = float("inf")
+    gather = layer.with_contract(boundary, oob, lk.ALGO_GATHER)
+    y, expect = lk.bspline_kan_forward(layer, xg).cpu().numpy()[rows], lk.bspline_kan_forward(gather, xg).cpu().numpy()[rows]
+    T, last = s.ext_knots[3:3 + G + 1], x[rows, d - 1]
+    masked = (oob == ZERO_SPLINE) & ~((last >= T[0]) & ((last <= T[-1]) if boundary == CLOSED else (last < T[-1])))
+    finite = np.where(masked[:, None], np.isfinite(ref.y), np.isfinite(expect))        # (the gather kernel multiplies a masked input's 0 too)
+    assert np.array_equal(np.isfinite(y), finite) and np.isinf(y[:, 1]).any()
+    assert np.array_equal(np.delete(np.isfinite(y), 1, axis=1), np.delete(np.isfinite(ref.y), 1, axis=1))
+    live = np.isfinite(y)
+    assert np.all(np.abs(y - ref.y)[live] <= (bound + d * 2.0 ** -21) * ref.A[live])      # (term by term: four products and additions an input)
+
+
+@pytest.mark.parametrize("exponent", [-20, -30, -40, -60])
+@pytest.mark.parametrize("case", [c for c in LONG_SUM_CASES if c[3] > 1], ids=lambda c: f"seed{c[0]}")
+def test_bspline_layer_of_many_inputs_keeps_small_coefficients(case, exponent):
+    """Every edge has a large coefficient, the first; the others are 2^exponent of it.  Rows whose inputs lie off its support are right
+    relative to the sum of their own terms, however small it is beside the table's largest value."""
+    seed, d, m, G, boundary, oob, B = case
+    w = random_layer(seed, d, m, G, 2, SYM_INT8, boundary, oob, 2, uniform=True)
+    s = w.layers[0]
+    coef = s.coef.copy()
+    coef[:, :, 1:] *= np.float32(2.0 ** exponent)
+    coef[:, :, 0] = np.copysign(np.float32(3.9), coef[:, :, 0])
+    T = s.ext_knots[3:3 + G + 1]
+    rng = np.random.Generator(np.random.PCG64(seed))
+    x = np.clip(rng.uniform(T[1], T[-1], size=(B, d)).astype(np.float32), T[1], np.nextafter(T[-1], np.float32(-np.inf)))
+    art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, coef, s.L, s.scheme, s.boundary, s.oob)
+    _say(f"case small coefficients d={d} m={m} G={G} 2^{exponent} B={B}")
+    y = lk.bspline_kan_forward(art.bspline_to_device(DEV), torch.from_numpy(x).to(DEV))
+    assert "slots" in lk.lutkan_last_plan()
+    rows = np.unique(rng.integers(0, B, 200))
+    ref = oracle.bspline_forward(s.d, s.m, s.G, s.p, s.ext_knots, coef, s.boundary, s.oob, x[rows])
+    worst = float(np.max(np.abs(y.cpu().numpy()[rows].astype(np.float64) - ref.y) / ref.A))
+    _say(f"  worst {worst:.3g} of the terms, bound {_long_sum_bound(d, G):.3g}")
+    assert worst <= _long_sum_bound(d, G), worst
 
 
 @pytest.mark.parametrize("G", [1, 5, 6, 9, 10, 13])

@@ -120,20 +120,6 @@ def test_device_struct_initialisers():
     assert I_tK_star(art, CLOSED) == art.knots[-1]
 
 
-@pytest.mark.parametrize("edges, exponent", [([1.0, 2.0], 2), ([3.9, 1e-3], 2), ([2.0 ** 20, 2.0 ** 5], 21), ([2.0 ** 20, 2.0 ** 4], None),
-                                             ([0.0, 0.25], -1), ([0.0, 0.0], None), ([1e30, 1e30], None), ([1e-25, 1e-25], None)])
-def test_recorded_magnitudes_of_the_coefficients(edges, exponent):
-    """Every coefficient below 2^e, every edge that is not all zero up to at least 2^(e-16); else nothing is recorded."""
-    coef = np.zeros((1, len(edges), 8), np.float32)
-    coef[0, :, 3] = edges
-    coef[0, :, 5] = np.float32(-0.5) * np.asarray(edges, np.float32)
-    tau = (-1.0 + (np.arange(12) - 3) * 0.4).astype(np.float32)
-    art = lk.lutkan_compile(1, len(edges), 5, 3, tau, coef, 2, SYM_INT8, CLOSED, CLIP_X)
-    bl = binding._SplineDevLayer()
-    assert lk.load_library().bspline_dev_layer_init(art._h, C.byref(bl)) == 0
-    assert bl.coef_range == (0 if exponent is None else 128 + exponent)
-
-
 def I_tK_star(art, boundary):
     return art.info.tK_star
 
