@@ -6,7 +6,7 @@
 //   locate   its threads run steps 1-4 of Sec. 4.5 on the row's inputs and leave the records in LDS (every column tile
 //            repeats this: a few instructions per input against the 64 edges it serves)
 //   gather   LPR lanes own 4 adjacent columns each, so a wave is 64/LPR groups and the row has WPR*64/LPR of them; group g
-//            takes the inputs g, g + groups, ..., four at a time with all their table reads in flight (256 inputs on
+//            takes the inputs g, g + groups, ..., four or two at a time with all their table reads in flight (256 inputs on
 //            64-column tiles: one round trip to L2), with the arithmetic of the gather kernel
 //   sum      a fixed butterfly over the groups of a wave, then over the waves through LDS, in wave order
 // No workspace, no partial sums in memory, bit-reproducible; nearer to a 64-bit evaluation than the passes (short sums).
@@ -168,12 +168,29 @@ __global__ __launch_bounds__(kRowsWaves * 64, DEPTH == 2 ? 8 : 4) void lutkan_ro
   }
 }
 
+int64_t rows_groups(int64_t B, int wpr, int n_tiles) {
+  const int rows = kRowsWaves / wpr;
+  return (B + rows - 1) / rows * n_tiles;
+}
+
+size_t rows_lds(int jt, int wpr, int d) { return (size_t)kRowsWaves * jt * 4 + (size_t)(kRowsWaves / wpr) * d * 16 + (LUTKAN_MAX_K + 1) * 4; }
+
+// Four rows per work-group, more work-groups than compute units, and LDS for two on each (up to 1211 inputs on 64-column tiles; LDS is
+// handed out in pieces of 1280 bytes): two share a unit, if their registers let them.
+bool two_on_a_unit(int64_t B, int n_tiles, int jt, int wpr, int d) {
+  return wpr == 4 && rows_groups(B, wpr, n_tiles) > 256 && 2 * round_up((int64_t)rows_lds(jt, wpr, d), 1280) <= lutkan::kLdsPerWorkGroup;
+}
+
+// inputs of every group in a round; see launch_rows_depth
+int rows_depth(int64_t B, int n_tiles, int jt, int wpr, int d) {
+  return (d <= 2 * wpr * (64 / (jt / 4)) || two_on_a_unit(B, n_tiles, jt, wpr, d)) ? 2 : 4;
+}
+
 template <int SCHEME, int LPR, int WPR, int DEPTH>
 int launch_rows_kernel(const RowsArgs &ra, hipStream_t s) {
-  constexpr int kRows = kRowsWaves / WPR;
-  const int64_t groups = (ra.B + kRows - 1) / kRows * ra.n_tiles;
+  const int64_t groups = rows_groups(ra.B, WPR, ra.n_tiles);
   if (groups > 0x7fffffffLL) return fail(LUTKAN_EUNSUPPORTED, "lutkan_rows_kernel: B * m too large for one launch");
-  const size_t lds = (size_t)kRowsWaves * 16 * LPR + (size_t)kRows * ra.d * 16 + (LUTKAN_MAX_K + 1) * 4;
+  const size_t lds = rows_lds(4 * LPR, WPR, ra.d);
   static LdsCap raised;
   if (int rc = raise_lds_cap(lutkan_rows_kernel<SCHEME, LPR, WPR, DEPTH>, &raised, "lutkan_rows_kernel")) return rc;
   hipLaunchKernelGGL((lutkan_rows_kernel<SCHEME, LPR, WPR, DEPTH>), dim3((unsigned)groups), dim3(kRowsWaves * 64), lds, s, ra);
@@ -181,15 +198,14 @@ int launch_rows_kernel(const RowsArgs &ra, hipStream_t s) {
 }
 
 // Two inputs a round where no group has more (a round reads the rows of the inputs that it lacks again), or where more work-groups of four
-// rows than compute units wait for one another: two run on a unit then, which is worth more than the longer rounds.  Replayed,
+// rows than compute units wait for one another and the LDS holds two: two run on a unit then, which is worth more than the longer rounds
+// (with one on a unit they cost: 1230 -> 64 at 1100 rows 63 -> 76, 1300 -> 64 66 -> 80).  Replayed,
 // us, four -> two: 64 -> 1024 at 16 rows 3.75 -> 3.40, 30 -> 700 at 500 20.3 -> 12.2, 11 -> 880 at 422 16.7 -> 9.8; 100 -> 200 at 600 15.4 -> 11.1,
 // 64 -> 1000 at 300 17.6 -> 13.0, 450 -> 200 at 300 33.5 -> 29.4, 256 -> 256 at 400 16.4 -> 14.6, 64 -> 64 at 1500 7.3 -> 6.0; but 256 -> 256 at 200 rows
 // (200 work-groups) 8.8 -> 10.2, 450 -> 200 at 100 rows with 16 waves a row 11.6 -> 12.0.
 template <int SCHEME, int LPR, int WPR>
 int launch_rows_depth(const RowsArgs &ra, hipStream_t s) {
-  constexpr int kRows = kRowsWaves / WPR;
-  const bool two = ra.d <= 2 * WPR * (64 / LPR) || (WPR == 4 && (ra.B + kRows - 1) / kRows * ra.n_tiles > 256);
-  return two ? launch_rows_kernel<SCHEME, LPR, WPR, 2>(ra, s) : launch_rows_kernel<SCHEME, LPR, WPR, 4>(ra, s);
+  return rows_depth(ra.B, ra.n_tiles, 4 * LPR, WPR, ra.d) == 2 ? launch_rows_kernel<SCHEME, LPR, WPR, 2>(ra, s) : launch_rows_kernel<SCHEME, LPR, WPR, 4>(ra, s);
 }
 
 template <int SCHEME, int LPR>
@@ -213,8 +229,7 @@ int launch_rows_width(const RowsArgs &ra, int jt, int wpr, hipStream_t s) {
 namespace lutkan {
 
 // The launch shape by a cost model (microseconds; constants from 30 -> 1000 ... 1024 -> 64 layers at 1 to 4000 rows): 3.5 for
-// launch, locate and sum; then 2.9 (3.2 with four rows, 1.6 where these are more than one work-group per compute unit and so run two
-// on a unit) per round of 512 work-groups -- 3.5 more where every input has its own
+// launch, locate and sum; then 2.9 (3.2 with four rows, 1.6 where two work-groups share a unit) per round of 512 work-groups -- 3.5 more where every input has its own
 // knots, read from memory -- and the table bytes a batch requests, in lines of 128, at 15 TB/s, or 1.3 per dependent round
 // of a wave's walk over its inputs, whichever is longer.
 // (1.6: the passes -> this kernel, replayed, 100 -> 200 at 1000 / 1500 rows 19.1 -> 14.1 / 20.3 -> 18.7, 150 -> 150 at 1000 25.3 -> 19.3, 32 -> 300 at 1500
@@ -225,11 +240,11 @@ RowsPlan rows_plan(const lutkan_dev_layer *l, int64_t B) {
   const BlobLayout lay = blob_layout(l->K, l->L, l->jt, l->scheme, l->value_repr, l->param_dtype);
   const double bytes = (double)B * l->n_tiles * l->d * (std::max(128, 2 * l->jt) + std::max(128, lay.param_row_bytes) + (lay.params_off ? std::max(128, lay.params_off) : 0));
   for (int wpr = 16; wpr >= 4; wpr -= 12) {
-    const int rows = kRowsWaves / wpr, inputs_per_round = 4 * wpr * (64 / (l->jt / 4));
-    const int64_t groups = (B + rows - 1) / rows * l->n_tiles;
-    const double rounds = std::max(1.0, (double)groups / 512.0);
-    const double per_round = (wpr == 16 ? 2.9 : groups > 256 ? 1.6 : 3.2) + (l->knots_per_input ? 3.5 : 0.0);
-    const double cost = 3.5 + std::max(rounds * per_round + bytes / 15e6, 1.3 * ((l->d + inputs_per_round - 1) / inputs_per_round));
+    const int row_groups = wpr * (64 / (l->jt / 4)), inputs_per_round = 4 * row_groups;
+    const double rounds = (double)rows_groups(B, wpr, l->n_tiles) / 512.0;
+    const bool two = two_on_a_unit(B, l->n_tiles, l->jt, wpr, l->d);
+    const double per_round = (wpr == 16 ? 2.9 : two ? 1.6 : 3.2) + (l->knots_per_input ? 3.5 : 0.0);
+    const double cost = 3.5 + std::max(std::max(1.0, rounds) * per_round + bytes / 15e6, 1.3 * ((l->d + inputs_per_round - 1) / inputs_per_round));
     if (cost < best.cost) best = RowsPlan{wpr, cost};
   }
   return best;
@@ -256,7 +271,7 @@ int rows_forward(const lutkan_dev_layer *l, const RowsPlan &plan, const float *x
   const int rc = (l->scheme == LUTKAN_SYM_INT8) ? launch_rows_width<LUTKAN_SYM_INT8>(ra, l->jt, plan.waves_per_row, s)
                                                 : launch_rows_width<LUTKAN_ASYM_UINT8>(ra, l->jt, plan.waves_per_row, s);
   if (rc) return rc;
-  plan_note("rows wpr=%d; ", plan.waves_per_row);
+  plan_note("rows wpr=%d depth=%d; ", plan.waves_per_row, rows_depth(B, l->n_tiles, l->jt, plan.waves_per_row, l->d));
   return LUTKAN_OK;
 }
 

@@ -1834,7 +1834,21 @@ ROUND_CASES = [
     (966, 100, 100, 5, 64, ASYM_UINT8, CLOSED, CLIP_X, 1021, False, True, False),
     (967, 47, 260, 7, 16, SYM_INT8, HALF_OPEN, CLIP_X, 600, False, False, True),
     (968, 1, 500, 5, 32, ASYM_UINT8, CLOSED, ZERO_SPLINE, 160, False, False, False),
+    (969, 1211, 64, 5, 16, SYM_INT8, CLOSED, CLIP_X, 1025, False, False, False),           # the most inputs whose records let two share a unit
+    (970, 1212, 64, 5, 16, SYM_INT8, HALF_OPEN, ZERO_SPLINE, 1025, False, False, False),
 ]
+
+
+def test_rounds_of_two_where_two_work_groups_share_a_compute_unit():
+    """The kernel for a few rows: two inputs a round where more work-groups than compute units wait and the LDS holds two of them, or where
+    no group has more; four else."""
+    for d, m, B, depth in ((128, 64, 9, 2), (256, 64, 1020, 4), (256, 64, 1025, 2), (1211, 64, 1025, 2), (1212, 64, 1025, 4), (1220, 64, 1030, 4)):
+        w = random_layer(971, d, m, 5, 16, SYM_INT8, CLOSED, CLIP_X, B)
+        s = w.layers[0]
+        art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.L, s.scheme, s.boundary, s.oob)
+        lk.lutkan_forward(art.to_device(DEV), torch.from_numpy(w.x).to(DEV))
+        plan = lk.lutkan_last_plan()
+        assert plan.startswith("rows wpr=") and plan.endswith(f" depth={depth}; "), (d, m, B, plan)
 
 
 @pytest.mark.parametrize("case", ROWS_CASES + ROUND_CASES, ids=lambda c: f"seed{c[0]}")
