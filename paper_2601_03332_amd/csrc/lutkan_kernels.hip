@@ -1283,9 +1283,9 @@ int forward_impl(const lutkan_dev_layer *l, const float *x, int64_t B, float *y,
   if (l->algo == LUTKAN_ALGO_AUTO && phases == (kLocate | kEdges) && !trace && !q01_out && !overlap(x, B * l->d, y, B * l->m)) {
     const double table = (double)l->n_tiles * l->d * l->blob_bytes;
     const double passes = 5.0 + (double)B * l->d * 12.0 / 4.7e6 + (tiled ? (wide ? tpw.cost : tp.cost) : 10.0 + (double)B * l->d * l->n_tiles * (2.0 * l->jt + lay.param_row_bytes) / 9.4e6);
-    const lutkan::RowsPlan rp = table <= 128.0 * 1024 * 1024 ? lutkan::rows_plan(l, B) : lutkan::RowsPlan{0, 1e300};
+    const lutkan::RowsPlan rp = table <= 128.0 * 1024 * 1024 ? lutkan::rows_plan(l, B) : lutkan::RowsPlan{0, 1e300, 1e300};
     const lutkan::NarrowPlan np = tiled ? lutkan::narrow_plan(l, B, need) : lutkan::NarrowPlan{0, 1, l->d, 0, 1e300};
-    if (rp.waves_per_row && rp.cost < std::min(passes, np.cost)) {
+    if (rp.waves_per_row && rp.cost < np.cost && rp.against_passes < passes) {
       if (int rc = lutkan::rows_forward(l, rp, x, B, y, hip_stream)) return rc;
       return stats ? count_oob(l, x, B, stats, s) : LUTKAN_OK;
     }
