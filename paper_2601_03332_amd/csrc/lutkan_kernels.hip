@@ -870,10 +870,13 @@ __global__ __launch_bounds__(kChainWaves * 64) void lutkan_chain_kernel(const Ch
     const int g = wr * S + (lane >> Y.jt_log2);
     const int stride = WPR * S;
     float acc = 0.0f;
-    // Rounds of eight (a row on four waves, where the registers cost no occupancy), four, two and one inputs of every group, their table
-    // reads in flight together: in rounds of four only, the last one read its missing inputs' rows again.  Microseconds replayed,
-    // so -> with them: 78 -> 16 -> 2 at 256 rows 6.08 -> 5.77, 10 -> 8 with base at 1024 3.93 -> 3.78, 78 -> 32 -> 16 -> 1 with base at 256 9.00 ->
-    // 8.32, 16 -> 2 at 20000 11.2 -> 9.6, 40 -> 8 at 8000 7.8 -> 6.8, 64 -> 64 at 512 5.82 -> 5.75, 300 -> 8 at 900 the same.
+    // Rounds of four inputs of every group, their table reads in flight together, then one of two or one (in rounds of four only, the
+    // last one read its missing inputs' rows again; three left are a round of four: two rounds would wait twice).  The short ones
+    // are laid out behind the kernel's end: skipping over their code costs 0.1 us, an instruction fetch.  Microseconds replayed, rounds of
+    // four only -> these (rounds of eight as well, in brackets): 78 -> 16 at 256 rows 4.56 -> 4.35 (4.37), 10 -> 8 with base at 1024 4.22 -> 3.90
+    // (3.90), 16 -> 2 at 20000 12.1 -> 10.1, 40 -> 8 at 8000 8.55 -> 7.37, 300 -> 8 at 900 7.37 -> 7.11 (7.32), 64 -> 64 at 512 6.27 -> 6.30 (6.18), 128 -> 32
+    // at 256 6.05 -> 6.17 (6.06); 836 single layers of up to 256 inputs 0.94 of the time, the worst 1.027 (1.032; 1.07 with two and one
+    // for three and the short rounds in the way).
     auto round = [&](auto count, int i0) {
       constexpr int U = decltype(count)::value;
       u32x4 rec[U];
@@ -912,17 +915,12 @@ __global__ __launch_bounds__(kChainWaves * 64) void lutkan_chain_kernel(const Ch
         }
       }
     };
-    int i0 = g, left = (Y.d - __builtin_amdgcn_readfirstlane(wr * S) + stride - 1) / stride;      // inputs of the wave's first group: no group has more
-    if constexpr (WPR == kChainWaves) {
-      for (; left >= 8; left -= 8, i0 += 8 * stride) round(std::integral_constant<int, 8>{}, i0);
+    int i0 = g, left = (Y.d - __builtin_amdgcn_readfirstlane(wr * S) + stride - 1) >> ((WPR == kChainWaves ? 8 : 6) - Y.jt_log2);      // inputs of the wave's first group: no group has more
+    for (; left >= 3; left -= 4, i0 += 4 * stride) round(std::integral_constant<int, 4>{}, i0);
+    if (__builtin_expect(left > 0, 0)) {
+      if (left == 2) round(std::integral_constant<int, 2>{}, i0);
+      else round(std::integral_constant<int, 1>{}, i0);
     }
-    for (; left >= 4; left -= 4, i0 += 4 * stride) round(std::integral_constant<int, 4>{}, i0);
-    if (left >= 2) {
-      round(std::integral_constant<int, 2>{}, i0);
-      left -= 2;
-      i0 += 2 * stride;
-    }
-    if (left >= 1) round(std::integral_constant<int, 1>{}, i0);
     for (int off = jt; off < 64; off <<= 1) acc += __shfl_xor(acc, off, kWave);          // fixed order over a wave's groups
     if (lane < jt) s_part[wave * kChainMaxColumns + lane] = acc;
     __syncthreads();                                     // the waves' sums are in place; everyone is done with the records
