@@ -418,8 +418,8 @@ constexpr double kBaseProductMinEdges = 5e8;      // batch * d * m from which th
 // on the stored values.
 //
 // PIPE: how the copies, the barrier and the LDS reads of consecutive inputs overlap.
-//   2  two buffers.  Every input ends in "wait for my copies of the next slice, read its first records, barrier", and every wave
-//      then refills its read pipeline (addresses -> codes and scales, an LDS round trip) at the same moment, with
+//   2  two buffers.  Every input ends in "wait for my copies of the next slice, read its first records (RECORDS_AHEAD), barrier", and
+//      every wave then refills its read pipeline (addresses -> codes and scales, an LDS round trip) at the same moment, with
 //      nothing else on the SIMD to cover it.
 //   3  three buffers, reads carried across inputs (no BASE, NP >= 2; where three buffers fit the LDS).  The slice of
 //      input i+2 is copied while input i is processed; the one barrier per input (before input i: "everyone has
@@ -448,6 +448,9 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
   static_assert(PIPE == 2 || (PIPE == 3 && !BASE && NP >= 2) || (PIPE == 4 && !BASE), "carried reads need two row steps of the same input; three buffers go with 8-byte records");
   constexpr int NBUF = (PIPE == 2) ? 2 : 3;
   constexpr bool CARRY = (PIPE == 3), DEEP = (PIPE == 4);
+  // Two buffers: the next input's first records are read ahead of the barrier where an input has four row steps and more.  With one
+  // or two, a launch of few rows, it is slower: 9 -> 308, uint8, at 1995 rows 10.9 -> 11.1 us, 15 -> 228 with base at 1506 14.45 -> 14.8.
+  constexpr bool RECORDS_AHEAD = (PIPE == 2 && NP >= 4);
   // Row steps between the issue of a step's code and parameter reads and their use.  One step of the byte form (18
   // vector instructions on each of a SIMD's four waves) covers the LDS latency; one of the wide forms (12 or 13) does
   // not: the waves of the binary16 form spent 13 % of their cycles waiting for LDS reads, so they read two steps ahead.
@@ -588,7 +591,7 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
     columns_of(0, cc, cp);
     read_records(rec_area + hrow * RB);
     read_codes(cc, cp);
-  } else if (PIPE == 2) {
+  } else if (RECORDS_AHEAD) {
     read_records(rec_area + hrow * RB);
   }
 
@@ -624,7 +627,7 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
     if (CARRY) columns_of(ahead, ahead_codes, ahead_params);
     f32x4 base_gain = {0.f, 0.f, 0.f, 0.f};
     if (BASE) base_gain = *reinterpret_cast<const f32x4 *>(slice + sub * 16) * (VALUES ? 1.0f : kTwoToMinus24);   // (the sums on fp32 values are not scaled)
-    if (DEEP) read_records(rec_buf);
+    if (!CARRY && !RECORDS_AHEAD) read_records(rec_buf);
     if (!CARRY) read_codes(col_codes, col_params);
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -718,7 +721,11 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
       for (int k = 0; k + 1 < AHEAD; ++k) fq[k] = fq[k + 1];
       fq[AHEAD - 1] = f_new;
     }
-    if (PIPE == 2) {
+    if (PIPE == 2 && !RECORDS_AHEAD) {
+      wait_all_vector_loads();                         // my share of the next slice has landed ...
+      lds_barrier();                                   // ... everyone's has, and everyone is done with this one
+    }
+    if (RECORDS_AHEAD) {
       wait_all_vector_loads();                         // my share of the next slice and my records have landed ...
       // The records of the next input's first row steps, the wave's own copies, are read ahead of the barrier (after the last input
       // this one's again, unused) and the barrier is the bare instruction: one LDS round trip behind it instead of two.  Every read
