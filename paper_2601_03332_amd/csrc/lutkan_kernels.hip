@@ -456,10 +456,11 @@ __global__ __launch_bounds__(NW * 64) void lutkan_tiled_kernel(const EdgeArgs a)
   // not: the waves of the binary16 form spent 13 % of their cycles waiting for LDS reads, so they read two steps ahead.
   constexpr int AHEAD = (CB > 1) ? 2 : 1;
   static_assert(!CARRY || NP > AHEAD, "carried reads: the pipeline must fit into one input's row steps");
-  // Records are read one row step ahead of the reads they address, three where the byte form carries its reads from input to input:
+  // Records are read one row step ahead of the reads they address, three where the byte form carries its reads from input to input
+  // over eight row steps and more (over four 61 -> 742 at 866 rows and the like take 1 % longer with them):
   // a step waits for its record, and everything older, at its start.  1024 -> 1024 at 32768 / 4096 rows, int8, 4765 / 629 -> 4713 / 622
   // us (four ahead 4732 / 624; in PIPE 2 uint8 at 32768 rows 5240 -> 5353; the wide forms: nothing, 16-bit codes 1 % slower).
-  constexpr int LEAD = (CARRY && CB == 1 && NP > AHEAD + 2) ? 2 : 0, RECS = AHEAD + LEAD;
+  constexpr int LEAD = (CARRY && CB == 1 && NP >= 8) ? 2 : 0, RECS = AHEAD + LEAD;
   extern __shared__ __align__(16) unsigned char lds[];
   constexpr int JT = 4 * LPR;
   constexpr int RPS = 64 / LPR;
