@@ -827,3 +827,26 @@ def test_product_package_does_not_touch_the_oracle():
         checked += 1
         assert "import oracle" not in text and "from oracle" not in text and "lutkan_oracle" not in text and "lko_" not in text, path
     assert checked >= 10
+
+
+# ---------------------------------------------------------------- the module of native forward calls
+@pytest.mark.parametrize("content", [None, b"", b"\x7fELF half a library"], ids=["missing", "empty", "half_written"])
+def test_without_the_native_module_calls_take_the_general_path(content, tmp_path, monkeypatch):
+    """Whatever keeps the module from loading is told once, and nothing is compiled in a call."""
+    torch = pytest.importorskip("torch")
+    monkeypatch.setattr(binding._build, "CALL", str(tmp_path / "_lutkan_call.so"))
+    monkeypatch.setattr(binding._build, "build_call", lambda *a, **k: pytest.fail("compiled in a call"))
+    monkeypatch.setattr(binding, "_native", None)
+    if content is not None:
+        (tmp_path / "_lutkan_call.so").write_bytes(content)
+    w = cfg1()
+    s = w.layers[0]
+    art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.L, s.scheme, s.boundary, s.oob)
+    layer, x = art.to_device("cpu"), torch.from_numpy(w.x)
+    calls = [(lk.lutkan_forward, layer), (lk.lutkan_model_forward, [layer]), (lk.bspline_kan_forward, art.bspline_to_device("cpu"))]
+    with pytest.warns(RuntimeWarning, match="_lutkan_call") as told:
+        for call, held in calls:
+            with pytest.raises(lk.LutKanError, match="CUDA tensor"):             # the general path's own words
+                call(held, x)
+    assert len(told) == 1
+    assert [f(held, x) for f, held in zip((binding._native.lut_forward, binding._native.lut_model_forward, binding._native.spline_forward), (h for _, h in calls))] == [None] * 3
