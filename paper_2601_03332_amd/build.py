@@ -1,9 +1,10 @@
 """Builds liblutkan.so (host LUT compiler + gfx950 kernels) in-tree with hipcc, and beside it the binding's forward calls as a
-CPython module (_lutkan_call.so, host code against torch's headers)."""
+CPython module (_lutkan_call.so, host code against torch's headers), which the library does not need."""
 from __future__ import annotations
 
 import os
 import subprocess
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -56,6 +57,7 @@ def build_call(verbose: bool = False) -> str:
 
 
 def build(verbose: bool = False) -> str:
+    """The library; then the module, without which (no torch, no g++) the binding works and says so."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
     def compile_one(src: str) -> str:
@@ -73,11 +75,14 @@ def build(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, os.cpu_count() or 1, 8)) as pool:
         call = pool.submit(build_call, verbose)
         objs = list(pool.map(compile_one, SOURCES))
-        call.result()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs + ["-lpthread"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    try:
+        call.result()
+    except Exception as error:
+        warnings.warn(f"{CALL} was not built ({type(error).__name__}: {error}); {LIB} was", RuntimeWarning)
     return LIB
 
 

@@ -850,3 +850,23 @@ def test_without_the_native_module_calls_take_the_general_path(content, tmp_path
                 call(held, x)
     assert len(told) == 1
     assert [f(held, x) for f, held in zip((binding._native.lut_forward, binding._native.lut_model_forward, binding._native.spline_forward), (h for _, h in calls))] == [None] * 3
+
+
+def test_the_library_is_built_without_torch_and_gxx(tmp_path, monkeypatch):
+    """A machine that cannot build the module still links liblutkan.so, and is told."""
+    lib_build, ran = binding._build, []
+
+    def run(cmd, **kwargs):
+        ran.append(cmd)
+        assert cmd[0] != "g++"
+    monkeypatch.setattr(lib_build, "LIB", str(tmp_path / "liblutkan.so"))
+    monkeypatch.setattr(lib_build.subprocess, "run", run)
+    for missing in (FileNotFoundError("g++"), ModuleNotFoundError("torch")):
+        ran.clear()
+
+        def build_call(verbose=False):
+            raise missing
+        monkeypatch.setattr(lib_build, "build_call", build_call)
+        with pytest.warns(RuntimeWarning, match="not built"):
+            assert lib_build.build() == lib_build.LIB
+        assert len(ran) == len(lib_build.SOURCES) + 1 and ran[-1][ran[-1].index("-o") + 1] == lib_build.LIB
