@@ -153,7 +153,7 @@ def _load_native():
     import importlib.util
     torch, lib = _torch(), load_library()
     try:
-        spec = importlib.util.spec_from_file_location("_lutkan_call", _build.CALL)
+        spec = importlib.util.spec_from_file_location("_lutkan_call", _build.call_module())
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
         entries = (lib.lutkan_forward_or_workspace, lib.lutkan_forward, lib.lutkan_model_forward_or_workspace, lib.lutkan_model_forward,
@@ -163,7 +163,7 @@ def _load_native():
         return module
     except Exception as error:
         import warnings
-        warnings.warn(f"{_build.CALL} was not loaded ({type(error).__name__}: {error}); forward calls go through ctypes, about 1.3 us of host time "
+        warnings.warn(f"_lutkan_call was not loaded ({type(error).__name__}: {error}); forward calls go through ctypes, about 1.3 us of host time "
                       "a call more (python -m paper_2601_03332_amd.build builds it)", RuntimeWarning, stacklevel=4)
         return _GeneralPath
 

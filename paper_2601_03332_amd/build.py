@@ -1,5 +1,5 @@
 """Builds liblutkan.so (host LUT compiler + gfx950 kernels) in-tree with hipcc, and beside it the binding's forward calls as a
-CPython module (_lutkan_call.so, host code against torch's headers), which the library does not need."""
+CPython module (_lutkan_call.*.so, host code against torch's headers), which the library does not need."""
 from __future__ import annotations
 
 import os
@@ -11,7 +11,6 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.environ.get("LUTKAN_LIBRARY", os.path.join(HERE, "liblutkan.so"))
-CALL = os.path.join(HERE, "_lutkan_call.so")
 CALL_SOURCE = os.path.join(CSRC, "lutkan_call.cpp")
 SOURCES = [os.path.join(CSRC, "lutkan_compile.cpp"), os.path.join(CSRC, "lutkan_kernels.hip"),
            os.path.join(CSRC, "bspline_kernels.hip"), os.path.join(CSRC, "lutkan_probes.hip"),
@@ -41,19 +40,42 @@ def stale() -> bool:
     return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS)
 
 
-def build_call(verbose: bool = False) -> str:
-    """The CPython module.  torch's libraries are named, not searched for at run time: the binding imports torch before the module."""
-    import importlib.util
+def call_module() -> str:
+    """Where the CPython module of these sources for this interpreter and this torch lies, built or not: it reads structures of both, so
+    that a module of other sources, another Python or another torch must not be taken for it."""
+    import hashlib
     import sysconfig
-    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    import torch
+    digest = hashlib.sha256()
+    for path in (CALL_SOURCE, os.path.join(ROOT, "include", "lutkan.h")):
+        with open(path, "rb") as f:
+            digest.update(f.read())
+    return os.path.join(HERE, f"_lutkan_call.{digest.hexdigest()[:12]}.torch-{torch.__version__}{sysconfig.get_config_var('EXT_SUFFIX')}")
+
+
+def build_call(verbose: bool = False) -> str:
+    """The CPython module, complete under its name or not there at all.  torch's libraries are named, not searched for at run time: the
+    binding imports torch before the module."""
+    import sysconfig
+    import tempfile
+    import torch
+    path, torch_dir = call_module(), os.path.dirname(torch.__file__)
+    handle, unfinished = tempfile.mkstemp(prefix=".lutkan_call.", suffix=".so", dir=os.path.dirname(path))
+    os.close(handle)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include")]
-    for path in (os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]):
-        cmd += ["-isystem", path]
-    cmd += [CALL_SOURCE, "-o", CALL, "-L" + os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    for include in (os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]):
+        cmd += ["-isystem", include]
+    cmd += [CALL_SOURCE, "-o", unfinished, "-L" + os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
-    return CALL
+    try:
+        subprocess.run(cmd, check=True)
+        os.chmod(unfinished, 0o755)
+        os.replace(unfinished, path)
+    finally:
+        if os.path.exists(unfinished):
+            os.unlink(unfinished)
+    return path
 
 
 def build(verbose: bool = False) -> str:
@@ -82,7 +104,7 @@ def build(verbose: bool = False) -> str:
     try:
         call.result()
     except Exception as error:
-        warnings.warn(f"{CALL} was not built ({type(error).__name__}: {error}); {LIB} was", RuntimeWarning)
+        warnings.warn(f"_lutkan_call was not built ({type(error).__name__}: {error}); {LIB} was", RuntimeWarning)
     return LIB
 
 

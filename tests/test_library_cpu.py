@@ -834,7 +834,7 @@ def test_product_package_does_not_touch_the_oracle():
 def test_without_the_native_module_calls_take_the_general_path(content, tmp_path, monkeypatch):
     """Whatever keeps the module from loading is told once, and nothing is compiled in a call."""
     torch = pytest.importorskip("torch")
-    monkeypatch.setattr(binding._build, "CALL", str(tmp_path / "_lutkan_call.so"))
+    monkeypatch.setattr(binding._build, "call_module", lambda: str(tmp_path / "_lutkan_call.so"))
     monkeypatch.setattr(binding._build, "build_call", lambda *a, **k: pytest.fail("compiled in a call"))
     monkeypatch.setattr(binding, "_native", None)
     if content is not None:
@@ -870,3 +870,35 @@ def test_the_library_is_built_without_torch_and_gxx(tmp_path, monkeypatch):
         with pytest.warns(RuntimeWarning, match="not built"):
             assert lib_build.build() == lib_build.LIB
         assert len(ran) == len(lib_build.SOURCES) + 1 and ran[-1][ran[-1].index("-o") + 1] == lib_build.LIB
+
+
+def test_the_native_module_is_of_its_sources_and_its_torch_and_appears_whole(tmp_path, monkeypatch):
+    """Its name changes with the source, the header and torch; while it is compiled nothing lies there, and a failed build leaves nothing."""
+    torch = pytest.importorskip("torch")
+    lib_build = binding._build
+    names = [lib_build.call_module()]
+    source = tmp_path / "lutkan_call.cpp"
+    source.write_bytes(open(lib_build.CALL_SOURCE, "rb").read() + b"// changed")
+    monkeypatch.setattr(lib_build, "CALL_SOURCE", str(source))
+    names.append(lib_build.call_module())
+    monkeypatch.setattr(torch, "__version__", "0.0")
+    names.append(lib_build.call_module())
+    assert len(set(names)) == 3 and all(n.endswith(".so") and "cpython" in n for n in names)
+    monkeypatch.setattr(lib_build, "HERE", str(tmp_path / "package"))
+    (tmp_path / "package").mkdir()
+    path, outcome = lib_build.call_module(), []
+
+    def run(cmd, check):
+        out = cmd[cmd.index("-o") + 1]
+        assert os.path.dirname(out) == os.path.dirname(path) and not os.path.exists(path)
+        open(out, "wb").write(b"half")
+        if not outcome:
+            outcome.append("failed")
+            raise lib_build.subprocess.CalledProcessError(1, cmd)
+        open(out, "ab").write(b" and half")
+    monkeypatch.setattr(lib_build.subprocess, "run", run)
+    with pytest.raises(lib_build.subprocess.CalledProcessError):
+        lib_build.build_call()
+    assert os.listdir(lib_build.HERE) == []
+    assert lib_build.build_call() == path and os.listdir(lib_build.HERE) == [os.path.basename(path)]
+    assert open(path, "rb").read() == b"half and half"
