@@ -4,7 +4,8 @@
 // 78 -> 16 -> 2 at 256 rows 7.2 -> 6.5.
 //
 // A function takes the layer object(s) and x, makes the checks of binding._check_io, allocates y (and the workspace, if the call
-// needs one) with torch's allocator and calls the library on the current stream, without the interpreter's lock, as ctypes does.
+// needs one) with torch's allocator and calls the library on the current stream, both without the interpreter's lock, as torch's own
+// functions and ctypes do: an allocation may wait for the device, and the device for a thread that needs the lock.
 // It returns None, having done nothing, for anything but the plain case -- a strided CUDA tensor of torch's own class with no
 // dispatch or function mode active, a layer of the binding's own struct -- and for whatever the library refuses: the binding then
 // takes the general path, which serves it or says what is wrong.
@@ -104,28 +105,31 @@ PyObject *not_taken() {
   Py_RETURN_NONE;
 }
 
+struct WithoutLock {
+  PyThreadState *state = PyEval_SaveThread();
+  ~WithoutLock() { PyEval_RestoreThread(state); }
+};
+
 // once(needed): the call that runs without a workspace or says how much one takes; again(workspace, bytes): the call with one.
 template <typename Once, typename Again>
 PyObject *forward(const at::Tensor &x, long m, c10::Device device, const Once &once, const Again &again) {
   try {
     void *stream = nullptr;
     if (!stream_of(device, &stream)) return not_taken();
-    at::Tensor y = at::empty({x.size(0), m}, x.options().requires_grad(false));
-    const float *in = x.const_data_ptr<float>();
-    float *out = y.mutable_data_ptr<float>();
-    const int64_t B = x.size(0);
-    size_t needed = 0;
+    at::Tensor y;
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = once(in, B, out, &needed, stream);
-    Py_END_ALLOW_THREADS
-    if (rc == LUTKAN_OK && needed != 0) {
-      const at::Tensor workspace = workspace_of(needed, device);
-      void *const scratch = workspace.mutable_data_ptr();
-      const size_t bytes = (size_t)workspace.numel();
-      Py_BEGIN_ALLOW_THREADS
-      rc = again(in, B, out, scratch, bytes, stream);
-      Py_END_ALLOW_THREADS
+    {
+      const WithoutLock unlocked;
+      y = at::empty({x.size(0), m}, x.options().requires_grad(false));
+      const float *in = x.const_data_ptr<float>();
+      float *out = y.mutable_data_ptr<float>();
+      const int64_t B = x.size(0);
+      size_t needed = 0;
+      rc = once(in, B, out, &needed, stream);
+      if (rc == LUTKAN_OK && needed != 0) {
+        const at::Tensor workspace = workspace_of(needed, device);
+        rc = again(in, B, out, workspace.mutable_data_ptr(), (size_t)workspace.numel(), stream);
+      }
     }
     if (rc != LUTKAN_OK) return not_taken();
     return THPVariable_Wrap(y);
