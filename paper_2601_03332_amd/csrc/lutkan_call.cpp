@@ -157,8 +157,13 @@ PyObject *lut_model_forward(PyObject *, PyObject *const *args, Py_ssize_t n) {
   long d = 0, m = 0;
   c10::Device device(c10::kCPU);
   for (Py_ssize_t i = 0; i < count; ++i) {
+    if (i >= PySequence_Fast_GET_SIZE(args[0])) return not_taken();                  // reading an attribute may run code that changes the list
+    PyObject *const item = PySequence_Fast_GET_ITEM(args[0], i);
+    Py_INCREF(item);
     Layer layer;
-    if (!layer.read(PySequence_Fast_GET_ITEM(args[0], i), g.lut_struct, sizeof(lutkan_dev_layer))) return not_taken();
+    const bool ok = layer.read(item, g.lut_struct, sizeof(lutkan_dev_layer));
+    Py_DECREF(item);
+    if (!ok) return not_taken();
     if (i == 0) { d = layer.d; device = layer.device; }
     if (layer.device != device) return not_taken();
     m = layer.m;

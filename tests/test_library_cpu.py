@@ -902,3 +902,25 @@ def test_the_native_module_is_of_its_sources_and_its_torch_and_appears_whole(tmp
     assert os.listdir(lib_build.HERE) == []
     assert lib_build.build_call() == path and os.listdir(lib_build.HERE) == [os.path.basename(path)]
     assert open(path, "rb").read() == b"half and half"
+
+
+def test_native_model_call_survives_a_list_that_changes_under_it():
+    """Reading a layer's attributes may run its class's code, which may drop the list's items, the one that is read among them."""
+    torch = pytest.importorskip("torch")
+    native = binding._native_calls()
+    s = cfg1().layers[0]
+    art = lk.lutkan_compile(s.d, s.m, s.G, s.p, s.ext_knots, s.coef, s.L, s.scheme, s.boundary, s.oob)
+    layers = []
+
+    class Shrinks:
+        held = art.to_device("cpu")
+        d, m, device = held.d, held.m, held.device
+
+        def __getattribute__(self, name):
+            if name == "c":
+                layers.clear()
+            return getattr(type(self), name) if name != "c" else type(self).held.c
+
+    for _ in range(100):
+        layers[:] = [Shrinks() for _ in range(3)]
+        assert native.lut_model_forward(layers, torch.zeros(4, s.d)) is None and layers == []
