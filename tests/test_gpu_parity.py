@@ -2051,3 +2051,47 @@ def test_native_calls_take_the_plain_case_and_leave_the_rest_to_the_general_path
     assert native.lut_forward(broken, x) is None
     with pytest.raises(lk.LutKanError, match="lutkan_forward"):
         lk.lutkan_forward(broken, x)
+
+
+def test_native_calls_leave_deferred_and_traced_operators_to_the_general_path():
+    """Inference mode is the plain case; fake tensors, functional transforms, functionalisation, tracing and dispatch modes are not."""
+    from paper_2601_03332_amd import binding
+    from torch._subclasses import FakeTensorMode
+    from torch.utils._python_dispatch import TorchDispatchMode
+    native = binding._native_calls()
+    w = random_layer(984, 12, 20, 5, 16, SYM_INT8, CLOSED, CLIP_X, 40)
+    art, _ = _compile_both(w.layers[0])
+    layer, x = art.to_device(DEV), torch.from_numpy(w.x).to(DEV)
+    calls = [(native.lut_forward, lk.lutkan_forward, layer), (native.lut_model_forward, lk.lutkan_model_forward, [layer]),
+             (native.spline_forward, lk.bspline_kan_forward, art.bspline_to_device(DEV))]
+    expect = [general(held, x) for _, general, held in calls]
+
+    with torch.inference_mode():
+        for (call, general, held), y in zip(calls, expect):
+            for got in (call(held, x), call(held, x.clone()), general(held, x, y=torch.empty_like(y))):
+                assert torch.equal(got, y) and got.is_inference()
+
+    class Passes(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    taken = []
+
+    def ask(t):
+        taken.extend(call(held, t if t.dim() == 2 else t[None]) for call, _, held in calls)
+        return t + 1.0
+
+    with FakeTensorMode(allow_non_fake_inputs=True) as mode:
+        ask(mode.from_tensor(x))
+        ask(x)
+    with Passes():
+        ask(x)
+        assert torch.equal(lk.lutkan_forward(layer, x), expect[0])            # the general path serves it
+    torch.func.vmap(ask)(x)
+    torch.func.grad(lambda t: ask(t).sum())(x)
+    torch.func.jvp(ask, (x,), (torch.ones_like(x),))
+    torch.func.functionalize(ask)(x)
+    torch.jit.trace(ask, (x,), check_trace=False)
+    assert len(taken) == 3 * 8 and all(y is None for y in taken), [y is None for y in taken]
+    for (call, _, held), y in zip(calls, expect):                           # and nothing of it is left behind
+        assert torch.equal(call(held, x), y)
