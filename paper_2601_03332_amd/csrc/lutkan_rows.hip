@@ -233,12 +233,14 @@ namespace lutkan {
 // knots, read from memory -- and the table bytes a batch requests, in lines of 128, at 15 TB/s, or 1.3 per dependent round
 // of a wave's walk over its inputs, whichever is longer.
 // (1.6: the passes -> this kernel, replayed, 100 -> 200 at 1000 / 1500 rows 19.1 -> 14.1 / 20.3 -> 18.7, 150 -> 150 at 1000 25.3 -> 19.3, 32 -> 300 at 1500
-// 18.0 -> 16.5; with 1.4 for all launches of rounds of two 60 -> 100 at 300 rows 4.3 -> 6.6, 8 -> 600 at 1000 10.1 -> 14.7.)
-// Against the passes 1.6 is too low for up to 64 inputs that share their knots, whose passes, also priced too high, are a few
+// 18.0 -> 16.5; not with knots per input where a row's 256 lanes locate more than one input each from memory: 401 -> 64 at 1045 rows 23.7 -> 30.0,
+// 793 -> 28 at 1863 35.7 -> 51.2; with 1.4 for all launches of rounds of two 60 -> 100 at 300 rows 4.3 -> 6.6, 8 -> 600 at 1000 10.1 -> 14.7.)
+// Against the passes 1.6 is too low for up to 64 inputs that share their knots and several column tiles (one tile: the chain kernel
+// leaves its layers to this kernel at this price, and none was slower), whose passes, also priced too high, are a few
 // launches without partial sums: 1 -> 272 at 1104 rows 5.8 by the passes and 9.8 here, 2 -> 976 at 290 6.4 and 9.0, 34 -> 1000 at 870 22.0 and 32.5.
 // Such a launch is taken if 3.2 a round is less than the passes, or if a price fitted to 240 launches (3.4, 1.8 and 0.6 per input of a group for every round,
-// and a quarter of the bytes' time) is less by 5.5, and by 1 less for every 20 inputs: of 1490 drawn calls 1.6 alone moves 61 from the passes (geometric
-// mean 1.01 of their time, the worst 1.64), with this 26 at 0.82, the worst 1.12.
+// and a quarter of the bytes' time) is less by 5.5, and by 1 less for every 20 inputs: of 1890 drawn calls 1.6 alone moves 85 from the passes (geometric
+// mean 0.90 of their time, the worst 1.53), with this 49 at 0.77, the worst 1.22.
 RowsPlan rows_plan(const lutkan_dev_layer *l, int64_t B) {
   RowsPlan best{0, 1e300, 1e300};
   if (l->d > kRowsMaxInputs || B > kRowsMaxBatch) return best;
@@ -251,10 +253,10 @@ RowsPlan rows_plan(const lutkan_dev_layer *l, int64_t B) {
     auto priced = [&](double per_round) {
       return 3.5 + std::max(std::max(1.0, rounds) * (per_round + (l->knots_per_input ? 3.5 : 0.0)) + bytes / 15e6, 1.3 * ((l->d + inputs_per_round - 1) / inputs_per_round));
     };
-    const double cost = priced(wpr == 16 ? 2.9 : two ? 1.6 : 3.2);
+    const double cost = priced(wpr == 16 ? 2.9 : two && !(l->knots_per_input && l->d > 256) ? 1.6 : 3.2);
     if (cost >= best.cost) continue;
     best = RowsPlan{wpr, cost, cost};
-    if (two && l->d <= 64 && !l->knots_per_input) {
+    if (two && l->d <= 64 && l->n_tiles > 1 && !l->knots_per_input) {
       const double fitted = 3.4 + rounds * (1.8 + 0.6 * ((l->d + row_groups - 1) / row_groups)) + 0.25 * bytes / 15e6;
       best.against_passes = std::max(cost, std::min(priced(3.2), fitted + 5.5 - l->d / 20.0));
     }

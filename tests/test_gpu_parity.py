@@ -1852,15 +1852,16 @@ def test_rounds_of_two_where_two_work_groups_share_a_compute_unit():
 
 
 @pytest.mark.parametrize("case", [
-    # d, m, G, L, scheme, B, with_base, the plan's first clause: narrow inputs by the passes, wider ones and launches of a round or so in one
-    (1, 272, 5, 64, SYM_INT8, 1104, False, "locate; tiled"), (2, 976, 8, 32, ASYM_UINT8, 290, False, "locate; tiled"),
-    (9, 298, 5, 32, ASYM_UINT8, 1952, False, "locate; tiled"), (34, 1000, 12, 64, SYM_INT8, 870, False, "locate; tiled"),
-    (1, 357, 5, 64, SYM_INT8, 338, False, "rows"), (100, 200, 5, 64, SYM_INT8, 1000, False, "rows"), (86, 249, 5, 32, ASYM_UINT8, 766, True, "rows"),
+    # d, m, G, L, scheme, B, with_base, per_input, the plan's first clause: narrow inputs, and many with knots each, by the passes, others and launches of a round or so in one
+    (1, 272, 5, 64, SYM_INT8, 1104, False, False, "locate; tiled"), (2, 976, 8, 32, ASYM_UINT8, 290, False, False, "locate; tiled"),
+    (9, 298, 5, 32, ASYM_UINT8, 1952, False, False, "locate; tiled"), (34, 1000, 12, 64, SYM_INT8, 870, False, False, "locate; tiled"),
+    (793, 28, 12, 64, SYM_INT8, 1863, False, True, "locate; tiled"), (123, 461, 3, 64, SYM_INT8, 534, False, True, "rows"),
+    (1, 357, 5, 64, SYM_INT8, 338, False, False, "rows"), (100, 200, 5, 64, SYM_INT8, 1000, False, False, "rows"), (86, 249, 5, 32, ASYM_UINT8, 766, True, False, "rows"),
 ], ids=lambda c: f"{c[0]}-{c[1]}x{c[5]}")
 def test_narrow_inputs_run_by_the_passes(case):
     """Which launches of more work-groups than compute units the kernel for a few rows takes; outputs against the oracle either way."""
-    d, m, G, L, scheme, B, with_base, clause = case
-    w = random_layer(972, d, m, G, L, scheme, CLOSED, CLIP_X, B, with_base=with_base)
+    d, m, G, L, scheme, B, with_base, per_input, clause = case
+    w = (per_input_layer if per_input else random_layer)(972, d, m, G, L, scheme, CLOSED, CLIP_X, B, with_base=with_base)
     art, ora = _compile_both(w.layers[0])
     y = lk.lutkan_forward(_device_layer(art, w.layers[0]), torch.from_numpy(w.x).to(DEV))
     assert lk.lutkan_last_plan().startswith(clause), lk.lutkan_last_plan()
