@@ -69,7 +69,7 @@ const char *lutkan_version(void);
  * "locate; tiled np=16 split=2 pipe=3; sum; " (row steps per wave, chunks of inputs, pipeline mode: 2 = two slice
  * buffers, 3 = three with the reads carried across inputs, 4 = three with two slices in flight; "tiled wide" on the
  * table's form with 16-bit codes, "tiled wide32" on the one with fp32 values) or "chain layers=2 wpr=4; " or "locate; gather split=16; sum; " or, where
- * one launch locates, gathers and sums, "rows wpr=16; " (a few rows; waves per row) or "narrow split=1 waves=16; " (a layer of at
+ * one launch locates, gathers and sums, "rows wpr=16 depth=2; " (a few rows; waves per row, inputs in a round) or "narrow split=1 waves=16; " (a layer of at
  * most 32 columns; chunks of inputs, waves per work-group) or, for a large spline_component layer, "locate; base_product; tiled
  * np=16 split=1 pipe=3; " (base_product cuts the base rows into pieces in a launch of its own) or, for a B-spline layer on the
  * matrix cores, "bspline_matrix np=1 split=2 slots=8; sum; " (slots: up to 8, 12 or 16 coefficient rows per input; model_forward: the clauses of all its layers).  Thread-local, overwritten by the next forward call, never null. */

@@ -33,14 +33,14 @@
 // SIMD, so that one's vector work (basis, pieces) overlaps the other's matrix instructions.
 //
 // Bound: matrix and vector issue, at the clock they leave the chip.  48 / 72 / 96 sparse flop per edge; 1024 -> 1024, G = 10, at 4096
-// rows: matrix pipes 0.41 busy, vector issue 0.39, LDS 0.30, 1.9 GHz.  One such instruction of each of two waves and the 7 vector
+// rows: matrix pipes 0.46 busy, vector issue 0.43, LDS 0.33, 1.9 GHz; 128 -> 128, G = 5, at 131072 rows 0.36, 0.46, 0.30.  One such instruction of each of two waves and the 7 vector
 // instructions that go with it take 64 cycles at 2.4 GHz when nothing else does, here 83: vector instructions hide behind a matrix
 // instruction only up to about four.  (Spreading them between the matrix instructions by hand, evaluating a step ahead: 4 %
 // faster with 128 columns, 4 - 10 % slower with 64 and fewer, whose registers then spill; four waves of 64 rows x 128 columns:
 // 13 % slower.)
 // Whole layers, dense matrix instructions -> sparse, microseconds (one run each): 64 -> 128 at 131072 rows, G = 5, 111 -> 84;
 // 128 -> 128 190 -> 142; 128 -> 128, G = 8, 338 -> 191; 256 -> 256 at 16384 rows, G = 8, 189 -> 110; 1024 -> 1024 at 4096 rows, G = 5 /
-// 8 / 10, 348 / 658 / 658 -> 255 / 350 / 441; 64 -> 8 at 131072 rows 36 -> 31.  The tiled kernel takes 587 for 128 -> 128 (G = 5), 790
+// 8 / 10, 348 / 658 / 658 -> 255 / 350 / 441; 64 -> 8 at 131072 rows 36 -> 31 (with scalar addresses, below, 128 -> 128 123, 1024 -> 1024 235 / 337 / 415).  The tiled kernel takes 587 for 128 -> 128 (G = 5), 790
 // for 1024 -> 1024 (G = 10).
 // The file is compiled with -ffp-contract=off; fused multiply-adds are written out as fmaf().
 #include "bspline_matrix.h"
